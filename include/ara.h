@@ -417,9 +417,9 @@ ara_status ara_batch_create(ara_ctx *ctx, const ara_job *jobs, int32_t n_jobs, a
 ara_status ara_batch_run(ara_batch *batch);
 
 /* PML and TVaR of every job's YLT at the given return periods (as
- * ara_risk_measures, bit for bit): pml[j * n_rp + r], tvar[j * n_rp + r].  YLTs of up
- * to 16384 trials are sorted in one workgroup's LDS, all in one launch; longer ones
- * with the radix sort.  Blocking.  Errors: ARA_E_EMPTY (an empty job),
+ * ara_risk_measures, bit for bit): pml[j * n_rp + r], tvar[j * n_rp + r].  All
+ * jobs share the launches of the selection.  The first call with a set of return periods
+ * uploads their ranks (later calls with the same ones reuse them).  Blocking.  Errors: ARA_E_EMPTY (an empty job),
  * ARA_E_INVALID_ARG (return period < 1 or NaN, more than 256 of them). */
 ara_status ara_batch_risk(ara_batch *batch, const double *return_periods, int32_t n_rp, double *pml,
                           double *tvar);

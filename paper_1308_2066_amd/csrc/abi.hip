@@ -1257,18 +1257,36 @@ static ara_status risk_ranks(ara_ctx *c, int64_t n, const double *rps, int32_t n
     return ARA_OK;
 }
 
-// PML/TVaR of the n_rp ranks ks of the device YLT dy (radix selection in workspace
-// w), results to the host (blocking).  Allocates nothing.
+// Descriptor of the ranks ks[0, m) of YLT y.
+static RiskJob risk_job(const double *y, int64_t n, const int64_t *ks, int32_t m, double *out, void *ws) {
+    RiskJob j{};
+    j.y = y;
+    j.n = n;
+    j.out = out;
+    j.ws = static_cast<unsigned char *>(ws);
+    j.m = m;
+    std::copy(ks, ks + m, j.k);
+    j.k_max = *std::max_element(ks, ks + m);
+    return j;
+}
+
+// PML/TVaR of the n_rp ranks ks of the device YLT dy (selection in the sort workspace
+// w), results to the host (blocking).  Allocates nothing.  The kernels write the results
+// and the error word straight to pinned host memory.
 static ara_status risk_on_device(ara_ctx *c, const double *dy, int64_t n, const int64_t *ks, int32_t n_rp, double *pml,
                                  double *tvar, void *w) {
-    hipError_t e = launch_risk_select(dy, n, w, ks, n_rp, c->d_out, c->stream);
-    // the error word and the results in one copy (they are adjacent)
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(c->h_err, c->d_err, kErrBytes + size_t(2 * n_rp) * 8, hipMemcpyDeviceToHost, c->stream);
-    ara_status s = e == hipSuccess ? sync_and_check(c, nullptr, true) : hip_fail(c, e, "risk measures");
+    void *ws = reinterpret_cast<void *>((reinterpret_cast<uintptr_t>(w) + 255) & ~uintptr_t(255));
+    hipError_t e = hipSuccess;
+    for (int32_t base = 0; base < n_rp && e == hipSuccess; base += kRiskGroup) {
+        const int32_t m = std::min<int32_t>(kRiskGroup, n_rp - base);
+        const RiskJob j = risk_job(dy, n, ks + base, m, c->h_out + 2 * base, ws);
+        const bool one = n <= kRiskOneWg;
+        e = launch_risk(&j, nullptr, one ? 1 : 0, one ? 0 : 1, c->d_err, c->h_err, c->stream);
+    }
+    ara_status s = e == hipSuccess ? sync_and_check(c, nullptr, n_rp > 0) : hip_fail(c, e, "risk measures");
     if (s != ARA_OK) return s;
-    for (int32_t base = 0; base < n_rp; base += 16) {
-        const int32_t m = std::min<int32_t>(16, n_rp - base);
+    for (int32_t base = 0; base < n_rp; base += kRiskGroup) {
+        const int32_t m = std::min<int32_t>(kRiskGroup, n_rp - base);
         for (int32_t i = 0; i < m; ++i) {
             pml[base + i] = c->h_out[2 * base + i];
             tvar[base + i] = c->h_out[2 * base + m + i];
@@ -1350,13 +1368,14 @@ struct ara_batch {
     hipStream_t cap = nullptr;       // private stream the launch is captured on
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    // risk measures
-    const double **d_ylts = nullptr;
-    int64_t *d_ns = nullptr, *d_ks = nullptr;
-    double *d_risk = nullptr;
-    int32_t risk_cap = 0;            // return periods d_ks/d_risk hold
-    void *ws = nullptr;              // sort workspace for YLTs too long for one workgroup
-    size_t ws_bytes = 0;
+    const double **d_ylts = nullptr; // the jobs' YLTs (portfolio sums)
+    // risk measures: the plan for the return periods risk_rps, kept until others are asked for
+    std::vector<double> risk_rps;
+    std::vector<RiskJob> rjobs;      // short YLTs first (RiskJob), one per job and group of return periods
+    std::vector<std::pair<int, int>> rlaunch;   // per launch: short and long descriptors, in order
+    RiskJob *d_rjobs = nullptr;
+    double *h_risk = nullptr;        // pinned: [job][2 n_rp], per group of return periods PML then TVaR
+    void *risk_ws = nullptr;         // the workspaces of one launch's long YLTs
     bool counted = false;            // counted in ctx->live
 };
 
@@ -1746,22 +1765,16 @@ extern "C" ara_status ara_batch_info(const ara_batch *b, int32_t *n_items, int32
     return ARA_OK;
 }
 
-// Device list of the jobs' YLT pointers and lengths (built once).
+// Device list of the jobs' YLT pointers (built once).
 static ara_status batch_ylt_list(ara_batch *b) {
     if (b->d_ylts) return ARA_OK;
     ara_ctx *c = b->ctx;
     const size_t nj = b->jobs.size();
     std::vector<const double *> yp(nj);
-    std::vector<int64_t> ns(nj);
-    for (size_t j = 0; j < nj; ++j) {
-        yp[j] = b->jobs[j].ylt;
-        ns[j] = b->jobs[j].trial_end - b->jobs[j].trial_begin;
-    }
+    for (size_t j = 0; j < nj; ++j) yp[j] = b->jobs[j].ylt;
     ara_status s = dev_alloc(c, &b->d_ylts, nj * sizeof(double *), "batch ylt list");
-    if (s == ARA_OK) s = dev_alloc(c, &b->d_ns, nj * 8, "batch sizes");
     if (s != ARA_OK) return s;
     HIP_OR_RETURN(c, hipMemcpy(b->d_ylts, yp.data(), nj * sizeof(double *), hipMemcpyHostToDevice), "upload");
-    HIP_OR_RETURN(c, hipMemcpy(b->d_ns, ns.data(), nj * 8, hipMemcpyHostToDevice), "upload");
     return ARA_OK;
 }
 
@@ -1779,6 +1792,79 @@ extern "C" ara_status ara_batch_portfolio(ara_batch *b, double *out) {
     return e == hipSuccess ? ARA_OK : hip_fail(c, e, "portfolio sum");
 }
 
+// Workspace that one launch's long YLTs may take together (at least one YLT's); the
+// launches of a call follow each other on the stream and share it.
+constexpr size_t kRiskWsBytes = size_t(64) << 20;
+
+static void batch_risk_free(ara_batch *b) {
+    dev_free(b->d_rjobs);
+    dev_free(b->risk_ws);
+    if (b->h_risk) (void)hipHostFree(b->h_risk);
+    b->d_rjobs = nullptr;
+    b->risk_ws = nullptr;
+    b->h_risk = nullptr;
+    b->rjobs.clear();
+    b->rlaunch.clear();
+    b->risk_rps.clear();
+}
+
+// Descriptors, launches and buffers for these return periods (an earlier call's plan for
+// the same ones stands: the jobs' YLTs are fixed).  Calls block, so no launch still reads
+// a plan that is replaced.
+static ara_status batch_risk_plan(ara_batch *b, const double *rps, int32_t n_rp) {
+    if (int32_t(b->risk_rps.size()) == n_rp && b->d_rjobs && std::equal(rps, rps + n_rp, b->risk_rps.begin()))
+        return ARA_OK;
+    ara_ctx *c = b->ctx;
+    const size_t nj = b->jobs.size();
+    std::vector<int64_t> ks(nj * size_t(n_rp));
+    for (size_t j = 0; j < nj; ++j)
+        for (int32_t r = 0; r < n_rp; ++r)
+            if (ara_return_period_rank(b->jobs[j].trial_end - b->jobs[j].trial_begin, rps[r], &ks[j * n_rp + r]) != ARA_OK)
+                return fail(c, ARA_E_INVALID_ARG, "return period %g invalid (must be >= 1)", rps[r]);
+    batch_risk_free(b);
+    ara_status s = ARA_OK;
+    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&b->h_risk), nj * 2 * size_t(n_rp) * 8, hipHostMallocDefault);
+    if (e != hipSuccess) return hip_fail(c, e, "batch risk results");
+    // short YLTs first, then the long ones in launches whose workspaces fit together
+    size_t used = 0, most = 0;
+    std::vector<size_t> ws_off;
+    for (int pass = 0; pass < 2; ++pass)
+        for (size_t j = 0; j < nj; ++j) {
+            const int64_t n = b->jobs[j].trial_end - b->jobs[j].trial_begin;
+            if ((n <= kRiskOneWg) != (pass == 0)) continue;
+            for (int32_t base = 0; base < n_rp; base += kRiskGroup) {
+                const int32_t m = std::min<int32_t>(kRiskGroup, n_rp - base);
+                const size_t need = risk_workspace_bytes(n, m);
+                if (b->rlaunch.empty() || b->rlaunch.back().second >= 65535 || b->rlaunch.back().first >= (1 << 30) ||
+                    (pass == 1 && used > 0 && used + need > kRiskWsBytes)) {
+                    b->rlaunch.emplace_back(0, 0);
+                    used = 0;
+                }
+                b->rjobs.push_back(risk_job(b->jobs[j].ylt, n, &ks[j * n_rp + size_t(base)], m,
+                                            b->h_risk + j * 2 * n_rp + 2 * base, nullptr));
+                ws_off.push_back(used);
+                used += need;
+                most = std::max(most, used);
+                (pass == 0 ? b->rlaunch.back().first : b->rlaunch.back().second)++;
+            }
+        }
+    if (most > 0) s = dev_alloc(c, &b->risk_ws, most, "batch risk workspace");
+    if (s == ARA_OK) s = dev_alloc(c, &b->d_rjobs, b->rjobs.size() * sizeof(RiskJob), "batch risk jobs");
+    if (s != ARA_OK) {
+        batch_risk_free(b);
+        return s;
+    }
+    for (size_t i = 0; i < b->rjobs.size(); ++i)
+        if (b->rjobs[i].n > kRiskOneWg) b->rjobs[i].ws = static_cast<unsigned char *>(b->risk_ws) + ws_off[i];
+    e = hipMemcpy(b->d_rjobs, b->rjobs.data(), b->rjobs.size() * sizeof(RiskJob), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        batch_risk_free(b);
+        return hip_fail(c, e, "batch risk jobs upload");
+    }
+    b->risk_rps.assign(rps, rps + n_rp);
+    return ARA_OK;
+}
+
 extern "C" ara_status ara_batch_risk(ara_batch *b, const double *rps, int32_t n_rp, double *pml, double *tvar) {
     if (!b || n_rp < 0 || (n_rp > 0 && (!rps || !pml || !tvar))) return ARA_E_INVALID_ARG;
     ara_ctx *c = b->ctx;
@@ -1788,67 +1874,25 @@ extern "C" ara_status ara_batch_risk(ara_batch *b, const double *rps, int32_t n_
     for (int32_t j = 0; j < nj; ++j)
         if (b->jobs[size_t(j)].trial_end == b->jobs[size_t(j)].trial_begin)
             return fail(c, ARA_E_EMPTY, "job %d: risk measures of an empty YLT", j);
-    std::vector<int64_t> ks(size_t(nj) * size_t(n_rp));
-    for (int32_t j = 0; j < nj; ++j) {
-        const int64_t n = b->jobs[size_t(j)].trial_end - b->jobs[size_t(j)].trial_begin;
-        for (int32_t r = 0; r < n_rp; ++r)
-            if (ara_return_period_rank(n, rps[r], &ks[size_t(j) * n_rp + r]) != ARA_OK)
-                return fail(c, ARA_E_INVALID_ARG, "return period %g invalid (must be >= 1)", rps[r]);
-    }
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
-    {
-        ara_status s = batch_ylt_list(b);
-        if (s != ARA_OK) return s;
-    }
-    if (b->risk_cap < n_rp) {
-        dev_free(b->d_ks);
-        dev_free(b->d_risk);
-        b->d_ks = nullptr;
-        b->d_risk = nullptr;
-        ara_status s = dev_alloc(c, &b->d_ks, ks.size() * 8, "batch ranks");
-        if (s == ARA_OK) s = dev_alloc(c, &b->d_risk, size_t(nj) * 2 * size_t(n_rp) * 8, "batch risk");
-        if (s != ARA_OK) return s;
-        b->risk_cap = n_rp;
-    }
-    HIP_OR_RETURN(c, hipMemcpyAsync(b->d_ks, ks.data(), ks.size() * 8, hipMemcpyHostToDevice, c->stream), "upload ranks");
-    // short YLTs: one workgroup each, all in one launch; long ones: radix selection,
-    // one after another in the workspace, each into its own results
-    hipError_t e = launch_risk_batch(b->d_ylts, b->d_ns, b->d_ks, nj, n_rp, b->d_risk, c->stream);
-    for (int32_t j = 0; j < nj && e == hipSuccess; ++j) {
-        const int64_t n = b->jobs[size_t(j)].trial_end - b->jobs[size_t(j)].trial_begin;
-        if (n <= kRiskLdsKeys) continue;
-        const size_t need = sort_workspace_bytes(n);
-        if (b->ws_bytes < need) {
-            e = hipStreamSynchronize(c->stream);
-            dev_free(b->ws);
-            b->ws = nullptr;
-            b->ws_bytes = 0;
-            if (e == hipSuccess) e = hipMalloc(&b->ws, need);
-            if (e != hipSuccess) break;
-            b->ws_bytes = need;
-        }
-        // groups of 16 return periods: pml[m] then tvar[m] per group
-        e = launch_risk_select(b->jobs[size_t(j)].ylt, n, b->ws, &ks[size_t(j) * n_rp], n_rp,
-                               b->d_risk + size_t(j) * 2 * n_rp, c->stream);
+    ara_status s = batch_risk_plan(b, rps, n_rp);
+    if (s != ARA_OK) return s;
+    hipError_t e = hipSuccess;
+    size_t at = 0;
+    for (size_t l = 0; l < b->rlaunch.size() && e == hipSuccess; ++l) {
+        const int ns = b->rlaunch[l].first, nl = b->rlaunch[l].second;
+        e = launch_risk(b->rjobs.data() + at, b->d_rjobs + at, ns, nl, c->d_err, c->h_err, c->stream);
+        at += size_t(ns + nl);
     }
     if (e != hipSuccess) return hip_fail(c, e, "batch risk measures");
-    std::vector<double> small(size_t(nj) * 2 * size_t(n_rp));
-    HIP_OR_RETURN(c, hipMemcpyAsync(small.data(), b->d_risk, small.size() * 8, hipMemcpyDeviceToHost, c->stream),
-                  "download risk");
-    ara_status s = sync_and_check(c);
+    s = sync_and_check(c, nullptr, true);   // the kernels wrote the results and the error word to the host
     if (s != ARA_OK) return s;
     for (int32_t j = 0; j < nj; ++j) {
-        const int64_t n = b->jobs[size_t(j)].trial_end - b->jobs[size_t(j)].trial_begin;
-        const double *src = &small[size_t(j) * 2 * n_rp];
-        for (int32_t r = 0; r < n_rp; ++r) {
-            if (n <= kRiskLdsKeys) {   // the batched kernel: pml[n_rp], then tvar[n_rp]
-                pml[size_t(j) * n_rp + r] = src[r];
-                tvar[size_t(j) * n_rp + r] = src[n_rp + r];
-            } else {                   // the selection: per group of 16, pml[m] then tvar[m]
-                const int32_t base = r / 16 * 16, m = std::min<int32_t>(16, n_rp - base), i = r - base;
-                pml[size_t(j) * n_rp + r] = src[2 * base + i];
-                tvar[size_t(j) * n_rp + r] = src[2 * base + m + i];
-            }
+        const double *src = b->h_risk + size_t(j) * 2 * n_rp;
+        for (int32_t r = 0; r < n_rp; ++r) {   // per group of return periods: pml[m] then tvar[m]
+            const int32_t base = r / kRiskGroup * kRiskGroup, m = std::min<int32_t>(kRiskGroup, n_rp - base);
+            pml[size_t(j) * n_rp + r] = src[2 * base + r - base];
+            tvar[size_t(j) * n_rp + r] = src[2 * base + m + r - base];
         }
     }
     return ARA_OK;
@@ -1868,10 +1912,7 @@ extern "C" ara_status ara_batch_release(ara_batch *b) {
     dev_free(b->d_titems);
     dev_free(b->d_next);
     dev_free(b->d_ylts);
-    dev_free(b->d_ns);
-    dev_free(b->d_ks);
-    dev_free(b->d_risk);
-    dev_free(b->ws);
+    batch_risk_free(b);
     if (b->counted) c->live--;
     delete b;
     return ARA_OK;
@@ -1932,10 +1973,10 @@ struct ServerLane {
     int32_t item_cap = 0;
     int32_t mode_off[kBatchModes] = {}, mode_cnt[kBatchModes] = {};
     EltDesc *h_descs = nullptr;       // pinned: every slot's descriptors
-    const double **d_ylts = nullptr, **h_ylts = nullptr;
-    int64_t *d_ns = nullptr, *d_ks = nullptr, *h_nks = nullptr;   // h_nks: ns then ks, pinned
-    double *d_res = nullptr, *h_res = nullptr;                    // [slot][2 * n_rp]
-    void *ws = nullptr;               // radix sort workspace for the YET's length
+    RiskJob *d_rjobs = nullptr, *h_rjobs = nullptr;   // h_rjobs: pinned
+    double *h_res = nullptr;          // pinned: [slot][2 * n_rp], written by the risk kernels
+    unsigned char *ws = nullptr;      // workspaces of the risk measures of long YLTs
+    size_t ws_bytes = 0;
     std::vector<ServerRequest *> reqs;   // the iteration in flight (empty: the lane is free)
     ara_status launch_status = ARA_OK;   // an error while enqueueing it (then its event is not waited on)
 };
@@ -2007,7 +2048,6 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
         h.mode = batch_mode(tl, h.a.ids24 != nullptr);
         h.placement = tl.placement;
         if (h.mode == kModeTiled) tiled.emplace_back(tiled_args(sv->yet, L, r->t0, r->t1, ylt, tl.grid), tl.grid);
-        ln.h_ylts[i] = ylt;
     }
     std::vector<BatchItem> items;
     {
@@ -2026,27 +2066,39 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
         e = hipMemcpyAsync(ln.d_items, ln.h_items, sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice, ln.stream);
     if (e == hipSuccess)
         e = launch_grouped(ln.d_jobs, ln.d_items, ln.mode_off, ln.mode_cnt, pc->n_cu, true, ln.stream, tiled);
-    // risk measures: ranks per request, short YLTs in one launch, long ones by radix
-    // selection (nothing waits on the host here)
-    int64_t *hn = ln.h_nks, *hk = ln.h_nks + sv->slots_per_lane;
-    for (int32_t i = 0; i < nj; ++i) {
-        const int64_t n = take[size_t(i)]->t1 - take[size_t(i)]->t0;
-        hn[i] = n;
-        for (int32_t r = 0; r < nr; ++r) (void)ara_return_period_rank(n, sv->rps[size_t(r)], &hk[size_t(i) * nr + r]);
+    // risk measures: short YLTs first, then the long ones, as many at a time as the
+    // workspace holds (nothing waits on the host here); the kernels write the results and
+    // the error word to pinned host memory
+    int32_t ns = 0, nd = 0;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int32_t i = 0; i < nj; ++i) {
+            ServerRequest *r = take[size_t(i)];
+            const int64_t n = r->t1 - r->t0;
+            if ((n <= kRiskOneWg) != (pass == 0)) continue;
+            int64_t ks[kRiskGroup];
+            for (int32_t q = 0; q < nr; ++q) (void)ara_return_period_rank(n, sv->rps[size_t(q)], &ks[q]);
+            ln.h_rjobs[nd++] = risk_job(sv->arena + r->ylt_off, n, ks, nr, ln.h_res + size_t(i) * 2 * nr, nullptr);
+            if (pass == 0) ns++;
+        }
+    std::vector<int32_t> ends;   // launches after the short YLTs: [previous end, end)
+    size_t used = 0;
+    for (int32_t i = ns; i < nd; ++i) {
+        const size_t need = risk_workspace_bytes(ln.h_rjobs[i].n, nr);
+        if (used > 0 && used + need > ln.ws_bytes) {
+            ends.push_back(i);
+            used = 0;
+        }
+        ln.h_rjobs[i].ws = ln.ws + used;
+        used += need;
     }
+    if (nd > ns) ends.push_back(nd);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(ln.d_ylts, ln.h_ylts, sizeof(double *) * size_t(nj), hipMemcpyHostToDevice, ln.stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(ln.d_ns, hn, 8 * size_t(nj), hipMemcpyHostToDevice, ln.stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(ln.d_ks, hk, 8 * size_t(nj) * nr, hipMemcpyHostToDevice, ln.stream);
-    if (e == hipSuccess) e = launch_risk_batch(ln.d_ylts, ln.d_ns, ln.d_ks, nj, nr, ln.d_res, ln.stream);
-    for (int32_t i = 0; i < nj && e == hipSuccess; ++i) {
-        if (hn[i] <= kRiskLdsKeys) continue;
-        e = launch_risk_select(ln.h_ylts[i], hn[i], ln.ws, &hk[size_t(i) * nr], nr, ln.d_res + size_t(i) * 2 * nr,
-                               ln.stream);
+        e = hipMemcpyAsync(ln.d_rjobs, ln.h_rjobs, sizeof(RiskJob) * size_t(nd), hipMemcpyHostToDevice, ln.stream);
+    if (e == hipSuccess && ns > 0) e = launch_risk(ln.h_rjobs, ln.d_rjobs, ns, 0, pc->d_err, pc->h_err, ln.stream);
+    for (size_t l = 0; l < ends.size() && e == hipSuccess; ++l) {
+        const int32_t i0 = l == 0 ? ns : ends[l - 1];
+        e = launch_risk(ln.h_rjobs + i0, ln.d_rjobs + i0, 0, ends[l] - i0, pc->d_err, pc->h_err, ln.stream);
     }
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ln.h_res, ln.d_res, sizeof(double) * 2 * size_t(nr) * nj, hipMemcpyDeviceToHost, ln.stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(pc->h_err, pc->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, ln.stream);
     if (e == hipSuccess) e = hipEventRecord(ln.done, ln.stream);
     return e == hipSuccess ? ARA_OK : hip_fail(pc, e, "server iteration");
 }
@@ -2159,16 +2211,12 @@ static void server_free(ara_server *sv) {
             if (L) ara_layer_release(L);
         dev_free(ln.d_jobs);
         dev_free(ln.d_items);
-        dev_free(ln.d_ylts);
-        dev_free(ln.d_ns);
-        dev_free(ln.d_ks);
-        dev_free(ln.d_res);
+        dev_free(ln.d_rjobs);
         dev_free(ln.ws);
         if (ln.h_jobs) (void)hipHostFree(ln.h_jobs);
         if (ln.h_items) (void)hipHostFree(ln.h_items);
         if (ln.h_descs) (void)hipHostFree(ln.h_descs);
-        if (ln.h_ylts) (void)hipHostFree(ln.h_ylts);
-        if (ln.h_nks) (void)hipHostFree(ln.h_nks);
+        if (ln.h_rjobs) (void)hipHostFree(ln.h_rjobs);
         if (ln.h_res) (void)hipHostFree(ln.h_res);
         if (ln.done) (void)hipEventDestroy(ln.done);
         if (ln.pc) (void)ara_ctx_destroy(ln.pc);
@@ -2211,11 +2259,10 @@ static ara_status server_lane_create(ara_ctx *c, ara_server *sv, ServerLane &ln,
     const size_t nr = size_t(cfg->n_rp);
     s = dev_alloc(c, &ln.d_jobs, sizeof(BatchJob) * size_t(ns), "server jobs");
     if (s == ARA_OK) s = dev_alloc(c, &ln.d_items, sizeof(BatchItem) * size_t(ln.item_cap), "server items");
-    if (s == ARA_OK) s = dev_alloc(c, &ln.d_ylts, sizeof(double *) * size_t(ns), "server ylt list");
-    if (s == ARA_OK) s = dev_alloc(c, &ln.d_ns, 8 * size_t(ns), "server sizes");
-    if (s == ARA_OK) s = dev_alloc(c, &ln.d_ks, 8 * size_t(ns) * nr, "server ranks");
-    if (s == ARA_OK) s = dev_alloc(c, &ln.d_res, 16 * size_t(ns) * nr, "server results");
-    if (s == ARA_OK) s = dev_alloc(c, &ln.ws, sort_workspace_bytes(y->n_trials), "server sort workspace");
+    if (s == ARA_OK) s = dev_alloc(c, &ln.d_rjobs, sizeof(RiskJob) * size_t(ns), "server risk jobs");
+    const size_t one_ws = risk_workspace_bytes(y->n_trials, int(nr));
+    ln.ws_bytes = std::max(one_ws, std::min(size_t(ns) * one_ws, kRiskWsBytes));
+    if (s == ARA_OK) s = dev_alloc(c, &ln.ws, ln.ws_bytes, "server risk workspace");
     if (s != ARA_OK) return s;
     hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_jobs), sizeof(BatchJob) * size_t(ns), hipHostMallocDefault);
     if (e == hipSuccess)
@@ -2225,9 +2272,7 @@ static ara_status server_lane_create(ara_ctx *c, ara_server *sv, ServerLane &ln,
         e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_descs), sizeof(EltDesc) * size_t(ns) * sv->pool.size(),
                           hipHostMallocDefault);
     if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_ylts), sizeof(double *) * size_t(ns), hipHostMallocDefault);
-    if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_nks), 8 * size_t(ns) * (1 + nr), hipHostMallocDefault);
+        e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_rjobs), sizeof(RiskJob) * size_t(ns), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_res), 16 * size_t(ns) * nr, hipHostMallocDefault);
     return e == hipSuccess ? ARA_OK : hip_fail(c, e, "server pinned staging");
 }

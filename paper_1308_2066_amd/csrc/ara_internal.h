@@ -160,9 +160,6 @@ hipError_t launch_batch(int32_t mode, const BatchJob *jobs, const BatchItem *ite
                         int grid, hipStream_t s);
 int32_t batch_mode(const TrialLaunch &l, bool packed);
 hipError_t launch_sum_ylts(const double *const *ylts, int32_t n_jobs, int64_t n, double *out, hipStream_t s);
-constexpr int kRiskLdsKeys = 16384;   // YLTs up to this length are sorted in one workgroup's LDS
-hipError_t launch_risk_batch(const double *const *ylts, const int64_t *ns, const int64_t *ks, int n_jobs, int n_k,
-                             double *out, hipStream_t s);
 // bitmap placement (static LDS: filter tables up to trial_bitmap_table_capacity() bytes + event queues)
 hipError_t launch_trial_ylt_bitmap(const TrialArgs &a, int grid, int block, hipStream_t s);
 size_t trial_bitmap_table_capacity();
@@ -261,10 +258,29 @@ size_t sort_workspace_bytes(int64_t n);
 hipError_t launch_sort_desc_keys(const double *in, int64_t n, void *ws, hipStream_t s,
                                  uint32_t *host_plan = nullptr);   // sorted keys -> ws
 hipError_t launch_sort_decode(const void *ws, int64_t n, double *out, hipStream_t s);
-// PML/TVaR of the n losses y (device) at ranks ks[0, n_k) by radix selection (no
-// sort): out holds, per group of up to 16 ranks, pml[m] then tvar[m].  ws: a sort
-// workspace for n.  Asynchronous; no host waits.
-hipError_t launch_risk_select(const double *y, int64_t n, void *ws, const int64_t *ks, int n_k, double *out_pml_tvar,
-                              hipStream_t s);
+
+// ---- risk measures (k_risk.hip): PML and TVaR of many YLTs by selection
+constexpr int kRiskGroup = 16;       // ranks per descriptor
+constexpr int kRiskOneWg = 16384;    // YLTs up to this length take one workgroup, no workspace
+struct RiskJob {
+    const double *y;        // the losses (device)
+    int64_t n;              // >= 1, below 2^32
+    double *out;            // PML of the m ranks, then their TVaR: device, or pinned host memory
+    unsigned char *ws;      // risk_workspace_bytes(n, m), 256-byte aligned
+    int64_t m;              // 1..kRiskGroup
+    int64_t k_max;          // the largest of them
+    int64_t k[kRiskGroup];  // ranks, 1..n
+};
+struct RiskArgs {
+    const RiskJob *jobs;    // device array, or null: `one`
+    RiskJob one;
+    const uint32_t *err;    // the device error word, copied to *err_out (may be null) with the results
+    uint32_t *err_out;
+};
+size_t risk_workspace_bytes(int64_t n, int m);
+// jobs [0, n_short) have n <= kRiskOneWg, the n_long after them are longer; dev: the same
+// array in device memory (null: one job, host[0]).  Asynchronous.
+hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int n_long, const uint32_t *err,
+                       uint32_t *err_out, hipStream_t s);
 
 }  // namespace ara

@@ -1,0 +1,846 @@
+// Risk measures (the PML and TVaR filters of Section I over the YLT of Section II-C)
+// by selection.  PML(rp) = the k-th largest loss, TVaR(rp) = the mean of the k largest,
+// k = ara_return_period_rank(n, rp).  In descending-order keys PML is the k-th smallest
+// key K; the k largest losses are the losses whose key is below K plus (k - their
+// number) copies of PML, so
+//   TVaR = (sum of the losses whose key is below K + copies * PML) / k.
+// That sum is taken in a fixed order: per tile of 2048 losses in index order, 256 slots
+// (slot t adds the tile's losses t, t + 256, ..., t + 1792 in turn; the others add
+// +0.0) and a fixed tree over the slots; then the tile sums, slot t adding tiles t,
+// t + 256, ... in turn, and the same tree.  So every path below gives the same bits.
+//
+// K is found from a sample of 1024 losses, one pass that counts bins and one that copies a
+// few keys out.  The sample gives the smallest sampled key L and a key T that the largest
+// rank asked for lies below (five standard deviations beyond its place in the sample).
+// The pass counts the keys below L, the keys equal to L (years capped at the aggregate
+// limit share it) and 4096 equal bins of [L, T]; keys past T, nine in ten when the
+// shortest return period is 10, are not counted at all.  In a YLT without negative losses
+// zeros (quiet years) come last: they are counted on their own and do not stretch the
+// bins.  The few keys of each rank's bin then go to LDS.  A rank that the counts do not
+// reach (the sample misled) is found by refine(), which needs no sample, in more passes.
+//
+//   up to kRiskOneWg losses: one workgroup (k_risk_one).
+//   longer: k_risk_sample (one workgroup; clears the counts), k_risk_bins, k_risk_collect
+//   (the last workgroup to finish picks K), k_risk_sum (tile sums; the last workgroup to
+//   finish forms PML and TVaR).
+// Both take many YLTs at once (one descriptor each), so a batch pays for the launches
+// once.
+//
+// What bounds it: launches, and the chain of round trips within each.  A launch of
+// dependent kernels takes 4.5-5 us whatever it does (8 MB of losses are 1.3 us of HBM), so
+// the passes that replaced one 8-bit digit each (12 launches, 105 us for 10^6 distinct
+// losses and 135 us when a rank fell among capped years, whose bucket never became small)
+// are now four (39 us for 10^6 losses, 31 us for 50,000).  Within a launch, code that runs once costs its fetch: with the keys in
+// registers and every loop unrolled (31 KB of code) k_risk_one took 21 us for 1000
+// losses.  Counting every key in bins of the whole range took 26 us for 10^6 losses: most
+// years fall in a few of those bins, and LDS atomics on one word go one after another.
+//
+// The last workgroup of a launch reads what the others wrote in the same launch: those
+// words are stored and loaded with agent-scope atomics (write-through past the XCDs' L2s,
+// which do not snoop each other), each workgroup waits for its stores to complete, then
+// counts itself; the one that completes the count continues.  No workgroup waits for
+// another, and no fence writes an L2 back (one per workgroup cost 50 us a pass).
+#include <algorithm>
+
+#include "ara_internal.h"
+
+namespace ara {
+
+constexpr int kRiskThreads = 1024;
+constexpr int kRiskWaves = kRiskThreads / 64;
+constexpr int kRiskBins = 4096;
+constexpr int kRiskSample = 1024;      // one loss per thread
+constexpr int kRiskTile = 2048;        // losses per tile of the TVaR sum
+constexpr int kRiskBlocks = 128;       // most workgroups of a pass over one YLT
+constexpr int kRiskRow = 4096;         // fewest losses per workgroup
+constexpr int kRiskLoads = 8;          // losses a thread reads at a time
+constexpr int kRiskCollect = 8192;     // largest bin whose keys are copied out
+constexpr uint32_t kFewKeys = 64;      // a bin that one wave sorts out
+static_assert(kRiskGroup <= kRiskWaves, "one wave per rank");
+static_assert(kRiskTile == 8 * 256, "a tile is 8 losses for each of 256 slots");
+
+__device__ __forceinline__ uint64_t desc_key(double d) {
+    uint64_t u = __builtin_bit_cast(uint64_t, d + 0.0);   // -0.0 + 0.0 == +0.0
+    u = (u >> 63) ? ~u : (u | 0x8000000000000000ull);       // ascending order key
+    return ~u;                                             // descending
+}
+
+__device__ __forceinline__ double key_value(uint64_t k) {
+    uint64_t u = ~k;
+    u = (u >> 63) ? (u & 0x7FFFFFFFFFFFFFFFull) : ~u;
+    return __builtin_bit_cast(double, u);
+}
+
+constexpr uint64_t kZeroKey = 0x7FFFFFFFFFFFFFFFull;   // desc_key(0.0): keys above it are negative losses
+
+// (min and max of mixed 64-bit integer types would go through binary64)
+__device__ __forceinline__ uint64_t umin(uint64_t a, uint64_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint64_t umax(uint64_t a, uint64_t b) { return a > b ? a : b; }
+
+template <typename T>
+__device__ __forceinline__ T agent_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void agent_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Whether this workgroup is the last of n to come here (whole workgroup).  Its earlier
+// agent-scope stores and atomics have completed before it is counted.
+__device__ __forceinline__ bool last_to_finish(uint32_t *done, uint32_t n, uint32_t *lds) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0)
+        *lds = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return *lds == n - 1;
+}
+
+__device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
+    return uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(x)), l))) |
+           uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(x >> 32)), l))) << 32;
+}
+
+__host__ __device__ inline int64_t risk_tiles(int64_t n) { return (n + kRiskTile - 1) / kRiskTile; }
+
+// Descriptor i's fields (uniform: scalar loads), and its rank r.
+struct JobView {
+    const double *y;
+    int64_t n;
+    double *out;
+    unsigned char *ws;
+    int m;
+    int64_t k_max;
+};
+typedef const __attribute__((address_space(4))) RiskJob *ConstJob;
+__device__ __forceinline__ JobView job_view(const RiskArgs &a, int i) {
+    if (!a.jobs) return JobView{a.one.y, a.one.n, a.one.out, a.one.ws, int(a.one.m), a.one.k_max};
+    const ConstJob j = (ConstJob)(a.jobs + i);
+    return JobView{j->y, j->n, j->out, j->ws, int(j->m), j->k_max};
+}
+__device__ __forceinline__ int64_t job_rank(const RiskArgs &a, int i, int r) {
+    return a.jobs ? ((ConstJob)(a.jobs + i))->k[r] : a.one.k[r];
+}
+
+// ------------------------------------------------------------------ sample and bins
+// What the passes count, from the sample: keys below lo, keys equal to lo, and bins
+// (key - lo) >> shift of the keys in (lo, hi]; with zeros_last, zeros on their own (every
+// key in the bins is a positive loss's, and hi is below zero's key).
+struct Binning {
+    uint64_t lo, hi;
+    uint32_t shift;
+    uint32_t zeros_last;
+};
+struct Counts {          // beside the bins
+    uint32_t below, equal, zero;
+};
+
+// The right shift that maps keys 0 .. range (>= 1) to kRiskBins bins.
+__device__ __forceinline__ uint32_t bin_shift(uint64_t range) {
+    constexpr int own = __builtin_ctz(kRiskBins);
+    const int bits = 64 - __builtin_clzll(range);
+    return bits > own ? uint32_t(bits - own) : 0u;
+}
+
+__device__ __forceinline__ bool in_bins(const Binning &b, uint64_t k) { return k > b.lo && k <= b.hi; }
+
+// Reductions and scans over a wave by DPP lane moves: within rows of 16 lanes, then the
+// four rows (a cross-lane permute through the LDS unit takes three times as long).
+template <int Ctrl>
+__device__ __forceinline__ uint64_t dpp64(uint64_t x) {
+    return uint64_t(uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(x)), Ctrl, 0xF, 0xF, false))) |
+           uint64_t(uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(x >> 32)), Ctrl, 0xF, 0xF, false))) << 32;
+}
+template <typename Op>
+__device__ __forceinline__ uint64_t wave_reduce(uint64_t x, Op op) {
+    x = op(x, dpp64<0xB1>(x));    // quad_perm [1,0,3,2]
+    x = op(x, dpp64<0x4E>(x));    // quad_perm [2,3,0,1]
+    x = op(x, dpp64<0x141>(x));   // row_half_mirror
+    x = op(x, dpp64<0x140>(x));   // row_mirror
+    return op(op(readlane64(x, 0), readlane64(x, 16)), op(readlane64(x, 32), readlane64(x, 48)));
+}
+__device__ __forceinline__ uint64_t wave_min(uint64_t x) {
+    return wave_reduce(x, [](uint64_t p, uint64_t q) { return umin(p, q); });
+}
+__device__ __forceinline__ uint64_t wave_max(uint64_t x) {
+    return wave_reduce(x, [](uint64_t p, uint64_t q) { return umax(p, q); });
+}
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {   // inclusive
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x111, 0xF, 0xF, true));    // row_shr 1
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x112, 0xF, 0xF, true));    // row_shr 2
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x114, 0xF, 0xF, true));    // row_shr 4
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x118, 0xF, 0xF, true));    // row_shr 8
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x142, 0xA, 0xF, false));   // row_bcast 15 into rows 1, 3
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x143, 0xC, 0xF, false));   // row_bcast 31 into rows 2, 3
+    return x;
+}
+
+// ------------------------------------------------------------------ picking
+// The state of one rank: its keys are those of [lo, lo + span], `count` of them, and
+// the rank is the left-th smallest of these; or it is solved: K, and the copies of K
+// among the k largest.
+struct RankState {
+    uint64_t lo, span, K;
+    int64_t left, copies;
+    uint32_t count;
+    bool solved;
+};
+
+// The rank's bin in a row of 64 PER counts (whole wave): the state within it (bins of
+// 2^width keys from lo on), or false when the rank lies past the row's last key (total).
+// The lanes' shares first, then the PER bins of the lane whose share holds the rank.
+template <int PER>
+__device__ __forceinline__ bool wave_pick(const uint32_t *row, uint64_t lo, uint32_t width, int64_t left, RankState &out,
+                                          uint32_t &total) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    static_assert(PER % 4 == 0 && PER <= 64, "whole 16-byte reads; one lane per bin of a share");
+    const int lane = threadIdx.x & 63;
+    uint32_t own = 0;
+#pragma unroll 8
+    for (int i = 0; i < PER / 4; ++i) {
+        const u32x4 q = reinterpret_cast<const u32x4 *>(row + PER * lane)[i];
+        own += q[0] + q[1] + q[2] + q[3];
+    }
+    const uint32_t inc = wave_scan(own);
+    total = uint32_t(__builtin_amdgcn_readlane(int(inc), 63));
+    if (left > int64_t(total)) return false;
+    const int l = __ffsll(static_cast<unsigned long long>(__ballot(left <= int64_t(inc)))) - 1;
+    const uint32_t before = uint32_t(__builtin_amdgcn_readlane(int(inc - own), l));
+    const uint32_t c = lane < PER ? row[PER * l + lane] : 0u;
+    const uint32_t run = before + wave_scan(c);
+    const int at = __ffsll(static_cast<unsigned long long>(__ballot(left <= int64_t(run)))) - 1;
+    out.count = uint32_t(__builtin_amdgcn_readlane(int(c), at));
+    out.lo = lo + (uint64_t(PER * l + at) << width);
+    out.span = (1ull << width) - 1ull;
+    out.left = left - int64_t(uint32_t(__builtin_amdgcn_readlane(int(run - c), at)));
+    out.solved = false;
+    return true;
+}
+
+// Rank k after the counting pass (a wave on its own).  Keys come in the order: below lo,
+// equal to lo, bins, and with zeros_last zeros.  A bin's first key is kept out of [lo, ..]
+// when it is b.lo itself, and its last one ends at b.hi.
+__device__ __forceinline__ RankState pick_bin(const uint32_t *row, const Binning &b, const Counts &n, int64_t k) {
+    RankState s;
+    s.solved = false;
+    s.K = b.lo;
+    s.lo = 0, s.span = ~0ull;      // unless found below: anywhere among all keys
+    s.left = k, s.copies = 0;
+    s.count = ~0u;
+    if (k <= int64_t(n.below)) {
+        s.span = b.lo - 1ull;
+        s.count = n.below;
+        return s;
+    }
+    const int64_t before = int64_t(n.below) + int64_t(n.equal);
+    if (k <= before) {
+        s.copies = k - int64_t(n.below);
+        s.solved = true;
+        return s;
+    }
+    uint32_t total;
+    if (wave_pick<kRiskBins / 64>(row, b.lo, b.shift, k - before, s, total)) {
+        const bool last = s.lo == b.lo + (uint64_t(kRiskBins - 1) << b.shift);   // holds the keys up to b.hi
+        const uint64_t end = last ? b.hi : umin(s.lo + s.span, b.hi);
+        s.lo = umax(s.lo, b.lo + 1ull);
+        s.span = end - s.lo;
+        return s;
+    }
+    // past the bins: a zero, if the bins held every positive loss
+    if (b.zeros_last && b.hi == kZeroKey - 1ull && k <= before + int64_t(total) + int64_t(n.zero)) {
+        s.K = kZeroKey;
+        s.copies = k - before - int64_t(total);
+        s.solved = true;
+    }
+    return s;
+}
+
+// The first rank whose bin is rank r's too (r itself if none before it); a wave on its own.
+__device__ __forceinline__ int first_of_bin(const RankState *st, int r) {
+    const int q = threadIdx.x & 63;
+    const bool same = q <= r && !st[q].solved && st[q].lo == st[r].lo && st[q].span == st[r].span;
+    return __ffsll(static_cast<unsigned long long>(__ballot(same))) - 1;
+}
+
+// The left-th smallest of the c <= 64 keys the lanes hold.
+__device__ __forceinline__ void wave_select(uint64_t key, int c, int64_t left, uint64_t &K, int64_t &copies) {
+    const int lane = threadIdx.x & 63;
+    int less = 0, eq = 0;
+#pragma unroll 1
+    for (int j = 0; j < c; ++j) {
+        const uint64_t o = readlane64(key, j);
+        less += o < key ? 1 : 0;
+        eq += o == key ? 1 : 0;
+    }
+    const bool hit = lane < c && int64_t(less) < left && left <= int64_t(less + eq);
+    const int l = __ffsll(static_cast<unsigned long long>(__ballot(hit))) - 1;
+    K = readlane64(key, l);
+    copies = left - int64_t(__builtin_amdgcn_readlane(less, l));
+}
+
+// ------------------------------------------------------------------ one workgroup on its own
+struct RefineLds {
+    __attribute__((aligned(16))) uint32_t bins[kRiskBins];
+    uint64_t lo[kRiskWaves], hi[kRiskWaves];
+    RankState st;
+};
+
+// Smallest and largest of the workgroup's keys, in every thread.
+__device__ __forceinline__ void wg_range(uint64_t &lo, uint64_t &hi, RefineLds &lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    if (lane == 0) lds.lo[wave] = lo, lds.hi[wave] = hi;
+    __syncthreads();
+    lo = wave_min(lds.lo[lane & (kRiskWaves - 1)]);
+    hi = wave_max(lds.hi[lane & (kRiskWaves - 1)]);
+}
+
+// The left-th smallest of the keys in [lo, lo + span] that each() visits (every key of the
+// workgroup once, each call): their range, bins of that range, the rank's bin, and so on;
+// every round narrows the range at least 2048 times.  Whole workgroup.
+template <typename Each>
+__device__ __forceinline__ void refine(Each each, RankState s, uint64_t &K, int64_t &copies, RefineLds &lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll 1
+    for (;;) {
+        const uint64_t lo0 = s.lo, span = s.span;
+        uint64_t lo = ~0ull, hi = 0ull;
+        each([&](uint64_t k) {
+            if (k - lo0 <= span) lo = umin(lo, k), hi = umax(hi, k);
+        });
+        __syncthreads();   // the previous round's (or caller's) use of lds is over
+        for (int i = tid; i < kRiskBins; i += kRiskThreads) lds.bins[i] = 0u;
+        wg_range(lo, hi, lds);
+        if (lo >= hi) {   // one key value
+            K = lo;
+            copies = s.left;
+            return;
+        }
+        const uint32_t width = bin_shift(hi - lo);
+        each([&](uint64_t k) {
+            if (k >= lo && k <= hi) atomicAdd(&lds.bins[(k - lo) >> width], 1u);
+        });
+        __syncthreads();
+        if (wave == 0) {
+            uint32_t total;
+            RankState n = s;
+            (void)wave_pick<kRiskBins / 64>(lds.bins, lo, width, s.left, n, total);
+            if (lane == 0) lds.st = n;
+        }
+        __syncthreads();
+        s = lds.st;
+        if (s.span == 0) {   // one key per bin
+            K = s.lo;
+            copies = s.left;
+            return;
+        }
+    }
+}
+
+// What to count for ranks up to k_max of y[0, n), from a sample (whole workgroup; lds.bins
+// cleared on return).  Sample j is a loss of the j-th of 1024 equal stretches of the
+// YLT, at a place within it that varies from stretch to stretch.
+__device__ __forceinline__ Binning sample_binning(const double *__restrict__ y, int64_t n, int64_t k_max, RefineLds &lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t a = int64_t(tid) * n / kRiskSample, e = int64_t(tid + 1) * n / kRiskSample;
+    const bool have = e > a;
+    const uint64_t key = have ? desc_key(y[a + __umulhi(uint32_t(tid) * 2654435761u, uint32_t(e - a))]) : ~0ull;
+    for (int i = tid; i < kRiskBins; i += kRiskThreads) lds.bins[i] = 0u;
+    // no negative loss sampled: zeros are taken to come last
+    uint64_t lo = key, hi = have ? key : 0ull;
+    wg_range(lo, hi, lds);
+    Binning b;
+    b.lo = lo;
+    b.zeros_last = hi <= kZeroKey && lo < kZeroKey ? 1u : 0u;
+    const uint64_t last = b.zeros_last ? kZeroKey - 1ull : ~0ull;   // the bins' last key unless the sample ends them before
+    __syncthreads();
+    uint64_t top = have && key <= last ? key : 0ull, none = ~0ull;
+    wg_range(none, top, lds);
+    const int64_t ns = n < kRiskSample ? n : kRiskSample;
+    const double q = double(k_max) / double(n), at = q * double(ns);
+    const int64_t place = int64_t(at + 5.0 * __builtin_sqrt(at * (1.0 - q)) + 6.0);
+    const uint32_t width = top > lo ? bin_shift(top - lo) : 0u;
+    if (have && key <= top) atomicAdd(&lds.bins[(key - lo) >> width], 1u);
+    __syncthreads();
+    if (wave == 0) {
+        uint32_t total;
+        RankState s;
+        s.span = last;
+        if (wave_pick<kRiskBins / 64>(lds.bins, lo, width, place, s, total)) s.span = umin(s.lo + s.span, last);
+        if (lane == 0) lds.st.span = s.span;
+    }
+    __syncthreads();
+    b.hi = lds.st.span;
+    // the bins cover the sampled keys; those past the last one sampled share the last bin
+    const uint64_t end = b.hi == last ? umax(top, lo) : b.hi;
+    b.shift = end > lo ? bin_shift(end - lo) : 0u;
+    for (int i = tid; i < kRiskBins; i += kRiskThreads) lds.bins[i] = 0u;
+    __syncthreads();
+    return b;
+}
+
+// The losses from y[i0] (i0 wave-uniform) on as a buffer record, at most 2^28 of them:
+// reads past the YLT's end give +0.0 without a branch.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t losses_from(const double *y, int64_t n, int64_t i0) {
+    const int64_t left = max(int64_t(0), min(n - i0, int64_t(1) << 28));
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(y + (left ? i0 : 0)), 0, int(uint32_t(left) * 8u), kBufWord3);
+}
+__device__ __forceinline__ double loss_at(__amdgpu_buffer_rsrc_t r, uint32_t i) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, int(i * 8u), 0, 0));
+}
+
+// A workgroup's share of a YLT's keys, kRiskLoads per thread at a time: f(keys, which of
+// them are losses of the YLT, a bit each).  The workgroup takes 1024 consecutive losses
+// from `first` on, then from first + step on, ... (step at most 2^20).
+template <typename F>
+__device__ __forceinline__ void each_keys(const double *__restrict__ y, int64_t n, int64_t first, uint32_t step, F f) {
+    const uint32_t tid = threadIdx.x;
+#pragma unroll 1
+    for (int64_t i0 = first; i0 < n; i0 += int64_t(step) * kRiskLoads) {
+        const __amdgpu_buffer_rsrc_t r = losses_from(y, n, i0);
+        const uint32_t left = uint32_t(min(n - i0, int64_t(1) << 28));
+        double v[kRiskLoads];
+#pragma unroll
+        for (int u = 0; u < kRiskLoads; ++u) v[u] = loss_at(r, tid + u * step);
+        uint64_t k[kRiskLoads];
+        uint32_t in = 0;
+#pragma unroll
+        for (int u = 0; u < kRiskLoads; ++u) {
+            k[u] = desc_key(v[u]);
+            in |= tid + uint32_t(u) * step < left ? 1u << u : 0u;
+        }
+        f(k, in);
+    }
+}
+
+// Counts the keys of f's calls: the bins in LDS, the other three as the wave's totals.
+__device__ __forceinline__ void count_keys(const uint64_t (&k)[kRiskLoads], uint32_t in, const Binning &b, uint32_t *bins,
+                                           Counts &n) {
+#pragma unroll
+    for (int u = 0; u < kRiskLoads; ++u) {
+        const bool ok = (in >> u & 1u) != 0;
+        if (ok && in_bins(b, k[u])) atomicAdd(&bins[min(uint32_t((k[u] - b.lo) >> b.shift), uint32_t(kRiskBins - 1))], 1u);
+        n.below += uint32_t(__popcll(__ballot(ok && k[u] < b.lo)));
+        n.equal += uint32_t(__popcll(__ballot(ok && k[u] == b.lo)));
+        n.zero += uint32_t(__popcll(__ballot(ok && b.zeros_last && k[u] == kZeroKey)));
+    }
+}
+__device__ __forceinline__ void add_counts(const Counts &n, Counts *to) {   // lane 0 of each wave
+    if ((threadIdx.x & 63) != 0) return;
+    if (n.below) atomicAdd(&to->below, n.below);
+    if (n.equal) atomicAdd(&to->equal, n.equal);
+    if (n.zero) atomicAdd(&to->zero, n.zero);
+}
+
+// Bins of up to kRiskCollect keys together: where each rank's lie among the copied keys
+// (ranks of one bin share the first one's; larger bins are not copied), and at
+// off[kRiskGroup] the number of copied keys.  st[0, m) set, first and off written; whole
+// workgroup, with barriers on both sides.
+__device__ __forceinline__ void place_bins(const RankState *st, int m, int wave, int *first, uint32_t *off) {
+    const int lane = threadIdx.x & 63;
+    if (wave < m) {
+        const int f = st[wave].solved ? -1 : first_of_bin(st, wave);
+        if (lane == 0) first[wave] = f;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const bool own = lane < m && first[lane] == lane && st[lane].count <= uint32_t(kRiskCollect);
+        const uint32_t c = own ? st[lane].count : 0u;
+        const uint32_t inc = wave_scan(c);
+        if (lane < m) off[lane] = inc - c;
+        if (lane == 63) off[kRiskGroup] = inc;
+    }
+    __syncthreads();
+}
+
+// Copies the keys of each rank's bin (the first ranks' of them) through put(r, key).
+template <typename Put>
+__device__ __forceinline__ void copy_bins(const uint64_t (&k)[kRiskLoads], uint32_t in, const RankState *st,
+                                          const int *first, int m, Put put) {
+#pragma unroll 1
+    for (int r = 0; r < m; ++r) {
+        if (first[r] != r || st[r].count > uint32_t(kRiskCollect)) continue;
+        const uint64_t lo = st[r].lo, span = st[r].span;
+#pragma unroll
+        for (int u = 0; u < kRiskLoads; ++u)
+            if ((in >> u & 1u) && k[u] - lo <= span) put(r, k[u]);
+    }
+}
+
+// Lane t + o into lane t, o = 32, 16, ..., 1; the result in lane 0.
+template <int Ctrl>
+__device__ __forceinline__ double add_row_shl(double x) {
+    return x + __builtin_bit_cast(double, dpp64<Ctrl>(__builtin_bit_cast(uint64_t, x)));
+}
+__device__ __forceinline__ double wave_tree(double x) {
+    x += __shfl_down(x, 32, 64);
+    x += __shfl_down(x, 16, 64);
+    x = add_row_shl<0x108>(x);
+    x = add_row_shl<0x104>(x);
+    x = add_row_shl<0x102>(x);
+    return add_row_shl<0x101>(x);
+}
+
+// One wave's sums of tile `tile`'s losses below each rank's K: put(rank, sum).  Lane l
+// holds slots l, l + 64, l + 128 and l + 192; the tree over the 256 slots adds slot t + o
+// into slot t, o = 128, 64, ..., 1.
+template <typename Put>
+__device__ __forceinline__ void wave_tile_sums(const double *__restrict__ y, int64_t n, int64_t tile, const uint64_t *K,
+                                               int m, Put put) {
+    const int lane = threadIdx.x & 63;
+    const __amdgpu_buffer_rsrc_t rs = losses_from(y, n, tile * kRiskTile);
+    double v[4][8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q][u] = loss_at(rs, uint32_t(lane + 64 * q + 256 * u)) + 0.0;
+#pragma unroll 1
+    for (int r = 0; r < m; ++r) {
+        const uint64_t k = K[r];
+        double s[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            s[q] = 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                asm volatile("" : "+v"(v[q][u]));   // the keys are not kept over the ranks (64 registers)
+                s[q] += desc_key(v[q][u]) < k ? v[q][u] : 0.0;
+            }
+        }
+        const double x = wave_tree((s[0] + s[2]) + (s[1] + s[3]));
+        if (lane == 0) put(r, x);
+    }
+}
+
+// The tile sums of one rank in the same order (slot t adds tiles t, t + 256, ...), by one
+// wave; the result in lane 0.  Eight of a lane's loads are in flight together.
+template <typename At>
+__device__ __forceinline__ double wave_sum_tiles(int64_t tiles, At at) {
+    const int lane = threadIdx.x & 63;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int64_t t0 = lane; t0 - lane < tiles; t0 += 512) {
+        double v[2][4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t t = t0 + 256 * i + 64 * q;
+                v[i][q] = t < tiles ? at(t) : 0.0;
+            }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s[q] += v[i][q];
+    }
+    return wave_tree((s[0] + s[2]) + (s[1] + s[3]));
+}
+
+__device__ __forceinline__ void write_measures(double *out, int m, int r, uint64_t K, int64_t copies, double s, int64_t k) {
+    const double pml = key_value(K);
+    out[r] = pml;
+    out[m + r] = (s + double(copies) * pml) / double(k);
+}
+
+// A YLT of at most kRiskOneWg losses per workgroup (blockIdx.x), read three times after the
+// sample: bins, the few keys of each rank's bin, tile sums.
+constexpr int kOneTiles = kRiskOneWg / kRiskTile;
+__global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
+    __shared__ RefineLds ref;
+    __shared__ Counts cnt;
+    __shared__ RankState st[64];
+    __shared__ int first[kRiskGroup];
+    __shared__ uint32_t off[kRiskGroup + 1], n_cand[kRiskGroup];
+    __shared__ uint64_t K[kRiskGroup];
+    __shared__ uint64_t cand[kRiskCollect];
+    __shared__ double tile_s[kRiskGroup][kOneTiles];
+    const JobView j = job_view(a, blockIdx.x);
+    const double *y = j.y;
+    const int64_t n = j.n;
+    const int m = j.m;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < kRiskGroup) n_cand[tid] = 0u;
+    if (tid == 0) cnt = Counts{0u, 0u, 0u};
+    const Binning b = sample_binning(y, n, j.k_max, ref);
+    Counts c{0u, 0u, 0u};
+    each_keys(y, n, 0, kRiskThreads,
+              [&](const uint64_t (&k)[kRiskLoads], uint32_t in) { count_keys(k, in, b, ref.bins, c); });
+    add_counts(c, &cnt);
+    __syncthreads();
+    if (wave < m) {   // wave r picks rank r's bin
+        const RankState s = pick_bin(ref.bins, b, cnt, job_rank(a, blockIdx.x, wave));
+        if (lane == 0) st[wave] = s;
+    }
+    __syncthreads();
+    place_bins(st, m, wave, first, off);
+    const bool fits = off[kRiskGroup] <= uint32_t(kRiskCollect);   // the copied keys fit in LDS
+    if (fits && off[kRiskGroup] > 0u) {
+        each_keys(y, n, 0, kRiskThreads, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
+            copy_bins(k, in, st, first, m, [&](int q, uint64_t x) { cand[off[q] + atomicAdd(&n_cand[q], 1u)] = x; });
+        });
+    }
+    __syncthreads();
+    if (wave < m && lane == 0) K[wave] = st[wave].K;
+    if (fits && wave < m && !st[wave].solved && st[wave].count <= kFewKeys) {
+        const int nc = int(st[wave].count);
+        uint64_t x;
+        int64_t copies;
+        wave_select(lane < nc ? cand[off[first[wave]] + lane] : ~0ull, nc, st[wave].left, x, copies);
+        if (lane == 0) K[wave] = x, st[wave].copies = copies, st[wave].solved = true;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int q = 0; q < m; ++q) {   // larger bins, one after another
+        if (st[q].solved) continue;
+        uint64_t x;
+        int64_t copies;
+        if (fits && st[q].count <= uint32_t(kRiskCollect)) {
+            const uint64_t *from = cand + off[first[q]];
+            const int nc = int(st[q].count);
+            refine([&](auto f) { for (int i = tid; i < nc; i += kRiskThreads) f(from[i]); }, st[q], x, copies, ref);
+        } else {
+            refine([&](auto f) { for (int64_t i = tid; i < n; i += kRiskThreads) f(desc_key(y[i])); }, st[q], x, copies, ref);
+        }
+        __syncthreads();
+        if (tid == 0) K[q] = x, st[q].copies = copies;
+    }
+    __syncthreads();
+    const int nt = int(risk_tiles(n));
+#pragma unroll 1
+    for (int t = wave; t < nt; t += kRiskWaves)
+        wave_tile_sums(y, n, t, K, m, [&](int q, double s) { tile_s[q][t] = s; });
+    __syncthreads();
+    if (wave < m) {
+        const double s = wave_sum_tiles(nt, [&](int64_t t) { return tile_s[wave][t]; });
+        if (lane == 0) write_measures(j.out, m, wave, K[wave], st[wave].copies, s, job_rank(a, blockIdx.x, wave));
+    }
+    if (tid == 0 && a.err_out) *a.err_out = *a.err;
+}
+
+// ------------------------------------------------------------------ longer YLTs
+// Workspace of one YLT and group of ranks (risk_workspace_bytes), 256-byte aligned.
+struct RiskWs {
+    uint32_t *done;      // [2]: workgroups that finished k_risk_collect, k_risk_sum
+    Counts *counts;
+    Binning *binning;
+    uint32_t *n_cand;    // [kRiskGroup] keys copied out per bin
+    uint64_t *b_lo, *b_hi;   // [kRiskGroup] range of a bin too large to copy out
+    uint64_t *K;         // [kRiskGroup]
+    int64_t *copies;     // [kRiskGroup]
+    uint32_t *bins;      // [kRiskBins]
+    double *tile_sum;    // [m][tiles]
+    uint64_t *cand;      // the copied bins, one after another: at most min(n, m kRiskCollect) keys
+};
+
+__host__ __device__ inline size_t risk_align(size_t x) { return (x + 255) & ~size_t(255); }
+__host__ __device__ inline int risk_blocks(int64_t n) {
+    const int64_t b = (n + kRiskRow - 1) / kRiskRow;
+    return int(b < kRiskBlocks ? b : kRiskBlocks);
+}
+constexpr size_t kRiskCtrlBytes = 1024;
+
+__device__ __forceinline__ RiskWs risk_ws(const JobView &j) {
+    RiskWs w;
+    unsigned char *p = j.ws;
+    w.done = reinterpret_cast<uint32_t *>(p);
+    w.counts = reinterpret_cast<Counts *>(p + 16);
+    w.binning = reinterpret_cast<Binning *>(p + 32);
+    w.n_cand = reinterpret_cast<uint32_t *>(p + 64);
+    w.b_lo = reinterpret_cast<uint64_t *>(p + 128);
+    w.b_hi = w.b_lo + kRiskGroup;
+    w.K = w.b_hi + kRiskGroup;
+    w.copies = reinterpret_cast<int64_t *>(w.K + kRiskGroup);
+    static_assert(sizeof(Counts) <= 16 && sizeof(Binning) <= 32 && 4 * kRiskGroup <= 64 &&
+                  128 + 4 * kRiskGroup * 8 <= kRiskCtrlBytes, "control block");
+    p += kRiskCtrlBytes;
+    w.bins = reinterpret_cast<uint32_t *>(p);
+    p += kRiskBins * 4;
+    w.tile_sum = reinterpret_cast<double *>(p);
+    p += risk_align(size_t(j.m) * size_t(risk_tiles(j.n)) * 8);
+    w.cand = reinterpret_cast<uint64_t *>(p);
+    return w;
+}
+
+size_t risk_workspace_bytes(int64_t n, int m) {
+    if (n <= kRiskOneWg) return 0;
+    return kRiskCtrlBytes + size_t(kRiskBins) * 4 + risk_align(size_t(m) * size_t(risk_tiles(n)) * 8) +
+           risk_align(size_t(std::min<int64_t>(n, int64_t(m) * kRiskCollect)) * 8);
+}
+
+template <typename F>
+__device__ __forceinline__ void each_keys_of_grid(const JobView &j, int nb, F f) {
+    each_keys(j.y, j.n, int64_t(blockIdx.x) * kRiskThreads, uint32_t(nb) * kRiskThreads, f);
+}
+
+// The binning from the sample; clears the counts.
+__global__ __launch_bounds__(kRiskThreads) void k_risk_sample(RiskArgs a) {
+    __shared__ RefineLds ref;
+    const JobView j = job_view(a, blockIdx.x);
+    const RiskWs w = risk_ws(j);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < kRiskBins; i += kRiskThreads) w.bins[i] = 0u;
+    if (tid < 2) w.done[tid] = 0u;
+    if (tid < kRiskGroup) w.n_cand[tid] = 0u, w.b_lo[tid] = ~0ull, w.b_hi[tid] = 0ull;
+    const Binning b = sample_binning(j.y, j.n, j.k_max, ref);
+    if (tid == 0) {
+        *w.counts = Counts{0u, 0u, 0u};
+        *w.binning = b;
+    }
+}
+
+__global__ __launch_bounds__(kRiskThreads) void k_risk_bins(RiskArgs a) {
+    __shared__ uint32_t bins[kRiskBins];
+    __shared__ Counts cnt;
+    const JobView j = job_view(a, blockIdx.y);
+    const int nb = risk_blocks(j.n);
+    if (int(blockIdx.x) >= nb) return;
+    const RiskWs w = risk_ws(j);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < kRiskBins; i += kRiskThreads) bins[i] = 0u;
+    if (tid == 0) cnt = Counts{0u, 0u, 0u};
+    const Binning b = *w.binning;
+    __syncthreads();
+    Counts c{0u, 0u, 0u};
+    each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) { count_keys(k, in, b, bins, c); });
+    add_counts(c, &cnt);
+    __syncthreads();
+    // one addition per workgroup: one per wave, all on the same three words, took 20 us
+    if (tid == 0) add_counts(cnt, w.counts);
+    for (int i = tid; i < kRiskBins; i += kRiskThreads)
+        if (bins[i]) atomicAdd(&w.bins[i], bins[i]);
+}
+
+// The keys left in each rank's bin, copied out; the last workgroup picks each rank's K
+// among them.  A bin of more than kRiskCollect keys is not copied: its smallest and
+// largest key are kept instead (equal for a loss that occurs that often), else the last
+// workgroup goes through the YLT for it.
+__global__ __launch_bounds__(kRiskThreads) void k_risk_collect(RiskArgs a) {
+    __shared__ RefineLds ref;
+    __shared__ RankState st[64];
+    __shared__ int first[kRiskGroup];
+    __shared__ uint32_t off[kRiskGroup + 1];
+    __shared__ uint32_t last;
+    const JobView j = job_view(a, blockIdx.y);
+    const int nb = risk_blocks(j.n), m = j.m;
+    if (int(blockIdx.x) >= nb) return;
+    const RiskWs w = risk_ws(j);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    RankState s;
+    if (wave < m) {
+        s = pick_bin(w.bins, *w.binning, *w.counts, job_rank(a, blockIdx.y, wave));
+        if (lane == 0) st[wave] = s;
+    }
+    __syncthreads();
+    place_bins(st, m, wave, first, off);
+    each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
+        copy_bins(k, in, st, first, m,
+                  [&](int r, uint64_t x) { agent_store(&w.cand[off[r] + atomicAdd(&w.n_cand[r], 1u)], x); });
+    });
+#pragma unroll 1
+    for (int r = 0; r < m; ++r) {
+        if (first[r] != r || st[r].count <= uint32_t(kRiskCollect) || st[r].count == ~0u) continue;
+        const uint64_t lo = st[r].lo, span = st[r].span;
+        uint64_t mn = ~0ull, mx = 0ull;
+        each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
+#pragma unroll
+            for (int u = 0; u < kRiskLoads; ++u)
+                if ((in >> u & 1u) && k[u] - lo <= span) mn = umin(mn, k[u]), mx = umax(mx, k[u]);
+        });
+        mn = wave_min(mn);
+        mx = wave_max(mx);
+        if (lane == 0 && mn <= mx) {
+            atomicMin(reinterpret_cast<unsigned long long *>(&w.b_lo[r]), static_cast<unsigned long long>(mn));
+            atomicMax(reinterpret_cast<unsigned long long *>(&w.b_hi[r]), static_cast<unsigned long long>(mx));
+        }
+    }
+    if (!last_to_finish(&w.done[0], uint32_t(nb), &last)) return;
+    if (wave < m) {
+        const int f = first[wave];
+        if (!s.solved && s.count <= kFewKeys) {
+            const uint64_t key = lane < int(s.count) ? agent_load(&w.cand[off[f] + lane]) : ~0ull;
+            wave_select(key, int(s.count), s.left, s.K, s.copies);
+            s.solved = true;
+        } else if (!s.solved && s.count > uint32_t(kRiskCollect) && s.count != ~0u) {
+            const uint64_t lo = agent_load(&w.b_lo[f]), hi = agent_load(&w.b_hi[f]);
+            if (lo == hi) s.K = lo, s.copies = s.left, s.solved = true;
+        }
+        if (lane == 0) st[wave] = s;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int r = 0; r < m; ++r) {
+        if (st[r].solved) continue;
+        uint64_t K;
+        int64_t copies;
+        if (st[r].count <= uint32_t(kRiskCollect)) {
+            const uint64_t *c = w.cand + off[first[r]];
+            const int nc = int(st[r].count);
+            refine([&](auto f) { for (int i = tid; i < nc; i += kRiskThreads) f(agent_load(&c[i])); }, st[r], K, copies, ref);
+        } else {
+            refine([&](auto f) { for (int64_t i = tid; i < j.n; i += kRiskThreads) f(desc_key(j.y[i])); }, st[r], K, copies,
+                   ref);
+        }
+        __syncthreads();
+        if (tid == 0) st[r].K = K, st[r].copies = copies;
+    }
+    __syncthreads();
+    if (tid < m) {
+        w.K[tid] = st[tid].K;
+        w.copies[tid] = st[tid].copies;
+    }
+}
+
+// Each tile's sum of the losses below each rank's K, a wave per tile; the last workgroup
+// adds the tile sums up.  (Eight tiles per workgroup: with one, the workgroups' counting
+// themselves, one atomic each on one word, took 7 us of the 13 us for 489 tiles.)
+constexpr int kSumWaves = 8;
+__global__ __launch_bounds__(kSumWaves * 64) void k_risk_sum(RiskArgs a) {
+    __shared__ uint32_t last;
+    const JobView j = job_view(a, blockIdx.y);
+    const int64_t tiles = risk_tiles(j.n), wgs = (tiles + kSumWaves - 1) / kSumWaves;
+    if (int64_t(blockIdx.x) >= wgs) return;
+    const RiskWs w = risk_ws(j);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = j.m;
+    const int64_t tile = int64_t(blockIdx.x) * kSumWaves + wave;
+    if (tile < tiles)
+        wave_tile_sums(j.y, j.n, tile, w.K, m, [&](int r, double s) { agent_store(&w.tile_sum[r * tiles + tile], s); });
+    if (!last_to_finish(&w.done[1], uint32_t(wgs), &last)) return;
+#pragma unroll 1
+    for (int r = wave; r < m; r += kSumWaves) {
+        const double s = wave_sum_tiles(tiles, [&](int64_t t) { return agent_load(&w.tile_sum[r * tiles + t]); });
+        if (lane == 0) write_measures(j.out, m, r, w.K[r], w.copies[r], s, job_rank(a, blockIdx.y, r));
+    }
+    if (tid == 0 && a.err_out) *a.err_out = *a.err;
+}
+
+hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int n_long, const uint32_t *err,
+                       uint32_t *err_out, hipStream_t s) {
+    RiskArgs a{};
+    a.err = err;
+    a.err_out = err_out;
+    if (n_short > 0) {
+        a.jobs = dev;
+        if (!dev) a.one = host[0];
+        hipLaunchKernelGGL(k_risk_one, dim3(unsigned(n_short)), dim3(kRiskThreads), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (n_long <= 0) return hipSuccess;
+    a.jobs = dev ? dev + n_short : nullptr;
+    if (!dev) a.one = host[0];
+    int64_t n = 0;
+    for (int i = n_short; i < n_short + n_long; ++i) n = std::max(n, host[i].n);
+    const int64_t tiles = risk_tiles(n);
+    if (tiles > int64_t(INT32_MAX) || n_long > 65535) return hipErrorInvalidValue;
+    const dim3 grid(unsigned(risk_blocks(n)), unsigned(n_long)), block(kRiskThreads);
+    hipLaunchKernelGGL(k_risk_sample, dim3(unsigned(n_long)), block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_bins, grid, block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_collect, grid, block, 0, s, a);
+    const dim3 sum_grid(unsigned((tiles + kSumWaves - 1) / kSumWaves), unsigned(n_long));
+    hipLaunchKernelGGL(k_risk_sum, sum_grid, dim3(kSumWaves * 64), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace ara
