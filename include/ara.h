@@ -306,7 +306,9 @@ ara_status ara_layer_release(ara_layer *layer);
  * cumulative sum is non-decreasing and the aggregate clamp is non-decreasing with
  * value 0 at 0, so the differences telescope.  ylt has trial_end - trial_begin
  * doubles in memory `ylt_mem`.  The YET and the layer must share a catalog size.
- * Asynchronous for ARA_MEM_DEVICE output; blocking for ARA_MEM_HOST.  Trials with
+ * Asynchronous for ARA_MEM_DEVICE output; blocking for ARA_MEM_HOST.  Launches of the
+ * tiled placement over few trials keep a workspace of at most 64 MB per stream they run on
+ * (up to four streams) until the context is destroyed.  Trials with
  * no events get 0.  Kernel-detected errors: ARA_E_EVENT_ID_RANGE, ARA_E_BAD_OFFSETS.
  * Errors: ARA_E_INVALID_ARG, ARA_E_UNSUPPORTED (forced placement too small), ARA_E_DEVICE. */
 ara_status ara_analyze(ara_ctx *ctx, const ara_yet *yet, const ara_layer *layer,

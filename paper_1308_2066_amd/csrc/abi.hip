@@ -40,6 +40,14 @@ struct ara_ctx {
     std::vector<hipEvent_t> k_ev;    // ARA_OPT_KERNEL_TIMING: a ring of (start, stop) event pairs
     int64_t k_count = 0;             // trial kernels timed since the option was set
     std::map<std::string, std::pair<int64_t, bool>> tuned;   // batch shape -> (events per item, interleave)
+    // workspaces of split tiled launches, one per stream they ran on (launches on one stream
+    // follow each other; on two streams they may overlap): see tiled_scratch
+    struct Scratch {
+        hipStream_t stream;
+        void *p;
+        size_t bytes;
+    };
+    std::vector<Scratch> tiled_ws;
     int live = 0;                    // handles alive on this context
     std::string msg;
 };
@@ -59,6 +67,7 @@ struct ara_yet {
     int64_t *region = nullptr;    // n_bins + 1 element offsets
     int64_t stride = 0;
     int32_t n_bins = 0;
+    int32_t n_groups = 1, group_bins = 0;   // bin groups of the tiled kernel
     int64_t copy_bytes = 0;       // device memory of the packed or binned copy
 };
 
@@ -389,6 +398,7 @@ extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     dev_free(c->d_err);   // with d_out
+    for (auto &w : c->tiled_ws) dev_free(w.p);
     for (hipEvent_t ev : c->k_ev) (void)hipEventDestroy(ev);
     if (c->h_err) (void)hipHostFree(c->h_err);   // with h_out
     if (c->h_plan) (void)hipHostFree(c->h_plan);
@@ -576,6 +586,8 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
     dev_free(sums);
     if (s == ARA_OK) {
         y->n_bins = nb;
+        y->n_groups = tiled_group_count(n, nb, c->n_cu);
+        y->group_bins = (nb + y->n_groups - 1) / y->n_groups;
         y->copy_bytes = int64_t(ids16_bytes) + int64_t(nb + 1) * 8 + int64_t(nb) * y->stride * (y->boff24 ? 3 : 4) +
                         (y->boff24 ? 16 : 0);
         return ARA_OK;
@@ -996,10 +1008,70 @@ static TiledArgs tiled_args(const ara_yet *y, const ara_layer *L, int64_t t0, in
     a.occ = L->t.occ;
     a.catalog = L->catalog;
     a.n_bins = y->n_bins;
+    a.group_bins = y->group_bins;
+    a.n_groups = y->n_groups;
     a.agg_r = L->terms.agg_retention;
     a.agg_l = L->terms.agg_limit;
     a.ylt = ylt;
     return a;
+}
+
+// Makes `a` a split launch: its groups' sums in p, chunks of trials.
+static void tiled_split(TiledArgs &a, void *p, int64_t chunks) {
+    const int64_t n = a.t_end - a.t_begin;
+    a.part = static_cast<double *>(p);
+    a.part_stride = (n + 2) & ~int64_t(1);
+    a.chunks = int32_t(chunks);
+    a.per_wg = (n + chunks - 1) / chunks;
+}
+static size_t tiled_split_bytes(int64_t n, int32_t groups) { return size_t((n + 2) & ~int64_t(1)) * size_t(groups) * 8; }
+
+// Workspace of `bytes` for a split tiled launch on the context's stream, or null: while the
+// stream is being captured (a graph may be replayed on any stream, at any time), for more
+// than kTiledWsBytes, for more than kTiledWsStreams streams, or without memory.  The
+// launch then runs whole, with the same bits.
+constexpr size_t kTiledWsBytes = size_t(64) << 20;
+constexpr size_t kTiledWsStreams = 4;
+
+static void *tiled_scratch(ara_ctx *c, size_t bytes) {
+    if (bytes > kTiledWsBytes) return nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    size_t i = 0;
+    while (i < c->tiled_ws.size() && c->tiled_ws[i].stream != c->stream) ++i;
+    if (i < c->tiled_ws.size() && c->tiled_ws[i].bytes >= bytes) return c->tiled_ws[i].p;
+    if (i == c->tiled_ws.size() && i >= kTiledWsStreams) return nullptr;
+    void *p = nullptr;
+    const size_t take = std::max(bytes, size_t(4) << 20);
+    if (hipMalloc(&p, take) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (i == c->tiled_ws.size()) {
+        c->tiled_ws.push_back({c->stream, p, take});
+    } else {
+        (void)hipStreamSynchronize(c->stream);   // earlier launches may still use the smaller one
+        dev_free(c->tiled_ws[i].p);
+        c->tiled_ws[i].p = p;
+        c->tiled_ws[i].bytes = take;
+    }
+    return p;
+}
+
+// The tiled kernel over trials [t0, t1) on the context's stream, split over bin groups
+// where that is faster.
+static hipError_t run_tiled(ara_ctx *c, const ara_yet *y, const ara_layer *L, int64_t t0, int64_t t1, double *out, int grid,
+                            bool occ_max, hipEvent_t start, hipEvent_t stop) {
+    TiledArgs a = tiled_args(y, L, t0, t1, out, grid);
+    const int64_t chunks = tiled_chunks(t1 - t0, y->n_bins, y->n_groups, c->n_cu);
+    if (chunks > 0) {
+        void *p = tiled_scratch(c, tiled_split_bytes(t1 - t0, y->n_groups));
+        if (p) tiled_split(a, p, chunks);
+    }
+    return launch_trial_tiled(a, grid, c->stream, occ_max, start, stop);
 }
 
 static ara_status check_analysis(ara_ctx *c, const ara_yet *y, const ara_layer *L, int64_t t0, int64_t t1) {
@@ -1038,8 +1110,8 @@ extern "C" ara_status ara_analyze(ara_ctx *c, const ara_yet *y, const ara_layer 
         if (tiles) {
             // timed: events attached to the first launch's start and the last one's end
             const bool first = tb == t0, last = te == t1;
-            e = launch_trial_tiled(tiled_args(y, L, tb, te, dst + (tb - t0), tl.grid), tl.grid, c->stream, false,
-                                   first ? t_start : nullptr, last ? t_stop : nullptr);
+            e = run_tiled(c, y, L, tb, te, dst + (tb - t0), tl.grid, false, first ? t_start : nullptr,
+                          last ? t_stop : nullptr);
             continue;
         }
         TrialArgs a = trial_args(y, L, tb, te, dst + (tb - t0));
@@ -1086,7 +1158,7 @@ extern "C" ara_status ara_analyze_occ_max(ara_ctx *c, const ara_yet *y, const ar
         constexpr int64_t kMaxTrialsPerLaunch = int64_t(1) << 30;
         for (int64_t tb = t0; tb < t1 && e == hipSuccess; tb += kMaxTrialsPerLaunch) {
             const int64_t te = std::min(t1, tb + kMaxTrialsPerLaunch);
-            e = launch_trial_tiled(tiled_args(y, L, tb, te, dst + (tb - t0), tl.grid), tl.grid, c->stream, true);
+            e = run_tiled(c, y, L, tb, te, dst + (tb - t0), tl.grid, true, nullptr, nullptr);
         }
     } else {
         const TrialArgs a = trial_args(y, L, t0, t1, nullptr);
@@ -1357,6 +1429,10 @@ struct ara_batch {
     TiledArgs *d_tjobs = nullptr;
     TiledItem *d_titems = nullptr;
     uint32_t *d_next = nullptr;      // the tiled launch's item counter
+    std::vector<int32_t> split;      // tjobs split over bin groups, their sums in d_part
+    int32_t *d_split = nullptr;
+    void *d_part = nullptr;
+    int64_t split_max = 0;           // most trials of one of them
     std::vector<uint64_t> terms_gen; // per job: its layer's terms generation when last uploaded
     std::string shape;               // key of the tuning cache
     BatchJob *d_jobs = nullptr;
@@ -1412,18 +1488,21 @@ static void batch_shape(int32_t n_items, int n_cu, int32_t &grid, int32_t &per_w
 }
 
 // One persistent launch per mode present, in mode order; interleave: workgroups take
-// every G-th item instead of a contiguous run.  Jobs of the tiled kernel follow, one
-// launch each.
+// every G-th item instead of a contiguous run.  Jobs of the tiled kernel follow, in one
+// launch, and one more that adds up the split ones' bin groups.
 struct TiledBatch {
     const TiledArgs *jobs = nullptr;
     const TiledItem *items = nullptr;
     int32_t n_items = 0;
     uint32_t *next = nullptr;
+    const int32_t *split = nullptr;
+    int32_t n_split = 0;
+    int64_t split_max = 0;
 };
 
 static hipError_t launch_grouped(const BatchJob *d_jobs, const BatchItem *d_items, const int32_t *off,
                                  const int32_t *cnt, int n_cu, bool interleave, hipStream_t s,
-                                 const std::vector<std::pair<TiledArgs, int>> &tiled, const TiledBatch &tb = TiledBatch()) {
+                                 const TiledBatch &tb = TiledBatch()) {
     for (int m = 0; m < kBatchModes; ++m) {
         if (cnt[m] == 0) continue;
         int32_t grid = 1, per_wg = 0;
@@ -1435,13 +1514,10 @@ static hipError_t launch_grouped(const BatchJob *d_jobs, const BatchItem *d_item
         const hipError_t e = launch_batch(m, d_jobs, d_items + off[m], cnt[m], per_wg, grid, s);
         if (e != hipSuccess) return e;
     }
-    for (const auto &ta : tiled) {
-        const hipError_t e = launch_trial_tiled(ta.first, ta.second, s);
-        if (e != hipSuccess) return e;
-    }
-    if (tb.n_items > 0)
-        return launch_trial_tiled_items(tb.jobs, tb.items, tb.n_items, tb.next, std::min(tb.n_items, n_cu), s);
-    return hipSuccess;
+    if (tb.n_items <= 0) return hipSuccess;
+    const hipError_t e = launch_trial_tiled_items(tb.jobs, tb.items, tb.n_items, tb.next, std::min(tb.n_items, n_cu), s);
+    if (e != hipSuccess) return e;
+    return launch_tiled_combine_items(tb.jobs, tb.split, tb.n_split, tb.split_max, s);
 }
 
 static TiledBatch batch_tiled(const ara_batch *b) {
@@ -1450,15 +1526,19 @@ static TiledBatch batch_tiled(const ara_batch *b) {
     t.items = b->d_titems;
     t.n_items = int32_t(b->titems.size());
     t.next = b->d_next;
+    t.split = b->d_split;
+    t.n_split = int32_t(b->split.size());
+    t.split_max = b->split_max;
     return t;
 }
 
 // A tiled job's trials [tb, te) as work items of job index k: passes of nearly equal
 // size, as few as kTiledPassTrials allows (each pass stages every bin of the catalog
-// once), with each one's cost (occurrences, plus the staging).  A trial's YLT does not
-// depend on the pass that holds it (its lane adds the bins in order and each run's
-// occurrences in order), so the items give the plain launch's bits.
-static void tiled_passes(int32_t k, int64_t tb, int64_t te, double mean_len, double stage,
+// once), over every bin group or (split) one each, with each one's cost (occurrences,
+// plus the staging).  A trial's YLT does not depend on the pass that holds it (its lane
+// adds the bins of a group in order and each run's occurrences in order, and the groups'
+// sums are added in order), so the items give the plain launch's bits.
+static void tiled_passes(int32_t k, int64_t tb, int64_t te, double mean_len, double stage, int32_t groups, bool split,
                          std::vector<std::pair<double, TiledItem>> &out) {
     const int64_t n = te - tb;
     const int64_t passes = (n + kTiledPassTrials - 1) / kTiledPassTrials;
@@ -1468,8 +1548,59 @@ static void tiled_passes(int32_t k, int64_t tb, int64_t te, double mean_len, dou
         it.job = k;
         it.t0 = p;
         it.t1 = std::min(p + per, te);
-        out.emplace_back(double(it.t1 - it.t0) * mean_len + stage, it);
+        const double cost = double(it.t1 - it.t0) * mean_len + stage;
+        for (int32_t g = 0; g < (split ? groups : 1); ++g) {
+            it.group = split ? g : -1;
+            out.emplace_back(split ? cost / groups : cost, it);
+        }
     }
+}
+
+// Splits the batch's tiled jobs over bin groups when their passes are too few to keep the
+// CUs evenly busy (below four rounds of them, where the last pass to end is a long wait),
+// while their sums fit kBatchPartBytes; writes the items.
+constexpr int64_t kTiledFewRounds = 4;
+constexpr size_t kBatchPartBytes = size_t(256) << 20;
+
+static ara_status batch_tiled_items(ara_batch *b) {
+    ara_ctx *c = b->ctx;
+    int64_t passes = 0;
+    for (const TiledArgs &a : b->tjobs) passes += (a.t_end - a.t_begin + kTiledPassTrials - 1) / kTiledPassTrials;
+    std::vector<std::pair<double, TiledItem>> items;
+    std::vector<size_t> at(b->tjobs.size(), SIZE_MAX);
+    size_t used = 0;
+    for (size_t k = 0; k < b->tjobs.size(); ++k) {
+        const TiledArgs &a = b->tjobs[k];
+        const size_t need = tiled_split_bytes(a.t_end - a.t_begin, a.n_groups);
+        const bool split = passes < kTiledFewRounds * c->n_cu && a.n_groups > 1 && used + need <= kBatchPartBytes;
+        if (split) {
+            at[k] = used;
+            used += need;
+            b->split.push_back(int32_t(k));
+            b->split_max = std::max(b->split_max, a.t_end - a.t_begin);
+        }
+        const ara_job &jb = b->jobs[size_t(b->tiled_job[k])];
+        const double mean = jb.yet->n_trials ? double(jb.yet->n_events) / double(jb.yet->n_trials) : 0.0;
+        tiled_passes(int32_t(k), a.t_begin, a.t_end, mean, kTiledStageCost * double(jb.layer->catalog), a.n_groups, split,
+                     items);
+    }
+    ara_status s = ARA_OK;
+    if (used > 0) s = dev_alloc(c, &b->d_part, used, "batch tiled sums");
+    if (s == ARA_OK && used > 0) s = dev_alloc(c, &b->d_split, b->split.size() * 4, "batch tiled split jobs");
+    if (s != ARA_OK) return s;
+    for (size_t k = 0; k < b->tjobs.size(); ++k)
+        if (at[k] != SIZE_MAX) tiled_split(b->tjobs[k], static_cast<char *>(b->d_part) + at[k], 1);
+    if (used > 0) {
+        const hipError_t e = hipMemcpy(b->d_split, b->split.data(), b->split.size() * 4, hipMemcpyHostToDevice);
+        if (e != hipSuccess) return hip_fail(c, e, "batch tiled upload");
+    }
+    // costliest passes first, so that the last ones taken are short
+    std::stable_sort(items.begin(), items.end(),
+                     [](const std::pair<double, TiledItem> &x, const std::pair<double, TiledItem> &y) {
+                         return x.first > y.first;
+                     });
+    for (const auto &it : items) b->titems.push_back(it.second);
+    return ARA_OK;
 }
 
 static ara_status batch_set_items(ara_batch *b, int64_t events) {
@@ -1508,7 +1639,6 @@ extern "C" ara_status ara_batch_create(ara_ctx *c, const ara_job *jobs, int32_t 
     if (!b) return ARA_E_OOM;
     b->ctx = c;
     char key[160];
-    std::vector<std::pair<double, TiledItem>> titems;
     for (int32_t j = 0; j < n_jobs; ++j) {
         const ara_job &jb = jobs[j];
         ara_status s = check_analysis(c, jb.yet, jb.layer, jb.trial_begin, jb.trial_end);
@@ -1528,8 +1658,6 @@ extern "C" ara_status ara_batch_create(ara_ctx *c, const ara_job *jobs, int32_t 
         if (h.mode == kModeTiled && jb.trial_end > jb.trial_begin) {
             b->tjobs.push_back(tiled_args(jb.yet, jb.layer, jb.trial_begin, jb.trial_end, jb.ylt, tl.grid));
             b->tiled_job.push_back(j);
-            tiled_passes(int32_t(b->tjobs.size() - 1), jb.trial_begin, jb.trial_end, mean,
-                         kTiledStageCost * double(jb.layer->catalog), titems);
         }
         b->terms_gen.push_back(jb.layer->terms_gen);
         b->jobs.push_back(jb);
@@ -1547,13 +1675,8 @@ extern "C" ara_status ara_batch_create(ara_ctx *c, const ara_job *jobs, int32_t 
             if (e != hipSuccess) s = hip_fail(c, e, "batch jobs upload");
         }
     }
-    if (s == ARA_OK && !titems.empty()) {
-        // costliest passes first, so that the last ones taken are short
-        std::stable_sort(titems.begin(), titems.end(),
-                         [](const std::pair<double, TiledItem> &x, const std::pair<double, TiledItem> &y) {
-                             return x.first > y.first;
-                         });
-        for (const auto &it : titems) b->titems.push_back(it.second);
+    if (s == ARA_OK && !b->tjobs.empty()) s = batch_tiled_items(b);
+    if (s == ARA_OK && !b->titems.empty()) {
         s = dev_alloc(c, &b->d_tjobs, b->tjobs.size() * sizeof(TiledArgs), "batch tiled jobs");
         if (s == ARA_OK) s = dev_alloc(c, &b->d_titems, b->titems.size() * sizeof(TiledItem), "batch tiled items");
         if (s == ARA_OK) s = dev_alloc(c, &b->d_next, 256, "batch tiled counter");
@@ -1617,7 +1740,7 @@ static ara_status batch_tune(ara_batch *b, bool *computed) {
             for (int rep = 0; rep < kTuneReps && e == hipSuccess; ++rep) {
                 e = hipEventRecord(e0, c->stream);
                 if (e == hipSuccess)
-                    e = launch_grouped(b->d_jobs, b->d_items, b->mode_off, b->mode_cnt, c->n_cu, inter, c->stream, {},
+                    e = launch_grouped(b->d_jobs, b->d_items, b->mode_off, b->mode_cnt, c->n_cu, inter, c->stream,
                                        batch_tiled(b));
                 if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -1650,7 +1773,7 @@ static ara_status batch_capture(ara_batch *b) {
     ara_ctx *c = b->ctx;
     HIP_OR_RETURN(c, hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking), "capture stream");
     HIP_OR_RETURN(c, hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "begin capture");
-    hipError_t e = launch_grouped(b->d_jobs, b->d_items, b->mode_off, b->mode_cnt, c->n_cu, b->interleave, b->cap, {},
+    hipError_t e = launch_grouped(b->d_jobs, b->d_items, b->mode_off, b->mode_cnt, c->n_cu, b->interleave, b->cap,
                                   batch_tiled(b));
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(b->cap, &g);
@@ -1911,6 +2034,8 @@ extern "C" ara_status ara_batch_release(ara_batch *b) {
     dev_free(b->d_tjobs);
     dev_free(b->d_titems);
     dev_free(b->d_next);
+    dev_free(b->d_split);
+    dev_free(b->d_part);
     dev_free(b->d_ylts);
     batch_risk_free(b);
     if (b->counted) c->live--;
@@ -2016,7 +2141,7 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
     const size_t np = sv->pool.size();
     const int32_t nj = int32_t(take.size());
     const double mean_len = double(sv->yet->n_events) / double(std::max<int64_t>(1, sv->yet->n_trials));
-    std::vector<std::pair<TiledArgs, int>> tiled;
+    std::vector<std::pair<int32_t, int>> tiled;   // requests of the tiled kernel: index, grid
     for (int32_t i = 0; i < nj; ++i) {
         ServerRequest *r = take[size_t(i)];
         ara_layer *L = ln.slots[size_t(i)];
@@ -2047,7 +2172,7 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
         h.a.qcap = tl.qcap;
         h.mode = batch_mode(tl, h.a.ids24 != nullptr);
         h.placement = tl.placement;
-        if (h.mode == kModeTiled) tiled.emplace_back(tiled_args(sv->yet, L, r->t0, r->t1, ylt, tl.grid), tl.grid);
+        if (h.mode == kModeTiled) tiled.emplace_back(i, tl.grid);
     }
     std::vector<BatchItem> items;
     {
@@ -2065,7 +2190,12 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
     if (e == hipSuccess)
         e = hipMemcpyAsync(ln.d_items, ln.h_items, sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice, ln.stream);
     if (e == hipSuccess)
-        e = launch_grouped(ln.d_jobs, ln.d_items, ln.mode_off, ln.mode_cnt, pc->n_cu, true, ln.stream, tiled);
+        e = launch_grouped(ln.d_jobs, ln.d_items, ln.mode_off, ln.mode_cnt, pc->n_cu, true, ln.stream);
+    for (size_t k = 0; k < tiled.size() && e == hipSuccess; ++k) {
+        const ServerRequest *r = take[size_t(tiled[k].first)];
+        e = run_tiled(pc, sv->yet, ln.slots[size_t(tiled[k].first)], r->t0, r->t1, sv->arena + r->ylt_off, tiled[k].second,
+                      false, nullptr, nullptr);
+    }
     // risk measures: short YLTs first, then the long ones, as many at a time as the
     // workspace holds (nothing waits on the host here); the kernels write the results and
     // the error word to pinned host memory

@@ -230,21 +230,35 @@ struct TiledArgs {
     const uint8_t *boff24;      // or 3 bytes each (row b at byte 3 b stride)
     int64_t stride;             // entries per boff row
     int64_t t_begin, t_end;
-    int64_t per_wg;             // trials per workgroup
+    int64_t per_wg;             // trials per workgroup (split: at most kTiledPassTrials)
     const double *occ;          // the layer's occurrence-net values, one per catalog event
     int32_t catalog;
     int32_t n_bins;
+    int32_t group_bins;         // bins per group (the last group may have fewer)
+    int32_t n_groups;
     double agg_r, agg_l;
     double *ylt;
+    double *part;               // split: [n_groups][part_stride] sums, 16-byte aligned; null: whole
+    int64_t part_stride;        // even, at least t_end - t_begin + 1
+    int32_t chunks;             // split: chunks of per_wg trials
+    int32_t pad_;
 };
+// Bin groups of a YET, and the chunks a launch over n of its trials is split into (0:
+// whole); see k_trial_tiled.hip.
+constexpr int32_t kTiledMaxGroups = 32;
+constexpr int kXcds = 8;
+int32_t tiled_group_count(int64_t n, int32_t n_bins, int n_cu);
+int64_t tiled_chunks(int64_t n, int32_t n_bins, int32_t groups, int n_cu);
 // occ_max: each trial's largest occurrence-net loss into a.ylt instead of the YLT;
-// start/stop (or null): HIP events attached to the launch (its dispatch's start and end)
+// start/stop (or null): HIP events attached to the launch (its first dispatch's start, its
+// last one's end)
 hipError_t launch_trial_tiled(const TiledArgs &a, int grid, hipStream_t s, bool occ_max = false,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-// A pass of the tiled kernel as a work item: analysis `job`, trials [t0, t1).
+// A pass of the tiled kernel as a work item: analysis `job`, trials [t0, t1), bin group
+// `group`, or every group (-1).
 struct TiledItem {
     int32_t job;
-    int32_t pad_;
+    int32_t group;
     int64_t t0, t1;
 };
 static_assert(sizeof(TiledItem) == 24, "six words");
@@ -252,6 +266,11 @@ static_assert(sizeof(TiledItem) == 24, "six words");
 // device memory, cleared by a fill kernel first, so the launch can be graph-captured).
 hipError_t launch_trial_tiled_items(const TiledArgs *jobs, const TiledItem *items, int32_t n_items, uint32_t *next,
                                     int grid, hipStream_t s);
+
+// The YLTs of the analyses split[0, n_split) (indices into jobs), of at most n_max trials,
+// from their groups' sums.
+hipError_t launch_tiled_combine_items(const TiledArgs *jobs, const int32_t *split, int32_t n_split, int64_t n_max,
+                                      hipStream_t s);
 
 // ---- order statistics
 size_t sort_workspace_bytes(int64_t n);

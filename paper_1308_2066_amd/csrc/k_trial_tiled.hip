@@ -21,8 +21,10 @@
 //   group is added (three groups rotate through three register slots); the rest of a
 //   longer run is read when reached.  Each bin's values are loaded into registers
 //   while the previous bin is added, and written to LDS between two barriers.
-// A trial's P is added in a fixed order (bins, then positions): the same bits on
+// A trial's P is added in a fixed order (bin groups, bins, positions): the same bits on
 // every run.  The per-trial sums live in LDS (one binary64 per trial of the wave).
+#include <algorithm>
+
 #include <hip/hip_ext.h>
 
 #include "trial_common.h"
@@ -161,25 +163,19 @@ __device__ __forceinline__ void unit_run(const double *tab, const uint16_t *base
     }
 }
 
-// One pass of a workgroup over trials [pass, pass_end) of analysis a (at most
-// kTiledPassTrials, split evenly over the waves): every bin staged once, each lane's
-// trials added bin by bin, then their YLT (or maxima) written.
-// MAX = false: the YLT (sums of the occurrence-net losses, then the aggregate terms);
-// MAX = true: each trial's largest occurrence-net loss (0 for none).
+// One pass of a workgroup over trials [pass, pass_end) (at most kTiledPassTrials, split
+// evenly over the waves) and bins [bin0, bin1) of analysis a: every bin staged once, each
+// lane's trials added bin by bin into its sums ws[64 g + lane].
+// MAX = false: sums of the occurrence-net losses; MAX = true: each trial's largest.
 // Units u = 4 b + g (bin b, group g) rotate through three register slots (slot u % 3):
 // unit u + 3 is issued once unit u is added.  No load is issued under a condition, so
-// that every wait counts only the loads issued after the one it waits for: bins past
-// the last give empty runs and restage the last bin.
+// that every wait counts only the loads issued after the one it waits for: past the last
+// bin, the last one's loads are issued again and its runs are empty.
 // B24: run starts in 3 bytes each, read as an unaligned 4-byte word (its top byte,
 // the next entry's first, masked off where the value is taken).
 template <bool MAX, bool B24>
-__device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t pass, int64_t pass_end, double *tab, double *ws,
-                                           int lane, uint32_t wave) {
-    const int64_t span = pass_end - pass;
-    const int64_t per_wave = (span + kTiledWaves - 1) / kTiledWaves;
-    const int64_t T0 = min(pass + int64_t(wave) * per_wave, pass_end);
-    const int64_t T1 = min(T0 + per_wave, pass_end);
-    const int32_t nb = a.n_bins;
+__device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64_t T1, int32_t bin0, int32_t bin1,
+                                           double *tab, double *ws, int lane) {
 #pragma unroll
     for (int g = 0; g < kGroups; ++g)
         if (64 * g + lane < kTiledWaveTrials) ws[64 * g + lane] = 0.0;
@@ -202,25 +198,26 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t pass, int
         return uint32_t(w >> (8 * ((3 * i) & 3))) & kRunMask;
     };
     f64x2 st[kStageVecs];
-    stage_load(a, 0, st);
-    __amdgpu_buffer_rsrc_t rc = bin_rsrc(a, 0);
-    const uint16_t *pc = a.ids16 + offset_at(a.region, 0);
+    stage_load(a, bin0, st);
+    __amdgpu_buffer_rsrc_t rc = bin_rsrc(a, bin0);
+    const uint16_t *pc = a.ids16 + offset_at(a.region, bin0);
     Unit U[3];
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
-        U[g].s = run_start(0, g) & kRunMask;
+        U[g].s = run_start(bin0, g) & kRunMask;
         unit_issue(rc, U[g]);
     }
-    uint32_t s3 = run_start(0, 3) & kRunMask;
+    uint32_t s3 = run_start(bin0, 3) & kRunMask;
     uint32_t ge[kGroups];
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) ge[g] = group_end(0, g);
-    for (int32_t b0 = 0; b0 < nb; b0 += 3) {
+    for (int g = 0; g < kGroups; ++g) ge[g] = group_end(bin0, g);
+    for (int32_t b0 = bin0; b0 < bin1; b0 += 3) {
 #pragma unroll
         for (int db = 0; db < 3; ++db) {
             const int32_t b = b0 + db;
-            const bool live = b < nb, more = b + 1 < nb;
-            const int32_t bn = more ? b + 1 : nb - 1;
+            if (db > 0 && b >= bin1) return;   // an exit, not a join: the loop's waits stay exact
+            const bool more = b + 1 < bin1;
+            const int32_t bn = more ? b + 1 : bin1 - 1;
             const __amdgpu_buffer_rsrc_t rn = bin_rsrc(a, bn);
             const uint16_t *pn = a.ids16 + offset_at(a.region, bn);
             uint32_t sn[kGroups], gn[kGroups];
@@ -244,7 +241,7 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t pass, int
                 const uint32_t e = lane == 63 ? ge[g] : nx;
                 const int j = min(64 * g + lane, kTiledWaveTrials - 1);
                 double acc = ws[j];
-                unit_run<MAX>(tab, pc, U[slot], live ? e : 0u, acc);
+                unit_run<MAX>(tab, pc, U[slot], e, acc);
                 if (64 * g + lane < kTiledWaveTrials) ws[j] = acc;
                 if (g == 0) {
                     U[slot].s = s3;
@@ -261,14 +258,47 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t pass, int
             pc = pn;
         }
     }
-#pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        const int64_t t = T0 + 64 * g + lane;
-        if (t < T1) a.ylt[t - a.t_begin] = MAX ? ws[64 * g + lane] : excess(ws[64 * g + lane], a.agg_r, a.agg_l);
+}
+
+// Trials [t0, t1) (at most one pass) over bin groups [g0, g1) of analysis a.  A trial's
+// total is ((s_0 + s_1) + s_2) + ..., s_g its sum over group g's bins: whole (every group
+// here, the total so far in a.ylt, which only this lane touches), or with a.part one
+// group, whose s_g k_tiled_combine adds up in the same order.  So a trial's YLT does not
+// depend on how its groups are spread over workgroups.
+template <bool MAX, bool B24>
+__device__ __forceinline__ void tiled_groups(const TiledArgs &a, int64_t t0, int64_t t1, int32_t g0, int32_t g1,
+                                             double *tab, double *ws, int lane, uint32_t wave) {
+    const int64_t per_wave = (t1 - t0 + kTiledWaves - 1) / kTiledWaves;
+    const int64_t T0 = min(t0 + int64_t(wave) * per_wave, t1);
+    const int64_t T1 = min(T0 + per_wave, t1);
+#pragma unroll 1
+    for (int32_t bg = g0; bg < g1; ++bg) {
+        const int32_t bin0 = bg * a.group_bins;
+        tiled_pass<MAX, B24>(a, T0, T1, bin0, min(bin0 + a.group_bins, a.n_bins), tab, ws, lane);
+#pragma unroll 1
+        for (int g = 0; g < kGroups; ++g) {
+            const int64_t t = T0 + 64 * g + lane;
+            if (t >= T1) continue;
+            double s = ws[64 * g + lane];
+            if (a.part) {
+                a.part[bg * a.part_stride + (t - a.t_begin)] = s;
+                continue;
+            }
+            double *y = a.ylt + (t - a.t_begin);
+            if (bg > 0) {
+                const double x = *y;
+                s = MAX ? (s > x ? s : x) : x + s;
+            }
+            *y = MAX || bg + 1 < a.n_groups ? s : excess(s, a.agg_r, a.agg_l);
+        }
     }
 }
 
-// One analysis: workgroup w owns trials [t_begin + w per_wg, + per_wg), in passes.
+// One analysis.  Whole (part null): workgroup w owns trials [t_begin + w
+// per_wg, + per_wg), in passes, over every bin group.  Split: item i = (bin group, chunk of
+// per_wg trials), a workgroup each, chunks of a group in a row; XCD x (workgroups x, x + 8,
+// ...) takes a contiguous eighth of the items, so its L2 holds the values of its own
+// groups' bins only.
 template <bool MAX, bool B24>
 __global__ __launch_bounds__(1024) void k_trial_tiled(TiledArgs a) {
     __shared__ __attribute__((aligned(16))) double tab[kBinEvents + 2];   // a bin's values, the zero slot
@@ -276,11 +306,45 @@ __global__ __launch_bounds__(1024) void k_trial_tiled(TiledArgs a) {
     const int lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x == 0) tab[kBinEvents] = 0.0;
-    const int64_t wg0 = a.t_begin + int64_t(blockIdx.x) * a.per_wg;
+    int32_t g0 = 0, g1 = a.n_groups;
+    int64_t wg0 = a.t_begin + int64_t(blockIdx.x) * a.per_wg;
+    if (a.part) {
+        const int32_t items = a.chunks * a.n_groups, each = (items + kXcds - 1) / kXcds;
+        const int32_t i = int32_t(blockIdx.x % kXcds) * each + int32_t(blockIdx.x / kXcds);
+        if (i >= items || int32_t(blockIdx.x / kXcds) >= each) return;
+        g0 = i / a.chunks;
+        g1 = g0 + 1;
+        wg0 = a.t_begin + int64_t(i % a.chunks) * a.per_wg;
+    }
     const int64_t wg1 = min(wg0 + a.per_wg, a.t_end);
+#pragma unroll 1
     for (int64_t pass = wg0; pass < wg1; pass += kTiledPassTrials)
-        tiled_pass<MAX, B24>(a, pass, min(pass + int64_t(kTiledPassTrials), wg1), tab, sums + wave * kTiledWaveTrials,
-                             lane, wave);
+        tiled_groups<MAX, B24>(a, pass, min(pass + int64_t(kTiledPassTrials), wg1), g0, g1, tab,
+                               sums + wave * kTiledWaveTrials, lane, wave);
+}
+
+// The totals of split analyses from their bin groups' sums (grid.y: the analysis), two
+// trials per thread.
+template <bool MAX>
+__device__ __forceinline__ void combine_groups(const TiledArgs &a) {
+    const int64_t n = a.t_end - a.t_begin;
+    for (int64_t i = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 2; i < n; i += int64_t(gridDim.x) * 512) {
+        f64x2 s = *reinterpret_cast<const f64x2 *>(a.part + i);   // part rows are 16-byte aligned and padded
+#pragma unroll 4
+        for (int32_t g = 1; g < a.n_groups; ++g) {
+            const f64x2 x = *reinterpret_cast<const f64x2 *>(a.part + g * a.part_stride + i);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) s[k] = MAX ? (x[k] > s[k] ? x[k] : s[k]) : s[k] + x[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (i + k < n) a.ylt[i + k] = MAX ? s[k] : excess(s[k], a.agg_r, a.agg_l);
+    }
+}
+
+template <bool MAX>
+__global__ __launch_bounds__(256) void k_tiled_combine(TiledArgs a) {
+    combine_groups<MAX>(a);
 }
 
 // Analysis j's arguments from device memory, through the scalar data path.
@@ -296,9 +360,10 @@ __device__ __forceinline__ TiledArgs load_args(const TiledArgs *jobs, int32_t j)
 }
 
 // Many analyses in one launch (YLTs): each item is a pass over up to kTiledPassTrials
-// trials of one analysis, taken in list order from a counter by whichever workgroup is
-// free; a workgroup stops once the counter passes the list.  A trial's YLT does not
-// depend on the pass that holds it, so these give the bits of k_trial_tiled.
+// trials of one analysis, over every bin group or (split analyses) one of them, taken in
+// list order from a counter by whichever workgroup is free; a workgroup stops once the
+// counter passes the list.  A trial's YLT does not depend on the pass that holds it, so
+// these give the bits of k_trial_tiled.
 __global__ __launch_bounds__(1024) void k_trial_tiled_items(const TiledArgs *__restrict__ jobs,
                                                             const TiledItem *__restrict__ items, int32_t n_items,
                                                             uint32_t *__restrict__ next) {
@@ -315,13 +380,32 @@ __global__ __launch_bounds__(1024) void k_trial_tiled_items(const TiledArgs *__r
         __syncthreads();   // every wave has read `took` before it is taken again
         if (it >= uint32_t(n_items)) return;
         const uint32_t *iw = reinterpret_cast<const uint32_t *>(items + it);
-        const int32_t job = int32_t(sload(iw + 0));
+        const int32_t job = int32_t(sload(iw + 0)), group = int32_t(sload(iw + 1));
         const int64_t t0 = int64_t(uint64_t(sload(iw + 2)) | (uint64_t(sload(iw + 3)) << 32));
         const int64_t t1 = int64_t(uint64_t(sload(iw + 4)) | (uint64_t(sload(iw + 5)) << 32));
         const TiledArgs a = load_args(jobs, job);
-        if (a.boff24) tiled_pass<false, true>(a, t0, t1, tab, sums + wave * kTiledWaveTrials, lane, wave);
-        else tiled_pass<false, false>(a, t0, t1, tab, sums + wave * kTiledWaveTrials, lane, wave);
+        const int32_t g0 = group < 0 ? 0 : group, g1 = group < 0 ? a.n_groups : group + 1;
+        double *ws = sums + wave * kTiledWaveTrials;
+        if (a.boff24) tiled_groups<false, true>(a, t0, t1, g0, g1, tab, ws, lane, wave);
+        else tiled_groups<false, false>(a, t0, t1, g0, g1, tab, ws, lane, wave);
     }
+}
+
+__global__ __launch_bounds__(256) void k_tiled_combine_items(const TiledArgs *__restrict__ jobs,
+                                                             const int32_t *__restrict__ split) {
+    const TiledArgs a = load_args(jobs, int32_t(sload(split + blockIdx.y)));
+    combine_groups<false>(a);
+}
+
+static unsigned combine_blocks(int64_t n) {
+    return unsigned(std::max<int64_t>(1, std::min<int64_t>((n + 511) / 512, 1024)));
+}
+
+hipError_t launch_tiled_combine_items(const TiledArgs *jobs, const int32_t *split, int32_t n_split, int64_t n_max,
+                                      hipStream_t s) {
+    if (n_split <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tiled_combine_items, dim3(combine_blocks(n_max), unsigned(n_split)), dim3(256), 0, s, jobs, split);
+    return hipGetLastError();
 }
 
 hipError_t launch_trial_tiled_items(const TiledArgs *jobs, const TiledItem *items, int32_t n_items, uint32_t *next,
@@ -335,15 +419,77 @@ hipError_t launch_trial_tiled_items(const TiledArgs *jobs, const TiledItem *item
 
 hipError_t launch_trial_tiled(const TiledArgs &a, int grid, hipStream_t s, bool occ_max, hipEvent_t start,
                               hipEvent_t stop) {
-    const dim3 g(grid), b(kTiledWaves * 64);
+    const int items = a.part ? (a.chunks * a.n_groups + kXcds - 1) / kXcds * kXcds : grid;
+    const dim3 g(items), b(kTiledWaves * 64);
+    hipEvent_t end = a.part ? nullptr : stop;
     if (a.boff24) {
-        if (occ_max) hipExtLaunchKernelGGL((k_trial_tiled<true, true>), g, b, 0, s, start, stop, 0, a);
-        else hipExtLaunchKernelGGL((k_trial_tiled<false, true>), g, b, 0, s, start, stop, 0, a);
+        if (occ_max) hipExtLaunchKernelGGL((k_trial_tiled<true, true>), g, b, 0, s, start, end, 0, a);
+        else hipExtLaunchKernelGGL((k_trial_tiled<false, true>), g, b, 0, s, start, end, 0, a);
     } else {
-        if (occ_max) hipExtLaunchKernelGGL((k_trial_tiled<true, false>), g, b, 0, s, start, stop, 0, a);
-        else hipExtLaunchKernelGGL((k_trial_tiled<false, false>), g, b, 0, s, start, stop, 0, a);
+        if (occ_max) hipExtLaunchKernelGGL((k_trial_tiled<true, false>), g, b, 0, s, start, end, 0, a);
+        else hipExtLaunchKernelGGL((k_trial_tiled<false, false>), g, b, 0, s, start, end, 0, a);
     }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.part) return e;
+    const dim3 cg(combine_blocks(a.t_end - a.t_begin));
+    if (occ_max) hipExtLaunchKernelGGL((k_tiled_combine<true>), cg, dim3(256), 0, s, nullptr, stop, 0, a);
+    else hipExtLaunchKernelGGL((k_tiled_combine<false>), cg, dim3(256), 0, s, nullptr, stop, 0, a);
     return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------
+// Bin groups.  Every workgroup stages the bins it goes through (about 5 us each, from the
+// L2, with few trials; 8.2 us with a full pass of about 16 occurrences per trial), so a
+// launch of few trials spread over all CUs was bound by the staging: 10^5 trials of 1000
+// occurrences over 62 bins took 330 us on 256 workgroups of 391 trials, 50,000 of 600 over
+// 19 bins 122 us.  Instead a workgroup takes a chunk of up to a full pass of trials and a
+// few bins: 75 us + 5 us for the sums in the first case, 31 + 5 us in the second.  Costs in
+// full-pass bin times: 0.75 per workgroup (start, first bin's load,
+// sums written), 0.6 per bin at least.
+static double bin_cost(double trials) { return std::max(0.6, trials / kTiledPassTrials); }
+
+static double split_cost(int64_t n, int64_t chunks, int32_t n_bins, int32_t groups, int n_cu) {
+    const double rounds = double((chunks * groups + n_cu - 1) / n_cu);
+    const int32_t gb = (n_bins + groups - 1) / groups;
+    // the sums' traffic at 4 TB/s and the combining launch
+    return rounds * (0.75 + gb * bin_cost(double(n) / double(chunks))) + 0.7 + double(n) * groups * 16.0 / 4e12 / 8.2e-6;
+}
+
+static double whole_cost(int64_t n, int32_t n_bins, int32_t groups, int n_cu) {
+    const int64_t wgs = std::max<int64_t>(1, std::min<int64_t>(n_cu, (n + 63) / 64));
+    const int64_t per = (n + wgs - 1) / wgs, passes = (per + kTiledPassTrials - 1) / kTiledPassTrials;
+    return double(passes) * (0.75 * groups + n_bins * bin_cost(double(per) / double(passes)));
+}
+
+static double best_split(int64_t n, int32_t n_bins, int32_t groups, int n_cu, int64_t *chunks) {
+    double best = 1e300;
+    const int64_t least = (n + kTiledPassTrials - 1) / kTiledPassTrials;
+    for (int64_t k = least; k <= 4 * least && (k == least || n / k >= 64); k += least) {
+        const double c = split_cost(n, k, n_bins, groups, n_cu);
+        if (c < best) best = c, *chunks = k;
+    }
+    return best;
+}
+
+// Groups of a YET of n trials: as many as its whole trial range is fastest with, so that
+// every trial range of it, alone or in a batch, adds in the same order.
+int32_t tiled_group_count(int64_t n, int32_t n_bins, int n_cu) {
+    int32_t best = 1;
+    double least = whole_cost(n, n_bins, 1, n_cu);
+    for (int32_t g = 2; g <= std::min(n_bins, kTiledMaxGroups); ++g) {
+        const int32_t gb = (n_bins + g - 1) / g, groups = (n_bins + gb - 1) / gb;
+        int64_t chunks = 0;
+        const double c = best_split(n, n_bins, groups, n_cu, &chunks);
+        if (c < 0.97 * least) least = c, best = groups;   // fewer groups unless it pays
+    }
+    return best;
+}
+
+// Chunks to split n trials into, or 0: whole.
+int64_t tiled_chunks(int64_t n, int32_t n_bins, int32_t groups, int n_cu) {
+    if (groups <= 1) return 0;
+    int64_t chunks = 0;
+    return best_split(n, n_bins, groups, n_cu, &chunks) < whole_cost(n, n_bins, groups, n_cu) ? chunks : 0;
 }
 
 }  // namespace ara
