@@ -48,6 +48,9 @@ struct ara_ctx {
         size_t bytes;
     };
     std::vector<Scratch> tiled_ws;
+    std::map<void *, size_t> blocks;                    // device memory of live handles: see dev_alloc
+    std::vector<std::pair<void *, size_t>> kept;        // blocks given back, oldest first
+    size_t kept_bytes = 0;
     int live = 0;                    // handles alive on this context
     std::string msg;
 };
@@ -168,21 +171,86 @@ static ara_status sync_and_check(ara_ctx *c, bool *wide = nullptr, bool copied =
     return ARA_OK;
 }
 
+// Device memory of the context's handles.  A block that a handle gives back is kept for
+// the next one, up to kKeepBytes in all: mapping and unmapping device memory takes far
+// longer than the kernels that use it (10 ms of an 11 ms ingest of 2x10^8 occurrences that
+// replaced a YET of the same size).  The oldest blocks beyond that are returned, all of
+// them when an allocation fails and when the context is destroyed.  A block is kept only
+// once every stream of the device has finished, as hipFree would wait for, so a reused one
+// is idle whatever streams its last user ran on.
+constexpr size_t kKeepBytes = size_t(4) << 30;
+
+// Sizes of a MiB and more in sixteen steps per power of two, so that YETs and tables of
+// nearly the same size share blocks.
+static size_t block_size(size_t bytes) {
+    if (bytes == 0) bytes = 16;
+    if (bytes < (size_t(1) << 20)) return (bytes + 255) & ~size_t(255);
+    const size_t step = size_t(1) << (63 - __builtin_clzll(bytes) - 4);
+    return (bytes + step - 1) & ~(step - 1);
+}
+
+static void blocks_return(ara_ctx *c, size_t keep) {
+    size_t n = 0;
+    while (n < c->kept.size() && c->kept_bytes > keep) {
+        c->kept_bytes -= c->kept[n].second;
+        (void)hipFree(c->kept[n].first);
+        ++n;
+    }
+    c->kept.erase(c->kept.begin(), c->kept.begin() + ptrdiff_t(n));
+}
+
 template <typename T>
 static ara_status dev_alloc(ara_ctx *c, T **p, size_t bytes, const char *what) {
     *p = nullptr;
-    if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(p), bytes);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
-        return hip_fail(c, e, what);
+    const size_t take = block_size(bytes);
+    void *q = nullptr;
+    for (size_t i = c->kept.size(); i-- > 0;)
+        if (c->kept[i].second == take) {
+            q = c->kept[i].first;
+            c->kept.erase(c->kept.begin() + ptrdiff_t(i));
+            c->kept_bytes -= take;
+            break;
+        }
+    if (!q) {
+        hipError_t e = hipMalloc(&q, take);
+        if (e != hipSuccess && !c->kept.empty()) {
+            (void)hipGetLastError();
+            blocks_return(c, 0);
+            e = hipMalloc(&q, take);
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return hip_fail(c, e, what);
+        }
     }
+    try {
+        c->blocks[q] = take;
+    } catch (...) {
+        (void)hipFree(q);
+        return fail(c, ARA_E_OOM, "%s: host allocation", what);
+    }
+    *p = static_cast<T *>(q);
     return ARA_OK;
 }
 
-static void dev_free(void *p) {
-    if (p) (void)hipFree(p);
+static void dev_free(ara_ctx *c, const void *p) {
+    if (!p) return;
+    void *q = const_cast<void *>(p);
+    const auto it = c->blocks.find(q);
+    const size_t bytes = it == c->blocks.end() ? 0 : it->second;
+    if (it != c->blocks.end()) c->blocks.erase(it);
+    if (bytes == 0 || bytes > kKeepBytes || hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(q);
+        return;
+    }
+    blocks_return(c, kKeepBytes - bytes);
+    try {
+        c->kept.emplace_back(q, bytes);
+        c->kept_bytes += bytes;
+    } catch (...) {
+        (void)hipFree(q);
+    }
 }
 
 // The bitmap trial kernel keeps the filter tables and its per-wave event queues
@@ -382,7 +450,7 @@ extern "C" ara_status ara_ctx_create(int device, void *hip_stream, ara_ctx **out
     if (e != hipSuccess) {
         (void)hipGetLastError();
         fail(nullptr, ARA_E_DEVICE, "ctx: %s: %s", step, hipGetErrorString(e));
-        dev_free(c->d_err);
+        if (c->d_err) (void)hipFree(c->d_err);
         if (c->h_err) (void)hipHostFree(c->h_err);
         if (c->h_plan) (void)hipHostFree(c->h_plan);
         delete c;
@@ -397,8 +465,9 @@ extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
     if (c->live > 0) return fail(c, ARA_E_BUSY, "%d handles still alive on this context", c->live);
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    dev_free(c->d_err);   // with d_out
-    for (auto &w : c->tiled_ws) dev_free(w.p);
+    (void)hipFree(c->d_err);   // with d_out
+    for (auto &w : c->tiled_ws) (void)hipFree(w.p);
+    blocks_return(c, 0);
     for (hipEvent_t ev : c->k_ev) (void)hipEventDestroy(ev);
     if (c->h_err) (void)hipHostFree(c->h_err);   // with h_out
     if (c->h_plan) (void)hipHostFree(c->h_plan);
@@ -492,10 +561,10 @@ extern "C" ara_status ara_sync(ara_ctx *c) {
 
 // ------------------------------------------------------------------ YET
 static void yet_free_binned(ara_yet *y) {
-    dev_free(y->ids16);
-    dev_free(y->boff);
-    dev_free(y->boff24);
-    dev_free(y->region);
+    dev_free(y->ctx, y->ids16);
+    dev_free(y->ctx, y->boff);
+    dev_free(y->ctx, y->boff24);
+    dev_free(y->ctx, y->region);
     y->ids16 = nullptr;
     y->boff = nullptr;
     y->boff24 = nullptr;
@@ -553,7 +622,7 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
             s = e == hipSuccess ? sync_and_check(c, &wide) : hip_fail(c, e, "binned yet");
             *ids_checked = e == hipSuccess;   // an ID outside the catalog shows in s
             if (s == ARA_OK && wide) {   // a bin of 2^24 occurrences or more: again with 4-byte run starts
-                dev_free(y->boff24);
+                dev_free(c, y->boff24);
                 y->boff24 = nullptr;
                 b24 = false;
                 continue;
@@ -571,7 +640,7 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
         bool fits = true;
         for (int32_t b = 0; s == ARA_OK && b < nb; ++b) fits = fits && len[size_t(b)] < (1u << 31);
         if (s == ARA_OK && !fits) {
-            dev_free(sums);
+            dev_free(c, sums);
             yet_free_binned(y);
             return ARA_OK;
         }
@@ -583,7 +652,7 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
         }
         break;
     }
-    dev_free(sums);
+    dev_free(c, sums);
     if (s == ARA_OK) {
         y->n_bins = nb;
         y->n_groups = tiled_group_count(n, nb, c->n_cu);
@@ -619,15 +688,15 @@ extern "C" ara_status ara_yet_create(ara_ctx *c, const int32_t *ids, int64_t n_e
         ara_status s = dev_alloc(c, &di, size_t(n_events) * 4, "yet ids");
         if (s == ARA_OK) s = dev_alloc(c, &doff, size_t(n_trials + 1) * 8, "yet offsets");
         if (s != ARA_OK) {
-            dev_free(di);
+            dev_free(c, di);
             delete y;
             return s;
         }
         hipError_t e = hipMemcpy(di, ids, size_t(n_events) * 4, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(doff, offs, size_t(n_trials + 1) * 8, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
-            dev_free(di);
-            dev_free(doff);
+            dev_free(c, di);
+            dev_free(c, doff);
             delete y;
             return hip_fail(c, e, "yet upload");
         }
@@ -655,10 +724,10 @@ extern "C" ara_status ara_yet_create(ara_ctx *c, const int32_t *ids, int64_t n_e
     }
     if (s != ARA_OK) {
         if (y->owns) {
-            dev_free(const_cast<int32_t *>(y->ids));
-            dev_free(const_cast<int64_t *>(y->offs));
+            dev_free(c, const_cast<int32_t *>(y->ids));
+            dev_free(c, const_cast<int64_t *>(y->offs));
         }
-        dev_free(y->ids24);
+        dev_free(c, y->ids24);
         yet_free_binned(y);
         delete y;
         return s;
@@ -673,10 +742,10 @@ extern "C" ara_status ara_yet_release(ara_yet *y) {
     (void)hipSetDevice(y->ctx->device);
     (void)hipStreamSynchronize(y->ctx->stream);
     if (y->owns) {
-        dev_free(const_cast<int32_t *>(y->ids));
-        dev_free(const_cast<int64_t *>(y->offs));
+        dev_free(y->ctx, const_cast<int32_t *>(y->ids));
+        dev_free(y->ctx, const_cast<int64_t *>(y->offs));
     }
-    dev_free(y->ids24);
+    dev_free(y->ctx, y->ids24);
     yet_free_binned(y);
     y->ctx->live--;
     delete y;
@@ -727,12 +796,12 @@ extern "C" ara_status ara_yet_binned(const ara_yet *y, int32_t *n_bins, int64_t 
 // ------------------------------------------------------------------ ELT
 static void elt_free(ara_elt *t) {
     if (t->owns_pairs) {
-        dev_free(const_cast<int32_t *>(t->pair_ids));
-        dev_free(const_cast<double *>(t->pair_losses));
+        dev_free(t->ctx, const_cast<int32_t *>(t->pair_ids));
+        dev_free(t->ctx, const_cast<double *>(t->pair_losses));
     }
-    dev_free(t->dat);
-    dev_free(t->seen);
-    dev_free(t->d_desc);
+    dev_free(t->ctx, t->dat);
+    dev_free(t->ctx, t->seen);
+    dev_free(t->ctx, t->d_desc);
     delete t;
 }
 
@@ -854,16 +923,16 @@ static ara_status layer_enqueue_build(ara_layer *L, int flags, bool ranks) {
 }
 
 static void layer_free(ara_layer *L) {
-    dev_free(L->d_descs);
-    dev_free(L->t.comb);
-    dev_free(L->t.occ);
-    dev_free(L->t.bitmap);
-    dev_free(L->t.nz);
-    dev_free(L->t.rank);
-    dev_free(L->t.rel16);
-    dev_free(L->t.base32);
-    dev_free(L->t.vals);
-    dev_free(L->t.n_flagged);
+    dev_free(L->ctx, L->d_descs);
+    dev_free(L->ctx, L->t.comb);
+    dev_free(L->ctx, L->t.occ);
+    dev_free(L->ctx, L->t.bitmap);
+    dev_free(L->ctx, L->t.nz);
+    dev_free(L->ctx, L->t.rank);
+    dev_free(L->ctx, L->t.rel16);
+    dev_free(L->ctx, L->t.base32);
+    dev_free(L->ctx, L->t.vals);
+    dev_free(L->ctx, L->t.n_flagged);
     delete L;
 }
 
@@ -1054,7 +1123,7 @@ static void *tiled_scratch(ara_ctx *c, size_t bytes) {
         c->tiled_ws.push_back({c->stream, p, take});
     } else {
         (void)hipStreamSynchronize(c->stream);   // earlier launches may still use the smaller one
-        dev_free(c->tiled_ws[i].p);
+        (void)hipFree(c->tiled_ws[i].p);
         c->tiled_ws[i].p = p;
         c->tiled_ws[i].bytes = take;
     }
@@ -1127,7 +1196,7 @@ extern "C" ara_status ara_analyze(ara_ctx *c, const ara_yet *y, const ara_layer 
     }
     if (mem == ARA_MEM_HOST) {
         (void)hipStreamSynchronize(c->stream);
-        dev_free(dst);
+        dev_free(c, dst);
     }
     return s;
 }
@@ -1171,7 +1240,7 @@ extern "C" ara_status ara_analyze_occ_max(ara_ctx *c, const ara_yet *y, const ar
     }
     if (mem == ARA_MEM_HOST) {
         (void)hipStreamSynchronize(c->stream);
-        dev_free(dst);
+        dev_free(c, dst);
     }
     return s;
 }
@@ -1203,7 +1272,7 @@ extern "C" ara_status ara_analyze_events(ara_ctx *c, const ara_yet *y, const ara
             if (host[k] && len[k] > 0) {
                 s = dev_alloc(c, &dev[k], len[k] * 8, "event output staging");
                 if (s != ARA_OK) {
-                    for (int j = 0; j < k; ++j) dev_free(dev[j]);
+                    for (int j = 0; j < k; ++j) dev_free(c, dev[j]);
                     return s;
                 }
             }
@@ -1224,7 +1293,7 @@ extern "C" ara_status ara_analyze_events(ara_ctx *c, const ara_yet *y, const ara
             }
         ara_status s2 = sync_and_check(c);
         if (s == ARA_OK) s = s2;
-        for (int k = 0; k < 5; ++k) dev_free(dev[k]);
+        for (int k = 0; k < 5; ++k) dev_free(c, dev[k]);
     }
     return s;
 }
@@ -1252,9 +1321,9 @@ extern "C" ara_status ara_lookup(ara_ctx *c, const ara_layer *L, const int32_t *
         }
         di = ti;
         if (s != ARA_OK) {
-            dev_free(ti);
-            dev_free(dg);
-            dev_free(dout);
+            dev_free(c, ti);
+            dev_free(c, dg);
+            dev_free(c, dout);
             return s;
         }
     }
@@ -1272,9 +1341,9 @@ extern "C" ara_status ara_lookup(ara_ctx *c, const ara_layer *L, const int32_t *
         }
         ara_status s2 = sync_and_check(c);
         if (s == ARA_OK) s = s2;
-        dev_free(const_cast<int32_t *>(di));
-        dev_free(dg);
-        dev_free(dout);
+        dev_free(c, const_cast<int32_t *>(di));
+        dev_free(c, dg);
+        dev_free(c, dout);
     }
     return s;
 }
@@ -1312,7 +1381,7 @@ extern "C" ara_status ara_sort_desc(ara_ctx *c, const double *in, int64_t n, dou
     s = e == hipSuccess ? ARA_OK : hip_fail(c, e, "sort");
     if (owned) {
         (void)hipStreamSynchronize(c->stream);
-        dev_free(w);
+        dev_free(c, w);
     }
     return s;
 }
@@ -1384,7 +1453,7 @@ extern "C" ara_status ara_risk_measures(ara_ctx *c, const double *ylt, int64_t n
         if (s != ARA_OK) return s;
         hipError_t e = hipMemcpy(tmp, ylt, size_t(n) * 8, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
-            dev_free(tmp);
+            dev_free(c, tmp);
             return hip_fail(c, e, "ylt upload");
         }
         dy = tmp;
@@ -1394,8 +1463,8 @@ extern "C" ara_status ara_risk_measures(ara_ctx *c, const double *ylt, int64_t n
     s = workspace_for(c, n, ws, ws_bytes, &w, &owned);
     if (s == ARA_OK) s = risk_on_device(c, dy, n, ks, n_rp, pml, tvar, w);
     if (owned || tmp) (void)hipStreamSynchronize(c->stream);
-    if (owned) dev_free(w);
-    dev_free(tmp);
+    if (owned) dev_free(c, w);
+    dev_free(c, tmp);
     return s;
 }
 
@@ -1612,7 +1681,7 @@ static ara_status batch_set_items(ara_batch *b, int64_t events) {
     }
     const std::vector<BatchItem> items = group_items(b->hjobs, tb.data(), te.data(), b->mean_len, events, b->mode_off,
                                                      b->mode_cnt);
-    dev_free(b->d_items);
+    dev_free(c, b->d_items);
     b->d_items = nullptr;
     b->n_items = int32_t(items.size());
     if (b->n_items > 0) {
@@ -1920,8 +1989,8 @@ extern "C" ara_status ara_batch_portfolio(ara_batch *b, double *out) {
 constexpr size_t kRiskWsBytes = size_t(64) << 20;
 
 static void batch_risk_free(ara_batch *b) {
-    dev_free(b->d_rjobs);
-    dev_free(b->risk_ws);
+    dev_free(b->ctx, b->d_rjobs);
+    dev_free(b->ctx, b->risk_ws);
     if (b->h_risk) (void)hipHostFree(b->h_risk);
     b->d_rjobs = nullptr;
     b->risk_ws = nullptr;
@@ -2029,14 +2098,14 @@ extern "C" ara_status ara_batch_release(ara_batch *b) {
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->cap) (void)hipStreamDestroy(b->cap);
-    dev_free(b->d_jobs);
-    dev_free(b->d_items);
-    dev_free(b->d_tjobs);
-    dev_free(b->d_titems);
-    dev_free(b->d_next);
-    dev_free(b->d_split);
-    dev_free(b->d_part);
-    dev_free(b->d_ylts);
+    dev_free(c, b->d_jobs);
+    dev_free(c, b->d_items);
+    dev_free(c, b->d_tjobs);
+    dev_free(c, b->d_titems);
+    dev_free(c, b->d_next);
+    dev_free(c, b->d_split);
+    dev_free(c, b->d_part);
+    dev_free(c, b->d_ylts);
     batch_risk_free(b);
     if (b->counted) c->live--;
     delete b;
@@ -2339,10 +2408,10 @@ static void server_free(ara_server *sv) {
     for (ServerLane &ln : sv->lanes) {
         for (ara_layer *L : ln.slots)
             if (L) ara_layer_release(L);
-        dev_free(ln.d_jobs);
-        dev_free(ln.d_items);
-        dev_free(ln.d_rjobs);
-        dev_free(ln.ws);
+        dev_free(sv->ctx, ln.d_jobs);
+        dev_free(sv->ctx, ln.d_items);
+        dev_free(sv->ctx, ln.d_rjobs);
+        dev_free(sv->ctx, ln.ws);
         if (ln.h_jobs) (void)hipHostFree(ln.h_jobs);
         if (ln.h_items) (void)hipHostFree(ln.h_items);
         if (ln.h_descs) (void)hipHostFree(ln.h_descs);
@@ -2352,7 +2421,7 @@ static void server_free(ara_server *sv) {
         if (ln.pc) (void)ara_ctx_destroy(ln.pc);
         if (ln.stream) (void)hipStreamDestroy(ln.stream);
     }
-    dev_free(sv->arena);
+    dev_free(sv->ctx, sv->arena);
     for (auto &p : sv->live) delete p.second;
     delete sv;
 }
