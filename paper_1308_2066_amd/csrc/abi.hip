@@ -311,7 +311,11 @@ static ara_status plan_trial(ara_ctx *c, const ara_layer *L, int64_t n_trials, d
     tl.qcap = pl == ARA_PLACE_LDS_BITMAP ? qcap : 0;
     tl.lane = pl != ARA_PLACE_LDS_BITMAP &&
               (c->trial_mode == 2 || (c->trial_mode == 0 && mean_len <= double(kLaneModeMaxMean)));
-    tl.block = c->block_threads ? c->block_threads : (pl == ARA_PLACE_GLOBAL_DENSE || tl.lane ? 256 : 1024);
+    // a lane per trial: workgroups of 256 spread few trials over more CUs; with many, one
+    // table in LDS serves 1024 (two tables of a 10,000-event catalog fill a CU's LDS)
+    const bool many = n_trials >= int64_t(c->n_cu) * 1024;
+    tl.block = c->block_threads ? c->block_threads
+                                : (pl == ARA_PLACE_GLOBAL_DENSE || (tl.lane && !many) ? 256 : 1024);
     int per_cu = c->grid_per_cu;
     if (per_cu == 0) {
         const int by_threads = 2048 / tl.block;

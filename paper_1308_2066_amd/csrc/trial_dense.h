@@ -65,12 +65,21 @@ __device__ __forceinline__ void stage_lds(const TrialArgs &a, uint32_t *lds) {
         stage_bitmap(a, lds);
         return;
     } else if (PL == ARA_PLACE_LDS_DENSE) {
-        // occurrence-net table, catalog doubles = 2*catalog words
+        // occurrence-net table, catalog doubles = 2*catalog words; eight loads of a thread in
+        // flight (one at a time, the 20 loads of a 256-thread workgroup for a 10,000-event
+        // catalog took most of the 20 us of a small launch)
         const uint32_t *g = reinterpret_cast<const uint32_t *>(a.occ);
-        const int n = 2 * a.catalog, n4 = n >> 2;
+        const int n = 2 * a.catalog, n4 = n >> 2, bd = int(blockDim.x);
         u32x4 *l4 = reinterpret_cast<u32x4 *>(lds);
         const u32x4 *g4 = reinterpret_cast<const u32x4 *>(g);
-        for (int i = threadIdx.x; i < n4; i += blockDim.x) l4[i] = g4[i];
+        for (int i0 = threadIdx.x; i0 < n4; i0 += 8 * bd) {
+            u32x4 v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = g4[min(i0 + k * bd, n4 - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i0 + k * bd < n4) l4[i0 + k * bd] = v[k];
+        }
         for (int i = (n4 << 2) + threadIdx.x; i < n; i += blockDim.x) lds[i] = g[i];
     }
     __syncthreads();
@@ -192,47 +201,103 @@ __device__ __forceinline__ void dense_wave_run(const TrialArgs &a, uint32_t *lds
 // Lane per trial, for short trials: lane i of the workgroup's wave w takes trial
 // first + i, first + i + stride, ... and adds its occurrences' values in time order
 // (the same sequence of additions as a sequential loop over the trial, so P is
-// exactly the oracle's cumulative total).  IDs come in 16-byte groups of the lane's
-// own trial; the occurrence-net values from the dense table.
+// exactly the oracle's cumulative total).  The occurrence-net values come from the dense
+// table.
+//   A lane reads its trial 16 IDs (64 bytes) at a time from the trial's first ID, two such
+// chunks ahead, through a buffer record that starts at the wave's first trial and ends
+// with the YET (a 16-byte load gives 0 for its words past the end).
+//   What bounds it: VALU instructions per ID.  With 64-bit position tests for each ID,
+// about 20 a lookup, and each chunk's loads waited for before the next one's were issued,
+// 8.3x10^8 occurrences took 1.58 ms; here the lanes of a chunk that lies inside every
+// lane's trial test nothing.
+constexpr int kLaneIds = 16;
+
+__device__ __forceinline__ void lane_load(__amdgpu_buffer_rsrc_t r, uint32_t at, bool live, u32x4 (&q)[4]) {
+    const uint32_t off = live ? at * 4u : 0xFFFFFF00u;   // outside any record: no memory access
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = __builtin_amdgcn_raw_buffer_load_b128(r, int(off + 16u * u), 0, 0);
+}
+
+// Values of the first `left` IDs of q (all 16 when ALL); the others' are +0.0.
+template <int PL, bool ALL>
+__device__ __forceinline__ void lane_lookup(const double *tab, __amdgpu_buffer_rsrc_t vr, uint32_t C, const u32x4 (&q)[4],
+                                            int32_t left, double (&v)[kLaneIds], uint32_t &mx) {
+#pragma unroll
+    for (int j = 0; j < kLaneIds; ++j) {
+        const bool in = ALL || j < left;
+        const uint32_t id = in ? q[j >> 2][j & 3] : 0u;
+        mx = max(mx, id);
+        if constexpr (PL == ARA_PLACE_LDS_DENSE) {
+            const double x = tab[min(id, C - 1u)];
+            v[j] = in ? x : 0.0;   // adding +0.0 leaves P's bits unchanged
+        } else {
+            const uint32_t off = in ? id * 8u : 0xFFFFFFF8u;   // past the record: 0
+            v[j] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(vr, int(off), 0, 0));
+        }
+    }
+}
+
+template <int PL>
+__device__ __forceinline__ void lane_step(const double *tab, __amdgpu_buffer_rsrc_t vr, uint32_t C,
+                                          __amdgpu_buffer_rsrc_t rs, u32x4 (&q)[4], uint32_t at, int32_t left, double &P,
+                                          uint32_t &mx) {
+    double v[kLaneIds];
+    if (PL == ARA_PLACE_LDS_DENSE && __builtin_amdgcn_ballot_w64(left < kLaneIds) == 0)
+        lane_lookup<PL, true>(tab, vr, C, q, left, v, mx);
+    else
+        lane_lookup<PL, false>(tab, vr, C, q, left, v, mx);
+    lane_load(rs, at + 2 * kLaneIds, left > 2 * kLaneIds, q);   // the chunk after the next
+#pragma unroll
+    for (int j = 0; j < kLaneIds; ++j) P += v[j];
+}
+
 template <int PL>
 __device__ __forceinline__ void dense_lane_run(const TrialArgs &a, const uint32_t *lds, int64_t first, int64_t stride) {
     const uint32_t C = uint32_t(a.catalog);
-    const double *tab = PL == ARA_PLACE_LDS_DENSE ? reinterpret_cast<const double *>(lds) : a.occ;
-    const i32x4 *ids4 = reinterpret_cast<const i32x4 *>(a.ids);
-    uint32_t bad = 0;
-    for (int64_t t = first; t < a.t_end; t += stride) {
-        int64_t o0 = a.offs[t], o1 = a.offs[t + 1];
-        if (!(o0 >= 0 && o0 <= o1 && o1 <= a.n_events)) {
+    const double *tab = reinterpret_cast<const double *>(lds);
+    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)a.occ, 0, int(C * 8u), kBufWord3);
+    uint32_t bad = 0, mx = 0;
+    // the wave's trials are consecutive; lanes past the last trial go along with none
+    for (int64_t t = first; __builtin_amdgcn_ballot_w64(t < a.t_end) != 0; t += stride) {
+        const bool live = t < a.t_end;
+        int64_t o0 = 0, o1 = 0;
+        if (live) o0 = a.offs[t], o1 = a.offs[t + 1];
+        const bool ok = o0 >= 0 && o0 <= o1 && o1 <= a.n_events;
+        if (!ok) {
             bad |= ERR_OFFSETS;
             o0 = o1 = 0;
         }
+        const int64_t base = uniform64(o0);
+        constexpr int64_t kSpan = int64_t(1) << 28;
         double P = 0.0;
-        // 16 IDs (four 16-byte groups) are read before they are added, in time order
-        for (int64_t g0 = o0 >> 2; 4 * g0 < o1; g0 += 4) {
-            int32_t id16[16];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t g = g0 + u;
-                if (4 * g + 4 <= a.n_events) {
-                    const i32x4 x = ids4[g];
-                    id16[4 * u] = x.x, id16[4 * u + 1] = x.y, id16[4 * u + 2] = x.z, id16[4 * u + 3] = x.w;
-                } else {   // past the YET's last full group: no read past its end
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) id16[4 * u + j] = 4 * g + j < a.n_events ? a.ids[4 * g + j] : 0;
-                }
+        if (__builtin_amdgcn_ballot_w64(o1 > o0 && (o0 < base || o1 - base > kSpan)) != 0) {
+            // trials too long for one record (or bad offsets among them): one ID at a time
+            for (int64_t p = o0; p < o1; ++p) {
+                const uint32_t id = uint32_t(a.ids[p]);
+                mx = max(mx, id);
+                P += PL == ARA_PLACE_LDS_DENSE ? tab[min(id, C - 1u)] : a.occ[min(id, C - 1u)];
             }
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int64_t pos = 4 * g0 + j;
-                const uint32_t id = uint32_t(id16[j]);
-                const bool valid = pos >= o0 && pos < o1;
-                bad |= valid && id >= C ? uint32_t(ERR_ID_RANGE) : 0u;
-                const double v = tab[id < C ? id : C - 1u];
-                P += valid && id < C ? v : 0.0;   // adding +0.0 leaves P's bits unchanged
+        } else {
+            const int64_t n = min(a.n_events - base, kSpan);
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(a.ids + base), 0, int(uint32_t(n) * 4u), kBufWord3);
+            uint32_t at = o1 > o0 ? uint32_t(o0 - base) : 0u;
+            int32_t left = int32_t(o1 - o0);
+            u32x4 A[4], B[4];
+            lane_load(rs, at, left > 0, A);
+            lane_load(rs, at + kLaneIds, left > kLaneIds, B);
+            while (__builtin_amdgcn_ballot_w64(left > 0) != 0) {
+                lane_step<PL>(tab, vr, C, rs, A, at, left, P, mx);
+                at += kLaneIds;
+                left -= kLaneIds;
+                lane_step<PL>(tab, vr, C, rs, B, at, left, P, mx);
+                at += kLaneIds;
+                left -= kLaneIds;
             }
         }
-        a.ylt[t - a.t_begin] = excess(P, a.agg_r, a.agg_l);
+        if (live) a.ylt[t - a.t_begin] = excess(P, a.agg_r, a.agg_l);
     }
+    if (mx >= C) bad |= ERR_ID_RANGE;
     if (bad) atomicOr(a.err, bad);
 }
 
