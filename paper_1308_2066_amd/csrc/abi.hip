@@ -311,11 +311,19 @@ static ara_status plan_trial(ara_ctx *c, const ara_layer *L, int64_t n_trials, d
     tl.qcap = pl == ARA_PLACE_LDS_BITMAP ? qcap : 0;
     tl.lane = pl != ARA_PLACE_LDS_BITMAP &&
               (c->trial_mode == 2 || (c->trial_mode == 0 && mean_len <= double(kLaneModeMaxMean)));
-    // a lane per trial: workgroups of 256 spread few trials over more CUs; with many, one
-    // table in LDS serves 1024 (two tables of a 10,000-event catalog fill a CU's LDS)
-    const bool many = n_trials >= int64_t(c->n_cu) * 1024;
+    // a lane per trial: workgroups of 256 spread few trials over more CUs, and each lane reads
+    // its own IDs (10,000 trials of 100: 9.4 us, staged 12 us, the chain of round trips is
+    // longer); with many, one table in LDS serves 1024 and the IDs are staged (8.3x10^6
+    // trials of 100 in a batch: 0.73 ms, read by the lanes 1.19 ms)
+    const bool many = n_trials >= int64_t(c->n_cu) * 512;
     tl.block = c->block_threads ? c->block_threads
                                 : (pl == ARA_PLACE_GLOBAL_DENSE || (tl.lane && !many) ? 256 : 1024);
+    tl.staged = tl.lane && many && pl == ARA_PLACE_LDS_DENSE && c->lds_max >= kLdsMaxBytes &&
+                lane_staged_fits(L->catalog, tl.block / 64);
+    if (tl.staged) {
+        lds = int64_t(lane_table_bytes(L->catalog)) + int64_t(tl.block / 64) * kStageBytes;
+        tl.lds_bytes = size_t(lds);
+    }
     int per_cu = c->grid_per_cu;
     if (per_cu == 0) {
         const int by_threads = 2048 / tl.block;
@@ -891,15 +899,13 @@ extern "C" ara_status ara_elt_release(ara_elt *t) {
 static ara_status layer_enqueue_filter(ara_layer *L) {
     ara_ctx *c = L->ctx;
     L->ranks_ready = false;
-    hipError_t e = launch_layer_filter(L->catalog, L->f32, L->terms.occ_retention, L->terms.occ_limit, L->t, c->stream,
-                                       false);
+    hipError_t e = launch_layer_filter(L->catalog, L->f32, L->terms.occ_retention, L->terms.occ_limit, L->t, c->stream);
     return e == hipSuccess ? ARA_OK : hip_fail(c, e, "layer filter");
 }
 
-// The filter-based kernels (LDS bitmap, lookups, events, occurrence maxima outside the
-// tiled path, batches) read the layer's ranks and compacted values; the tiled kernel
-// reads its occurrence values only.  Enqueued on the context's stream, before the
-// caller's kernels.
+// The LDS-filter kernels read the layer's ranks and compacted values; the others its
+// occurrence values (or combined table) only.  Enqueued on the context's stream, before
+// the caller's kernels.
 static ara_status layer_ranks(const ara_layer *L) {
     if (L->ranks_ready) return ARA_OK;
     ara_ctx *c = L->ctx;
@@ -909,7 +915,7 @@ static ara_status layer_ranks(const ara_layer *L) {
     return ARA_OK;
 }
 
-static ara_status layer_enqueue_build(ara_layer *L, int flags, bool ranks) {
+static ara_status layer_enqueue_build(ara_layer *L, int flags) {
     ara_ctx *c = L->ctx;
     const int n = int(L->elts.size());
     hipError_t e = hipSuccess;
@@ -920,10 +926,8 @@ static ara_status layer_enqueue_build(ara_layer *L, int flags, bool ranks) {
     L->ranks_ready = false;
     if (e == hipSuccess)
         e = launch_layer_tables(L->d_descs, n, L->catalog, L->f32, L->terms.occ_retention, L->terms.occ_limit, L->t,
-                                c->stream, ranks);
-    if (e != hipSuccess) return hip_fail(c, e, "layer build");
-    L->ranks_ready = ranks;
-    return ARA_OK;
+                                c->stream);
+    return e == hipSuccess ? ARA_OK : hip_fail(c, e, "layer build");
 }
 
 static void layer_free(ara_layer *L) {
@@ -982,7 +986,7 @@ extern "C" ara_status ara_layer_create(ara_ctx *c, ara_elt *const *elts, int32_t
         hipError_t e = hipMemcpy(L->d_descs, d.data(), sizeof(EltDesc) * size_t(n_elts), hipMemcpyHostToDevice);
         if (e != hipSuccess) s = hip_fail(c, e, "layer descriptors upload");
     }
-    if (s == ARA_OK) s = layer_enqueue_build(L, 0, true);
+    if (s == ARA_OK) s = layer_enqueue_build(L, 0);
     if (s != ARA_OK) {
         layer_free(L);
         return s;
@@ -1005,7 +1009,7 @@ extern "C" ara_status ara_layer_set_terms(ara_ctx *c, ara_layer *L, const ara_la
 extern "C" ara_status ara_layer_build(ara_ctx *c, ara_layer *L, int flags) {
     if (!c || !L || L->ctx != c || (flags & ~ARA_BUILD_TABLES)) return ARA_E_INVALID_ARG;
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
-    return layer_enqueue_build(L, flags, false);
+    return layer_enqueue_build(L, flags);
 }
 
 extern "C" ara_status ara_layer_stats(ara_ctx *c, const ara_layer *L, int64_t *n_flagged, int32_t *placement,
@@ -1165,7 +1169,7 @@ extern "C" ara_status ara_analyze(ara_ctx *c, const ara_yet *y, const ara_layer 
     TrialLaunch tl{};
     s = plan_trial(c, L, t1 - t0, y->n_trials ? double(y->n_events) / double(y->n_trials) : 0.0, tl,
                    y->ids16 ? 1 : 0);
-    if (s == ARA_OK && tl.placement != ARA_PLACE_LDS_TILES) s = layer_ranks(L);
+    if (s == ARA_OK && tl.placement == ARA_PLACE_LDS_BITMAP) s = layer_ranks(L);
     if (s != ARA_OK) return s;
     double *dst = ylt;
     if (mem == ARA_MEM_HOST) {
@@ -1189,6 +1193,7 @@ extern "C" ara_status ara_analyze(ara_ctx *c, const ara_yet *y, const ara_layer 
         }
         TrialArgs a = trial_args(y, L, tb, te, dst + (tb - t0));
         a.qcap = tl.qcap;
+        a.staged = tl.staged ? 1 : 0;
         e = launch_trial_ylt(a, tl, c->stream);
     }
     if (e == hipSuccess && timing && !tiles) e = hipEventRecord(t_stop, c->stream);
@@ -1215,7 +1220,7 @@ extern "C" ara_status ara_analyze_occ_max(ara_ctx *c, const ara_yet *y, const ar
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
     TrialLaunch tl{};
     s = plan_trial(c, L, t1 - t0, 1e9, tl, y->ids16 ? 1 : 0);
-    if (s == ARA_OK && tl.placement != ARA_PLACE_LDS_TILES) s = layer_ranks(L);
+    if (s == ARA_OK && tl.placement == ARA_PLACE_LDS_BITMAP) s = layer_ranks(L);
     if (s != ARA_OK) return s;
     const int by_lds = tl.lds_bytes > 0 ? std::max(1, int(c->lds_max / int64_t(tl.lds_bytes))) : 8;
     const int64_t grid = std::min<int64_t>(int64_t(c->n_cu) * std::min(8, by_lds), (t1 - t0 + 255) / 256);
@@ -1256,8 +1261,6 @@ extern "C" ara_status ara_analyze_events(ara_ctx *c, const ara_yet *y, const ara
     if (mem != ARA_MEM_HOST && mem != ARA_MEM_DEVICE) return fail(c, ARA_E_INVALID_ARG, "analyze_events: bad memory kind");
     if (t1 == t0) return ARA_OK;
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
-    s = layer_ranks(L);
-    if (s != ARA_OK) return s;
     // number of occurrences in the range, from the device offsets
     HIP_OR_RETURN(c, hipMemcpyAsync(c->h_out, y->offs + t0, 8, hipMemcpyDeviceToHost, c->stream), "read offsets");
     HIP_OR_RETURN(c, hipMemcpyAsync(c->h_out + 1, y->offs + t1, 8, hipMemcpyDeviceToHost, c->stream), "read offsets");
@@ -1310,7 +1313,7 @@ extern "C" ara_status ara_lookup(ara_ctx *c, const ara_layer *L, const int32_t *
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
     TrialLaunch tl{};
     ara_status s = plan_trial(c, L, 1 << 20, 1e9, tl);
-    if (s == ARA_OK) s = layer_ranks(L);
+    if (s == ARA_OK && tl.placement == ARA_PLACE_LDS_BITMAP) s = layer_ranks(L);
     if (s != ARA_OK) return s;
     const int32_t *di = ids;
     double *dg = g, *dout = o;
@@ -1727,6 +1730,7 @@ extern "C" ara_status ara_batch_create(ara_ctx *c, const ara_job *jobs, int32_t 
         h.a = trial_args(jb.yet, jb.layer, jb.trial_begin, jb.trial_end, jb.ylt);
         h.a.qcap = tl.qcap;
         h.mode = batch_mode(tl, h.a.ids24 != nullptr);
+        h.a.staged = h.mode == kModeLaneLds && lane_staged_fits(jb.layer->catalog, 16) ? 1 : 0;   // k_batch: 16 waves
         h.placement = tl.placement;
         if (h.mode == kModeTiled && jb.trial_end > jb.trial_begin) {
             b->tjobs.push_back(tiled_args(jb.yet, jb.layer, jb.trial_begin, jb.trial_end, jb.ylt, tl.grid));
@@ -1896,7 +1900,8 @@ extern "C" ara_status ara_batch_run(ara_batch *b) {
     if (b->jobs.empty()) return ARA_OK;
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
     ara_status s = batch_refresh_terms(b);
-    for (size_t j = 0; j < b->jobs.size() && s == ARA_OK; ++j) s = layer_ranks(b->jobs[j].layer);
+    for (size_t j = 0; j < b->jobs.size() && s == ARA_OK; ++j)
+        if (b->hjobs[j].placement == ARA_PLACE_LDS_BITMAP) s = layer_ranks(b->jobs[j].layer);
     if (s != ARA_OK) return s;
     if (!b->exec) {
         bool computed = false;
@@ -2166,12 +2171,11 @@ struct ServerLane {
     hipStream_t stream = nullptr;
     hipEvent_t done = nullptr;        // recorded once the lane's results and error word are on the host
     std::vector<ara_layer *> slots;   // one request's tables each (member list: every pool ELT)
-    BatchJob *d_jobs = nullptr, *h_jobs = nullptr;
-    BatchItem *d_items = nullptr, *h_items = nullptr;
-    int32_t item_cap = 0;
+    // an iteration's descriptors (layer builds and their ELTs, jobs, work items, risk
+    // measures), written to pinned memory and copied to the device in one piece
+    unsigned char *h_stage = nullptr, *d_stage = nullptr;
+    size_t stage_bytes = 0;
     int32_t mode_off[kBatchModes] = {}, mode_cnt[kBatchModes] = {};
-    EltDesc *h_descs = nullptr;       // pinned: every slot's descriptors
-    RiskJob *d_rjobs = nullptr, *h_rjobs = nullptr;   // h_rjobs: pinned
     double *h_res = nullptr;          // pinned: [slot][2 * n_rp], written by the risk kernels
     unsigned char *ws = nullptr;      // workspaces of the risk measures of long YLTs
     size_t ws_bytes = 0;
@@ -2211,68 +2215,51 @@ static constexpr int64_t kServerEventsPerItem = int64_t(1) << 18;
 static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vector<ServerRequest *> &take) {
     ara_ctx *pc = ln.pc;
     const int32_t nr = int32_t(sv->rps.size());
-    const size_t np = sv->pool.size();
     const int32_t nj = int32_t(take.size());
     const double mean_len = double(sv->yet->n_events) / double(std::max<int64_t>(1, sv->yet->n_trials));
     std::vector<std::pair<int32_t, int>> tiled;   // requests of the tiled kernel: index, grid
+    std::vector<int32_t> filtered;                // requests of the LDS-filter kernel
+    std::vector<EltDesc> descs;
+    std::vector<LayerBuild> builds;
+    std::vector<BatchJob> jobs;
+    std::vector<RiskJob> risks;
+    std::vector<int64_t> tb, te, ml(size_t(nj), std::max<int64_t>(1, int64_t(std::llround(mean_len))));
     for (int32_t i = 0; i < nj; ++i) {
         ServerRequest *r = take[size_t(i)];
         ara_layer *L = ln.slots[size_t(i)];
-        EltDesc *hd = ln.h_descs + size_t(i) * np;
         // the slot layer keeps its member list (every pool ELT, for the ELTs' user
-        // counts); its descriptors, precision and terms become the request's
+        // counts); its precision and terms become the request's
         bool all_f32 = !r->elts.empty();
-        for (size_t k = 0; k < r->elts.size(); ++k) {
-            const ara_elt *e = sv->pool[size_t(r->elts[k])];
-            hd[k] = e->desc;
-            all_f32 = all_f32 && e->prec == ARA_F32;
+        for (int32_t k : r->elts) {
+            descs.push_back(sv->pool[size_t(k)]->desc);
+            all_f32 = all_f32 && sv->pool[size_t(k)]->prec == ARA_F32;
         }
         L->f32 = all_f32;
         L->terms = r->terms;
-        const int n = int(r->elts.size());
-        hipError_t e = hipMemcpyAsync(L->d_descs, hd, sizeof(EltDesc) * size_t(n), hipMemcpyHostToDevice, ln.stream);
-        if (e == hipSuccess)
-            e = launch_layer_tables(L->d_descs, n, L->catalog, L->f32, r->terms.occ_retention, r->terms.occ_limit, L->t,
-                                    ln.stream);
-        if (e != hipSuccess) return hip_fail(pc, e, "server layer build");
+        builds.push_back(layer_build(nullptr, int(r->elts.size()), L->catalog, L->f32, r->terms.occ_retention,
+                                     r->terms.occ_limit, L->t));
         TrialLaunch tl{};
         ara_status s = plan_trial(pc, L, r->t1 - r->t0, mean_len, tl, sv->yet->ids16 ? 1 : 0);
         if (s != ARA_OK) return s;
         double *ylt = sv->arena + r->ylt_off;
-        BatchJob &h = ln.h_jobs[i];
+        BatchJob h{};
         h.a = trial_args(sv->yet, L, r->t0, r->t1, ylt);
         h.a.err = pc->d_err;
         h.a.qcap = tl.qcap;
         h.mode = batch_mode(tl, h.a.ids24 != nullptr);
+        h.a.staged = h.mode == kModeLaneLds && lane_staged_fits(L->catalog, 16) ? 1 : 0;
         h.placement = tl.placement;
         if (h.mode == kModeTiled) tiled.emplace_back(i, tl.grid);
+        if (h.placement == ARA_PLACE_LDS_BITMAP) filtered.push_back(i);
+        jobs.push_back(h);
+        tb.push_back(r->t0);
+        te.push_back(r->t1);
     }
-    std::vector<BatchItem> items;
-    {
-        std::vector<BatchJob> hj(ln.h_jobs, ln.h_jobs + nj);
-        std::vector<int64_t> tb, te, ml(size_t(nj), std::max<int64_t>(1, int64_t(std::llround(mean_len))));
-        for (ServerRequest *r : take) {
-            tb.push_back(r->t0);
-            te.push_back(r->t1);
-        }
-        items = group_items(hj, tb.data(), te.data(), ml, kServerEventsPerItem, ln.mode_off, ln.mode_cnt);
-    }
-    if (int32_t(items.size()) > ln.item_cap) return fail(pc, ARA_E_OOM, "server: %zu work items", items.size());
-    std::copy(items.begin(), items.end(), ln.h_items);
-    hipError_t e = hipMemcpyAsync(ln.d_jobs, ln.h_jobs, sizeof(BatchJob) * size_t(nj), hipMemcpyHostToDevice, ln.stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ln.d_items, ln.h_items, sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice, ln.stream);
-    if (e == hipSuccess)
-        e = launch_grouped(ln.d_jobs, ln.d_items, ln.mode_off, ln.mode_cnt, pc->n_cu, true, ln.stream);
-    for (size_t k = 0; k < tiled.size() && e == hipSuccess; ++k) {
-        const ServerRequest *r = take[size_t(tiled[k].first)];
-        e = run_tiled(pc, sv->yet, ln.slots[size_t(tiled[k].first)], r->t0, r->t1, sv->arena + r->ylt_off, tiled[k].second,
-                      false, nullptr, nullptr);
-    }
+    const std::vector<BatchItem> items = group_items(jobs, tb.data(), te.data(), ml, kServerEventsPerItem, ln.mode_off,
+                                                     ln.mode_cnt);
     // risk measures: short YLTs first, then the long ones, as many at a time as the
-    // workspace holds (nothing waits on the host here); the kernels write the results and
-    // the error word to pinned host memory
-    int32_t ns = 0, nd = 0;
+    // workspace holds; the kernels write the results and the error word to pinned memory
+    int32_t ns = 0;
     for (int pass = 0; pass < 2; ++pass)
         for (int32_t i = 0; i < nj; ++i) {
             ServerRequest *r = take[size_t(i)];
@@ -2280,27 +2267,61 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
             if ((n <= kRiskOneWg) != (pass == 0)) continue;
             int64_t ks[kRiskGroup];
             for (int32_t q = 0; q < nr; ++q) (void)ara_return_period_rank(n, sv->rps[size_t(q)], &ks[q]);
-            ln.h_rjobs[nd++] = risk_job(sv->arena + r->ylt_off, n, ks, nr, ln.h_res + size_t(i) * 2 * nr, nullptr);
+            risks.push_back(risk_job(sv->arena + r->ylt_off, n, ks, nr, ln.h_res + size_t(i) * 2 * nr, nullptr));
             if (pass == 0) ns++;
         }
     std::vector<int32_t> ends;   // launches after the short YLTs: [previous end, end)
     size_t used = 0;
-    for (int32_t i = ns; i < nd; ++i) {
-        const size_t need = risk_workspace_bytes(ln.h_rjobs[i].n, nr);
+    for (int32_t i = ns; i < nj; ++i) {
+        const size_t need = risk_workspace_bytes(risks[size_t(i)].n, nr);
         if (used > 0 && used + need > ln.ws_bytes) {
             ends.push_back(i);
             used = 0;
         }
-        ln.h_rjobs[i].ws = ln.ws + used;
+        risks[size_t(i)].ws = ln.ws + used;
         used += need;
     }
-    if (nd > ns) ends.push_back(nd);
+    if (nj > ns) ends.push_back(nj);
+    // every descriptor to the device in one copy
+    size_t at = 0;
+    const auto place = [&](size_t bytes) {
+        const size_t o = at;
+        at = (at + bytes + 255) & ~size_t(255);
+        return o;
+    };
+    const size_t o_descs = place(descs.size() * sizeof(EltDesc)), o_builds = place(builds.size() * sizeof(LayerBuild)),
+                 o_jobs = place(jobs.size() * sizeof(BatchJob)), o_risks = place(risks.size() * sizeof(RiskJob)),
+                 o_items = place(items.size() * sizeof(BatchItem));
+    if (at > ln.stage_bytes) return fail(pc, ARA_E_OOM, "server: %zu work items", items.size());
+    EltDesc *d_descs = reinterpret_cast<EltDesc *>(ln.d_stage + o_descs);
+    for (size_t i = 0, k = 0; i < builds.size(); k += size_t(builds[i].n_elts), ++i) builds[i].d = d_descs + k;
+    std::memcpy(ln.h_stage + o_descs, descs.data(), descs.size() * sizeof(EltDesc));
+    std::memcpy(ln.h_stage + o_builds, builds.data(), builds.size() * sizeof(LayerBuild));
+    std::memcpy(ln.h_stage + o_jobs, jobs.data(), jobs.size() * sizeof(BatchJob));
+    std::memcpy(ln.h_stage + o_risks, risks.data(), risks.size() * sizeof(RiskJob));
+    if (!items.empty()) std::memcpy(ln.h_stage + o_items, items.data(), items.size() * sizeof(BatchItem));
+    hipError_t e = hipMemcpyAsync(ln.d_stage, ln.h_stage, at, hipMemcpyHostToDevice, ln.stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(ln.d_rjobs, ln.h_rjobs, sizeof(RiskJob) * size_t(nd), hipMemcpyHostToDevice, ln.stream);
-    if (e == hipSuccess && ns > 0) e = launch_risk(ln.h_rjobs, ln.d_rjobs, ns, 0, pc->d_err, pc->h_err, ln.stream);
+        e = launch_layers_tables(reinterpret_cast<const LayerBuild *>(ln.d_stage + o_builds), nj, ln.slots[0]->t.nblk,
+                                 ln.stream);
+    for (size_t k = 0; k < filtered.size() && e == hipSuccess; ++k) {
+        const ara_layer *L = ln.slots[size_t(filtered[k])];
+        e = launch_layer_ranks(L->catalog, L->t, ln.stream);
+    }
+    if (e == hipSuccess)
+        e = launch_grouped(reinterpret_cast<const BatchJob *>(ln.d_stage + o_jobs),
+                           reinterpret_cast<const BatchItem *>(ln.d_stage + o_items), ln.mode_off, ln.mode_cnt, pc->n_cu, true,
+                           ln.stream);
+    for (size_t k = 0; k < tiled.size() && e == hipSuccess; ++k) {
+        const ServerRequest *r = take[size_t(tiled[k].first)];
+        e = run_tiled(pc, sv->yet, ln.slots[size_t(tiled[k].first)], r->t0, r->t1, sv->arena + r->ylt_off, tiled[k].second,
+                      false, nullptr, nullptr);
+    }
+    const RiskJob *d_risks = reinterpret_cast<const RiskJob *>(ln.d_stage + o_risks);
+    if (e == hipSuccess && ns > 0) e = launch_risk(risks.data(), d_risks, ns, 0, pc->d_err, pc->h_err, ln.stream);
     for (size_t l = 0; l < ends.size() && e == hipSuccess; ++l) {
         const int32_t i0 = l == 0 ? ns : ends[l - 1];
-        e = launch_risk(ln.h_rjobs + i0, ln.d_rjobs + i0, 0, ends[l] - i0, pc->d_err, pc->h_err, ln.stream);
+        e = launch_risk(risks.data() + i0, d_risks + i0, 0, ends[l] - i0, pc->d_err, pc->h_err, ln.stream);
     }
     if (e == hipSuccess) e = hipEventRecord(ln.done, ln.stream);
     return e == hipSuccess ? ARA_OK : hip_fail(pc, e, "server iteration");
@@ -2412,14 +2433,9 @@ static void server_free(ara_server *sv) {
     for (ServerLane &ln : sv->lanes) {
         for (ara_layer *L : ln.slots)
             if (L) ara_layer_release(L);
-        dev_free(sv->ctx, ln.d_jobs);
-        dev_free(sv->ctx, ln.d_items);
-        dev_free(sv->ctx, ln.d_rjobs);
+        dev_free(sv->ctx, ln.d_stage);
         dev_free(sv->ctx, ln.ws);
-        if (ln.h_jobs) (void)hipHostFree(ln.h_jobs);
-        if (ln.h_items) (void)hipHostFree(ln.h_items);
-        if (ln.h_descs) (void)hipHostFree(ln.h_descs);
-        if (ln.h_rjobs) (void)hipHostFree(ln.h_rjobs);
+        if (ln.h_stage) (void)hipHostFree(ln.h_stage);
         if (ln.h_res) (void)hipHostFree(ln.h_res);
         if (ln.done) (void)hipEventDestroy(ln.done);
         if (ln.pc) (void)ara_ctx_destroy(ln.pc);
@@ -2456,26 +2472,18 @@ static ara_status server_lane_create(ara_ctx *c, ara_server *sv, ServerLane &ln,
     for (int32_t i = 0; i < ns && s == ARA_OK; ++i)
         s = ara_layer_create(c, sv->pool.data(), n_pool, y->catalog, &none, &ln.slots[size_t(i)]);
     if (s != ARA_OK) return s;
-    // a worst case of work items: every slot with the YET's longest possible range
+    // a worst case: every slot with all pool ELTs and the YET's longest possible range
     const int64_t per_slot_items = y->n_trials / 16 + 2;
-    ln.item_cap = int32_t(std::min<int64_t>(int64_t(ns) * per_slot_items, int64_t(1) << 30));
+    const size_t items = size_t(std::min<int64_t>(int64_t(ns) * per_slot_items, int64_t(1) << 30));
     const size_t nr = size_t(cfg->n_rp);
-    s = dev_alloc(c, &ln.d_jobs, sizeof(BatchJob) * size_t(ns), "server jobs");
-    if (s == ARA_OK) s = dev_alloc(c, &ln.d_items, sizeof(BatchItem) * size_t(ln.item_cap), "server items");
-    if (s == ARA_OK) s = dev_alloc(c, &ln.d_rjobs, sizeof(RiskJob) * size_t(ns), "server risk jobs");
+    ln.stage_bytes = size_t(ns) * (size_t(n_pool) * sizeof(EltDesc) + sizeof(LayerBuild) + sizeof(BatchJob) + sizeof(RiskJob)) +
+                     items * sizeof(BatchItem) + 5 * 256;
+    s = dev_alloc(c, &ln.d_stage, ln.stage_bytes, "server descriptors");
     const size_t one_ws = risk_workspace_bytes(y->n_trials, int(nr));
     ln.ws_bytes = std::max(one_ws, std::min(size_t(ns) * one_ws, kRiskWsBytes));
     if (s == ARA_OK) s = dev_alloc(c, &ln.ws, ln.ws_bytes, "server risk workspace");
     if (s != ARA_OK) return s;
-    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_jobs), sizeof(BatchJob) * size_t(ns), hipHostMallocDefault);
-    if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_items), sizeof(BatchItem) * size_t(ln.item_cap),
-                          hipHostMallocDefault);
-    if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_descs), sizeof(EltDesc) * size_t(ns) * sv->pool.size(),
-                          hipHostMallocDefault);
-    if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_rjobs), sizeof(RiskJob) * size_t(ns), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_stage), ln.stage_bytes, hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&ln.h_res), 16 * size_t(ns) * nr, hipHostMallocDefault);
     return e == hipSuccess ? ARA_OK : hip_fail(c, e, "server pinned staging");
 }

@@ -70,6 +70,14 @@ __host__ __device__ inline size_t bitmap_rel_offset(int32_t nblk) { return size_
 __host__ __device__ inline size_t bitmap_base_offset(int32_t nblk) { return bitmap_rel_offset(nblk) + align16(size_t(nblk) * 2); }
 __host__ __device__ inline size_t bitmap_table_bytes(int32_t nblk) { return bitmap_base_offset(nblk) + align16(size_t(bitmap_supers(nblk)) * 4); }
 
+// LDS of the lane-per-trial kernel that stages its IDs: the table with a zero entry, then
+// 4 KB per wave.
+constexpr int kStageBytes = 4096;
+__host__ __device__ inline size_t lane_table_bytes(int32_t catalog) { return align16((size_t(catalog) + 1) * 8); }
+__host__ __device__ inline bool lane_staged_fits(int32_t catalog, int waves) {
+    return lane_table_bytes(catalog) + size_t(waves) * kStageBytes <= size_t(kLdsMaxBytes);
+}
+
 // Arguments of the trial kernels.
 struct TrialArgs {
     const int32_t *ids;
@@ -87,7 +95,7 @@ struct TrialArgs {
     const uint32_t *base32;
     const double *vals;
     int32_t qcap;            // per-wave queue capacity (bitmap placement)
-    int32_t pad_;
+    int32_t staged;          // lane per trial, table in LDS: IDs staged through LDS (lane_staged_fits)
     double occ_r, occ_l, agg_r, agg_l;
     double *ylt;
     double *ev_gross, *ev_occ, *ev_cum, *ev_ceded;
@@ -104,15 +112,29 @@ hipError_t launch_yet_pack(const int32_t *ids, int64_t n_events, uint8_t *packed
 hipError_t launch_elt_clear(const EltDesc *d, int n_elts, int32_t catalog, hipStream_t s);
 hipError_t launch_elt_scatter(const EltDesc *d, int n_elts, int64_t max_pairs, int32_t catalog, uint32_t *err,
                               hipStream_t s);
-// combined table, occurrence values and bitmaps of a layer; with `ranks`, also its
-// ranks, flagged count and compacted values (launch_layer_ranks)
+// One layer's combined-table build.
+struct LayerBuild {
+    const EltDesc *d;
+    int32_t n_elts, f32, catalog, nblk;
+    double occ_r, occ_l;
+    void *comb;
+    double *occ;
+    uint32_t *bitmap, *nz;
+};
+inline LayerBuild layer_build(const EltDesc *d, int n_elts, int32_t catalog, bool f32, double occ_r, double occ_l,
+                              const LayerTables &t) {
+    return LayerBuild{d, n_elts, f32 ? 1 : 0, catalog, t.nblk, occ_r, occ_l, t.comb, t.occ, t.bitmap, t.nz};
+}
+// combined table, occurrence values and bitmaps of a layer
 hipError_t launch_layer_tables(const EltDesc *d, int n_elts, int32_t catalog, bool f32, double occ_r, double occ_l,
-                               const LayerTables &t, hipStream_t s, bool ranks = true);
+                               const LayerTables &t, hipStream_t s);
+// the same of n layers (device array) over catalogs of nblk bitmap blocks, in one launch
+hipError_t launch_layers_tables(const LayerBuild *many, int n, int32_t nblk, hipStream_t s);
 // the same from an existing combined table (new occurrence terms)
 hipError_t launch_layer_filter(int32_t catalog, bool f32, double occ_r, double occ_l, const LayerTables &t,
-                               hipStream_t s, bool ranks = true);
+                               hipStream_t s);
 // ranks (rank, rel16, base32), flagged count and compacted values from the bitmap and
-// occurrence values: what the filter-based kernels read; the tiled kernel reads occ only
+// occurrence values: what the LDS-filter kernels read; the others read occ only
 hipError_t launch_layer_ranks(int32_t catalog, const LayerTables &t, hipStream_t s);
 
 struct TrialLaunch {
@@ -123,6 +145,7 @@ struct TrialLaunch {
     size_t lds_bytes;
     int qcap;           // per-wave queue capacity (bitmap placement)
     bool lane;          // one lane per trial (short trials, dense tables) instead of one wave
+    bool staged;        // of those: IDs staged through LDS
 };
 
 // Trials with at most this many occurrences on average go one per lane (dense tables).

@@ -52,13 +52,14 @@ __global__ __launch_bounds__(1024) void k_batch(const BatchJob *__restrict__ job
         if (it.job != cur) {
             __syncthreads();   // every wave is done with the previous job's table
             if constexpr (MODE == kModeWaveBitmap || MODE == kModeWaveBitmap24) stage_bitmap(a, lds);
-            else if constexpr (MODE == kModeLaneLds || MODE == kModeWaveLds) stage_lds<ARA_PLACE_LDS_DENSE>(a, lds);
+            else if constexpr (MODE == kModeLaneLds) stage_lds<ARA_PLACE_LDS_DENSE>(a, lds, a.staged != 0);
+            else if constexpr (MODE == kModeWaveLds) stage_lds<ARA_PLACE_LDS_DENSE>(a, lds);
             // global-table modes read HBM/L2 directly: nothing to stage
             cur = it.job;
         }
         if constexpr (MODE == kModeLaneLds) {
             a.t_end = it.t1;
-            dense_lane_run<ARA_PLACE_LDS_DENSE>(a, lds, it.t0 + threadIdx.x, blockDim.x);
+            dense_lane_lds(a, lds, it.t0 + threadIdx.x, blockDim.x);
         } else if constexpr (MODE == kModeLaneGlobal) {
             a.t_end = it.t1;
             dense_lane_run<ARA_PLACE_GLOBAL_DENSE>(a, lds, it.t0 + threadIdx.x, blockDim.x);

@@ -58,12 +58,22 @@ __global__ __launch_bounds__(256) void k_layer_bitmap(const V *__restrict__ comb
 // are 8-byte buffer loads issued by every lane and for every ELT: a lane whose bit
 // is clear reads past the record (0, no memory access), so nothing branches around
 // a load.
-template <typename V>
-__global__ __launch_bounds__(256) void k_layer_combine_bitmap(const EltDesc *__restrict__ d, int n_elts,
-                                                              int32_t catalog, V *__restrict__ comb, double occ_r,
-                                                              double occ_l, double *__restrict__ occ,
-                                                              uint32_t *__restrict__ bitmap,
-                                                              uint32_t *__restrict__ nz, int64_t n_words) {
+// One layer (many null), or layer blockIdx.y of `many`; descriptors are read through the
+// scalar data path.
+__global__ __launch_bounds__(256) void k_layer_combine_bitmap(const LayerBuild *many, LayerBuild one) {
+    typedef const __attribute__((address_space(4))) LayerBuild *ConstBuild;
+    typedef const __attribute__((address_space(4))) EltDesc *ConstDesc;
+    if (many) {
+        const ConstBuild m = (ConstBuild)(many + blockIdx.y);
+        one.d = m->d, one.n_elts = m->n_elts, one.f32 = m->f32, one.occ_r = m->occ_r, one.occ_l = m->occ_l;
+        one.comb = m->comb, one.occ = m->occ, one.bitmap = m->bitmap, one.nz = m->nz;
+        one.catalog = m->catalog, one.nblk = m->nblk;
+    }
+    const ConstDesc d = (ConstDesc)one.d;
+    const int n_elts = one.n_elts;
+    const int32_t catalog = one.catalog;
+    const double occ_r = one.occ_r, occ_l = one.occ_l;
+    const int64_t n_words = int64_t(one.nblk) * 4;
     constexpr int kGroup = 8;
     const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & 63;
@@ -83,35 +93,36 @@ __global__ __launch_bounds__(256) void k_layer_combine_bitmap(const EltDesc *__r
 #pragma unroll
                 for (int k = 0; k < kGroup; ++k) {
                     // past the last ELT: the lanes' words are 0, every lane reads past the record
-                    const EltDesc &t = d[jb + i + k < n_elts ? jb + i + k : n_elts - 1];
+                    const ConstDesc t = d + (jb + i + k < n_elts ? jb + i + k : n_elts - 1);
                     const uint64_t m = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(wv), 2 * (i + k)))) |
                                        uint64_t(uint32_t(__builtin_amdgcn_readlane(int(wv), 2 * (i + k) + 1))) << 32;
                     // binary32 tables: the aligned pair holding the entry (allocated in whole
                     // pairs); catalog <= 2^28 events keeps byte offsets below 2^31
-                    const uint32_t rec = t.f32 ? (uint32_t(catalog) * 4u + 7u) & ~7u : uint32_t(catalog) * 8u;
-                    const uint32_t at = t.f32 ? (uint32_t(e) * 4u) & ~7u : uint32_t(e) * 8u;
-                    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(t.dat, 0, int(rec), kBufWord3);
+                    const uint32_t rec = t->f32 ? (uint32_t(catalog) * 4u + 7u) & ~7u : uint32_t(catalog) * 8u;
+                    const uint32_t at = t->f32 ? (uint32_t(e) * 4u) & ~7u : uint32_t(e) * 8u;
+                    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(t->dat, 0, int(rec), kBufWord3);
                     raw[k] = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(
                                                               r, (m >> lane) & 1u ? at : 0xFFFFFFF8u, 0, 0));
                 }
 #pragma unroll
                 for (int k = 0; k < kGroup; ++k) {
                     if (i + k < nj) {
-                        const EltDesc &t = d[jb + i + k];
-                        double v = t.f32 ? double(__builtin_bit_cast(float, uint32_t(raw[k] >> ((e & 1) * 32))))
+                        const ConstDesc t = d + jb + i + k;
+                        double v = t->f32 ? double(__builtin_bit_cast(float, uint32_t(raw[k] >> ((e & 1) * 32))))
                                          : __builtin_bit_cast(double, raw[k]);
-                        if (!t.identity) v = excess(t.fx * v, t.retention, t.limit);
+                        if (!t->identity) v = excess(t->fx * v, t->retention, t->limit);
                         s = s + v;
                     }
                 }
             }
         }
         if (e < catalog) {
-            const V c = V(s);
-            comb[e] = c;
-            nonzero = c != V(0);
-            const double o = excess(double(c), occ_r, occ_l);
-            occ[e] = o;
+            const double c = one.f32 ? double(float(s)) : s;
+            if (one.f32) static_cast<float *>(one.comb)[e] = float(s);
+            else static_cast<double *>(one.comb)[e] = s;
+            nonzero = c != 0.0;
+            const double o = excess(c, occ_r, occ_l);
+            one.occ[e] = o;
             flag = o > 0.0;
         }
     }
@@ -119,10 +130,10 @@ __global__ __launch_bounds__(256) void k_layer_combine_bitmap(const EltDesc *__r
     const uint64_t z = __ballot(nonzero);
     const int64_t w0 = e0 >> 5;   // even; n_words is a multiple of 4
     if (w0 >= n_words) return;
-    if (lane == 0) bitmap[w0] = uint32_t(m);
-    if (lane == 1) bitmap[w0 + 1] = uint32_t(m >> 32);
-    if (lane == 2) nz[w0] = uint32_t(z);
-    if (lane == 3) nz[w0 + 1] = uint32_t(z >> 32);
+    if (lane == 0) one.bitmap[w0] = uint32_t(m);
+    if (lane == 1) one.bitmap[w0 + 1] = uint32_t(m >> 32);
+    if (lane == 2) one.nz[w0] = uint32_t(z);
+    if (lane == 3) one.nz[w0 + 1] = uint32_t(z >> 32);
 }
 
 // Exclusive prefix of per-block set-bit counts (rank), the same split into a 16-bit
@@ -216,24 +227,26 @@ hipError_t launch_layer_ranks(int32_t catalog, const LayerTables &t, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_layer_tables(const EltDesc *d, int n_elts, int32_t catalog, bool f32, double occ_r, double occ_l,
-                               const LayerTables &t, hipStream_t s, bool ranks) {
+static unsigned combine_blocks(int32_t nblk) {
     // the bitmap covers nblk*128 event slots = nblk*2 waves; launch whole waves only
-    const unsigned blocks = unsigned((int64_t(t.nblk) * kEventsPerBlock + 255) / 256);
-    if (f32) {
-        hipLaunchKernelGGL(k_layer_combine_bitmap<float>, dim3(blocks), dim3(256), 0, s, d, n_elts, catalog,
-                           (float *)t.comb, occ_r, occ_l, t.occ, t.bitmap, t.nz, int64_t(t.nblk) * 4);
-    } else {
-        hipLaunchKernelGGL(k_layer_combine_bitmap<double>, dim3(blocks), dim3(256), 0, s, d, n_elts, catalog,
-                           (double *)t.comb, occ_r, occ_l, t.occ, t.bitmap, t.nz, int64_t(t.nblk) * 4);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !ranks) return e;
-    return launch_layer_ranks(catalog, t, s);
+    return unsigned((int64_t(nblk) * kEventsPerBlock + 255) / 256);
+}
+
+hipError_t launch_layer_tables(const EltDesc *d, int n_elts, int32_t catalog, bool f32, double occ_r, double occ_l,
+                               const LayerTables &t, hipStream_t s) {
+    hipLaunchKernelGGL(k_layer_combine_bitmap, dim3(combine_blocks(t.nblk)), dim3(256), 0, s, nullptr,
+                       layer_build(d, n_elts, catalog, f32, occ_r, occ_l, t));
+    return hipGetLastError();
+}
+
+hipError_t launch_layers_tables(const LayerBuild *many, int n, int32_t nblk, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_layer_combine_bitmap, dim3(combine_blocks(nblk), unsigned(n)), dim3(256), 0, s, many, LayerBuild{});
+    return hipGetLastError();
 }
 
 hipError_t launch_layer_filter(int32_t catalog, bool f32, double occ_r, double occ_l, const LayerTables &t,
-                               hipStream_t s, bool ranks) {
+                               hipStream_t s) {
     // the bitmap covers nblk*128 event slots = nblk*2 waves; launch whole waves only
     const unsigned bm_threads_blocks = unsigned((int64_t(t.nblk) * kEventsPerBlock + 255) / 256);
     if (f32) {
@@ -243,9 +256,7 @@ hipError_t launch_layer_filter(int32_t catalog, bool f32, double occ_r, double o
         hipLaunchKernelGGL(k_layer_bitmap<double>, dim3(bm_threads_blocks), dim3(256), 0, s, (const double *)t.comb,
                            catalog, occ_r, occ_l, t.occ, t.bitmap, int64_t(t.nblk) * 4);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !ranks) return e;
-    return launch_layer_ranks(catalog, t, s);
+    return hipGetLastError();
 }
 
 }  // namespace ara

@@ -43,9 +43,14 @@ __global__ __launch_bounds__(1024) void k_trial_ylt(TrialArgs a) {
 template <int PL>
 __global__ __launch_bounds__(1024) void k_trial_ylt_lane(TrialArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    stage_lds<PL>(a, lds);
-    dense_lane_run<PL>(a, lds, a.t_begin + int64_t(blockIdx.x) * blockDim.x + threadIdx.x,
-                       int64_t(gridDim.x) * blockDim.x);
+    const int64_t first = a.t_begin + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    if constexpr (PL == ARA_PLACE_LDS_DENSE) {
+        stage_lds<PL>(a, lds, a.staged != 0);
+        dense_lane_lds(a, lds, first, stride);
+    } else {
+        dense_lane_run<PL>(a, lds, first, stride);
+    }
 }
 
 // ---------------------------------------------------------------------------------

@@ -3,6 +3,8 @@
 // batched kernel (internal).
 #pragma once
 
+#include <type_traits>
+
 #include "trial_common.h"
 
 namespace ara {
@@ -60,7 +62,7 @@ __device__ __forceinline__ void load_seg(const TrialArgs &a, const Cursor &c, in
 
 // Stage the layer's table into LDS (whole workgroup; ends with a barrier).
 template <int PL>
-__device__ __forceinline__ void stage_lds(const TrialArgs &a, uint32_t *lds) {
+__device__ __forceinline__ void stage_lds(const TrialArgs &a, uint32_t *lds, bool zero = false) {
     if (PL == ARA_PLACE_LDS_BITMAP) {
         stage_bitmap(a, lds);
         return;
@@ -81,6 +83,7 @@ __device__ __forceinline__ void stage_lds(const TrialArgs &a, uint32_t *lds) {
                 if (i0 + k * bd < n4) l4[i0 + k * bd] = v[k];
         }
         for (int i = (n4 << 2) + threadIdx.x; i < n; i += blockDim.x) lds[i] = g[i];
+        if (zero && threadIdx.x < 2) lds[n + threadIdx.x] = 0u;   // an entry of +0.0 after the table
     }
     __syncthreads();
 }
@@ -299,6 +302,208 @@ __device__ __forceinline__ void dense_lane_run(const TrialArgs &a, const uint32_
     }
     if (mx >= C) bad |= ERR_ID_RANGE;
     if (bad) atomicOr(a.err, bad);
+}
+
+// The same with the IDs staged through LDS, for tables that leave a wave 4 KB
+// (lane_staged_fits).  A lane that reads its own trial touches lines no other lane of the
+// load does, and the vector-memory path takes about two clocks for each of those (2.65x10^11
+// lane requests a second over the chip: 0.9 ms of the 1.19 ms that 8.3x10^8 occurrences took
+// above).  Here eight lanes read 32 consecutive IDs of one trial, so a load instruction
+// covers eight 128-byte (packed: 96-byte) stretches instead of 64 lines; the IDs go to LDS as
+// 16-bit numbers, a row of 64 bytes per trial, and each lane reads its own row.
+//   Window w of a wave's 64 trials: IDs [32 w, 32 w + 32) of each, counted from the trial's
+// first group of four.  Window w + 1, or the first of the wave's next 64 trials, is loaded
+// while window w is added.
+//   IDs of the catalog size or more are clamped to it and read the zero entry after the
+// table; so do the positions outside the trial.
+constexpr int kRowBytes = 64;   // 32 IDs of one trial
+static_assert(64 * kRowBytes == kStageBytes, "a row per lane");
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+// LDS byte address of the value of the ID in the low / high half of w.
+__device__ __forceinline__ uint32_t value_lo(uint32_t w) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+        : "=v"(r) : "v"(3u), "v"(w));
+    return r;
+}
+__device__ __forceinline__ uint32_t value_hi(uint32_t w) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+        : "=v"(r) : "v"(3u), "v"(w));
+    return r;
+}
+
+// Adds the IDs of a row's words q (8 IDs, the row's j0-th on) at positions [lo, hi) of the
+// window, in order.  ALL: every position.
+template <bool ALL>
+__device__ __forceinline__ void row_add(const char *tab, const u32x4 &q, int32_t j0, int32_t lo, int32_t hi, uint32_t c2,
+                                        double &P, uint32_t &mx) {
+    double v[8];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        uint32_t w = q[d];
+        if (!ALL) {
+            const int32_t j = j0 + 2 * d;
+            const uint32_t m = (j >= lo && j < hi ? 0xFFFFu : 0u) | (j + 1 >= lo && j + 1 < hi ? 0xFFFF0000u : 0u);
+            mx = pk_max(mx, w & m);
+            w |= ~m;
+        } else {
+            mx = pk_max(mx, w);
+        }
+        w = pk_min(w, c2);
+        v[2 * d] = *reinterpret_cast<const double *>(tab + value_lo(w));
+        v[2 * d + 1] = *reinterpret_cast<const double *>(tab + value_hi(w));
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) P += v[j];
+}
+
+// tab: the table in LDS (occ, then a zero entry at index catalog); stage: this wave's rows.
+template <bool P24>
+__device__ __forceinline__ void dense_lane_staged(const TrialArgs &a, const char *tab, char *stage, int64_t first,
+                                                  int64_t stride) {
+    typedef typename std::conditional<P24, u32x3, u32x4>::type Ids;   // four IDs
+    constexpr int kBytes = P24 ? 3 : 4;
+    constexpr int64_t kSpan = int64_t(1) << 28;
+    const uint32_t C = uint32_t(a.catalog), c2 = C | (C << 16);
+    const int lane = threadIdx.x & 63, row8 = lane >> 3, col = lane & 7;
+    const char *src = P24 ? reinterpret_cast<const char *>(a.ids24) : reinterpret_cast<const char *>(a.ids);
+    // IDs that can be read: the packed copy is padded to whole groups
+    const int64_t n_ids = P24 ? (a.n_events + 3) & ~int64_t(3) : a.n_events;
+    uint32_t bad = 0, mx = 0, big = 0;
+    // the trials being loaded: trial 8 i + row8's first group and end, in IDs from the record's start
+    uint32_t st[8], en[8];
+    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, 0, kBufWord3);
+    Ids R[8];
+    auto load = [&](uint32_t w) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t at = st[i] + 32u * w + 4u * uint32_t(col);
+            const uint32_t off = at < en[i] ? at * uint32_t(kBytes) : 0xFFFFFF00u;   // outside any record
+            if constexpr (P24) R[i] = __builtin_amdgcn_raw_buffer_load_b96(rs, int(off), 0, 0);
+            else R[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, int(off), 0, 0);
+        }
+    };
+    // the trial's positions [lead, len) from its first group on, and its sum so far
+    struct Trial {
+        int32_t lead, len;
+        double P;
+    };
+    int64_t o0 = 0, o1 = 0;   // offsets of the trial to open next
+    auto fetch = [&](int64_t t) {
+        o0 = o1 = 0;
+        if (t < a.t_end) o0 = a.offs[t], o1 = a.offs[t + 1];
+    };
+    auto open = [&]() {
+        Trial x{0, 0, 0.0};
+        if (!(o0 >= 0 && o0 <= o1 && o1 <= a.n_events)) {
+            bad |= ERR_OFFSETS;
+            o0 = o1 = 0;
+        }
+        const int64_t base = uniform64(o0) & ~int64_t(3);
+        if (__builtin_amdgcn_ballot_w64(o1 > o0 && (o0 < base || o1 - base > kSpan)) != 0) {
+            // trials too long for one record (or bad offsets among them): one ID at a time
+            for (int64_t p = o0; p < o1; ++p) {
+                const uint32_t id = uint32_t(a.ids[p]);
+                big |= id >= C ? 1u : 0u;
+                x.P += *reinterpret_cast<const double *>(tab + 8u * min(id, C));
+            }
+            o0 = o1 = 0;
+        }
+        uint32_t s = 0;
+        if (o1 > o0) {
+            s = uint32_t((o0 & ~int64_t(3)) - base);
+            x.lead = int32_t(o0 & 3);
+            x.len = int32_t(o1 - (o0 & ~int64_t(3)));
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            st[i] = uint32_t(__shfl(int(s), 8 * i + row8, 64));
+            en[i] = st[i] + uint32_t(__shfl(x.len, 8 * i + row8, 64));
+        }
+        const int64_t n = min(n_ids - base, kSpan + 4);
+        rs = __builtin_amdgcn_make_buffer_rsrc((void *)(src + base * kBytes), 0, int(uint32_t(n) * uint32_t(kBytes)), kBufWord3);
+        return x;
+    };
+    int64_t t = first;
+    if (__builtin_amdgcn_ballot_w64(t < a.t_end) == 0) return;
+    fetch(t);
+    Trial cur = open();
+    fetch(t + stride);
+    load(0);
+    uint32_t w = 0;
+    for (;;) {
+        // this window's IDs to LDS; a row's 16-byte pieces are rotated by its number so that
+        // the lanes' reads below fall on different banks
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            uint32_t id[4];
+            if constexpr (P24) unpack_ids24(R[i], id);
+            else id[0] = R[i].x, id[1] = R[i].y, id[2] = R[i].z, id[3] = R[i].w;
+            const int r = 8 * i + row8;
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            u32x2 p;
+            p.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_u16(id[0], id[1]));   // saturated
+            p.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_u16(id[2], id[3]));
+            *reinterpret_cast<u32x2 *>(stage + r * kRowBytes + (((col >> 1) ^ ((r >> 2) & 3)) * 16) + (col & 1) * 8) = p;
+        }
+        const bool more = __builtin_amdgcn_ballot_w64(cur.len > int32_t(32u * w + 32u)) != 0;
+        Trial nxt = cur;
+        const int64_t tn = t + stride;
+        const bool last = !more && __builtin_amdgcn_ballot_w64(tn < a.t_end) == 0;
+        if (!more && !last) {
+            nxt = open();
+            fetch(tn + stride);
+        }
+        if (!last) load(more ? w + 1u : 0u);
+        __builtin_amdgcn_wave_barrier();
+        const int32_t lo = cur.lead - int32_t(32u * w), hi = cur.len - int32_t(32u * w);
+        const char *row = stage + lane * kRowBytes;
+        u32x4 q[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) q[p] = *reinterpret_cast<const u32x4 *>(row + ((p ^ ((lane >> 2) & 3)) * 16));
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if (__builtin_amdgcn_ballot_w64(lo > 8 * p || hi < 8 * p + 8) == 0)
+                row_add<true>(tab, q[p], 8 * p, lo, hi, c2, cur.P, mx);
+            else if (__builtin_amdgcn_ballot_w64(hi > 8 * p) != 0)
+                row_add<false>(tab, q[p], 8 * p, lo, hi, c2, cur.P, mx);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (more) {
+            ++w;
+            continue;
+        }
+        if (t < a.t_end) a.ylt[t - a.t_begin] = excess(cur.P, a.agg_r, a.agg_l);
+        if (last) break;
+        t = tn;
+        cur = nxt;
+        w = 0;
+    }
+    if (max(mx & 0xFFFFu, mx >> 16) >= C || big) bad |= ERR_ID_RANGE;
+    if (bad) atomicOr(a.err, bad);
+}
+
+// Lane per trial from a table in LDS: staged when the table leaves the workgroup's waves the
+// room, from the packed IDs if there are any.  lds: the table, staged with its zero entry in
+// that case; the rows follow it.
+__device__ __forceinline__ void dense_lane_lds(const TrialArgs &a, uint32_t *lds, int64_t first, int64_t stride) {
+    if (!a.staged) {
+        dense_lane_run<ARA_PLACE_LDS_DENSE>(a, lds, first, stride);
+        return;
+    }
+    char *tab = reinterpret_cast<char *>(lds);
+    char *stage = tab + lane_table_bytes(a.catalog) + (threadIdx.x >> 6) * kStageBytes;
+    if (a.ids24) dense_lane_staged<true>(a, tab, stage, first, stride);
+    else dense_lane_staged<false>(a, tab, stage, first, stride);
 }
 
 }  // namespace ara
