@@ -60,7 +60,12 @@ __device__ __forceinline__ uint32_t addr_lo(uint32_t w) {
         : "=v"(r) : "v"(3u), "v"(w));
     return r;
 }
-__device__ __forceinline__ uint32_t addr_hi(uint32_t w) { return (w >> 16) << 3; }
+__device__ __forceinline__ uint32_t addr_hi(uint32_t w) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+        : "=v"(r) : "v"(3u), "v"(w));
+    return r;
+}
 
 template <bool MAX>
 __device__ __forceinline__ void fold(double &acc, double v) {
@@ -110,32 +115,29 @@ __device__ __forceinline__ u32x4 load_ids_now(const uint16_t *p) {
     return r;
 }
 
+// Four IDs (words w0, w1) at positions p .. p + 3 of a run of `len`; those past the run
+// read the zero slot.  One test per ID everywhere costs two instructions each, but a wave
+// takes its longest run's words once (28 of 64 lanes' 16.4 on average): whole words under a
+// lane mask and then a tail of up to 7 apart took 0.500 ms for 10^6 trials of 1000
+// occurrences over 62 bins, this 0.483.  (What bounds it: the LDS is busy 60% of the time,
+// half of that with bank conflicts of the random reads, and the vector units 47%; twice as
+// many reads in flight per wave, or an untested path for full words, were slower: 0.500 and
+// 0.490.)
 template <bool MAX>
-__device__ __forceinline__ void add8(const double *tab, const u32x4 &q, double &acc) {
+__device__ __forceinline__ void add4(const double *tab, uint32_t w0, uint32_t w1, uint32_t p, uint32_t len, double &acc) {
+    uint32_t at[4] = {addr_lo(w0), addr_hi(w0), addr_lo(w1), addr_hi(w1)};
+    double v[4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        double v[4];
+    for (int j = 0; j < 4; ++j) v[j] = lds_f64(tab, p + uint32_t(j) < len ? at[j] : kZeroAddr);
 #pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            v[2 * d] = lds_f64(tab, addr_lo(q[2 * h + d]));
-            v[2 * d + 1] = lds_f64(tab, addr_hi(q[2 * h + d]));
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) fold<MAX>(acc, v[j]);
-    }
+    for (int j = 0; j < 4; ++j) fold<MAX>(acc, v[j]);
 }
 
-// The first n (1..7) IDs of q.
+// The 8 IDs of q at positions p .. p + 7, as far as any lane's run reaches.
 template <bool MAX>
-__device__ __forceinline__ void add_first(const double *tab, const u32x4 &q, uint32_t n, double &acc) {
-    double v[8];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        v[2 * d] = lds_f64(tab, uint32_t(2 * d) < n ? addr_lo(q[d]) : kZeroAddr);
-        v[2 * d + 1] = lds_f64(tab, uint32_t(2 * d + 1) < n ? addr_hi(q[d]) : kZeroAddr);
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) fold<MAX>(acc, v[j]);
+__device__ __forceinline__ void add8(const double *tab, const u32x4 &q, uint32_t p, uint32_t len, double &acc) {
+    add4<MAX>(tab, q[0], q[1], p, len, acc);
+    if (__builtin_amdgcn_ballot_w64(len > p + 4u) != 0) add4<MAX>(tab, q[2], q[3], p + 4u, len, acc);
 }
 
 // Adds the run [u.s, e) into acc, positions in order.  base: the bin's span.
@@ -143,22 +145,16 @@ template <bool MAX>
 __device__ __forceinline__ void unit_run(const double *tab, const uint16_t *base, Unit &u, uint32_t e, double &acc) {
     const uint32_t s1 = u.s & ~1u;
     const uint32_t len = e > s1 ? e - s1 : 0u;
-    const uint32_t nf = len >> 3, rest = len & 7u;
     if (u.s & 1u) u.q[0].x = (u.q[0].x & 0xFFFF0000u) | kZeroId;
 #pragma unroll
     for (int k = 0; k < kOct; ++k) {
-        if (__builtin_amdgcn_ballot_w64(uint32_t(k) < nf) == 0) break;
-        if (uint32_t(k) < nf) add8<MAX>(tab, u.q[k], acc);
+        if (__builtin_amdgcn_ballot_w64(len > 8u * k) == 0) return;
+        add8<MAX>(tab, u.q[k], 8u * k, len, acc);
     }
-    if (rest && nf < uint32_t(kOct)) {
-        const u32x4 q = nf == 0 ? u.q[0] : nf == 1 ? u.q[1] : nf == 2 ? u.q[2] : u.q[3];
-        add_first<MAX>(tab, q, rest, acc);
-    }
-    for (uint32_t k = kOct; __builtin_amdgcn_ballot_w64(k < nf || (k == nf && rest != 0)) != 0; ++k) {
-        if (k < nf || (k == nf && rest != 0)) {
-            const u32x4 q = load_ids_now(base + s1 + 8u * k);
-            if (k < nf) add8<MAX>(tab, q, acc);
-            else add_first<MAX>(tab, q, rest, acc);
+    for (uint32_t p = 8u * kOct; __builtin_amdgcn_ballot_w64(len > p) != 0; p += 8u) {
+        if (len > p) {
+            const u32x4 q = load_ids_now(base + s1 + p);
+            add8<MAX>(tab, q, p, len, acc);
         }
     }
 }
