@@ -60,6 +60,26 @@ def test_selection(ara_lib, gpu_ctx, n, kind):
             assert p.tobytes() == pml.tobytes() and t.tobytes() == tvar.tobytes()
 
 
+@pytest.mark.parametrize("share", [63, 64, 65, 700, 1023, 1024, 1025])
+@pytest.mark.parametrize("n", [9_000, 100_000])
+def test_shared_losses(ara_lib, gpu_ctx, n, share):
+    """Every loss occurs `share` times, next to its neighbour in binary64 (so two or more losses fall in a bin), or
+    alone in its bin."""
+    import torch
+    A = ara_lib
+    rng = np.random.default_rng(share)
+    print(f"shared losses n={n} share={share}", flush=True)
+    v = np.repeat(rng.lognormal(13, 2.2, size=n // share + 1), share)[:n]
+    near = rng.random(n) < 0.3
+    v[near] = np.nextafter(v[near], np.inf)
+    y = rng.permutation(v)
+    rps = [10.0, 50.0, 250.0, 1000.0, float(n)]
+    pml_o, tvar_o, ranks, _ = oracle.risk(y, rps)
+    pml, tvar = A.ara_risk_measures(gpu_ctx, torch.from_numpy(y).cuda(), rps)
+    assert np.asarray(pml).tobytes() == np.asarray(pml_o).tobytes()
+    assert np.all(np.abs(tvar - tvar_o) <= 2.0 * np.asarray(ranks, float) * 2.0 ** -53 * np.abs(tvar_o) + 1e-300)
+
+
 def test_batch_of_short_and_long(ara_lib, gpu_ctx):
     """A batch of YLTs on both sides of the one-workgroup limit, two sets of return periods:
     the same bits as one call per YLT."""
