@@ -28,7 +28,6 @@ struct ara_ctx {
     double *d_out = nullptr;         // small device result staging
     double *h_out = nullptr;         // pinned host mirror of d_out
     uint32_t *h_err = nullptr;       // pinned host error word
-    uint32_t *h_plan = nullptr;      // pinned copy of a radix sort's pass plan
     void *scratch = nullptr;         // device address of this device's `scratch` array
     int placement = ARA_PLACE_AUTO;
     int block_threads = 0;           // 0 = automatic
@@ -453,10 +452,6 @@ extern "C" ara_status ara_ctx_create(int device, void *hip_stream, ara_ctx **out
         e = hipHostMalloc(reinterpret_cast<void **>(&c->h_err), blk, hipHostMallocDefault);
     }
     if (e == hipSuccess) c->h_out = reinterpret_cast<double *>(reinterpret_cast<char *>(c->h_err) + kErrBytes);
-    if (e == hipSuccess) {
-        step = "pinned sort plan";
-        e = hipHostMalloc(reinterpret_cast<void **>(&c->h_plan), 32 * sizeof(uint32_t), hipHostMallocDefault);
-    }
     if (e == hipSuccess) { step = "clear error word"; e = launch_fill_u32(c->d_err, kErrBytes / 4, 0u, c->stream); }
     if (e == hipSuccess) { step = "synchronize"; e = hipStreamSynchronize(c->stream); }
     if (e != hipSuccess) {
@@ -464,7 +459,6 @@ extern "C" ara_status ara_ctx_create(int device, void *hip_stream, ara_ctx **out
         fail(nullptr, ARA_E_DEVICE, "ctx: %s: %s", step, hipGetErrorString(e));
         if (c->d_err) (void)hipFree(c->d_err);
         if (c->h_err) (void)hipHostFree(c->h_err);
-        if (c->h_plan) (void)hipHostFree(c->h_plan);
         delete c;
         return ARA_E_DEVICE;
     }
@@ -482,7 +476,6 @@ extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
     blocks_return(c, 0);
     for (hipEvent_t ev : c->k_ev) (void)hipEventDestroy(ev);
     if (c->h_err) (void)hipHostFree(c->h_err);   // with h_out
-    if (c->h_plan) (void)hipHostFree(c->h_plan);
     delete c;
     return ARA_OK;
 }
@@ -1383,8 +1376,7 @@ extern "C" ara_status ara_sort_desc(ara_ctx *c, const double *in, int64_t n, dou
     bool owned = false;
     ara_status s = workspace_for(c, n, ws, ws_bytes, &w, &owned);
     if (s != ARA_OK) return s;
-    hipError_t e = launch_sort_desc_keys(in, n, w, c->stream);   // stays asynchronous
-    if (e == hipSuccess) e = launch_sort_decode(w, n, out, c->stream);
+    const hipError_t e = launch_sort_desc(in, n, out, w, c->stream);   // stays asynchronous
     s = e == hipSuccess ? ARA_OK : hip_fail(c, e, "sort");
     if (owned) {
         (void)hipStreamSynchronize(c->stream);

@@ -297,9 +297,8 @@ hipError_t launch_tiled_combine_items(const TiledArgs *jobs, const int32_t *spli
 
 // ---- order statistics
 size_t sort_workspace_bytes(int64_t n);
-hipError_t launch_sort_desc_keys(const double *in, int64_t n, void *ws, hipStream_t s,
-                                 uint32_t *host_plan = nullptr);   // sorted keys -> ws
-hipError_t launch_sort_decode(const void *ws, int64_t n, double *out, hipStream_t s);
+// `out` may be `in`: it is written once `in` has been read.
+hipError_t launch_sort_desc(const double *in, int64_t n, double *out, void *ws, hipStream_t s);
 
 // ---- risk measures (k_risk.hip): PML and TVaR of many YLTs by selection
 constexpr int kRiskGroup = 16;       // ranks per descriptor
