@@ -57,6 +57,7 @@ constexpr int kEventsPerBlock = 128;        // events per bitmap block
 constexpr int kBlocksPerSuper = 256;        // bitmap blocks per rank superblock (32768 events)
 constexpr int kLdsMaxBytes = 160 * 1024;    // LDS per workgroup on gfx950
 constexpr int kBufWord3 = 0x00020000;       // raw buffer descriptor word 3 (32-bit data format)
+constexpr int kNonTemporal = 2;           // cache policy of the ID stream loads
 constexpr int kQueueRow = 64;               // queued events are processed one wave-row at a time
 constexpr int kQueueCapMax = 192;           // per-wave queue capacity (events), a multiple of kQueueRow
 constexpr int kQueueCapMin = 128;

@@ -95,10 +95,12 @@ __global__ __launch_bounds__(kCountWaves * 64) void k_bin_count(const int32_t *_
 // more of a 10^9-occurrence ingest, and scanning the counts in separate passes
 // 0.2 ms more.)
 constexpr int kCountBlock = 64;
+constexpr int kBlockWaves = 8;   // (4 the same, 16 are 10% slower: reads of too many places at once)
 typedef uint32_t u32x3b __attribute__((ext_vector_type(3)));
+typedef uint32_t u32x4c __attribute__((ext_vector_type(4)));
 
 template <bool B24>
-__global__ __launch_bounds__(kCountWaves * 64) void k_bin_count_block(const int32_t *__restrict__ ids,
+__global__ __launch_bounds__(kBlockWaves * 64) void k_bin_count_block(const int32_t *__restrict__ ids,
                                                                       const int64_t *__restrict__ offs,
                                                                       int64_t n_events, int64_t n_trials,
                                                                       int32_t n_bins, RunStarts r, int32_t catalog,
@@ -109,16 +111,60 @@ __global__ __launch_bounds__(kCountWaves * 64) void k_bin_count_block(const int3
     const int64_t nblk = (n_trials + kCountBlock - 1) / kCountBlock;
     bool bad = false, bad_offs = false;
     for (int64_t t0 = int64_t(blockIdx.x) * kCountBlock; t0 < n_trials; t0 += int64_t(gridDim.x) * kCountBlock) {
-        for (int i = threadIdx.x; i < kCountBlock * 65; i += kCountWaves * 64) (&hist[0][0])[i] = 0u;
+        for (int i = threadIdx.x; i < kCountBlock * 65; i += kBlockWaves * 64) (&hist[0][0])[i] = 0u;
         __syncthreads();
-        for (int j = wave; j < kCountBlock; j += kCountWaves) {
-            const int64_t t = t0 + j;
-            if (t >= n_trials) break;
-            count_trial(ids, offs, t, n_events, n_trials, cat, lane, hist[j], bad, bad_offs);
+        // lane j: the offsets of the block's trial j
+        const int64_t tj = min(t0 + lane, n_trials - 1);
+        int64_t o0 = offs[tj], o1 = offs[tj + 1];
+        if (o0 < 0 || o1 < o0 || o1 > n_events || (tj == 0 && o0 != 0) || (tj == n_trials - 1 && o1 != n_events)) {
+            bad_offs = true;
+            o1 = o0 = 0;   // read none of this trial's IDs
+        }
+        if (t0 + lane >= n_trials) o1 = o0;
+        auto lane64 = [](int64_t v, int l) {
+            return int64_t(uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), l))) |
+                           uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(uint64_t(v) >> 32)), l))) << 32);
+        };
+        // A wave's chunks of up to 1024 IDs, trial after trial, four 16-byte loads per lane;
+        // the next chunk's are issued before this one is counted.  Bound by reading: 177 us
+        // for 2 10^8 IDs (4.5 TB/s), 182 without the counting and the non-temporal hint;
+        // sixteen 4-byte loads took 197 us, and without the hint 187.
+        constexpr int kLoads = 4, kIds = 256 * kLoads;
+        auto load = [&](int64_t start, int64_t end, u32x4c (&c)[kLoads]) {
+            const int32_t avail = int32_t(max(int64_t(0), min(end - start, int64_t(kIds))));
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(ids + (avail ? start : 0)), 0, avail * 4, kBufWord3);
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) c[u] = __builtin_bit_cast(u32x4c, __builtin_amdgcn_raw_buffer_load_b128(rs, (64 * u + lane) * 16, 0, kNonTemporal));
+        };
+        int j = wave;
+        int64_t at = lane64(o0, j), end = lane64(o1, j);
+        u32x4c v[kLoads], nv[kLoads];
+        load(at, end, v);
+        while (j < kCountBlock) {
+            const bool same = at + kIds < end;
+            const int nj = same ? j : j + kBlockWaves, jj = min(nj, kCountBlock - 1);
+            const int64_t nat = same ? at + kIds : lane64(o0, jj), nend = nj < kCountBlock ? lane64(o1, jj) : nat;
+            load(nat, nend, nv);
+            uint32_t *h = hist[j];
+            const int32_t len = int32_t(max(int64_t(0), min(end - at, int64_t(kIds))));
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (256 * u + 4 * lane + k >= len) continue;
+                    if (v[u][k] < cat) atomicAdd(&h[v[u][k] >> kBinShift], 1u);
+                    else bad = true;
+                }
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) v[u] = nv[u];
+            j = nj;
+            at = nat;
+            end = nend;
         }
         __syncthreads();
         const int64_t t = t0 + lane;
-        for (int32_t b = wave; b < n_bins; b += kCountWaves) {
+        for (int32_t b = wave; b < n_bins; b += kBlockWaves) {
             const uint32_t x = hist[lane][b];   // 0 past the last trial
             uint32_t inc = x;
             for (int k = 1; k < 64; k <<= 1) {
@@ -324,7 +370,7 @@ hipError_t launch_bin_offsets(const int32_t *ids, const int64_t *offs, int64_t n
         if (add_blocks > 65535) return hipErrorInvalidValue;
         const dim3 grid{unsigned(std::min<int64_t>(nblk, 65536))}, add_grid{unsigned(add_blocks), unsigned(n_bins)};
         if (r.b24) {
-            hipLaunchKernelGGL(k_bin_count_block<true>, grid, dim3(kCountWaves * 64), 0, s, ids, offs, n_events,
+            hipLaunchKernelGGL(k_bin_count_block<true>, grid, dim3(kBlockWaves * 64), 0, s, ids, offs, n_events,
                                n_trials, n_bins, r, catalog, sums, err);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             hipLaunchKernelGGL(k_bin_block_scan<true>, dim3(unsigned(n_bins)), dim3(1024), 0, s, sums, nblk, r,
@@ -333,7 +379,7 @@ hipError_t launch_bin_offsets(const int32_t *ids, const int64_t *offs, int64_t n
             hipLaunchKernelGGL(k_bin_block_add<true>, add_grid, dim3(1024), 0, s, r, n_trials, sums, nblk);
             return hipGetLastError();
         }
-        hipLaunchKernelGGL(k_bin_count_block<false>, grid, dim3(kCountWaves * 64), 0, s, ids, offs, n_events, n_trials,
+        hipLaunchKernelGGL(k_bin_count_block<false>, grid, dim3(kBlockWaves * 64), 0, s, ids, offs, n_events, n_trials,
                            n_bins, r, catalog, sums, err);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(k_bin_block_scan<false>, dim3(unsigned(n_bins)), dim3(1024), 0, s, sums, nblk, r, n_trials,
@@ -396,14 +442,22 @@ hipError_t launch_bin_regions(const RunStarts &r, int64_t n_trials, int32_t n_bi
 //
 // Either way a wave takes one trial at a time, 64 occurrences per step in time
 // order; lanes of a step that share a bin are ranked in lane order, so each run keeps
-// the trial's time order.  The mask of lanes with the same bin comes from LDS when
-// the bins fit a wave's table (at most 64: every lane ORs its bit into its bin's
-// word and reads the word back; ORs do not depend on the order the lanes are taken
-// in), else from one ballot per bit of the bin number (six ballots per step cost
-// 1.6 ms of a 10^9-occurrence ingest, the LDS masks 0.5 ms).  With at most 64 bins
-// and staging, lane l keeps bin l's next position in a register (read by the other
-// lanes with a cross-lane permute) and clears bin l's mask word after the step by
-// exchanging it for 0, which also gives it the bin's count for the step.
+// the trial's time order.  The mask of lanes with the same bin comes from one ballot per
+// bit of the bin number (same_bin_rank), or from LDS when the bins fit a wave's table (at
+// most 64: every lane ORs its bit into its bin's word and reads the word back; ORs do not
+// depend on the order the lanes are taken in).  Ballots load the vector units (76% busy
+// with six of them per step), the LDS masks the LDS; whole steps go four at a time, two
+// each way, with their masks side by side and one read and one write of the bin's next
+// position per step after them.
+//
+// What it measured, 2 10^8 occurrences in 62 bins: 477 us with the LDS masks alone, one
+// step after another, each waiting for its OR, read and exchange; 358 four at a time; 357
+// by ballots alone; 342 two and two.  1.2 GB read and written are 245 us at the rate of a
+// large copy; the rest is the workgroups' start (spans, first chunks) and end, which the
+// other workgroup of the CU covers in part, and the waves' uneven shares of a block (27
+// trials over 8 waves; blocks of 24 took 383 us, fewer occurrences per start).  Workgroups
+// x, x + 8, ... (one XCD) take a contiguous eighth of the blocks, so that both ends of a
+// bin's span meet their neighbours' in one L2.
 //
 // Staging: 72 KB of LDS per 8-wave workgroup, so two workgroups share a CU and one
 // places occurrences while the other starts or writes out.  Each bin's span starts
@@ -421,18 +475,24 @@ int64_t bin_scatter_block_trials(int64_t n_events, int64_t n_trials) {
 }
 
 // Rank of this lane among the lanes of `valid` whose bin equals its own, and their
-// number; NBITS = bits needed for the largest bin number.
+// number (valid lanes); NBITS = bits needed for the largest bin number.  Per bit: the
+// ID's bit as 0 or -1, one ballot, and a three-input bit operation per half of the mask
+// of lanes of another bin.
 template <int NBITS>
-__device__ __forceinline__ void same_bin_rank(uint32_t b, uint64_t valid, uint32_t &rank, uint32_t &count) {
-    uint64_t m = valid;
+__device__ __forceinline__ void same_bin_rank(uint32_t id, uint64_t valid, uint32_t &rank, uint32_t &count) {
+    constexpr uint32_t kOrXor = 0xF6;    // a | (b ^ c)
+    uint32_t other_lo = 0u, other_hi = 0u;
 #pragma unroll
     for (int k = 0; k < NBITS; ++k) {
-        const bool bit = (b >> k) & 1u;
-        const uint64_t ones = __builtin_amdgcn_ballot_w64(bit);
-        m &= bit ? ones : ~ones;
+        int own;   // (as asm: the compiler takes three instructions for the two uses)
+        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(own) : "v"(id), "n"(kBinShift + k));
+        const uint64_t ones = __builtin_amdgcn_ballot_w64(own != 0);
+        other_lo = __builtin_amdgcn_bitop3_b32(other_lo, uint32_t(own), uint32_t(ones), kOrXor);
+        other_hi = __builtin_amdgcn_bitop3_b32(other_hi, uint32_t(own), uint32_t(ones >> 32), kOrXor);
     }
-    rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-    count = uint32_t(__popcll(m));
+    const uint32_t lo = ~other_lo & uint32_t(valid), hi = ~other_hi & uint32_t(valid >> 32);
+    rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    count = uint32_t(__popc(lo)) + uint32_t(__popc(hi));
 }
 
 template <int NBITS>
@@ -448,9 +508,12 @@ __global__ __launch_bounds__(kScatterWaves * 64) void k_bin_scatter(const int32_
     __shared__ uint32_t lbase[kBins + 1];               // start of bin b's span in `stage`
     __shared__ uint32_t bstart[kBins];                  // run(b, t0)
     __shared__ uint32_t blen[kBins];                    // bin b's span length
-    __shared__ uint64_t lanes_of[NBITS <= 6 ? kScatterWaves : 1][NBITS <= 6 ? 64 : 1];   // per wave and bin: its lanes
+    __shared__ uint16_t *bdst[kBins];                   // its place in region b
+    constexpr bool kMasks = NBITS > 3 && NBITS <= 6;    // (few bits: ballots are cheaper)
+    __shared__ uint64_t lanes_of[kMasks ? kScatterWaves : 1][kMasks ? 64 : 1];   // per wave and bin: its lanes
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t t0 = int64_t(blockIdx.x) * per_block;
+    const int64_t each = (gridDim.x + kXcds - 1) / kXcds;
+    const int64_t t0 = (int64_t(blockIdx.x % kXcds) * each + blockIdx.x / kXcds) * per_block;
     if (t0 >= n_trials) return;
     // the count pass found a bad ID or offset: the counts do not describe the input
     if (*err != 0u) return;
@@ -461,42 +524,8 @@ __global__ __launch_bounds__(kScatterWaves * 64) void k_bin_scatter(const int32_
     auto body = [&](auto staged_case) {
     constexpr bool staged = decltype(staged_case)::value;
     uint32_t *wc = cur[wave];
-    uint64_t *lm = lanes_of[NBITS <= 6 ? wave : 0];
-    if (NBITS <= 6) lm[lane] = 0;
-    if (staged) {
-        for (int32_t b = threadIdx.x; b < n_bins; b += kScatterWaves * 64) {
-            const uint32_t s = run_at(r, b, t0);
-            bstart[b] = s;
-            lbase[b + 1] = run_at(r, b, t1) - s;
-        }
-        __syncthreads();
-        if (wave == 0) {   // exclusive scan of the padded span lengths, 8 bins per lane
-            uint32_t v[8], own = 0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int32_t b = lane * 8 + k;
-                v[k] = b < n_bins ? lbase[b + 1] + kScatterPad : 0u;
-                own += v[k];
-            }
-            uint32_t inc = own;
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t y = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += y;
-            }
-            uint32_t run = inc - own;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int32_t b = lane * 8 + k;
-                if (b < n_bins) {   // the span starts at the destination's position modulo 8
-                    lbase[b] = run + ((bstart[b] - run) & 7u);
-                    blen[b] = v[k] - kScatterPad;
-                }
-                run += v[k];
-            }
-            if (lane == 63) lbase[n_bins] = run;
-        }
-        __syncthreads();
-    }
+    uint64_t *lm = lanes_of[kMasks ? wave : 0];
+    if (kMasks) lm[lane] = 0;
     // A wave places its trials t0 + wave, t0 + wave + kScatterWaves, ... one chunk of
     // kChunkSteps steps at a time.  Before it places a chunk it issues the loads of the
     // next one, with the next trial's run starts and the offsets of the trial after
@@ -506,7 +535,14 @@ __global__ __launch_bounds__(kScatterWaves * 64) void k_bin_scatter(const int32_
     // wait for every load in flight before each chunk: 0.35 ms more of a
     // 10^9-occurrence ingest).
     constexpr int kChunkSteps = 16, kChunkIds = 64 * kChunkSteps;
+    constexpr int kFull = 4;     // whole steps taken together
+    constexpr int kByLds = kMasks ? 2 : 0;   // of these, masks from LDS
     constexpr int kWB = (kBins + 63) / 64;
+    auto put = [&](uint32_t b, uint32_t at, uint32_t id) {
+        const uint16_t local = uint16_t(id & uint32_t(kBinEvents - 1));
+        if (staged) stage[at] = local;
+        else ids16[region[b] + int64_t(at)] = local;
+    };
     typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
     auto load_offs = [&](int64_t tt) -> i64x2 {   // offs[tt], offs[tt + 1], tt clamped to a trial
         const int64_t tc = min(tt, n_trials - 1);
@@ -543,20 +579,50 @@ __global__ __launch_bounds__(kScatterWaves * 64) void k_bin_scatter(const int32_
         }
         load_chunk(o0, o1, cv);
     }
+    if (staged) {
+        for (int32_t b = threadIdx.x; b < n_bins; b += kScatterWaves * 64) {
+            const uint32_t s = run_at(r, b, t0), e = run_at(r, b, t1);
+            bdst[b] = ids16 + region[b] + int64_t(s);
+            bstart[b] = s;
+            lbase[b + 1] = e - s;
+        }
+        __syncthreads();
+        if (wave == 0) {   // exclusive scan of the padded span lengths, 8 bins per lane
+            uint32_t v[8], own = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int32_t b = lane * 8 + k;
+                v[k] = b < n_bins ? lbase[b + 1] + kScatterPad : 0u;
+                own += v[k];
+            }
+            uint32_t inc = own;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(inc, o, 64);
+                if (lane >= o) inc += y;
+            }
+            uint32_t run = inc - own;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int32_t b = lane * 8 + k;
+                if (b < n_bins) {   // the span starts at the destination's position modulo 8
+                    lbase[b] = run + ((bstart[b] - run) & 7u);
+                    blen[b] = v[k] - kScatterPad;
+                }
+                run += v[k];
+            }
+            if (lane == 63) lbase[n_bins] = run;
+        }
+        __syncthreads();
+    }
     int64_t base = o0;
-    uint32_t curs = 0;   // NBITS <= 6, staged: lane l holds bin l's next position
     while (t < t1) {
         if (base == o0) {
-            if (NBITS <= 6 && staged) {
-                curs = lane < n_bins ? lbase[lane] + wb[0] - bstart[lane] : 0u;
-            } else {
 #pragma unroll
-                for (int k = 0; k < kWB; ++k) {
-                    const int32_t b = lane + 64 * k;
-                    if (b < n_bins) wc[b] = staged ? lbase[b] + wb[k] - bstart[b] : wb[k];
-                }
-                __builtin_amdgcn_wave_barrier();
+            for (int k = 0; k < kWB; ++k) {
+                const int32_t b = lane + 64 * k;
+                if (b < n_bins) wc[b] = staged ? lbase[b] + wb[k] - bstart[b] : wb[k];
             }
+            __builtin_amdgcn_wave_barrier();
         }
         // the next chunk: the rest of trial t, else the start of trial t + kScatterWaves
         const bool same = base + kChunkIds < o1;
@@ -569,50 +635,45 @@ __global__ __launch_bounds__(kScatterWaves * 64) void k_bin_scatter(const int32_
         load_chunk(nb, ne, nxt);
         const int32_t len = int32_t(min(o1 - base, int64_t(kChunkIds)));
 #pragma unroll
-        for (int u = 0; u < kChunkSteps; ++u) {
-            const bool valid = 64 * u + lane < len;
-            const uint32_t id = cv[u];
-            const uint32_t b = id >> kBinShift;
-            uint32_t rank, count;
-            if (NBITS <= 6 && staged) {
-                const uint32_t bb = valid ? b : 63u;
-                __hip_atomic_fetch_or(&lm[bb], valid ? uint64_t(1) << lane : uint64_t(0), __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_WAVEFRONT);
-                const uint64_t m = lm[bb];
-                __builtin_amdgcn_wave_barrier();
-                // lane l takes bin l's mask and clears it in one exchange
-                const uint64_t ml = __hip_atomic_exchange(&lm[lane], uint64_t(0), __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_WAVEFRONT);
-                rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-                const uint32_t at = uint32_t(__builtin_amdgcn_ds_bpermute(int(b << 2), int(curs)));
-                if (valid) stage[at + rank] = uint16_t(id & uint32_t(kBinEvents - 1));
-                curs += uint32_t(__popcll(ml));
-                __builtin_amdgcn_wave_barrier();
+        for (int u = 0; u < kChunkSteps; u += kFull) {
+            if (64 * (u + kFull) <= len) {   // whole steps, without masks: their ranks side by side
+                uint32_t rank[kFull], count[kFull];
+#pragma unroll
+                for (int j = 0; j < kFull; ++j) {
+                    if (j < kByLds) {
+                        uint64_t *at = lm + (cv[u + j] >> kBinShift);
+                        __hip_atomic_fetch_or(at, uint64_t(1) << lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                        const uint64_t m = *at;
+                        __builtin_amdgcn_wave_barrier();
+                        *at = 0;
+                        __builtin_amdgcn_wave_barrier();
+                        rank[j] = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
+                        count[j] = uint32_t(__popcll(m));
+                    } else {
+                        same_bin_rank<NBITS>(cv[u + j], ~0ull, rank[j], count[j]);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kFull; ++j) {
+                    const uint32_t b = cv[u + j] >> kBinShift, at = wc[b];
+                    put(b, at + rank[j], cv[u + j]);
+                    wc[b] = at + count[j];   // every lane of the bin, the same value
+                    __builtin_amdgcn_wave_barrier();
+                }
                 continue;
             }
-            if (NBITS <= 6) {
-                // the lanes of this step with bin b: every lane ORs its bit into its bin's
-                // mask (an OR does not depend on the order the lanes are taken in), reads the
-                // mask back and clears it
-                const uint32_t bb = valid ? b : 63u;
-                __hip_atomic_fetch_or(&lm[bb], valid ? uint64_t(1) << lane : uint64_t(0), __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_WAVEFRONT);
-                const uint64_t m = lm[bb];
+#pragma unroll
+            for (int j = 0; j < kFull; ++j) {
+                const bool valid = 64 * (u + j) + lane < len;
+                uint32_t rank, count;
+                same_bin_rank<NBITS>(cv[u + j], __builtin_amdgcn_ballot_w64(valid), rank, count);
+                if (valid) {
+                    const uint32_t b = cv[u + j] >> kBinShift, at = wc[b];
+                    put(b, at + rank, cv[u + j]);
+                    wc[b] = at + count;
+                }
                 __builtin_amdgcn_wave_barrier();
-                lm[bb] = 0;
-                rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-                count = uint32_t(__popcll(m));
-            } else {
-                same_bin_rank<NBITS>(b, __builtin_amdgcn_ballot_w64(valid), rank, count);
             }
-            const uint32_t at = wc[b];
-            const uint16_t local = uint16_t(id & uint32_t(kBinEvents - 1));
-            if (valid) {
-                if (staged) stage[at + rank] = local;
-                else ids16[region[b] + int64_t(at + rank)] = local;
-                if (rank + 1 == count) wc[b] = at + count;
-            }
-            __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll
         for (int u = 0; u < kChunkSteps; ++u) cv[u] = nxt[u];
@@ -631,7 +692,7 @@ __global__ __launch_bounds__(kScatterWaves * 64) void k_bin_scatter(const int32_
     typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
     for (int32_t b = wave; b < n_bins; b += kScatterWaves) {
         const uint32_t l0 = lbase[b], len = blen[b];
-        uint16_t *dst = ids16 + region[b] + int64_t(bstart[b]);
+        uint16_t *dst = bdst[b];
         const uint32_t head = min(len, (8u - (bstart[b] & 7u)) & 7u);
         const uint32_t n16 = (len - head) >> 3, tail = (len - head) & 7u;
         if (uint32_t(lane) < head) dst[lane] = stage[l0 + lane];
@@ -651,7 +712,7 @@ hipError_t launch_bin_scatter(const int32_t *ids, const int64_t *offs, int64_t n
     if (n_trials <= 0) return hipSuccess;
     if (n_bins > kMaxBins) return hipErrorInvalidValue;
     const int64_t per = bin_scatter_block_trials(n_events, n_trials);
-    const int64_t grid = (n_trials + per - 1) / per;
+    const int64_t grid = ((n_trials + per - 1) / per + kXcds - 1) / kXcds * kXcds;
     if (grid > int64_t(INT32_MAX)) return hipErrorInvalidValue;
     const int nbits = n_bins > 1 ? 32 - __builtin_clz(uint32_t(n_bins - 1)) : 0;
     // one instantiation per bit count of the bin numbers (the rank's ballots unrolled)

@@ -13,7 +13,6 @@ constexpr int kChunk = 256;               // events per wave-wide 16-byte load (
 constexpr int kNch = 4;                   // loads per segment
 constexpr int kSeg = kChunk * kNch;       // events per segment
 constexpr int kSlots = kNch * 4;          // events per lane per segment
-constexpr int kNonTemporal = 2;           // cache policy of the ID stream loads
 
 // min(max(x - retention, 0), limit): the excess-of-loss clamp of Table I.
 __device__ __forceinline__ double excess(double x, double retention, double limit) {
