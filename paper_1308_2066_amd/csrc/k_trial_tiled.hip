@@ -17,10 +17,16 @@
 //   one span of the bin; a lane reads its run 8 IDs (16 bytes) at a time from the run's
 //   first even position.  An odd-starting run's first ID slot is the previous run's
 //   last ID: it is redirected to a zero slot after the table.
-//   Four such loads (runs of up to 32 occurrences) are issued two groups before the
-//   group is added (three groups rotate through three register slots); the rest of a
-//   longer run is read when reached.  Each bin's values are loaded into registers
+//   Four such loads (runs of up to 32 occurrences) are issued one group before the
+//   group is added (the groups take turns in two register slots); the rest of a longer
+//   run is read 32 IDs at a time when reached.  Each bin's values are loaded into registers
 //   while the previous bin is added, and written to LDS between two barriers.
+//   (Three slots, two groups ahead, need an unrolled loop over three bins and more
+//   registers than a wave has: 30 KB of code and 15 spilled registers.  Two take 17 KB and
+//   none, and are faster everywhere: 10^6 trials of 1000 occurrences over 62 bins 0.483 ->
+//   0.470 ms, 50,000 of 600 over 19 bins 36 -> 30 us.  With runs of 36 to 88 occurrences
+//   per bin the rest of the run, read 8 IDs at a time with a wait each, took another 5% of
+//   eight uneven analyses: 638 -> 602 -> 575 us.)
 // A trial's P is added in a fixed order (bin groups, bins, positions): the same bits on
 // every run.  The per-trial sums live in LDS (one binary64 per trial of the wave).
 #include <algorithm>
@@ -79,6 +85,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t bin_rsrc(const TiledArgs &a, i
     return __builtin_amdgcn_make_buffer_rsrc((void *)(a.ids16 + r0), 0, int(uint32_t((r1 - r0) * 2)), kBufWord3);
 }
 
+// The same record as four words, for inline assembly.
+__device__ __forceinline__ i32x4 bin_words(const TiledArgs &a, int32_t b) {
+    const int64_t r0 = offset_at(a.region, b), r1 = offset_at(a.region, b + 1);
+    const uint64_t base = reinterpret_cast<uint64_t>(a.ids16 + r0);
+    return i32x4{int32_t(uint32_t(base)), int32_t(uint32_t(base >> 32) & 0xFFFFu), int32_t(uint32_t((r1 - r0) * 2)), kBufWord3};
+}
+
 // Bin b's values into registers: occ[2^14 b + i] (zero past the catalog).
 __device__ __forceinline__ void stage_load(const TiledArgs &a, int32_t b, f64x2 (&st)[kStageVecs]) {
     const int64_t e0 = int64_t(b) * kBinEvents;
@@ -106,20 +119,27 @@ __device__ __forceinline__ void unit_issue(__amdgpu_buffer_rsrc_t r, Unit &u) {
     for (int k = 0; k < kOct; ++k) u.q[k] = __builtin_amdgcn_raw_buffer_load_b128(r, int((s1 + 8u * k) * 2u), 0, 0);
 }
 
-// 8 IDs of a run longer than kOct loads, read when reached.  The load waits for itself
-// inside the asm block, so the compiler's count of the outstanding prefetch loads
-// (which it uses to wait for exactly the group it adds next) stays exact.
-__device__ __forceinline__ u32x4 load_ids_now(const uint16_t *p) {
-    u32x4 r;
-    asm volatile("global_load_dwordx4 %0, %1, off\n\ts_waitcnt vmcnt(0)" : "=v"(r) : "v"(p) : "memory");
-    return r;
+// The 32 IDs from byte offset `at` of the span on, for the part of a run past the loads
+// issued ahead.  The loads wait for themselves inside the asm block, so the compiler's
+// count of the outstanding prefetch loads (which it uses to wait for exactly the group it
+// adds next) stays exact (as builtins they cost runs without such a part 2%).  s_nop: a
+// scalar register of the record that a vector instruction wrote is ready.
+__device__ __forceinline__ void load_ids_now(const i32x4 &span, uint32_t at, u32x4 (&q)[kOct]) {
+    static_assert(kOct == 4, "four loads");
+    asm volatile("s_nop 4\n\t"
+                 "buffer_load_dwordx4 %0, %4, %5, 0 offen\n\t"
+                 "buffer_load_dwordx4 %1, %4, %5, 0 offen offset:16\n\t"
+                 "buffer_load_dwordx4 %2, %4, %5, 0 offen offset:32\n\t"
+                 "buffer_load_dwordx4 %3, %4, %5, 0 offen offset:48\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3]) : "v"(at), "s"(span) : "memory");
 }
 
 // Four IDs (words w0, w1) at positions p .. p + 3 of a run of `len`; those past the run
 // read the zero slot.  One test per ID everywhere costs two instructions each, but a wave
 // takes its longest run's words once (28 of 64 lanes' 16.4 on average): whole words under a
 // lane mask and then a tail of up to 7 apart took 0.500 ms for 10^6 trials of 1000
-// occurrences over 62 bins, this 0.483.  (What bounds it: the LDS is busy 60% of the time,
+// occurrences over 62 bins, this 0.483 (both with three slots).  (What bounds it: the LDS is busy 60% of the time,
 // half of that with bank conflicts of the random reads, and the vector units 47%; twice as
 // many reads in flight per wave, or an untested path for full words, were slower: 0.500 and
 // 0.490.)
@@ -140,9 +160,10 @@ __device__ __forceinline__ void add8(const double *tab, const u32x4 &q, uint32_t
     if (__builtin_amdgcn_ballot_w64(len > p + 4u) != 0) add4<MAX>(tab, q[2], q[3], p + 4u, len, acc);
 }
 
-// Adds the run [u.s, e) into acc, positions in order.  base: the bin's span.
+// Adds the run [u.s, e) into acc, positions in order.  span: the bin's record.
+constexpr uint32_t kPastSpan = 0xFFFFFF00u;   // no access (with the loads' offsets too)
 template <bool MAX>
-__device__ __forceinline__ void unit_run(const double *tab, const uint16_t *base, Unit &u, uint32_t e, double &acc) {
+__device__ __forceinline__ void unit_run(const double *tab, const i32x4 &span, Unit &u, uint32_t e, double &acc) {
     const uint32_t s1 = u.s & ~1u;
     const uint32_t len = e > s1 ? e - s1 : 0u;
     if (u.s & 1u) u.q[0].x = (u.q[0].x & 0xFFFF0000u) | kZeroId;
@@ -151,10 +172,13 @@ __device__ __forceinline__ void unit_run(const double *tab, const uint16_t *base
         if (__builtin_amdgcn_ballot_w64(len > 8u * k) == 0) return;
         add8<MAX>(tab, u.q[k], 8u * k, len, acc);
     }
-    for (uint32_t p = 8u * kOct; __builtin_amdgcn_ballot_w64(len > p) != 0; p += 8u) {
-        if (len > p) {
-            const u32x4 q = load_ids_now(base + s1 + p);
-            add8<MAX>(tab, q, p, len, acc);
+#pragma unroll 1
+    for (uint32_t p = 8u * kOct; __builtin_amdgcn_ballot_w64(len > p) != 0; p += 8u * kOct) {
+        load_ids_now(span, len > p ? (s1 + p) * 2u : kPastSpan, u.q);
+#pragma unroll
+        for (int k = 0; k < kOct; ++k) {
+            if (__builtin_amdgcn_ballot_w64(len > p + 8u * k) == 0) return;
+            add8<MAX>(tab, u.q[k], p + 8u * k, len, acc);
         }
     }
 }
@@ -163,8 +187,8 @@ __device__ __forceinline__ void unit_run(const double *tab, const uint16_t *base
 // evenly over the waves) and bins [bin0, bin1) of analysis a: every bin staged once, each
 // lane's trials added bin by bin into its sums ws[64 g + lane].
 // MAX = false: sums of the occurrence-net losses; MAX = true: each trial's largest.
-// Units u = 4 b + g (bin b, group g) rotate through three register slots (slot u % 3):
-// unit u + 3 is issued once unit u is added.  No load is issued under a condition, so
+// Units u = 4 b + g (bin b, group g) take turns in two register slots (slot u % 2): unit
+// u + 2 is issued once unit u is added.  No load is issued under a condition, so
 // that every wait counts only the loads issued after the one it waits for: past the last
 // bin, the last one's loads are issued again and its runs are empty.
 // B24: run starts in 3 bytes each, read as an unaligned 4-byte word (its top byte,
@@ -196,63 +220,54 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64
     f64x2 st[kStageVecs];
     stage_load(a, bin0, st);
     __amdgpu_buffer_rsrc_t rc = bin_rsrc(a, bin0);
-    const uint16_t *pc = a.ids16 + offset_at(a.region, bin0);
-    Unit U[3];
+    i32x4 pc = bin_words(a, bin0);
+    Unit U[2];
+    uint32_t sc[kGroups], ge[kGroups];   // this bin's run starts and group ends
 #pragma unroll
-    for (int g = 0; g < 3; ++g) {
-        U[g].s = run_start(bin0, g) & kRunMask;
+    for (int g = 0; g < kGroups; ++g) sc[g] = run_start(bin0, g) & kRunMask;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        U[g].s = sc[g];
         unit_issue(rc, U[g]);
     }
-    uint32_t s3 = run_start(bin0, 3) & kRunMask;
-    uint32_t ge[kGroups];
 #pragma unroll
     for (int g = 0; g < kGroups; ++g) ge[g] = group_end(bin0, g);
-    for (int32_t b0 = bin0; b0 < bin1; b0 += 3) {
+#pragma unroll 1
+    for (int32_t b = bin0; b < bin1; ++b) {
+        const bool more = b + 1 < bin1;
+        const int32_t bn = more ? b + 1 : bin1 - 1;
+        const __amdgpu_buffer_rsrc_t rn = bin_rsrc(a, bn);
+        const i32x4 pn = bin_words(a, bn);
+        uint32_t sn[kGroups], gn[kGroups];
 #pragma unroll
-        for (int db = 0; db < 3; ++db) {
-            const int32_t b = b0 + db;
-            if (db > 0 && b >= bin1) return;   // an exit, not a join: the loop's waits stay exact
-            const bool more = b + 1 < bin1;
-            const int32_t bn = more ? b + 1 : bin1 - 1;
-            const __amdgpu_buffer_rsrc_t rn = bin_rsrc(a, bn);
-            const uint16_t *pn = a.ids16 + offset_at(a.region, bn);
-            uint32_t sn[kGroups], gn[kGroups];
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {
-                const uint32_t x = run_start(bn, g), y = group_end(bn, g);
-                sn[g] = more ? x & kRunMask : 0u;
-                gn[g] = more ? y : 0u;
-            }
-            __syncthreads();   // every wave is done with the previous bin
-            f64x2 *dst = reinterpret_cast<f64x2 *>(tab);
-#pragma unroll
-            for (int u = 0; u < kStageVecs; ++u) dst[threadIdx.x + u * kTiledWaves * 64] = st[u];
-            __syncthreads();
-            stage_load(a, bn, st);
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {
-                const int slot = (db + g) % 3;
-                // a run ends where the next lane's starts; lane 63's at the group end
-                const uint32_t nx = uint32_t(__builtin_amdgcn_ds_bpermute(((lane + 1) & 63) * 4, int(U[slot].s)));
-                const uint32_t e = lane == 63 ? ge[g] : nx;
-                const int j = min(64 * g + lane, kTiledWaveTrials - 1);
-                double acc = ws[j];
-                unit_run<MAX>(tab, pc, U[slot], e, acc);
-                if (64 * g + lane < kTiledWaveTrials) ws[j] = acc;
-                if (g == 0) {
-                    U[slot].s = s3;
-                    unit_issue(rc, U[slot]);
-                } else {
-                    U[slot].s = sn[g - 1];
-                    unit_issue(rn, U[slot]);
-                }
-            }
-            s3 = sn[3];
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) ge[g] = gn[g];
-            rc = rn;
-            pc = pn;
+        for (int g = 0; g < kGroups; ++g) {
+            const uint32_t x = run_start(bn, g), y = group_end(bn, g);
+            sn[g] = more ? x & kRunMask : 0u;
+            gn[g] = more ? y : 0u;
         }
+        __syncthreads();   // every wave is done with the previous bin
+        f64x2 *dst = reinterpret_cast<f64x2 *>(tab);
+#pragma unroll
+        for (int u = 0; u < kStageVecs; ++u) dst[threadIdx.x + u * kTiledWaves * 64] = st[u];
+        __syncthreads();
+        stage_load(a, bn, st);
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            const int slot = g & 1;
+            // a run ends where the next lane's starts; lane 63's at the group end
+            const uint32_t nx = uint32_t(__builtin_amdgcn_ds_bpermute(((lane + 1) & 63) * 4, int(U[slot].s)));
+            const uint32_t e = lane == 63 ? ge[g] : nx;
+            const int j = min(64 * g + lane, kTiledWaveTrials - 1);
+            double acc = ws[j];
+            unit_run<MAX>(tab, pc, U[slot], e, acc);
+            if (64 * g + lane < kTiledWaveTrials) ws[j] = acc;
+            U[slot].s = g < 2 ? sc[g + 2] : sn[g - 2];
+            unit_issue(g < 2 ? rc : rn, U[slot]);
+        }
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) sc[g] = sn[g], ge[g] = gn[g];
+        rc = rn;
+        pc = pn;
     }
 }
 
