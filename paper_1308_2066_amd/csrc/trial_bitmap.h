@@ -11,7 +11,7 @@
 // A wave walks its trials in segments of 1024 events (four non-temporal loads per
 // lane: 16 bytes of int32 IDs, or 12 bytes of the YET's packed 3-byte copy, which
 // cuts the dominant stream by a quarter).  Per segment:
-//   filter  each lane tests the LDS bit of its 16 events (one LDS read each, all
+//   filter  each lane tests the LDS bit of its events, up to 16 (one LDS read each, all
 //           issued together); only events whose occurrence-net loss is nonzero pass;
 //   queue   passing events are appended to the wave's LDS queue in slot-then-lane
 //           order (mbcnt positions), so they end up dense;
@@ -125,14 +125,16 @@ __device__ __forceinline__ void drain_queue(const TrialArgs &a, const uint32_t *
 // it counts if that position lies in [lo, hi) and the event's filter bit is set.
 // lo < 4, so only lane 0 of the first load can hold events before the trial.
 // The int32 IDs are range-checked here (mx); the packed copy was checked when built.
-template <bool P24>
+// NC: the 256-event chunks looked at (hi <= 256 NC).
+template <bool P24, int NC>
 __device__ __forceinline__ uint32_t seg_queue(const TrialArgs &a, const uint32_t *tab, uint32_t *q,
                                               const IdRegs<P24> &g, int lane, int lo, int hi, uint32_t &mx,
                                               double &dacc) {
     const uint32_t cmax = uint32_t(a.catalog) - 1u;
-    uint32_t id[kSlots], e[kSlots], w[kSlots];
+    constexpr int kS = 4 * NC;
+    uint32_t id[kS], e[kS], w[kS];
 #pragma unroll
-    for (int k = 0; k < kNch; ++k) {
+    for (int k = 0; k < NC; ++k) {
         if constexpr (P24) {
             unpack_ids24(g.r[k], id + 4 * k);
         } else {
@@ -142,16 +144,16 @@ __device__ __forceinline__ uint32_t seg_queue(const TrialArgs &a, const uint32_t
         }
     }
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
+    for (int s = 0; s < kS; ++s) {
         // the packed copy was checked against the catalog when it was built
         e[s] = P24 ? id[s] : min(id[s], cmax);
         w[s] = tab[e[s] >> 5];
     }
     const int l4 = lane * 4;
-    bool f[kSlots];
+    bool f[kS];
     uint32_t total = 0;
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
+    for (int s = 0; s < kS; ++s) {
         const int base = (s >> 2) * kChunk + (s & 3);
         f[s] = (__builtin_amdgcn_ubfe(w[s], e[s], 1) != 0u) & (l4 < hi - base);
         if (s < 4) f[s] = f[s] & (l4 + base >= lo);
@@ -161,7 +163,7 @@ __device__ __forceinline__ uint32_t seg_queue(const TrialArgs &a, const uint32_t
     if (total <= uint32_t(a.qcap)) {
         // common case: the whole segment fits the queue
 #pragma unroll
-        for (int s = 0; s < kSlots; ++s) {
+        for (int s = 0; s < kS; ++s) {
             const uint64_t m = __builtin_amdgcn_ballot_w64(f[s]);
             uint32_t *qs = q + qn;
             if (f[s]) qs[__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u))] = e[s];
@@ -171,7 +173,7 @@ __device__ __forceinline__ uint32_t seg_queue(const TrialArgs &a, const uint32_t
     }
     // many flagged events: resolve the queue whenever the next slot would overflow it
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
+    for (int s = 0; s < kS; ++s) {
         const uint64_t m = __builtin_amdgcn_ballot_w64(f[s]);
         const uint32_t cnt = uint32_t(__popcll(m));
         if (qn + cnt > uint32_t(a.qcap)) {
@@ -219,7 +221,15 @@ __device__ __forceinline__ void issue(const TrialArgs &a, const uint32_t *tab, u
     p.t = cur.t;
     p.last = bcur_last(cur) ? 1u : 0u;
     p.dacc = 0.0;
-    const uint32_t qn = seg_queue<P24>(a, tab, q, r, lane, int(cur.lo), hi, mx, p.dacc);
+    // Chunks past the trial's end are not looked at (wave-uniform).  The kernel is bound by
+    // its instructions (vector units 62% busy; with all four chunks of every segment
+    // looked at 265 of them per trial of 250 events, now 160): 200,000 trials of 250 events
+    // 145 -> 95 us, of 450 154 -> 126, of 50 142 -> 84.  (A wave's trials next to each other,
+    // their offsets in its lanes, instead of a grid apart: 102.)
+    const int lo = int(cur.lo);
+    const uint32_t qn = hi <= kChunk       ? seg_queue<P24, 1>(a, tab, q, r, lane, lo, hi, mx, p.dacc)
+                        : hi <= 2 * kChunk ? seg_queue<P24, 2>(a, tab, q, r, lane, lo, hi, mx, p.dacc)
+                                           : seg_queue<P24, kNch>(a, tab, q, r, lane, lo, hi, mx, p.dacc);
     seg_rows(a, tab, q, qn, lane, v);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
