@@ -87,9 +87,10 @@ typedef struct ara_elt_terms {
 /* Where a layer's combined loss table lives while trials are analysed. */
 typedef enum ara_placement {
     ARA_PLACE_AUTO = 0,         /* pick from the catalog size (default)                              */
-    ARA_PLACE_LDS_BITMAP = 1,   /* LDS: 1 bit/event "occurrence loss nonzero" + ranks; values in L2  */
+    ARA_PLACE_LDS_BITMAP = 1,   /* LDS: 1 bit/event "occurrence loss nonzero"; values in HBM/L2       */
     ARA_PLACE_LDS_DENSE = 2,    /* LDS: the whole combined table (small catalogs)                    */
-    ARA_PLACE_GLOBAL_DENSE = 3, /* HBM/L2: the whole combined table, gathered per occurrence         */
+    ARA_PLACE_GLOBAL_DENSE = 3, /* HBM/L2: the whole combined table, gathered per occurrence (AUTO: of
+                                   the occurrences that pass a folded LDS filter, unless most would)  */
     ARA_PLACE_LDS_TILES = 4     /* LDS: the occurrence-net values of one 2^14-event catalog bin at a
                                    time, each lane adding its trial's occurrences of the bin from the
                                    YET's binned copy (needs one: see ara_yet_create).  AUTO picks it
@@ -284,7 +285,7 @@ ara_status ara_layer_set_terms(ara_ctx *ctx, ara_layer *layer, const ara_layer_t
 /* Re-enqueues the layer's table builds: with ARA_BUILD_TABLES, each member ELT's
  * direct access table from its (resident) records, then the combined table and
  * the occurrence filter.  The filter's ranks and compacted values, which only
- * ARA_PLACE_LDS_BITMAP reads, are enqueued by the first call that does;
+ * lookups with ARA_PLACE_LDS_BITMAP and ara_layer_stats read, are enqueued by the first call that does;
  * ara_layer_create and ara_layer_set_terms do the same.  Asynchronous; record errors surface at the next blocking call.
  * Errors: ARA_E_INVALID_ARG, ARA_E_DEVICE. */
 ara_status ara_layer_build(ara_ctx *ctx, ara_layer *layer, int flags);

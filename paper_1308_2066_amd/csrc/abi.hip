@@ -96,6 +96,7 @@ struct ara_layer {
     bool f32;
     EltDesc *d_descs;    // device copy of the member ELTs' descriptors
     int64_t max_pairs;
+    int64_t all_pairs = 0;    // records of its ELTs together: at most so many events are in the layer
     LayerTables t;
     uint64_t terms_gen = 0;   // incremented by every ara_layer_set_terms
     // t.rank, rel16, base32, n_flagged and vals match the current tables: rebuilds
@@ -252,13 +253,26 @@ static void dev_free(ara_ctx *c, const void *p) {
     }
 }
 
-// The bitmap trial kernel keeps the filter tables and its per-wave event queues
-// (16 waves x kQueueCapMax events) in static LDS.  Returns the queue capacity for a
-// workgroup of wpb waves, or 0 if the catalog's tables do not fit.
+// The bitmap placement: filter and ranks of the catalog in LDS beside the per-wave event
+// queues (16 waves x kQueueCapMax events).  Returns the queue capacity for a workgroup of
+// wpb waves, or 0 if the catalog's tables do not fit.
+constexpr size_t kFilterTableMax = size_t(kLdsMaxBytes) - size_t(kQueueWords) * 4;
 static int bitmap_qcap(int32_t catalog, int wpb, int lds_max) {
     const size_t table = bitmap_table_bytes(bitmap_blocks(catalog));
-    if (wpb > 16 || lds_max < kLdsMaxBytes || table > trial_bitmap_table_capacity()) return 0;
+    if (wpb > 16 || lds_max < kLdsMaxBytes || table > kFilterTableMax) return 0;
     return kQueueCapMax;
+}
+
+// Whether a table read from HBM/L2 goes behind a folded LDS filter (trial_bitmap.h): by the
+// events that pass, at most the layer's records times the folds.  100,000 trials of 400 over
+// 6 10^6 events, us behind the filter and without: 116 and 679 at 0.3 times the catalog,
+// 286 and 680 at 1.2, 616 and 687 at 4.8, 692 and 680 at 12; over 1.5 10^6, 732 and 916 at
+// 5.3.
+constexpr double kFoldPass = 5.0;
+static bool fold_pays(const ara_ctx *c, const ara_layer *L) {
+    const int64_t folds = (int64_t(L->catalog) + (int64_t(1) << kFoldBits) - 1) >> kFoldBits;
+    const int wpb = (c->block_threads ? c->block_threads : 1024) / 64;
+    return wpb <= 16 && c->lds_max >= kLdsMaxBytes && double(L->all_pairs) * double(folds) <= kFoldPass * double(L->catalog);
 }
 
 // Chooses where the layer's table lives during the trial kernel and the launch shape.
@@ -307,8 +321,10 @@ static ara_status plan_trial(ara_ctx *c, const ara_layer *L, int64_t n_trials, d
     tl.placement = pl;
     tl.f32 = L->f32;
     tl.lds_bytes = size_t(lds);
-    tl.qcap = pl == ARA_PLACE_LDS_BITMAP ? qcap : 0;
-    tl.lane = pl != ARA_PLACE_LDS_BITMAP &&
+    tl.filter = pl == ARA_PLACE_LDS_BITMAP || (pl == ARA_PLACE_GLOBAL_DENSE && c->placement == ARA_PLACE_AUTO &&
+                                              c->trial_mode == 0 && fold_pays(c, L));
+    tl.qcap = tl.filter ? kQueueCapMax : 0;
+    tl.lane = !tl.filter &&
               (c->trial_mode == 2 || (c->trial_mode == 0 && mean_len <= double(kLaneModeMaxMean)));
     // a lane per trial: workgroups of 256 spread few trials over more CUs, and each lane reads
     // its own IDs (10,000 trials of 100: 9.4 us, staged 12 us, the chain of round trips is
@@ -316,7 +332,7 @@ static ara_status plan_trial(ara_ctx *c, const ara_layer *L, int64_t n_trials, d
     // trials of 100 in a batch: 0.73 ms, read by the lanes 1.19 ms)
     const bool many = n_trials >= int64_t(c->n_cu) * 512;
     tl.block = c->block_threads ? c->block_threads
-                                : (pl == ARA_PLACE_GLOBAL_DENSE || (tl.lane && !many) ? 256 : 1024);
+                                : ((pl == ARA_PLACE_GLOBAL_DENSE && !tl.filter) || (tl.lane && !many) ? 256 : 1024);
     tl.staged = tl.lane && many && pl == ARA_PLACE_LDS_DENSE && c->lds_max >= kLdsMaxBytes &&
                 lane_staged_fits(L->catalog, tl.block / 64);
     if (tl.staged) {
@@ -326,7 +342,7 @@ static ara_status plan_trial(ara_ctx *c, const ara_layer *L, int64_t n_trials, d
     int per_cu = c->grid_per_cu;
     if (per_cu == 0) {
         const int by_threads = 2048 / tl.block;
-        const int64_t lds_all = pl == ARA_PLACE_LDS_BITMAP ? int64_t(kLdsMaxBytes) : lds;   // static LDS = all of it
+        const int64_t lds_all = tl.filter ? int64_t(kLdsMaxBytes) : lds;   // static LDS = all of it
         const int by_lds = lds_all > 0 ? int(c->lds_max / lds_all) : by_threads;
         per_cu = std::max(1, std::min(by_threads, by_lds));
     }
@@ -896,8 +912,8 @@ static ara_status layer_enqueue_filter(ara_layer *L) {
     return e == hipSuccess ? ARA_OK : hip_fail(c, e, "layer filter");
 }
 
-// The LDS-filter kernels read the layer's ranks and compacted values; the others its
-// occurrence values (or combined table) only.  Enqueued on the context's stream, before
+// Lookups with the bitmap placement read the layer's ranks and compacted values; the other
+// kernels its filter and occurrence values (or combined table) only.  Enqueued on the context's stream, before
 // the caller's kernels.
 static ara_status layer_ranks(const ara_layer *L) {
     if (L->ranks_ready) return ARA_OK;
@@ -962,6 +978,7 @@ extern "C" ara_status ara_layer_create(ara_ctx *c, ara_elt *const *elts, int32_t
     for (int32_t j = 0; j < n_elts; ++j) {
         d[size_t(j)] = elts[j]->desc;
         L->max_pairs = std::max(L->max_pairs, elts[j]->n_pairs);
+        L->all_pairs += elts[j]->n_pairs;
     }
     const int32_t nblk = bitmap_blocks(catalog);
     L->t.nblk = nblk;
@@ -1162,7 +1179,6 @@ extern "C" ara_status ara_analyze(ara_ctx *c, const ara_yet *y, const ara_layer 
     TrialLaunch tl{};
     s = plan_trial(c, L, t1 - t0, y->n_trials ? double(y->n_events) / double(y->n_trials) : 0.0, tl,
                    y->ids16 ? 1 : 0);
-    if (s == ARA_OK && tl.placement == ARA_PLACE_LDS_BITMAP) s = layer_ranks(L);
     if (s != ARA_OK) return s;
     double *dst = ylt;
     if (mem == ARA_MEM_HOST) {
@@ -1213,7 +1229,6 @@ extern "C" ara_status ara_analyze_occ_max(ara_ctx *c, const ara_yet *y, const ar
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
     TrialLaunch tl{};
     s = plan_trial(c, L, t1 - t0, 1e9, tl, y->ids16 ? 1 : 0);
-    if (s == ARA_OK && tl.placement == ARA_PLACE_LDS_BITMAP) s = layer_ranks(L);
     if (s != ARA_OK) return s;
     const int by_lds = tl.lds_bytes > 0 ? std::max(1, int(c->lds_max / int64_t(tl.lds_bytes))) : 8;
     const int64_t grid = std::min<int64_t>(int64_t(c->n_cu) * std::min(8, by_lds), (t1 - t0 + 255) / 256);
@@ -1223,13 +1238,19 @@ extern "C" ara_status ara_analyze_occ_max(ara_ctx *c, const ara_yet *y, const ar
         if (s != ARA_OK) return s;
     }
     hipError_t e = hipSuccess;
-    if (tl.placement == ARA_PLACE_LDS_TILES) {
-        // the tiled kernel with a maximum in place of the sum (trial indices inside a
-        // launch are 32-bit: very long ranges are split)
+    if (tl.placement == ARA_PLACE_LDS_TILES || tl.filter) {
+        // the tiled or filter kernel with a maximum in place of the sum (trial indices inside
+        // a launch are 32-bit: very long ranges are split)
         constexpr int64_t kMaxTrialsPerLaunch = int64_t(1) << 30;
         for (int64_t tb = t0; tb < t1 && e == hipSuccess; tb += kMaxTrialsPerLaunch) {
             const int64_t te = std::min(t1, tb + kMaxTrialsPerLaunch);
-            e = run_tiled(c, y, L, tb, te, dst + (tb - t0), tl.grid, true, nullptr, nullptr);
+            if (!tl.filter) {
+                e = run_tiled(c, y, L, tb, te, dst + (tb - t0), tl.grid, true, nullptr, nullptr);
+                continue;
+            }
+            TrialArgs a = trial_args(y, L, tb, te, dst + (tb - t0));
+            a.qcap = tl.qcap;
+            e = launch_trial_occ_max_bitmap(a, tl.grid, tl.block, c->stream);
         }
     } else {
         const TrialArgs a = trial_args(y, L, t0, t1, nullptr);
@@ -1892,8 +1913,6 @@ extern "C" ara_status ara_batch_run(ara_batch *b) {
     if (b->jobs.empty()) return ARA_OK;
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
     ara_status s = batch_refresh_terms(b);
-    for (size_t j = 0; j < b->jobs.size() && s == ARA_OK; ++j)
-        if (b->hjobs[j].placement == ARA_PLACE_LDS_BITMAP) s = layer_ranks(b->jobs[j].layer);
     if (s != ARA_OK) return s;
     if (!b->exec) {
         bool computed = false;
@@ -2210,7 +2229,6 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
     const int32_t nj = int32_t(take.size());
     const double mean_len = double(sv->yet->n_events) / double(std::max<int64_t>(1, sv->yet->n_trials));
     std::vector<std::pair<int32_t, int>> tiled;   // requests of the tiled kernel: index, grid
-    std::vector<int32_t> filtered;                // requests of the LDS-filter kernel
     std::vector<EltDesc> descs;
     std::vector<LayerBuild> builds;
     std::vector<BatchJob> jobs;
@@ -2222,11 +2240,14 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
         // the slot layer keeps its member list (every pool ELT, for the ELTs' user
         // counts); its precision and terms become the request's
         bool all_f32 = !r->elts.empty();
+        int64_t pairs = 0;
         for (int32_t k : r->elts) {
             descs.push_back(sv->pool[size_t(k)]->desc);
             all_f32 = all_f32 && sv->pool[size_t(k)]->prec == ARA_F32;
+            pairs += sv->pool[size_t(k)]->n_pairs;
         }
         L->f32 = all_f32;
+        L->all_pairs = pairs;
         L->terms = r->terms;
         builds.push_back(layer_build(nullptr, int(r->elts.size()), L->catalog, L->f32, r->terms.occ_retention,
                                      r->terms.occ_limit, L->t));
@@ -2242,7 +2263,6 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
         h.a.staged = h.mode == kModeLaneLds && lane_staged_fits(L->catalog, 16) ? 1 : 0;
         h.placement = tl.placement;
         if (h.mode == kModeTiled) tiled.emplace_back(i, tl.grid);
-        if (h.placement == ARA_PLACE_LDS_BITMAP) filtered.push_back(i);
         jobs.push_back(h);
         tb.push_back(r->t0);
         te.push_back(r->t1);
@@ -2296,10 +2316,6 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
     if (e == hipSuccess)
         e = launch_layers_tables(reinterpret_cast<const LayerBuild *>(ln.d_stage + o_builds), nj, ln.slots[0]->t.nblk,
                                  ln.stream);
-    for (size_t k = 0; k < filtered.size() && e == hipSuccess; ++k) {
-        const ara_layer *L = ln.slots[size_t(filtered[k])];
-        e = launch_layer_ranks(L->catalog, L->t, ln.stream);
-    }
     if (e == hipSuccess)
         e = launch_grouped(reinterpret_cast<const BatchJob *>(ln.d_stage + o_jobs),
                            reinterpret_cast<const BatchItem *>(ln.d_stage + o_items), ln.mode_off, ln.mode_cnt, pc->n_cu, true,

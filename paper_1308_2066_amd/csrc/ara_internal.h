@@ -60,7 +60,7 @@ constexpr int kBufWord3 = 0x00020000;       // raw buffer descriptor word 3 (32-
 constexpr int kNonTemporal = 2;           // cache policy of the ID stream loads
 constexpr int kQueueRow = 64;               // queued events are processed one wave-row at a time
 constexpr int kQueueCapMax = 192;           // per-wave queue capacity (events), a multiple of kQueueRow
-constexpr int kQueueCapMin = 128;
+constexpr int kFoldBits = 20;               // log2 of the LDS filter's bits
 constexpr int kQueueWords = 16 * kQueueCapMax;  // static LDS of the bitmap trial kernel (16 waves)
 
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
@@ -147,6 +147,7 @@ struct TrialLaunch {
     int qcap;           // per-wave queue capacity (bitmap placement)
     bool lane;          // one lane per trial (short trials, dense tables) instead of one wave
     bool staged;        // of those: IDs staged through LDS
+    bool filter;        // YLTs and maxima by the LDS-filter kernel (LDS_BITMAP, and GLOBAL_DENSE where it pays)
 };
 
 // Trials with at most this many occurrences on average go one per lane (dense tables).
@@ -184,9 +185,9 @@ hipError_t launch_batch(int32_t mode, const BatchJob *jobs, const BatchItem *ite
                         int grid, hipStream_t s);
 int32_t batch_mode(const TrialLaunch &l, bool packed);
 hipError_t launch_sum_ylts(const double *const *ylts, int32_t n_jobs, int64_t n, double *out, hipStream_t s);
-// bitmap placement (static LDS: filter tables up to trial_bitmap_table_capacity() bytes + event queues)
+// LDS filter (static LDS: the folded filter and event queues)
 hipError_t launch_trial_ylt_bitmap(const TrialArgs &a, int grid, int block, hipStream_t s);
-size_t trial_bitmap_table_capacity();
+hipError_t launch_trial_occ_max_bitmap(const TrialArgs &a, int grid, int block, hipStream_t s);
 
 // ---- catalog-binned YET copy and the tiled trial kernel
 // The catalog is cut into bins of 2^14 events (a bin's binary64 values fill most of

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(1024) void k_batch(const BatchJob *__restrict__ job
         TrialArgs a = load_uniform(&jobs[it.job].a);
         if (it.job != cur) {
             __syncthreads();   // every wave is done with the previous job's table
-            if constexpr (MODE == kModeWaveBitmap || MODE == kModeWaveBitmap24) stage_bitmap(a, lds);
+            if constexpr (MODE == kModeWaveBitmap || MODE == kModeWaveBitmap24) stage_fold(a, lds);
             else if constexpr (MODE == kModeLaneLds) stage_lds<ARA_PLACE_LDS_DENSE>(a, lds, a.staged != 0);
             else if constexpr (MODE == kModeWaveLds) stage_lds<ARA_PLACE_LDS_DENSE>(a, lds);
             // global-table modes read HBM/L2 directly: nothing to stage
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(1024) void k_batch(const BatchJob *__restrict__ job
             a.ylt += it.t0 - a.t_begin;
             a.t_begin = it.t0;
             a.t_end = it.t1;
-            bitmap_wave_run<MODE == kModeWaveBitmap24>(a, lds, lds + kTabWords + wave * uint32_t(a.qcap), wave, wpb,
+            bitmap_wave_run<MODE == kModeWaveBitmap24, false>(a, lds, lds + kFoldWords + wave * uint32_t(a.qcap), wave, wpb,
                                                        lane);
         }
     }
@@ -98,8 +98,8 @@ hipError_t launch_sum_ylts(const double *const *ylts, int32_t n_jobs, int64_t n,
 }
 
 int32_t batch_mode(const TrialLaunch &l, bool packed) {
+    if (l.filter) return packed ? kModeWaveBitmap24 : kModeWaveBitmap;
     switch (l.placement) {
-    case ARA_PLACE_LDS_BITMAP: return packed ? kModeWaveBitmap24 : kModeWaveBitmap;
     case ARA_PLACE_LDS_TILES: return kModeTiled;
     case ARA_PLACE_LDS_DENSE: return l.lane ? kModeLaneLds : kModeWaveLds;
     default: return l.lane ? kModeLaneGlobal : kModeWaveGlobal;

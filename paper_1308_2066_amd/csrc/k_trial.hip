@@ -58,12 +58,7 @@ __global__ __launch_bounds__(1024) void k_trial_ylt_lane(TrialArgs a) {
 // any order.  Its distribution over trials is the occurrence exceedance curve.
 template <int PL>
 __device__ __forceinline__ double occ_value(const TrialArgs &a, const uint32_t *lds, uint32_t id) {
-    if (PL == ARA_PLACE_LDS_BITMAP) {
-        const uint32_t w = lds[id >> 5];
-        return ((w >> (id & 31u)) & 1u) ? a.vals[bitmap_rank(lds, a.nblk, id)] : 0.0;
-    } else if (PL == ARA_PLACE_LDS_DENSE) {
-        return reinterpret_cast<const double *>(lds)[id];
-    }
+    if (PL == ARA_PLACE_LDS_DENSE) return reinterpret_cast<const double *>(lds)[id];
     return a.occ[id];
 }
 
@@ -280,7 +275,6 @@ hipError_t prepare_trial_kernels() {
     ARA_SET_LDS(k_trial_ylt<ARA_PLACE_LDS_DENSE>)
     ARA_SET_LDS(k_trial_ylt_lane<ARA_PLACE_LDS_DENSE>)
     ARA_SET_LDS(k_trial_occ_max<ARA_PLACE_LDS_DENSE>)
-    ARA_SET_LDS(k_trial_occ_max<ARA_PLACE_LDS_BITMAP>)
     ARA_SET_LDS((k_lookup<ARA_PLACE_LDS_BITMAP, double>))
     ARA_SET_LDS((k_lookup<ARA_PLACE_LDS_DENSE, double>))
     ARA_SET_LDS((k_lookup<ARA_PLACE_LDS_BITMAP, float>))
@@ -292,9 +286,8 @@ hipError_t prepare_trial_kernels() {
 }
 
 hipError_t launch_trial_ylt(const TrialArgs &a, const TrialLaunch &l, hipStream_t s) {
+    if (l.filter) return launch_trial_ylt_bitmap(a, l.grid, l.block, s);
     switch (l.placement) {
-    case ARA_PLACE_LDS_BITMAP:
-        return launch_trial_ylt_bitmap(a, l.grid, l.block, s);
     case ARA_PLACE_LDS_DENSE:
         if (l.lane)
             hipLaunchKernelGGL(k_trial_ylt_lane<ARA_PLACE_LDS_DENSE>, dim3(l.grid), dim3(l.block), l.lds_bytes, s, a);
@@ -313,9 +306,6 @@ hipError_t launch_trial_ylt(const TrialArgs &a, const TrialLaunch &l, hipStream_
 
 hipError_t launch_trial_occ_max(const TrialArgs &a, const TrialLaunch &l, int grid, double *out, hipStream_t s) {
     switch (l.placement) {
-    case ARA_PLACE_LDS_BITMAP:
-        hipLaunchKernelGGL(k_trial_occ_max<ARA_PLACE_LDS_BITMAP>, dim3(grid), dim3(256), l.lds_bytes, s, a, out);
-        break;
     case ARA_PLACE_LDS_DENSE:
         hipLaunchKernelGGL(k_trial_occ_max<ARA_PLACE_LDS_DENSE>, dim3(grid), dim3(256), l.lds_bytes, s, a, out);
         break;
