@@ -120,16 +120,30 @@ __device__ __forceinline__ void store2(double *out, int64_t pos, double v0, doub
 // ---------------------------------------------------------------------------------
 // Per-occurrence form: every quantity of the basic algorithm, with the cumulative
 // sum as wave-wide inclusive scans (lane-local over 2 consecutive events, then a
-// 64-lane scan, plus the carry from the previous 128 events).  NZ: the layer's
-// "combined loss nonzero" bits are staged in LDS and only events with a set bit
-// read the combined table (the others' gross loss is +0.0, as the table holds).
-template <typename V, bool NZ>
-__global__ __launch_bounds__(1024) void k_trial_events(TrialArgs a) {
+// 64-lane scan, plus the carry from the previous 128 events).  The layer's "combined
+// loss nonzero" bits are staged in LDS, folded to nz_blocks blocks of 128 (a power of two;
+// word index & nz_mask) where a catalog's do not fit, and only events with a set bit read
+// the combined table (the others' gross loss is +0.0, as the table holds).
+//
+// Bound by writing: 50,000 trials of 900 events write 1.44 GB and read 0.18 GB of IDs and
+// 0.25 GB of table lines in 370 us (5.0 TB/s; a large copy reaches 4.9).  Segments of trials
+// of more than 512 events start at multiples of 16, so that a wave's store covers whole
+// 128-byte lines: from multiples of 4 it took 428 us (plain instead of non-temporal stores
+// 464, and 415 from multiples of 16).  Shorter trials would pay for the events before them:
+// 30,000 of 400 139 us from multiples of 4, 143 of 16.  Reading the next segment ahead and scanning by lane moves instead of
+// LDS permutes changed nothing.  30,000 trials over 2 10^6 events, whose bits were not
+// looked at before: 510 us, folded 252.
+template <typename V>
+__global__ __launch_bounds__(1024) void k_trial_events(TrialArgs a, int nz_blocks, uint32_t nz_mask) {
     extern __shared__ __attribute__((aligned(16))) uint32_t nzl[];
-    if (NZ) {
+    {
         const u32x4 *src = reinterpret_cast<const u32x4 *>(a.nz);
         u32x4 *dst = reinterpret_cast<u32x4 *>(nzl);
-        for (int i = threadIdx.x; i < a.nblk; i += blockDim.x) dst[i] = src[i];
+        for (int i = threadIdx.x; i < nz_blocks; i += blockDim.x) {
+            u32x4 w = src[i];
+            for (int k = i + nz_blocks; k < a.nblk; k += nz_blocks) w |= src[k];
+            dst[i] = w;
+        }
         __syncthreads();
     }
     const int lane = threadIdx.x & 63;
@@ -143,6 +157,7 @@ __global__ __launch_bounds__(1024) void k_trial_events(TrialArgs a) {
     for (int64_t t = a.t_begin + int64_t(blockIdx.x) * wpb + wave; t < a.t_end; t += stride) {
         Cursor c;
         open_trial(a, t, c, bad);
+        if (c.o1 - c.o0 > 2 * kChunk) c.sbase = c.o0 & ~int64_t(15);
         double carryP = 0.0, carryF = 0.0, lr = 0.0;
         while (true) {
             u32x4 r[kNch];
@@ -177,13 +192,14 @@ __global__ __launch_bounds__(1024) void k_trial_events(TrialArgs a) {
                     if (valid && !inr) bad |= ERR_ID_RANGE;
                     ok[j] = valid && inr;
                     const uint32_t idc = ok[j] ? id : 0u;   // lanes outside the trial read word 0
-                    const bool look = NZ ? ok[j] && ((nzl[idc >> 5] >> (idc & 31u)) & 1u) : ok[j];
+                    const bool look = ok[j] && ((nzl[(idc >> 5) & nz_mask] >> (idc & 31u)) & 1u);
                     x[j] = look ? double(comb[id]) : 0.0;
                     o[j] = ok[j] ? excess(x[j], a.occ_r, a.occ_l) : 0.0;
                 }
                 // cumulative sums: the chunk's first 128 events, then its last 128
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
+                    if (k * kChunk + 128 * h >= hi) break;
                     const double q0 = o[2 * h], q1 = o[2 * h] + o[2 * h + 1];
                     double inc = q1;
 #pragma unroll
@@ -279,8 +295,8 @@ hipError_t prepare_trial_kernels() {
     ARA_SET_LDS((k_lookup<ARA_PLACE_LDS_DENSE, double>))
     ARA_SET_LDS((k_lookup<ARA_PLACE_LDS_BITMAP, float>))
     ARA_SET_LDS((k_lookup<ARA_PLACE_LDS_DENSE, float>))
-    ARA_SET_LDS((k_trial_events<double, true>))
-    ARA_SET_LDS((k_trial_events<float, true>))
+    ARA_SET_LDS(k_trial_events<double>)
+    ARA_SET_LDS(k_trial_events<float>)
 #undef ARA_SET_LDS
     return hipSuccess;
 }
@@ -318,17 +334,13 @@ hipError_t launch_trial_occ_max(const TrialArgs &a, const TrialLaunch &l, int gr
 
 hipError_t launch_trial_events(const TrialArgs &a, bool f32, int n_cu, int lds_max, hipStream_t s) {
     const int64_t waves = a.t_end - a.t_begin;
-    const size_t nz_bytes = size_t(a.nblk) * 16;
-    if (a.nz && nz_bytes <= size_t(lds_max)) {
-        // one workgroup of 16 waves per CU holds the bits
-        const int grid = int(std::max<int64_t>(1, std::min<int64_t>(n_cu, (waves + 15) / 16)));
-        if (f32) hipLaunchKernelGGL((k_trial_events<float, true>), dim3(grid), dim3(1024), nz_bytes, s, a);
-        else hipLaunchKernelGGL((k_trial_events<double, true>), dim3(grid), dim3(1024), nz_bytes, s, a);
-    } else {
-        const int grid = int(std::max<int64_t>(1, std::min<int64_t>(int64_t(n_cu) * 8, (waves + 3) / 4)));
-        if (f32) hipLaunchKernelGGL((k_trial_events<float, false>), dim3(grid), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((k_trial_events<double, false>), dim3(grid), dim3(256), 0, s, a);
-    }
+    // one workgroup of 16 waves per CU holds the bits: the catalog's, or 2^kFoldBits
+    const bool fold = size_t(a.nblk) * 16 > size_t(lds_max);
+    const int blocks = fold ? 1 << (kFoldBits - 7) : a.nblk;
+    const uint32_t mask = fold ? (1u << (kFoldBits - 5)) - 1u : ~0u;
+    const int grid = int(std::max<int64_t>(1, std::min<int64_t>(n_cu, (waves + 15) / 16)));
+    if (f32) hipLaunchKernelGGL(k_trial_events<float>, dim3(grid), dim3(1024), size_t(blocks) * 16, s, a, blocks, mask);
+    else hipLaunchKernelGGL(k_trial_events<double>, dim3(grid), dim3(1024), size_t(blocks) * 16, s, a, blocks, mask);
     return hipGetLastError();
 }
 
