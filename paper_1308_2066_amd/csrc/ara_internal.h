@@ -71,10 +71,12 @@ __host__ __device__ inline size_t bitmap_rel_offset(int32_t nblk) { return size_
 __host__ __device__ inline size_t bitmap_base_offset(int32_t nblk) { return bitmap_rel_offset(nblk) + align16(size_t(nblk) * 2); }
 __host__ __device__ inline size_t bitmap_table_bytes(int32_t nblk) { return bitmap_base_offset(nblk) + align16(size_t(bitmap_supers(nblk)) * 4); }
 
-// LDS of the lane-per-trial kernel that stages its IDs: the table with a zero entry, then
-// 4 KB per wave.
+// LDS of the lane-per-trial kernel that stages its IDs: the table with a zero entry, the
+// masks of a row's last IDs (trial_dense.h), then 4 KB per wave.
 constexpr int kStageBytes = 4096;
-__host__ __device__ inline size_t lane_table_bytes(int32_t catalog) { return align16((size_t(catalog) + 1) * 8); }
+constexpr int kRowMaskBytes = 9 * 16;
+__host__ __device__ inline size_t lane_masks_at(int32_t catalog) { return align16((size_t(catalog) + 1) * 8); }
+__host__ __device__ inline size_t lane_table_bytes(int32_t catalog) { return lane_masks_at(catalog) + kRowMaskBytes; }
 __host__ __device__ inline bool lane_staged_fits(int32_t catalog, int waves) {
     return lane_table_bytes(catalog) + size_t(waves) * kStageBytes <= size_t(kLdsMaxBytes);
 }

@@ -83,7 +83,14 @@ __device__ __forceinline__ void stage_lds(const TrialArgs &a, uint32_t *lds, boo
                 if (i0 + k * bd < n4) l4[i0 + k * bd] = v[k];
         }
         for (int i = (n4 << 2) + threadIdx.x; i < n; i += blockDim.x) lds[i] = g[i];
-        if (zero && threadIdx.x < 2) lds[n + threadIdx.x] = 0u;   // an entry of +0.0 after the table
+        if (zero) {   // an entry of +0.0 after the table, and the row masks (see row_add)
+            uint32_t *m = lds + lane_masks_at(a.catalog) / 4;
+            if (threadIdx.x < 2) lds[n + threadIdx.x] = 0u;
+            if (threadIdx.x < kRowMaskBytes / 4) {
+                const int r = int(threadIdx.x >> 2), j = 2 * int(threadIdx.x & 3);   // IDs j, j + 1 of a piece that holds r
+                m[threadIdx.x] = (j < r ? 0u : 0xFFFFu) | (j + 1 < r ? 0u : 0xFFFF0000u);
+            }
+        }
     }
     __syncthreads();
 }
@@ -315,7 +322,13 @@ __device__ __forceinline__ void dense_lane_run(const TrialArgs &a, const uint32_
 // first group of four.  Window w + 1, or the first of the wave's next 64 trials, is loaded
 // while window w is added.
 //   IDs of the catalog size or more are clamped to it and read the zero entry after the
-// table; so do the positions outside the trial.
+// table; so do the positions outside the trial.  The packed copy was checked when it was
+// built, so its IDs take no test or clamp, and two bytes of each go to LDS as they are.
+//   What it measured: 7.2x10^8 occurrences of 13 requests in a batch 715 us; with the masks,
+// the packed IDs as they are, and no address kept over the loop that two instructions form
+// (ten of them were spilled, and a reload goes the way of the loads) 657; 64 jobs over
+// 10,000 trials 49 -> 39.  2.4 GB of IDs come from HBM (390 us at 6.1 TB/s); the LDS is busy
+// 40% of the time, the path that returns loads 70%.
 constexpr int kRowBytes = 64;   // 32 IDs of one trial
 static_assert(64 * kRowBytes == kStageBytes, "a row per lane");
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
@@ -341,26 +354,28 @@ __device__ __forceinline__ uint32_t value_hi(uint32_t w) {
     return r;
 }
 
-// Adds the IDs of a row's words q (8 IDs, the row's j0-th on) at positions [lo, hi) of the
-// window, in order.  ALL: every position.
-template <bool ALL>
-__device__ __forceinline__ void row_add(const char *tab, const u32x4 &q, int32_t j0, int32_t lo, int32_t hi, uint32_t c2,
-                                        double &P, uint32_t &mx) {
+// Adds the 8 IDs of a row's piece q in order: all of them, or those before the r-th (TAIL,
+// any r) and from the lead-th on (FIRST: the trial's first piece, lead < 4).  The others
+// become 0xFFFF, which the clamp turns into the zero entry's: by a row of masks in LDS for
+// each r (two comparisons and selections for each ID took twice the instructions).
+// CHECKED: the IDs are known to be in the catalog.
+template <bool FIRST, bool TAIL, bool CHECKED>
+__device__ __forceinline__ void row_add(const char *tab, const char *masks, const u32x4 &q, int32_t lead, int32_t r,
+                                        uint32_t c2, double &P, uint32_t &mx) {
+    u32x4 w = q, out{0u, 0u, 0u, 0u};   // out: what is not to be added
+    if (TAIL) out = *reinterpret_cast<const u32x4 *>(masks + 16 * max(0, min(r, 8)));
+    if (FIRST) {
+        out[0] |= lead >= 2 ? ~0u : lead == 1 ? 0xFFFFu : 0u;
+        out[1] |= lead == 3 ? 0xFFFFu : 0u;
+    }
     double v[8];
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        uint32_t w = q[d];
-        if (!ALL) {
-            const int32_t j = j0 + 2 * d;
-            const uint32_t m = (j >= lo && j < hi ? 0xFFFFu : 0u) | (j + 1 >= lo && j + 1 < hi ? 0xFFFF0000u : 0u);
-            mx = pk_max(mx, w & m);
-            w |= ~m;
-        } else {
-            mx = pk_max(mx, w);
-        }
-        w = pk_min(w, c2);
-        v[2 * d] = *reinterpret_cast<const double *>(tab + value_lo(w));
-        v[2 * d + 1] = *reinterpret_cast<const double *>(tab + value_hi(w));
+        if (!CHECKED) mx = pk_max(mx, FIRST || TAIL ? w[d] & ~out[d] : w[d]);
+        if (FIRST || TAIL) w[d] |= out[d];
+        if (FIRST || TAIL || !CHECKED) w[d] = pk_min(w[d], c2);
+        v[2 * d] = *reinterpret_cast<const double *>(tab + value_lo(w[d]));
+        v[2 * d + 1] = *reinterpret_cast<const double *>(tab + value_hi(w[d]));
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) P += v[j];
@@ -375,21 +390,24 @@ __device__ __forceinline__ void dense_lane_staged(const TrialArgs &a, const char
     constexpr int64_t kSpan = int64_t(1) << 28;
     const uint32_t C = uint32_t(a.catalog), c2 = C | (C << 16);
     const int lane = threadIdx.x & 63, row8 = lane >> 3, col = lane & 7;
+    const char *masks = tab + lane_masks_at(a.catalog);
     const char *src = P24 ? reinterpret_cast<const char *>(a.ids24) : reinterpret_cast<const char *>(a.ids);
     // IDs that can be read: the packed copy is padded to whole groups
     const int64_t n_ids = P24 ? (a.n_events + 3) & ~int64_t(3) : a.n_events;
     uint32_t bad = 0, mx = 0, big = 0;
-    // the trials being loaded: trial 8 i + row8's first group and end, in IDs from the record's start
-    uint32_t st[8], en[8];
+    // the trials being loaded, of trial 8 i + row8 for column col of its windows: the byte
+    // offset in window 0, and the IDs from there to the trial's end
+    uint32_t st[8];
+    int32_t left[8];
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)src, 0, 0, kBufWord3);
     Ids R[8];
     auto load = [&](uint32_t w) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const uint32_t at = st[i] + 32u * w + 4u * uint32_t(col);
-            const uint32_t off = at < en[i] ? at * uint32_t(kBytes) : 0xFFFFFF00u;   // outside any record
-            if constexpr (P24) R[i] = __builtin_amdgcn_raw_buffer_load_b96(rs, int(off), 0, 0);
-            else R[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, int(off), 0, 0);
+            const uint32_t off = int32_t(32u * w) < left[i] ? st[i] : 0xF0000000u;   // outside any record
+            const int window = int(32u * w * uint32_t(kBytes));
+            if constexpr (P24) R[i] = __builtin_amdgcn_raw_buffer_load_b96(rs, int(off), window, 0);
+            else R[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, int(off), window, 0);
         }
     };
     // the trial's positions [lead, len) from its first group on, and its sum so far
@@ -426,8 +444,8 @@ __device__ __forceinline__ void dense_lane_staged(const TrialArgs &a, const char
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            st[i] = uint32_t(__shfl(int(s), 8 * i + row8, 64));
-            en[i] = st[i] + uint32_t(__shfl(x.len, 8 * i + row8, 64));
+            st[i] = (uint32_t(__shfl(int(s), 8 * i + row8, 64)) + 4u * uint32_t(col)) * uint32_t(kBytes);
+            left[i] = __shfl(x.len, 8 * i + row8, 64) - 4 * col;
         }
         const int64_t n = min(n_ids - base, kSpan + 4);
         rs = __builtin_amdgcn_make_buffer_rsrc((void *)(src + base * kBytes), 0, int(uint32_t(n) * uint32_t(kBytes)), kBufWord3);
@@ -441,19 +459,22 @@ __device__ __forceinline__ void dense_lane_staged(const TrialArgs &a, const char
     load(0);
     uint32_t w = 0;
     for (;;) {
-        // this window's IDs to LDS; a row's 16-byte pieces are rotated by its number so that
+        // this window's IDs to LDS; a row's 16-byte pieces are rotated by its number / 4 so that
         // the lanes' reads below fall on different banks
+        uint32_t to = uint32_t(row8 * kRowBytes + ((col >> 1) ^ (row8 >> 2)) * 16 + (col & 1) * 8);
+        asm volatile("" : "+v"(to));   // formed here, not kept over the loop (as turn below)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            uint32_t id[4];
-            if constexpr (P24) unpack_ids24(R[i], id);
-            else id[0] = R[i].x, id[1] = R[i].y, id[2] = R[i].z, id[3] = R[i].w;
-            const int r = 8 * i + row8;
             typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
             u32x2 p;
-            p.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_u16(id[0], id[1]));   // saturated
-            p.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_u16(id[2], id[3]));
-            *reinterpret_cast<u32x2 *>(stage + r * kRowBytes + (((col >> 1) ^ ((r >> 2) & 3)) * 16) + (col & 1) * 8) = p;
+            if constexpr (P24) {   // the low two bytes of each three (the IDs are below the catalog, it below 2^16)
+                p.x = __builtin_amdgcn_perm(R[i].y, R[i].x, 0x04030100u);
+                p.y = __builtin_amdgcn_perm(R[i].z, R[i].y, 0x06050302u);
+            } else {
+                p.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_u16(R[i].x, R[i].y));   // saturated
+                p.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_u16(R[i].z, R[i].w));
+            }
+            *reinterpret_cast<u32x2 *>(stage + (to ^ (i & 1 ? 32u : 0u)) + 8 * i * kRowBytes) = p;
         }
         const bool more = __builtin_amdgcn_ballot_w64(cur.len > int32_t(32u * w + 32u)) != 0;
         Trial nxt = cur;
@@ -465,17 +486,21 @@ __device__ __forceinline__ void dense_lane_staged(const TrialArgs &a, const char
         }
         if (!last) load(more ? w + 1u : 0u);
         __builtin_amdgcn_wave_barrier();
-        const int32_t lo = cur.lead - int32_t(32u * w), hi = cur.len - int32_t(32u * w);
+        const int32_t hi = cur.len - int32_t(32u * w);
         const char *row = stage + lane * kRowBytes;
+        uint32_t turn = uint32_t((lane >> 2) & 3) * 16u;
+        asm volatile("" : "+v"(turn));   // four addresses formed here, not kept over the loop
         u32x4 q[4];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) q[p] = *reinterpret_cast<const u32x4 *>(row + ((p ^ ((lane >> 2) & 3)) * 16));
+        for (int p = 0; p < 4; ++p) q[p] = *reinterpret_cast<const u32x4 *>(row + (turn ^ uint32_t(16 * p)));
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            if (__builtin_amdgcn_ballot_w64(lo > 8 * p || hi < 8 * p + 8) == 0)
-                row_add<true>(tab, q[p], 8 * p, lo, hi, c2, cur.P, mx);
+            if (p == 0 && w == 0)
+                row_add<true, true, P24>(tab, masks, q[0], cur.lead, hi, c2, cur.P, mx);
+            else if (__builtin_amdgcn_ballot_w64(hi < 8 * p + 8) == 0)
+                row_add<false, false, P24>(tab, masks, q[p], 0, 0, c2, cur.P, mx);
             else if (__builtin_amdgcn_ballot_w64(hi > 8 * p) != 0)
-                row_add<false>(tab, q[p], 8 * p, lo, hi, c2, cur.P, mx);
+                row_add<false, true, P24>(tab, masks, q[p], 0, hi - 8 * p, c2, cur.P, mx);
         }
         __builtin_amdgcn_wave_barrier();
         if (more) {
