@@ -96,6 +96,7 @@ struct ara_layer {
     bool f32;
     EltDesc *d_descs;    // device copy of the member ELTs' descriptors
     int64_t max_pairs;
+    bool repeats = false;     // an ELT is listed more than once
     int64_t all_pairs = 0;    // records of its ELTs together: at most so many events are in the layer
     LayerTables t;
     uint64_t terms_gen = 0;   // incremented by every ara_layer_set_terms
@@ -457,6 +458,7 @@ extern "C" ara_status ara_ctx_create(int device, void *hip_stream, ara_ctx **out
     c->lds_max = std::min(lds, kLdsMaxBytes);
     const char *step = "kernel attributes";
     e = prepare_trial_kernels();
+    if (e == hipSuccess) e = prepare_ingest_kernels();
     if (e == hipSuccess) { step = "scratch address"; e = scratch_address(device, &c->scratch); }
     // the error word (and a spare word) followed by the result staging, on the device and
     // pinned on the host, so one copy brings back results and error bits together
@@ -881,8 +883,7 @@ extern "C" ara_status ara_elt_create(ara_ctx *c, const int32_t *ids, const doubl
     d.retention = terms ? terms->retention : 0.0;
     d.limit = terms ? terms->limit : INFINITY;
     hipError_t e = hipMemcpy(t->d_desc, &d, sizeof(EltDesc), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = launch_elt_clear(t->d_desc, 1, catalog, c->stream);
-    if (e == hipSuccess) e = launch_elt_scatter(t->d_desc, 1, n_pairs, catalog, c->d_err, c->stream);
+    if (e == hipSuccess) e = launch_elt_tables(t->d_desc, 1, n_pairs, catalog, false, c->n_cu, c->d_err, c->stream);
     s = e == hipSuccess ? sync_and_check(c) : hip_fail(c, e, "elt build");
     if (s != ARA_OK) {
         elt_free(t);
@@ -928,10 +929,8 @@ static ara_status layer_enqueue_build(ara_layer *L, int flags) {
     ara_ctx *c = L->ctx;
     const int n = int(L->elts.size());
     hipError_t e = hipSuccess;
-    if ((flags & ARA_BUILD_TABLES) && n > 0) {
-        e = launch_elt_clear(L->d_descs, n, L->catalog, c->stream);
-        if (e == hipSuccess) e = launch_elt_scatter(L->d_descs, n, L->max_pairs, L->catalog, c->d_err, c->stream);
-    }
+    if (flags & ARA_BUILD_TABLES)
+        e = launch_elt_tables(L->d_descs, n, L->max_pairs, L->catalog, L->repeats, c->n_cu, c->d_err, c->stream);
     L->ranks_ready = false;
     if (e == hipSuccess)
         e = launch_layer_tables(L->d_descs, n, L->catalog, L->f32, L->terms.occ_retention, L->terms.occ_limit, L->t,
@@ -980,6 +979,9 @@ extern "C" ara_status ara_layer_create(ara_ctx *c, ara_elt *const *elts, int32_t
         L->max_pairs = std::max(L->max_pairs, elts[j]->n_pairs);
         L->all_pairs += elts[j]->n_pairs;
     }
+    std::vector<ara_elt *> sorted(L->elts);
+    std::sort(sorted.begin(), sorted.end());
+    L->repeats = std::adjacent_find(sorted.begin(), sorted.end()) != sorted.end();
     const int32_t nblk = bitmap_blocks(catalog);
     L->t.nblk = nblk;
     ara_status s = dev_alloc(c, &L->d_descs, sizeof(EltDesc) * size_t(n_elts), "layer descriptors");

@@ -112,9 +112,10 @@ hipError_t launch_validate_yet(const int32_t *ids, int64_t n_events, const int64
                                bool check_ids = true);
 size_t yet_packed_bytes(int64_t n_events);
 hipError_t launch_yet_pack(const int32_t *ids, int64_t n_events, uint8_t *packed, hipStream_t s);
-hipError_t launch_elt_clear(const EltDesc *d, int n_elts, int32_t catalog, hipStream_t s);
-hipError_t launch_elt_scatter(const EltDesc *d, int n_elts, int64_t max_pairs, int32_t catalog, uint32_t *err,
-                              hipStream_t s);
+// The ELTs' direct access tables from their records; repeats: one may be listed twice.
+hipError_t launch_elt_tables(const EltDesc *d, int n_elts, int64_t max_pairs, int32_t catalog, bool repeats, int n_cu,
+                             uint32_t *err, hipStream_t s);
+hipError_t prepare_ingest_kernels();
 // One layer's combined-table build.
 struct LayerBuild {
     const EltDesc *d;

@@ -93,7 +93,7 @@ __global__ void k_elt_clear(const EltDesc *__restrict__ d, int32_t catalog) {
     for (size_t k = i; k < seen_words; k += stride) e.seen[k] = 0u;
 }
 
-hipError_t launch_elt_clear(const EltDesc *d, int n_elts, int32_t catalog, hipStream_t s) {
+static hipError_t launch_elt_clear(const EltDesc *d, int n_elts, int32_t catalog, hipStream_t s) {
     if (n_elts <= 0) return hipSuccess;
     const size_t words = (size_t(catalog) + 31) / 32;
     unsigned bx = unsigned(std::min<size_t>((words + 255) / 256, 1024));
@@ -123,12 +123,95 @@ __global__ void k_elt_scatter(const EltDesc *__restrict__ d, int32_t catalog, ui
     if (bad) atomicOr(err, bad);
 }
 
-hipError_t launch_elt_scatter(const EltDesc *d, int n_elts, int64_t max_pairs, int32_t catalog, uint32_t *err,
+static hipError_t launch_elt_scatter(const EltDesc *d, int n_elts, int64_t max_pairs, int32_t catalog, uint32_t *err,
                               hipStream_t s) {
     if (n_elts <= 0 || max_pairs <= 0) return hipSuccess;
     unsigned bx = unsigned(std::min<int64_t>((max_pairs + 255) / 256, 1024));
     hipLaunchKernelGGL(k_elt_scatter, dim3(bx, unsigned(n_elts)), dim3(256), 0, s, d, catalog, err);
     return hipGetLastError();
+}
+
+// Both in one launch, without atomics on memory: a workgroup takes one stretch of one ELT's
+// events (grid: stretches x ELTs), reads all of the ELT's record IDs, and for those of its
+// stretch sets the bit in LDS (which shows a repeated event), writes the value, and at the
+// end the stretch's bits.  Every workgroup of an ELT reads its IDs, from the L2 after the
+// first; the marks' atomics, each of which went to memory, took most of the time: 30 ELTs
+// of 30,000 records over 2 10^6 events 5 + 35 us, now 30 (a line per value written); 16 of
+// 20,000 over 10^6 2.8 + 16, now 15; 4 of 2000 over 10,000 2 + 5, now 4.
+constexpr int kBuildThreads = 1024, kBuildLoads = 8;
+__global__ __launch_bounds__(kBuildThreads) void k_elt_build(const EltDesc *__restrict__ d, int32_t catalog,
+                                                             uint32_t stretch_words, uint32_t *err) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t bits[];
+    typedef const __attribute__((address_space(4))) EltDesc *ConstDesc;
+    const ConstDesc e = (ConstDesc)d + blockIdx.y;
+    const uint32_t tid = threadIdx.x, w0 = blockIdx.x * stretch_words;
+    const uint32_t words = (uint32_t(catalog) + 31u) / 32u, w1 = min(words, w0 + stretch_words);
+    const int n = int(e->n_pairs);
+    const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc((void *)e->pair_ids, 0, n * 4, kBufWord3);
+    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc((void *)e->pair_losses, 0, n * 8, kBufWord3);
+    void *dat = e->dat;
+    const bool f32 = e->f32 != 0;
+    for (uint32_t i = tid; i < stretch_words; i += kBuildThreads) bits[i] = 0u;
+    __syncthreads();
+    uint32_t bad = 0;
+    for (int i0 = int(tid); __builtin_amdgcn_ballot_w64(i0 < n) != 0; i0 += kBuildThreads * kBuildLoads) {
+        uint32_t id[kBuildLoads], at[kBuildLoads];
+        double l[kBuildLoads];
+#pragma unroll
+        for (int u = 0; u < kBuildLoads; ++u)
+            id[u] = uint32_t(__builtin_amdgcn_raw_buffer_load_b32(ri, (i0 + u * kBuildThreads) * 4, 0, 0));
+#pragma unroll
+        for (int u = 0; u < kBuildLoads; ++u) {
+            const int i = i0 + u * kBuildThreads;
+            const bool in = i < n && id[u] < uint32_t(catalog);
+            if (i < n && !in) bad |= ERR_ID_RANGE;
+            at[u] = in && (id[u] >> 5) - w0 < w1 - w0 && (id[u] >> 5) >= w0 ? uint32_t(i) * 8u : 0xFFFFFFF8u;
+            l[u] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rl, int(at[u]), 0, 0));
+        }
+#pragma unroll
+        for (int u = 0; u < kBuildLoads; ++u) {
+            if (at[u] == 0xFFFFFFF8u) continue;
+            if (!(l[u] >= 0.0) || __builtin_isinf(l[u])) {
+                bad |= ERR_LOSS;
+                continue;
+            }
+            const uint32_t bit = 1u << (id[u] & 31u);
+            if (atomicOr(&bits[(id[u] >> 5) - w0], bit) & bit) bad |= ERR_DUP;
+            if (f32) static_cast<float *>(dat)[id[u]] = float(l[u]);
+            else static_cast<double *>(dat)[id[u]] = l[u];
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = tid; w0 + i < w1; i += kBuildThreads) e->seen[w0 + i] = bits[i];
+    if (bad) atomicOr(err, bad);
+}
+
+// Every workgroup of an ELT reads its IDs, so ELTs of many records, and catalogs whose
+// stretches would be many, take the two launches above.
+constexpr int64_t kBuildMaxPairs = int64_t(1) << 17;
+constexpr int32_t kBuildMaxCatalog = 1 << 25;
+constexpr uint32_t kBuildMaxWords = 1u << 15;   // 128 KB of bits
+
+hipError_t launch_elt_tables(const EltDesc *d, int n_elts, int64_t max_pairs, int32_t catalog, bool repeats, int n_cu,
+                             uint32_t *err, hipStream_t s) {
+    if (n_elts <= 0) return hipSuccess;
+    if (repeats || max_pairs > kBuildMaxPairs || catalog > kBuildMaxCatalog) {
+        const hipError_t e = launch_elt_clear(d, n_elts, catalog, s);
+        return e == hipSuccess ? launch_elt_scatter(d, n_elts, max_pairs, catalog, err, s) : e;
+    }
+    const uint32_t words = (uint32_t(catalog) + 31u) / 32u;
+    // about a workgroup per CU, at most 32 stretches of an ELT unless its bits need more
+    uint32_t parts = uint32_t(std::min(32, std::max(1, n_cu / n_elts)));
+    parts = std::max(parts, (words + kBuildMaxWords - 1) / kBuildMaxWords);
+    const uint32_t each = (words + parts - 1) / parts;
+    hipLaunchKernelGGL(k_elt_build, dim3((words + each - 1) / each, unsigned(n_elts)), dim3(kBuildThreads), each * 4u, s, d,
+                       catalog, each, err);
+    return hipGetLastError();
+}
+
+hipError_t prepare_ingest_kernels() {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(k_elt_build), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               int(kBuildMaxWords * 4u));
 }
 
 }  // namespace ara

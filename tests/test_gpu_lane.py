@@ -11,7 +11,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("catalog", [1, 2, 1000, 12_287, 12_288, 20_480])
+@pytest.mark.parametrize("catalog", [1, 2, 1000, 12_268, 12_269, 12_270, 12_287, 12_288, 20_480])
 @pytest.mark.parametrize("n,kind", [(1, "one"), (63, "edges"), (64, "edges"), (700, "edges"), (3000, "poisson")])
 def test_lane_bits(ara_lib, gpu_ctx, catalog, n, kind):
     import torch
