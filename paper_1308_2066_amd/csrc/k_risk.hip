@@ -30,9 +30,9 @@
 // dependent kernels takes 4.5-5 us whatever it does (8 MB of losses are 1.3 us of HBM), so
 // the passes that replaced one 8-bit digit each (12 launches, 105 us for 10^6 distinct
 // losses and 135 us when a rank fell among capped years, whose bucket never became small)
-// are now four (39 us for 10^6 losses, 31 us for 50,000).  Within a launch, code that runs once costs its fetch: with the keys in
+// are now four (36 us for 10^6 losses, 28 us for 50,000).  Within a launch, code that runs once costs its fetch: with the keys in
 // registers and every loop unrolled (31 KB of code) k_risk_one took 21 us for 1000
-// losses.  Counting every key in bins of the whole range took 26 us for 10^6 losses: most
+// losses (13 now).  Counting every key in bins of the whole range took 26 us for 10^6 losses: most
 // years fall in a few of those bins, and LDS atomics on one word go one after another.
 //
 // The last workgroup of a launch reads what the others wrote in the same launch: those
@@ -529,36 +529,34 @@ __device__ __forceinline__ double wave_tree(double x) {
     return add_row_shl<0x101>(x);
 }
 
-// One wave's sums of tile `tile`'s losses below each rank's K: put(rank, sum).  Lane l
-// holds slots l, l + 64, l + 128 and l + 192; the tree over the 256 slots adds slot t + o
-// into slot t, o = 128, 64, ..., 1.
-template <typename Put>
-__device__ __forceinline__ void wave_tile_sums(const double *__restrict__ y, int64_t n, int64_t tile, const uint64_t *K,
-                                               int m, Put put) {
-    const int lane = threadIdx.x & 63;
+// A quarter of a tile: the losses of the tile's slots 64 q .. 64 q + 63, a slot per lane.
+// (A wave per tile had four times the losses and formed their keys again for each rank:
+// the sums of 50,000 losses took 9.4 us, now 6.2, of 10^6 10.5 and 8.1.)
+struct Quarter {
+    double v[8];
+    uint64_t key[8];
+};
+__device__ __forceinline__ void quarter_load(const double *__restrict__ y, int64_t n, int64_t tile, int q, Quarter &x) {
     const __amdgpu_buffer_rsrc_t rs = losses_from(y, n, tile * kRiskTile);
-    double v[4][8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < 8; ++u) x.v[u] = loss_at(rs, uint32_t(threadIdx.x & 63) + 64u * uint32_t(q) + 256u * uint32_t(u)) + 0.0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q][u] = loss_at(rs, uint32_t(lane + 64 * q + 256 * u)) + 0.0;
-#pragma unroll 1
-    for (int r = 0; r < m; ++r) {
-        const uint64_t k = K[r];
-        double s[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            s[q] = 0.0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                asm volatile("" : "+v"(v[q][u]));   // the keys are not kept over the ranks (64 registers)
-                s[q] += desc_key(v[q][u]) < k ? v[q][u] : 0.0;
-            }
-        }
-        const double x = wave_tree((s[0] + s[2]) + (s[1] + s[3]));
-        if (lane == 0) put(r, x);
-    }
+    for (int u = 0; u < 8; ++u) x.key[u] = desc_key(x.v[u]);
 }
+// The slot's sum of the losses below K.
+__device__ __forceinline__ double quarter_sum(const Quarter &x, uint64_t K) {
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += x.key[u] < K ? x.v[u] : 0.0;
+    return s;
+}
+// The tree over a tile's 256 slots (quarter q's at s + 64 q) by one wave: slot t + o into
+// slot t, o = 128, 64, ..., 1; the result in lane 0.
+__device__ __forceinline__ double tile_tree(const double *s) {
+    const int lane = threadIdx.x & 63;
+    return wave_tree((s[lane] + s[128 + lane]) + (s[64 + lane] + s[192 + lane]));
+}
+constexpr int kSumRanks = 4;   // ranks whose slots are in LDS together
 
 // The tile sums of one rank in the same order (slot t adds tiles t, t + 256, ...), by one
 // wave; the result in lane 0.  Eight of a lane's loads are in flight together.
@@ -654,11 +652,32 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
         if (tid == 0) K[q] = x, st[q].copies = copies;
     }
     __syncthreads();
+    // quarter tiles wave and wave + 16; their slots go where the candidates were
     const int nt = int(risk_tiles(n));
+    static_assert(4 * kOneTiles <= 2 * kRiskWaves && kSumRanks * 4 * kOneTiles * 64 <= kRiskCollect, "two per wave; slots");
+    double *slots = reinterpret_cast<double *>(cand);   // [rank][tile][256]
+    Quarter x0, x1;
+    const int i1 = wave + kRiskWaves;
+    if (wave < 4 * nt) quarter_load(y, n, wave >> 2, wave & 3, x0);
+    if (i1 < 4 * nt) quarter_load(y, n, i1 >> 2, i1 & 3, x1);
 #pragma unroll 1
-    for (int t = wave; t < nt; t += kRiskWaves)
-        wave_tile_sums(y, n, t, K, m, [&](int q, double s) { tile_s[q][t] = s; });
-    __syncthreads();
+    for (int r0 = 0; r0 < m; r0 += kSumRanks) {
+#pragma unroll 1
+        for (int r = r0; r < min(r0 + kSumRanks, m); ++r) {
+            double *to = slots + ((r - r0) * kOneTiles) * 256 + lane;
+            if (wave < 4 * nt) to[64 * wave] = quarter_sum(x0, K[r]);
+            if (i1 < 4 * nt) to[64 * i1] = quarter_sum(x1, K[r]);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int i = wave; i < kSumRanks * nt; i += kRiskWaves) {
+            const int r = r0 + (i & (kSumRanks - 1)), t = i / kSumRanks;
+            if (r >= m) continue;
+            const double s = tile_tree(slots + ((r - r0) * kOneTiles + t) * 256);
+            if (lane == 0) tile_s[r][t] = s;
+        }
+        __syncthreads();
+    }
     if (wave < m) {
         const double s = wave_sum_tiles(nt, [&](int64_t t) { return tile_s[wave][t]; });
         if (lane == 0) write_measures(j.out, m, wave, K[wave], st[wave].copies, s, job_rank(a, blockIdx.x, wave));
@@ -839,20 +858,34 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_collect(RiskArgs a) {
     }
 }
 
-// Each tile's sum of the losses below each rank's K, a wave per tile; the last workgroup
-// adds the tile sums up.  (Eight tiles per workgroup: with one, the workgroups' counting
-// themselves, one atomic each on one word, took 7 us of the 13 us for 489 tiles.)
-constexpr int kSumWaves = 8;
+// Each tile's sum of the losses below each rank's K, four waves per tile; the last
+// workgroup adds the tile sums up.  (Four tiles per workgroup: with one, the workgroups'
+// counting themselves, one atomic each on one word, took 7 us of the 13 us for 489 tiles.)
+constexpr int kSumTiles = 4;
+constexpr int kSumWaves = 4 * kSumTiles;
 __global__ __launch_bounds__(kSumWaves * 64) void k_risk_sum(RiskArgs a) {
+    __shared__ double slots[kSumRanks][kSumTiles][256];
     __shared__ uint32_t last;
     const JobView j = job_view(a, blockIdx.y);
-    const int64_t tiles = risk_tiles(j.n), wgs = (tiles + kSumWaves - 1) / kSumWaves;
+    const int64_t tiles = risk_tiles(j.n), wgs = (tiles + kSumTiles - 1) / kSumTiles;
     if (int64_t(blockIdx.x) >= wgs) return;
     const RiskWs w = risk_ws(j);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = j.m;
-    const int64_t tile = int64_t(blockIdx.x) * kSumWaves + wave;
-    if (tile < tiles)
-        wave_tile_sums(j.y, j.n, tile, w.K, m, [&](int r, double s) { agent_store(&w.tile_sum[r * tiles + tile], s); });
+    const int t = wave >> 2, q = wave & 3;
+    const int64_t tile = int64_t(blockIdx.x) * kSumTiles + t;
+    Quarter x;
+    quarter_load(j.y, j.n, tile, q, x);   // past the last tile: zeros
+#pragma unroll 1
+    for (int r0 = 0; r0 < m; r0 += kSumRanks) {
+#pragma unroll 1
+        for (int r = r0; r < min(r0 + kSumRanks, m); ++r) slots[r - r0][t][64 * q + lane] = quarter_sum(x, w.K[r]);
+        __syncthreads();
+        if (r0 + q < m && tile < tiles) {
+            const double s = tile_tree(slots[q][t]);
+            if (lane == 0) agent_store(&w.tile_sum[(r0 + q) * tiles + tile], s);
+        }
+        __syncthreads();
+    }
     if (!last_to_finish(&w.done[1], uint32_t(wgs), &last)) return;
 #pragma unroll 1
     for (int r = wave; r < m; r += kSumWaves) {
@@ -885,7 +918,7 @@ hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int
     hipLaunchKernelGGL(k_risk_sample, dim3(unsigned(n_long)), block, 0, s, a);
     hipLaunchKernelGGL(k_risk_bins, grid, block, 0, s, a);
     hipLaunchKernelGGL(k_risk_collect, grid, block, 0, s, a);
-    const dim3 sum_grid(unsigned((tiles + kSumWaves - 1) / kSumWaves), unsigned(n_long));
+    const dim3 sum_grid(unsigned((tiles + kSumTiles - 1) / kSumTiles), unsigned(n_long));
     hipLaunchKernelGGL(k_risk_sum, sum_grid, dim3(kSumWaves * 64), 0, s, a);
     return hipGetLastError();
 }
