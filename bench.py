@@ -7,8 +7,8 @@ the path in libara's kernels:
      combined table and occurrence filter (ara_layer_build with ARA_BUILD_TABLES);
   2. the trial kernel: YLT of every trial, with the event-ID range checks of the
      YET fused into the same pass (ara_analyze);
-  3. descending radix sort of the YLT and PML/TVaR at the return periods, results
-     copied to the host (ara_risk_measures, blocking).
+  3. PML/TVaR at the return periods by selection from the YLT, results on the
+     host (ara_risk_measures, blocking).
 
 Default workload: the paper's headline shape -- 1,000,000 trials x 1,000 events,
 IDs uniform over a 1,000,000-event catalog, one layer of 16 ELTs x 20,000
@@ -743,9 +743,8 @@ def main():
     # YET released before the next, the last one kept for the analysis).
     ids_dev = session.to_device(np.asarray(w.event_ids, np.int32))
     offs_dev = session.to_device(np.asarray(w.trial_offsets, np.int64))
-    # PML/TVaR input with as many distinct year losses (all eight radix passes run;
-    # the workload's own year losses all equal the aggregate limit, so the step's
-    # sort skips its passes).  Made here, before the GPU work that leads into the
+    # PML/TVaR input with as many distinct year losses (the workload's own year losses
+    # all equal the aggregate limit, so the step's selection ends with its counts).  Made here, before the GPU work that leads into the
     # timed steps, so that no long host-only spell precedes them
     y_distinct = torch.from_numpy(np.random.default_rng(7).lognormal(15.0, 2.0, size=w.n_trials)).cuda()
     # the layer's ELTs and the layer itself need no YET: created here for the same reason
@@ -978,7 +977,7 @@ def main():
                           "ms_per_step_with_distinct_ylt_sort": ms_step_distinct,
                           "value_with_distinct_ylt_sort": te / (ms_step_distinct * 1e-3)},
         "risk_measures_distinct_ylt": {"ms": risk_distinct_ms, "trials": w.n_trials,
-                                       "data": "lognormal(15, 2) year losses, seed 7: all 8 radix passes run"},
+                                       "data": "lognormal(15, 2) year losses, seed 7: distinct"},
         "lean_yet": lean,
         ("f32_tables" if other == ara.ARA_F32 else "f64_tables"): {
             "ms_per_step": ms2, "value": te / (ms2 * 1e-3), "kernel_ms": k2, "algorithmic_bytes": alg2,

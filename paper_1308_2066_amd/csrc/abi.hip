@@ -1306,7 +1306,7 @@ extern "C" ara_status ara_analyze_events(ara_ctx *c, const ara_yet *y, const ara
     a.ev_occ = dev[2];
     a.ev_cum = dev[3];
     a.ev_ceded = dev[4];
-    hipError_t e = launch_trial_events(a, L->f32, c->n_cu, c->lds_max, c->stream);
+    hipError_t e = launch_trial_events(a, L->f32, 2 * L->all_pairs <= L->catalog, c->n_cu, c->lds_max, c->stream);
     s = e == hipSuccess ? ARA_OK : hip_fail(c, e, "event kernel");
     if (mem == ARA_MEM_HOST) {
         for (int k = 0; k < 5 && s == ARA_OK; ++k)

@@ -156,7 +156,8 @@ struct TrialLaunch {
 // Trials with at most this many occurrences on average go one per lane (dense tables).
 constexpr int kLaneModeMaxMean = 256;
 hipError_t launch_trial_ylt(const TrialArgs &a, const TrialLaunch &l, hipStream_t s);
-hipError_t launch_trial_events(const TrialArgs &a, bool f32, int n_cu, int lds_max, hipStream_t s);
+// sparse: at most half of the catalog's events are in the layer
+hipError_t launch_trial_events(const TrialArgs &a, bool f32, bool sparse, int n_cu, int lds_max, hipStream_t s);
 hipError_t launch_trial_occ_max(const TrialArgs &a, const TrialLaunch &l, int grid, double *out, hipStream_t s);
 hipError_t launch_lookup(const TrialArgs &a, const TrialLaunch &l, const int32_t *ids, int64_t n, double *gross,
                          double *occ, hipStream_t s);

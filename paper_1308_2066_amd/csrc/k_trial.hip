@@ -126,15 +126,18 @@ __device__ __forceinline__ void store2(double *out, int64_t pos, double v0, doub
 // the combined table (the others' gross loss is +0.0, as the table holds).
 //
 // Bound by writing: 50,000 trials of 900 events write 1.44 GB and read 0.18 GB of IDs and
-// 0.25 GB of table lines in 370 us (5.0 TB/s; a large copy reaches 4.9).  Segments of trials
-// of more than 512 events start at multiples of 16, so that a wave's store covers whole
-// 128-byte lines: from multiples of 4 it took 428 us (plain instead of non-temporal stores
-// 464, and 415 from multiples of 16).  Shorter trials would pay for the events before them:
-// 30,000 of 400 139 us from multiples of 4, 143 of 16.  Reading the next segment ahead and scanning by lane moves instead of
+// 0.25 GB of table lines in 370 us (5.0 TB/s; a large copy reaches 4.9).  Segments of longer
+// trials (lines_from < events <= lines_to) start at multiples of 16, so that a wave's store
+// covers whole 128-byte lines: from multiples of 4 it took 428 us (plain instead of
+// non-temporal stores 464, and 415 from multiples of 16).  Shorter trials would pay for the
+// events before them: 30,000 of 400 139 us from multiples of 4, 143 of 16.  Where most
+// events read the table only trials of one segment gain (events of 84% nonzero, whole calls:
+// 900 per trial 387 and 351 us, but 1185 507 and 521, 519 123 and 126; of 20%, 1185 489 and
+// 424).  Reading the next segment ahead and scanning by lane moves instead of
 // LDS permutes changed nothing.  30,000 trials over 2 10^6 events, whose bits were not
 // looked at before: 510 us, folded 252.
 template <typename V>
-__global__ __launch_bounds__(1024) void k_trial_events(TrialArgs a, int nz_blocks, uint32_t nz_mask) {
+__global__ __launch_bounds__(1024) void k_trial_events(TrialArgs a, int nz_blocks, uint32_t nz_mask, int lines_from, int lines_to) {
     extern __shared__ __attribute__((aligned(16))) uint32_t nzl[];
     {
         const u32x4 *src = reinterpret_cast<const u32x4 *>(a.nz);
@@ -157,7 +160,7 @@ __global__ __launch_bounds__(1024) void k_trial_events(TrialArgs a, int nz_block
     for (int64_t t = a.t_begin + int64_t(blockIdx.x) * wpb + wave; t < a.t_end; t += stride) {
         Cursor c;
         open_trial(a, t, c, bad);
-        if (c.o1 - c.o0 > 2 * kChunk) c.sbase = c.o0 & ~int64_t(15);
+        if (c.o1 - c.o0 > lines_from && c.o1 - c.o0 <= lines_to) c.sbase = c.o0 & ~int64_t(15);
         double carryP = 0.0, carryF = 0.0, lr = 0.0;
         while (true) {
             u32x4 r[kNch];
@@ -332,15 +335,17 @@ hipError_t launch_trial_occ_max(const TrialArgs &a, const TrialLaunch &l, int gr
     return hipGetLastError();
 }
 
-hipError_t launch_trial_events(const TrialArgs &a, bool f32, int n_cu, int lds_max, hipStream_t s) {
+hipError_t launch_trial_events(const TrialArgs &a, bool f32, bool sparse, int n_cu, int lds_max, hipStream_t s) {
     const int64_t waves = a.t_end - a.t_begin;
     // one workgroup of 16 waves per CU holds the bits: the catalog's, or 2^kFoldBits
     const bool fold = size_t(a.nblk) * 16 > size_t(lds_max);
     const int blocks = fold ? 1 << (kFoldBits - 7) : a.nblk;
     const uint32_t mask = fold ? (1u << (kFoldBits - 5)) - 1u : ~0u;
     const int grid = int(std::max<int64_t>(1, std::min<int64_t>(n_cu, (waves + 15) / 16)));
-    if (f32) hipLaunchKernelGGL(k_trial_events<float>, dim3(grid), dim3(1024), size_t(blocks) * 16, s, a, blocks, mask);
-    else hipLaunchKernelGGL(k_trial_events<double>, dim3(grid), dim3(1024), size_t(blocks) * 16, s, a, blocks, mask);
+    const int from = sparse ? 2 * kChunk : 5 * kChunk / 2, to = sparse ? INT32_MAX : kSeg - 16;
+    const size_t lds = size_t(blocks) * 16;
+    if (f32) hipLaunchKernelGGL(k_trial_events<float>, dim3(grid), dim3(1024), lds, s, a, blocks, mask, from, to);
+    else hipLaunchKernelGGL(k_trial_events<double>, dim3(grid), dim3(1024), lds, s, a, blocks, mask, from, to);
     return hipGetLastError();
 }
 
