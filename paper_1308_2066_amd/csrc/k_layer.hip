@@ -12,9 +12,10 @@
 // min(max(comb[e] - OccR, 0), OccL) is again a function of the event alone; it is
 // computed once per catalog event (binary64, same operations as per occurrence).
 // Events whose occurrence-net loss is zero contribute nothing to a trial, so the
-// filter also records one bit per event ("nonzero"), per-128-event prefix counts of
-// set bits, and the nonzero values compacted in event order.  A trial kernel can
-// keep the bits and counts in LDS and read only the flagged values from L2.
+// filter also records one bit per event ("nonzero").  The trial kernels keep the bits in
+// LDS and read a flagged event's value from the dense table; per-128-event prefix counts
+// of set bits and the nonzero values compacted in event order serve ara_lookup and the
+// flagged count, and are built when one of them is asked for.
 #include "ara_internal.h"
 
 namespace ara {

@@ -59,8 +59,7 @@ struct SortWs {
                         // plan[16 + p]: pass p is skipped
 };
 
-constexpr size_t kSortSpareBytes = 128 * 1024;   // room for the risk measures' counts (k_risk.hip uses the
-                                                 // same workspace)
+constexpr size_t kSortSpareBytes = 128 * 1024;   // room for the splitters and counts of the sort by buckets
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
