@@ -145,6 +145,11 @@ __device__ __forceinline__ uint32_t bin_shift(uint64_t range) {
 }
 
 __device__ __forceinline__ bool in_bins(const Binning &b, uint64_t k) { return k > b.lo && k <= b.hi; }
+// The bin of a key in the bins; one far past the sampled keys (in 64 bits: its place may not
+// fit in 32) is in the last.
+__device__ __forceinline__ uint32_t bin_of(const Binning &b, uint64_t k) {
+    return uint32_t(umin((k - b.lo) >> b.shift, uint64_t(kRiskBins - 1)));
+}
 
 // Reductions and scans over a wave by DPP lane moves: within rows of 16 lanes, then the
 // four rows (a cross-lane permute through the LDS unit takes three times as long).
@@ -467,7 +472,7 @@ __device__ __forceinline__ void count_keys(const uint64_t (&k)[kRiskLoads], uint
 #pragma unroll
     for (int u = 0; u < kRiskLoads; ++u) {
         const bool ok = (in >> u & 1u) != 0;
-        if (ok && in_bins(b, k[u])) atomicAdd(&bins[min(uint32_t((k[u] - b.lo) >> b.shift), uint32_t(kRiskBins - 1))], 1u);
+        if (ok && in_bins(b, k[u])) atomicAdd(&bins[bin_of(b, k[u])], 1u);
         n.below += uint32_t(__popcll(__ballot(ok && k[u] < b.lo)));
         n.equal += uint32_t(__popcll(__ballot(ok && k[u] == b.lo)));
         n.zero += uint32_t(__popcll(__ballot(ok && b.zeros_last && k[u] == kZeroKey)));

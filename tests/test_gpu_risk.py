@@ -106,3 +106,20 @@ def test_batch_of_short_and_long(ara_lib, gpu_ctx):
     finally:
         A.ara_batch_release(batch)
         an.release()
+
+
+@pytest.mark.parametrize("few", (10.0, 40.0))
+@pytest.mark.parametrize("n", (1_500, 10_000, 16_384, 16_385, 600_001))
+def test_one_loss_but_for_a_few(ara_lib, gpu_ctx, n, few):
+    """A sample of one value says nothing about the range: the few other losses, whose keys differ from it in the
+    high bits alone, belong in the last bin (or below the bins)."""
+    import torch
+    A = ara_lib
+    print(f"risk one loss n={n} few={few}", flush=True)
+    y = np.full(n, 20.0)
+    y[[n // 3, n // 2 + 1, n - 2]] = few
+    rps = [1.0, 10.0, 100.0, float(n)]
+    pml_o, tvar_o, ranks, _ = oracle.risk(y, rps)
+    pml, tvar = A.ara_risk_measures(gpu_ctx, torch.from_numpy(y).cuda(), rps)
+    assert np.asarray(pml).tobytes() == np.asarray(pml_o).tobytes()
+    assert np.asarray(tvar).tobytes() == np.asarray(tvar_o).tobytes()   # sums of whole numbers below 2^53
