@@ -30,10 +30,11 @@
 // dependent kernels takes 4.5-5 us whatever it does (8 MB of losses are 1.3 us of HBM), so
 // the passes that replaced one 8-bit digit each (12 launches, 105 us for 10^6 distinct
 // losses and 135 us when a rank fell among capped years, whose bucket never became small)
-// are now four (36 us for 10^6 losses, 28 us for 50,000).  Within a launch, code that runs once costs its fetch: with the keys in
-// registers and every loop unrolled (31 KB of code) k_risk_one took 21 us for 1000
-// losses (13 now).  Counting every key in bins of the whole range took 26 us for 10^6 losses: most
-// years fall in a few of those bins, and LDS atomics on one word go one after another.
+// are now four (36 us for 10^6 losses, 27 us for 50,000).  Within a launch, code that runs
+// once costs its fetch: with every loop over a thread's 16 keys unrolled for each rank (31 KB
+// of code) k_risk_one took 21 us for 1000 losses (11 now).  Counting every key in bins of the
+// whole range took 26 us for 10^6 losses: most years fall in a few of those bins, and LDS
+// atomics on one word go one after another.
 //
 // The last workgroup of a launch reads what the others wrote in the same launch: those
 // words are stored and loaded with agent-scope atomics (write-through past the XCDs' L2s,
@@ -195,17 +196,19 @@ struct RankState {
 
 // The rank's bin in a row of 64 PER counts (whole wave): the state within it (bins of
 // 2^width keys from lo on), or false when the rank lies past the row's last key (total).
-// The lanes' shares first, then the PER bins of the lane whose share holds the rank.
+// The lanes' shares first, then the PER bins of the lane whose share holds the rank.  Each
+// lane starts its share at another place: from the same one, 64 lanes read the same four
+// LDS banks.
 template <int PER>
 __device__ __forceinline__ bool wave_pick(const uint32_t *row, uint64_t lo, uint32_t width, int64_t left, RankState &out,
                                           uint32_t &total) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    static_assert(PER % 4 == 0 && PER <= 64, "whole 16-byte reads; one lane per bin of a share");
+    static_assert(PER % 4 == 0 && PER <= 64 && (PER & (PER - 1)) == 0, "16-byte reads; one lane per bin of a share");
     const int lane = threadIdx.x & 63;
     uint32_t own = 0;
 #pragma unroll 8
     for (int i = 0; i < PER / 4; ++i) {
-        const u32x4 q = reinterpret_cast<const u32x4 *>(row + PER * lane)[i];
+        const u32x4 q = reinterpret_cast<const u32x4 *>(row + PER * lane)[(i + lane) & (PER / 4 - 1)];
         own += q[0] + q[1] + q[2] + q[3];
     }
     const uint32_t inc = wave_scan(own);
@@ -291,8 +294,9 @@ __device__ __forceinline__ void wave_select(uint64_t key, int c, int64_t left, u
 // own wave; refine() takes the workgroup through them one after another, and k_risk_collect
 // took 25 us for the three ranks of 10^5 trials' largest occurrences, now 15.
 template <typename Key>
-__device__ __forceinline__ void wave_select_any(int c, int64_t left, uint64_t &K, int64_t &copies, Key key) {
+__device__ __forceinline__ void wave_select_any(int count, int64_t left, uint64_t &K, int64_t &copies, Key key) {
     const int lane = threadIdx.x & 63;
+    const int c = __builtin_amdgcn_readfirstlane(count);
     if (c <= 64) {
         wave_select(lane < c ? key(lane) : ~0ull, c, left, K, copies);
         return;
@@ -301,6 +305,7 @@ __device__ __forceinline__ void wave_select_any(int c, int64_t left, uint64_t &K
     uint32_t in = 0;   // the keys still in question, a bit each
 #pragma unroll
     for (int u = 0; u < kWaveKeys; ++u) {
+        if (64 * u >= c) continue;
         const bool have = lane + 64 * u < c;
         x[u] = have ? key(lane + 64 * u) : 0ull;
         in |= have ? 1u << u : 0u;
@@ -310,7 +315,7 @@ __device__ __forceinline__ void wave_select_any(int c, int64_t left, uint64_t &K
         uint64_t lo = ~0ull, hi = 0ull;
 #pragma unroll
         for (int u = 0; u < kWaveKeys; ++u)
-            if (in >> u & 1u) lo = umin(lo, x[u]), hi = umax(hi, x[u]);
+            if (64 * u < c && (in >> u & 1u)) lo = umin(lo, x[u]), hi = umax(hi, x[u]);
         lo = wave_min(lo);
         hi = wave_max(hi);
         if (lo == hi) {
@@ -321,7 +326,7 @@ __device__ __forceinline__ void wave_select_any(int c, int64_t left, uint64_t &K
         const uint64_t mid = lo + (hi - lo) / 2;
         uint32_t low = 0;
 #pragma unroll
-        for (int u = 0; u < kWaveKeys; ++u) low |= x[u] <= mid ? 1u << u : 0u;
+        for (int u = 0; u < kWaveKeys; ++u) low |= 64 * u < c && x[u] <= mid ? 1u << u : 0u;
         uint32_t n = uint32_t(__popc(in & low));
         n = wave_scan(n);
         const int64_t below = int64_t(uint32_t(__builtin_amdgcn_readlane(int(n), 63)));
@@ -393,11 +398,21 @@ __device__ __forceinline__ void refine(Each each, RankState s, uint64_t &K, int6
 // What to count for ranks up to k_max of y[0, n), from a sample (whole workgroup; lds.bins
 // cleared on return).  Sample j is a loss of the j-th of 1024 equal stretches of the
 // YLT, at a place within it that varies from stretch to stretch.
-__device__ __forceinline__ Binning sample_binning(const double *__restrict__ y, int64_t n, int64_t k_max, RefineLds &lds) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+struct Sampled {
+    double loss;
+    bool have;
+};
+__device__ __forceinline__ Sampled sample_loss(const double *__restrict__ y, int64_t n) {
+    const int tid = threadIdx.x;
     const int64_t a = int64_t(tid) * n / kRiskSample, e = int64_t(tid + 1) * n / kRiskSample;
-    const bool have = e > a;
-    const uint64_t key = have ? desc_key(y[a + __umulhi(uint32_t(tid) * 2654435761u, uint32_t(e - a))]) : ~0ull;
+    Sampled s{0.0, e > a};
+    if (s.have) s.loss = y[a + __umulhi(uint32_t(tid) * 2654435761u, uint32_t(e - a))];
+    return s;
+}
+__device__ __forceinline__ Binning sample_binning(Sampled own, int64_t n, int64_t k_max, RefineLds &lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool have = own.have;
+    const uint64_t key = have ? desc_key(own.loss) : ~0ull;
     for (int i = tid; i < kRiskBins; i += kRiskThreads) lds.bins[i] = 0u;
     // no negative loss sampled: zeros are taken to come last
     uint64_t lo = key, hi = have ? key : 0ull;
@@ -506,18 +521,69 @@ __device__ __forceinline__ void place_bins(const RankState *st, int m, int wave,
     __syncthreads();
 }
 
-// Copies the keys of each rank's bin (the first ranks' of them) through put(r, key).
-template <typename Put>
+// Copies the keys of each rank's bin (the first ranks' of them), a whole wave together:
+// reserve(r, c) by one lane gives the wave room for its c keys of rank r, put(r, place, key)
+// stores one.  One returning atomic per rank, not one per key register (k_risk_collect, for the
+// largest occurrences of 10^5 trials: 15 us, with wave_pick's banks 14.3).
+template <typename Reserve, typename Put>
 __device__ __forceinline__ void copy_bins(const uint64_t (&k)[kRiskLoads], uint32_t in, const RankState *st,
-                                          const int *first, int m, Put put) {
+                                          const int *first, int m, Reserve reserve, Put put) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll 1
     for (int r = 0; r < m; ++r) {
         if (first[r] != r || st[r].count > uint32_t(kRiskCollect)) continue;
         const uint64_t lo = st[r].lo, span = st[r].span;
+        uint32_t hit = 0, c = 0;
+#pragma unroll
+        for (int u = 0; u < kRiskLoads; ++u) {
+            const bool h = (in >> u & 1u) && k[u] - lo <= span;
+            hit |= h ? 1u << u : 0u;
+            c += uint32_t(__popcll(__ballot(h)));
+        }
+        if (c == 0) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = reserve(r, c);
+        at = uint32_t(__builtin_amdgcn_readfirstlane(int(at)));
+#pragma unroll
+        for (int u = 0; u < kRiskLoads; ++u) {
+            const bool h = (hit >> u & 1u) != 0;
+            const uint64_t all = __ballot(h);
+            if (h) put(r, at + __builtin_amdgcn_mbcnt_hi(uint32_t(all >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(all), 0u)), k[u]);
+            at += uint32_t(__popcll(all));
+        }
+    }
+}
+
+// The same where the bins' counts are in LDS: a bin marked kTaken holds the place of its next
+// key, so that a key takes one lookup however many ranks there are.  (With a pass over the keys
+// per rank the copying took 4.3 of k_risk_one's 21.3 us for 10,000 losses of 74 values, now 1.9
+// of 18.6.)
+constexpr uint32_t kTaken = 0x80000000u;
+template <typename Put>
+__device__ __forceinline__ void copy_taken(const uint64_t (&k)[kRiskLoads], uint32_t in, const Binning &b, uint32_t *bins,
+                                           uint32_t *to_below, Put put) {
+    uint32_t at[kRiskLoads], to[kRiskLoads];
+#pragma unroll
+    for (int u = 0; u < kRiskLoads; ++u) {
+        at[u] = in_bins(b, k[u]) ? bin_of(b, k[u]) : 0u;
+        to[u] = bins[at[u]];
+    }
+    if (*to_below & kTaken) {
 #pragma unroll
         for (int u = 0; u < kRiskLoads; ++u)
-            if ((in >> u & 1u) && k[u] - lo <= span) put(r, k[u]);
+            if ((in >> u & 1u) && k[u] < b.lo) put(atomicAdd(to_below, 1u) & ~kTaken, k[u]);
     }
+    uint32_t hit = 0;
+#pragma unroll
+    for (int u = 0; u < kRiskLoads; ++u) hit |= (to[u] & kTaken) && in_bins(b, k[u]) ? 1u << u : 0u;
+    hit &= in;
+    if (hit == 0u) return;
+#pragma unroll
+    for (int u = 0; u < kRiskLoads; ++u)   // all on their way before the first is waited for
+        if (hit >> u & 1u) to[u] = atomicAdd(&bins[at[u]], 1u);
+#pragma unroll
+    for (int u = 0; u < kRiskLoads; ++u)
+        if (hit >> u & 1u) put(to[u] & ~kTaken, k[u]);
 }
 
 // Lane t + o into lane t, o = 32, 16, ..., 1; the result in lane 0.
@@ -541,12 +607,23 @@ struct Quarter {
     double v[8];
     uint64_t key[8];
 };
-__device__ __forceinline__ void quarter_load(const double *__restrict__ y, int64_t n, int64_t tile, int q, Quarter &x) {
+__device__ __forceinline__ void quarter_losses(const double *__restrict__ y, int64_t n, int64_t tile, int q, Quarter &x) {
     const __amdgpu_buffer_rsrc_t rs = losses_from(y, n, tile * kRiskTile);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) x.v[u] = loss_at(rs, uint32_t(threadIdx.x & 63) + 64u * uint32_t(q) + 256u * uint32_t(u)) + 0.0;
+    for (int u = 0; u < 8; ++u) x.v[u] = loss_at(rs, uint32_t(threadIdx.x & 63) + 64u * uint32_t(q) + 256u * uint32_t(u));
+}
+__device__ __forceinline__ void quarter_keys(Quarter &x) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) x.key[u] = desc_key(x.v[u]);
+    for (int u = 0; u < 8; ++u) {
+        x.v[u] += 0.0;
+        x.key[u] = desc_key(x.v[u]);
+    }
+}
+// Which of them are losses of the YLT, a bit each.
+__device__ __forceinline__ uint32_t quarter_in(int64_t n, int64_t tile, int q) {
+    const int64_t left = n - tile * kRiskTile - 64 * q - (threadIdx.x & 63);   // slot's losses: every 256th of these
+    const int64_t c = (left + 255) >> 8;
+    return c >= 8 ? 0xFFu : c <= 0 ? 0u : (1u << int(c)) - 1u;
 }
 // The slot's sum of the losses below K.
 __device__ __forceinline__ double quarter_sum(const Quarter &x, uint64_t K) {
@@ -593,15 +670,19 @@ __device__ __forceinline__ void write_measures(double *out, int m, int r, uint64
     out[m + r] = (s + double(copies) * pml) / double(k);
 }
 
-// A YLT of at most kRiskOneWg losses per workgroup (blockIdx.x), read three times after the
-// sample: bins, the few keys of each rank's bin, tile sums.
+// A YLT of at most kRiskOneWg losses per workgroup (blockIdx.x), in its registers from the
+// start: quarter tiles wave and wave + 16, for the bins, the few keys of each rank's bin and
+// the tile sums.  Its instructions bound it: 16 losses per lane, four waves per SIMD (of 20 us
+// forming the keys and counting them take 3, sampling 5.6 with its round trips).  Reading the
+// YLT anew for each of the three it took 16.9 us for 10,000 losses, now 13.7, and 12.8 and 11.2
+// for 1000.
 constexpr int kOneTiles = kRiskOneWg / kRiskTile;
 __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
     __shared__ RefineLds ref;
     __shared__ Counts cnt;
     __shared__ RankState st[64];
     __shared__ int first[kRiskGroup];
-    __shared__ uint32_t off[kRiskGroup + 1], n_cand[kRiskGroup];
+    __shared__ uint32_t off[kRiskGroup + 1], to_below;
     __shared__ uint64_t K[kRiskGroup];
     __shared__ uint64_t cand[kRiskCollect];
     __shared__ double tile_s[kRiskGroup][kOneTiles];
@@ -610,12 +691,20 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
     const int64_t n = j.n;
     const int m = j.m;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid < kRiskGroup) n_cand[tid] = 0u;
-    if (tid == 0) cnt = Counts{0u, 0u, 0u};
-    const Binning b = sample_binning(y, n, j.k_max, ref);
+    if (tid == 0) cnt = Counts{0u, 0u, 0u}, to_below = 0u;
+    const int nt = int(risk_tiles(n)), i0 = wave, i1 = wave + kRiskWaves;
+    static_assert(4 * kOneTiles <= 2 * kRiskWaves, "two quarters per wave");
+    const Sampled own = sample_loss(y, n);
+    Quarter x0, x1;   // past the last tile: zeros
+    quarter_losses(y, n, i0 >> 2, i0 & 3, x0);
+    quarter_losses(y, n, i1 >> 2, i1 & 3, x1);
+    const Binning b = sample_binning(own, n, j.k_max, ref);
+    quarter_keys(x0);
+    quarter_keys(x1);
     Counts c{0u, 0u, 0u};
-    each_keys(y, n, 0, kRiskThreads,
-              [&](const uint64_t (&k)[kRiskLoads], uint32_t in) { count_keys(k, in, b, ref.bins, c); });
+    const uint32_t in0 = quarter_in(n, i0 >> 2, i0 & 3), in1 = quarter_in(n, i1 >> 2, i1 & 3);
+    if (i0 < 4 * nt) count_keys(x0.key, in0, b, ref.bins, c);
+    if (i1 < 4 * nt) count_keys(x1.key, in1, b, ref.bins, c);
     add_counts(c, &cnt);
     __syncthreads();
     if (wave < m) {   // wave r picks rank r's bin
@@ -626,9 +715,15 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
     place_bins(st, m, wave, first, off);
     const bool fits = off[kRiskGroup] <= uint32_t(kRiskCollect);   // the copied keys fit in LDS
     if (fits && off[kRiskGroup] > 0u) {
-        each_keys(y, n, 0, kRiskThreads, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
-            copy_bins(k, in, st, first, m, [&](int q, uint64_t x) { cand[off[q] + atomicAdd(&n_cand[q], 1u)] = x; });
-        });
+        // the count of a rank's bin becomes where its next key goes (the keys below b.lo: to_below)
+        if (tid < m && first[tid] == tid && st[tid].count <= uint32_t(kRiskCollect)) {
+            const uint64_t at = st[tid].lo;
+            (at < b.lo ? to_below : ref.bins[bin_of(b, at)]) = kTaken | off[tid];
+        }
+        __syncthreads();
+        auto put = [&](uint32_t i, uint64_t k) { cand[i] = k; };
+        if (i0 < 4 * nt) copy_taken(x0.key, in0, b, ref.bins, &to_below, put);
+        if (i1 < 4 * nt) copy_taken(x1.key, in1, b, ref.bins, &to_below, put);
     }
     __syncthreads();
     if (wave < m && lane == 0) K[wave] = st[wave].K;
@@ -641,9 +736,10 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
         if (lane == 0) K[wave] = x, st[wave].copies = copies, st[wave].solved = true;
     }
     __syncthreads();
+    const uint64_t open = __ballot(lane < m && !st[lane].solved);
 #pragma unroll 1
-    for (int q = 0; q < m; ++q) {   // larger bins, one after another
-        if (st[q].solved) continue;
+    for (int q = 0; __builtin_expect(open >> q != 0, 0); ++q) {   // larger bins, one after another
+        if (!(open >> q & 1)) continue;
         uint64_t x;
         int64_t copies;
         if (fits && st[q].count <= uint32_t(kRiskCollect)) {
@@ -657,20 +753,15 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
         if (tid == 0) K[q] = x, st[q].copies = copies;
     }
     __syncthreads();
-    // quarter tiles wave and wave + 16; their slots go where the candidates were
-    const int nt = int(risk_tiles(n));
-    static_assert(4 * kOneTiles <= 2 * kRiskWaves && kSumRanks * 4 * kOneTiles * 64 <= kRiskCollect, "two per wave; slots");
+    // the quarters' slots go where the candidates were
+    static_assert(kSumRanks * 4 * kOneTiles * 64 <= kRiskCollect, "slots");
     double *slots = reinterpret_cast<double *>(cand);   // [rank][tile][256]
-    Quarter x0, x1;
-    const int i1 = wave + kRiskWaves;
-    if (wave < 4 * nt) quarter_load(y, n, wave >> 2, wave & 3, x0);
-    if (i1 < 4 * nt) quarter_load(y, n, i1 >> 2, i1 & 3, x1);
 #pragma unroll 1
     for (int r0 = 0; r0 < m; r0 += kSumRanks) {
 #pragma unroll 1
         for (int r = r0; r < min(r0 + kSumRanks, m); ++r) {
             double *to = slots + ((r - r0) * kOneTiles) * 256 + lane;
-            if (wave < 4 * nt) to[64 * wave] = quarter_sum(x0, K[r]);
+            if (i0 < 4 * nt) to[64 * i0] = quarter_sum(x0, K[r]);
             if (i1 < 4 * nt) to[64 * i1] = quarter_sum(x1, K[r]);
         }
         __syncthreads();
@@ -754,7 +845,7 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_sample(RiskArgs a) {
     for (int i = tid; i < kRiskBins; i += kRiskThreads) w.bins[i] = 0u;
     if (tid < 2) w.done[tid] = 0u;
     if (tid < kRiskGroup) w.n_cand[tid] = 0u, w.b_lo[tid] = ~0ull, w.b_hi[tid] = 0ull;
-    const Binning b = sample_binning(j.y, j.n, j.k_max, ref);
+    const Binning b = sample_binning(sample_loss(j.y, j.n), j.n, j.k_max, ref);
     if (tid == 0) {
         *w.counts = Counts{0u, 0u, 0u};
         *w.binning = b;
@@ -806,8 +897,8 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_collect(RiskArgs a) {
     __syncthreads();
     place_bins(st, m, wave, first, off);
     each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
-        copy_bins(k, in, st, first, m,
-                  [&](int r, uint64_t x) { agent_store(&w.cand[off[r] + atomicAdd(&w.n_cand[r], 1u)], x); });
+        copy_bins(k, in, st, first, m, [&](int r, uint32_t c) { return atomicAdd(&w.n_cand[r], c); },
+                  [&](int r, uint32_t i, uint64_t x) { agent_store(&w.cand[off[r] + i], x); });
     });
 #pragma unroll 1
     for (int r = 0; r < m; ++r) {
@@ -879,7 +970,8 @@ __global__ __launch_bounds__(kSumWaves * 64) void k_risk_sum(RiskArgs a) {
     const int t = wave >> 2, q = wave & 3;
     const int64_t tile = int64_t(blockIdx.x) * kSumTiles + t;
     Quarter x;
-    quarter_load(j.y, j.n, tile, q, x);   // past the last tile: zeros
+    quarter_losses(j.y, j.n, tile, q, x);   // past the last tile: zeros
+    quarter_keys(x);
 #pragma unroll 1
     for (int r0 = 0; r0 < m; r0 += kSumRanks) {
 #pragma unroll 1
