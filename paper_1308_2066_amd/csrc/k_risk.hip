@@ -856,7 +856,7 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_bins(RiskArgs a) {
     __shared__ uint32_t bins[kRiskBins];
     __shared__ Counts cnt;
     const JobView j = job_view(a, blockIdx.y);
-    const int nb = risk_blocks(j.n);
+    const int nb = min(risk_blocks(j.n), int(gridDim.x));
     if (int(blockIdx.x) >= nb) return;
     const RiskWs w = risk_ws(j);
     const int tid = threadIdx.x;
@@ -885,7 +885,7 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_collect(RiskArgs a) {
     __shared__ uint32_t off[kRiskGroup + 1];
     __shared__ uint32_t last;
     const JobView j = job_view(a, blockIdx.y);
-    const int nb = risk_blocks(j.n), m = j.m;
+    const int nb = min(risk_blocks(j.n), int(gridDim.x)), m = j.m;
     if (int(blockIdx.x) >= nb) return;
     const RiskWs w = risk_ws(j);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -992,6 +992,27 @@ __global__ __launch_bounds__(kSumWaves * 64) void k_risk_sum(RiskArgs a) {
     if (tid == 0 && a.err_out) *a.err_out = *a.err;
 }
 
+// Workgroups per YLT of a pass over several: no more together than are resident at once, where
+// that can be had, since each has a fixed part (clearing and adding its bins; in the collection,
+// picking the ranks' bins and being counted) however few losses it takes.  A workgroup of
+// k_risk_bins leaves room for another on its CU, one of k_risk_collect does not.  15 YLTs of
+// 10^5 to 10^6 losses with 128 workgroups each: bins 32 us, collection 65; now 24 and 50.
+constexpr int kResidentBins = 512, kResidentCollect = 256;
+static int blocks_each(const RiskJob *jobs, int n_jobs, int resident) {
+    auto total = [&](int most) {
+        int64_t t = 0;
+        for (int i = 0; i < n_jobs; ++i) t += std::min(risk_blocks(jobs[i].n), most);
+        return t;
+    };
+    if (total(kRiskBlocks) <= resident) return kRiskBlocks;
+    int fits = 1, over = kRiskBlocks;   // total(over) > resident
+    while (over - fits > 1) {
+        const int mid = (fits + over) / 2;
+        (total(mid) <= resident ? fits : over) = mid;
+    }
+    return fits;
+}
+
 hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int n_long, const uint32_t *err,
                        uint32_t *err_out, hipStream_t s) {
     RiskArgs a{};
@@ -1011,10 +1032,12 @@ hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int
     for (int i = n_short; i < n_short + n_long; ++i) n = std::max(n, host[i].n);
     const int64_t tiles = risk_tiles(n);
     if (tiles > int64_t(INT32_MAX) || n_long > 65535) return hipErrorInvalidValue;
-    const dim3 grid(unsigned(risk_blocks(n)), unsigned(n_long)), block(kRiskThreads);
+    const dim3 block(kRiskThreads);
+    const int bins = std::min(risk_blocks(n), blocks_each(host + n_short, n_long, kResidentBins));
+    const int collect = std::min(risk_blocks(n), blocks_each(host + n_short, n_long, kResidentCollect));
     hipLaunchKernelGGL(k_risk_sample, dim3(unsigned(n_long)), block, 0, s, a);
-    hipLaunchKernelGGL(k_risk_bins, grid, block, 0, s, a);
-    hipLaunchKernelGGL(k_risk_collect, grid, block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_bins, dim3(unsigned(bins), unsigned(n_long)), block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_collect, dim3(unsigned(collect), unsigned(n_long)), block, 0, s, a);
     const dim3 sum_grid(unsigned((tiles + kSumTiles - 1) / kSumTiles), unsigned(n_long));
     hipLaunchKernelGGL(k_risk_sum, sum_grid, dim3(kSumWaves * 64), 0, s, a);
     return hipGetLastError();

@@ -123,3 +123,31 @@ def test_one_loss_but_for_a_few(ara_lib, gpu_ctx, n, few):
     pml, tvar = A.ara_risk_measures(gpu_ctx, torch.from_numpy(y).cuda(), rps)
     assert np.asarray(pml).tobytes() == np.asarray(pml_o).tobytes()
     assert np.asarray(tvar).tobytes() == np.asarray(tvar_o).tobytes()   # sums of whole numbers below 2^53
+
+
+@pytest.mark.parametrize("longest", (9, 18))
+def test_batch_of_many_long(ara_lib, gpu_ctx, longest):
+    """More long YLTs than the passes have workgroups for at 4096 losses each (in the collection; in both): the same
+    bits as one call per YLT."""
+    import torch
+    import synth
+    from paper_1308_2066_amd import session
+    A = ara_lib
+    rng = np.random.default_rng(6)
+    n, C = 120_000, 3_000
+    ids, offs = synth.yet_poisson(rng, n, 3.0, C)
+    an = session.open_analysis(gpu_ctx, ids, offs, C, [synth.elt_sparse(rng, 900, C, 10.0, 2.0)],
+                               (1e3, 1e6, 1e4, 2e6))
+    ranges = [(j, n) for j in range(longest)] + [(0, 16_385), (7, 30_000)]
+    ylts = [torch.empty(b - a, dtype=torch.float64, device="cuda") for a, b in ranges]
+    batch = A.ara_batch_create(gpu_ctx, [(an.yet, an.layer, a, b, y) for (a, b), y in zip(ranges, ylts)])
+    try:
+        A.ara_batch_run(batch)
+        for rps in ([10.0, 100.0, 250.0], list(np.geomspace(1.0, 500.0, 19))):
+            pml, tvar = A.ara_batch_risk(batch, rps)
+            for j, y in enumerate(ylts):
+                p, t = A.ara_risk_measures(gpu_ctx, y, rps)
+                assert p.tobytes() == pml[j].tobytes() and t.tobytes() == tvar[j].tobytes(), (j, len(rps))
+    finally:
+        A.ara_batch_release(batch)
+        an.release()
