@@ -227,6 +227,13 @@ __device__ __forceinline__ bool wave_pick(const uint32_t *row, uint64_t lo, uint
     return true;
 }
 
+// The last key of [lo, lo + span] up to hi >= lo.  lo + span itself may lie past the last key
+// there is (bins 2^52 wide from a positive loss's key on, the rank among negative NaNs): taken
+// modulo 2^64, the range went on among the smallest keys, more of them than were counted.
+__device__ __forceinline__ uint64_t range_end(uint64_t lo, uint64_t span, uint64_t hi) {
+    return span < hi - lo ? lo + span : hi;
+}
+
 // Rank k after the counting pass (a wave on its own).  Keys come in the order: below lo,
 // equal to lo, bins, and with zeros_last zeros.  A bin's first key is kept out of [lo, ..]
 // when it is b.lo itself, and its last one ends at b.hi.
@@ -251,7 +258,7 @@ __device__ __forceinline__ RankState pick_bin(const uint32_t *row, const Binning
     uint32_t total;
     if (wave_pick<kRiskBins / 64>(row, b.lo, b.shift, k - before, s, total)) {
         const bool last = s.lo == b.lo + (uint64_t(kRiskBins - 1) << b.shift);   // holds the keys up to b.hi
-        const uint64_t end = last ? b.hi : umin(s.lo + s.span, b.hi);
+        const uint64_t end = last ? b.hi : range_end(s.lo, s.span, b.hi);
         s.lo = umax(s.lo, b.lo + 1ull);
         s.span = end - s.lo;
         return s;
@@ -383,6 +390,7 @@ __device__ __forceinline__ void refine(Each each, RankState s, uint64_t &K, int6
             uint32_t total;
             RankState n = s;
             (void)wave_pick<kRiskBins / 64>(lds.bins, lo, width, s.left, n, total);
+            n.span = range_end(n.lo, n.span, hi) - n.lo;
             if (lane == 0) lds.st = n;
         }
         __syncthreads();
@@ -434,7 +442,7 @@ __device__ __forceinline__ Binning sample_binning(Sampled own, int64_t n, int64_
         uint32_t total;
         RankState s;
         s.span = last;
-        if (wave_pick<kRiskBins / 64>(lds.bins, lo, width, place, s, total)) s.span = umin(s.lo + s.span, last);
+        if (wave_pick<kRiskBins / 64>(lds.bins, lo, width, place, s, total)) s.span = range_end(s.lo, s.span, last);
         if (lane == 0) lds.st.span = s.span;
     }
     __syncthreads();
