@@ -678,8 +678,8 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
     dev_free(c, sums);
     if (s == ARA_OK) {
         y->n_bins = nb;
-        y->n_groups = tiled_group_count(n, nb, c->n_cu);
-        y->group_bins = (nb + y->n_groups - 1) / y->n_groups;
+        y->group_bins = tiled_group_bins(nb);
+        y->n_groups = (nb + y->group_bins - 1) / y->group_bins;
         y->copy_bytes = int64_t(ids16_bytes) + int64_t(nb + 1) * 8 + int64_t(nb) * y->stride * (y->boff24 ? 3 : 4) +
                         (y->boff24 ? 16 : 0);
         return ARA_OK;
@@ -1105,13 +1105,16 @@ static TiledArgs tiled_args(const ara_yet *y, const ara_layer *L, int64_t t0, in
     return a;
 }
 
-// Makes `a` a split launch: its groups' sums in p, chunks of trials.
-static void tiled_split(TiledArgs &a, void *p, int64_t chunks) {
+// Makes `a` a split launch: its groups' sums in p.
+static void set_split(TiledArgs &a, void *p, const TiledSplit &how) {
     const int64_t n = a.t_end - a.t_begin;
     a.part = static_cast<double *>(p);
     a.part_stride = (n + 2) & ~int64_t(1);
-    a.chunks = int32_t(chunks);
-    a.per_wg = (n + chunks - 1) / chunks;
+    a.chunks = int32_t(how.chunks);
+    a.group_bins = how.group_bins;
+    a.n_groups = how.n_groups;
+    a.span_groups = how.span_groups;
+    a.per_wg = (n + how.chunks - 1) / how.chunks;
 }
 static size_t tiled_split_bytes(int64_t n, int32_t groups) { return size_t((n + 2) & ~int64_t(1)) * size_t(groups) * 8; }
 
@@ -1119,7 +1122,7 @@ static size_t tiled_split_bytes(int64_t n, int32_t groups) { return size_t((n + 
 // stream is being captured (a graph may be replayed on any stream, at any time), for more
 // than kTiledWsBytes, for more than kTiledWsStreams streams, or without memory.  The
 // launch then runs whole, with the same bits.
-constexpr size_t kTiledWsBytes = size_t(64) << 20;
+constexpr size_t kTiledWsBytes = size_t(128) << 20;
 constexpr size_t kTiledWsStreams = 4;
 
 static void *tiled_scratch(ara_ctx *c, size_t bytes) {
@@ -1155,10 +1158,10 @@ static void *tiled_scratch(ara_ctx *c, size_t bytes) {
 static hipError_t run_tiled(ara_ctx *c, const ara_yet *y, const ara_layer *L, int64_t t0, int64_t t1, double *out, int grid,
                             bool occ_max, hipEvent_t start, hipEvent_t stop) {
     TiledArgs a = tiled_args(y, L, t0, t1, out, grid);
-    const int64_t chunks = tiled_chunks(t1 - t0, y->n_bins, y->n_groups, c->n_cu);
-    if (chunks > 0) {
-        void *p = tiled_scratch(c, tiled_split_bytes(t1 - t0, y->n_groups));
-        if (p) tiled_split(a, p, chunks);
+    const TiledSplit how = tiled_split(t1 - t0, y->n_bins, c->n_cu, occ_max);
+    if (how.chunks > 0) {
+        void *p = tiled_scratch(c, tiled_split_bytes(t1 - t0, how.n_groups));
+        if (p) set_split(a, p, how);
     }
     return launch_trial_tiled(a, grid, c->stream, occ_max, start, stop);
 }
@@ -1623,13 +1626,12 @@ static TiledBatch batch_tiled(const ara_batch *b) {
     return t;
 }
 
-// A tiled job's trials [tb, te) as work items of job index k: passes of nearly equal
-// size, as few as kTiledPassTrials allows (each pass stages every bin of the catalog
-// once), over every bin group or (split) one each, with each one's cost (occurrences,
-// plus the staging).  A trial's YLT does not depend on the pass that holds it (its lane
-// adds the bins of a group in order and each run's occurrences in order, and the groups'
-// sums are added in order), so the items give the plain launch's bits.
-static void tiled_passes(int32_t k, int64_t tb, int64_t te, double mean_len, double stage, int32_t groups, bool split,
+// The passes of tiled job k: trials of nearly equal number, as few passes as
+// kTiledPassTrials allows (each pass stages every bin once), with each one's cost
+// (occurrences, plus the staging).  A trial's YLT does not depend on the pass that holds it
+// (its lane adds the bins of a group in order and each run's occurrences in order, and the
+// groups' sums are added in order), so the items give the plain launch's bits.
+static void tiled_passes(int32_t k, int64_t tb, int64_t te, double mean_len, double stage,
                          std::vector<std::pair<double, TiledItem>> &out) {
     const int64_t n = te - tb;
     const int64_t passes = (n + kTiledPassTrials - 1) / kTiledPassTrials;
@@ -1639,57 +1641,74 @@ static void tiled_passes(int32_t k, int64_t tb, int64_t te, double mean_len, dou
         it.job = k;
         it.t0 = p;
         it.t1 = std::min(p + per, te);
-        const double cost = double(it.t1 - it.t0) * mean_len + stage;
-        for (int32_t g = 0; g < (split ? groups : 1); ++g) {
-            it.group = split ? g : -1;
-            out.emplace_back(split ? cost / groups : cost, it);
-        }
+        out.emplace_back(double(it.t1 - it.t0) * mean_len + stage, it);
     }
 }
 
-// Splits the batch's tiled jobs over bin groups when their passes are too few to keep the
-// CUs evenly busy (below four rounds of them, where the last pass to end is a long wait),
-// while their sums fit kBatchPartBytes; writes the items.
+// Splits the batch's tiled jobs over spans of bin groups when their passes are too few to keep
+// the CUs evenly busy (below four rounds of them, where the last pass to end is a long wait),
+// while their sums fit kBatchPartBytes; writes the items, costliest first, so that the last
+// ones taken are short.  Items cost about 6 us each beside their bins, so the first
+// kTiledLongShare of the work goes in items of a CU's share / kTiledLong, the rest in shorter ones.
 constexpr int64_t kTiledFewRounds = 4;
+constexpr double kTiledLongShare = 0.75, kTiledLong = 2.0, kTiledShort = 6.0;
 constexpr size_t kBatchPartBytes = size_t(256) << 20;
 
 static ara_status batch_tiled_items(ara_batch *b) {
     ara_ctx *c = b->ctx;
-    int64_t passes = 0;
-    for (const TiledArgs &a : b->tjobs) passes += (a.t_end - a.t_begin + kTiledPassTrials - 1) / kTiledPassTrials;
-    std::vector<std::pair<double, TiledItem>> items;
-    std::vector<size_t> at(b->tjobs.size(), SIZE_MAX);
-    size_t used = 0;
+    std::vector<std::pair<double, TiledItem>> passes, items;
     for (size_t k = 0; k < b->tjobs.size(); ++k) {
         const TiledArgs &a = b->tjobs[k];
-        const size_t need = tiled_split_bytes(a.t_end - a.t_begin, a.n_groups);
-        const bool split = passes < kTiledFewRounds * c->n_cu && a.n_groups > 1 && used + need <= kBatchPartBytes;
-        if (split) {
-            at[k] = used;
-            used += need;
-            b->split.push_back(int32_t(k));
-            b->split_max = std::max(b->split_max, a.t_end - a.t_begin);
-        }
         const ara_job &jb = b->jobs[size_t(b->tiled_job[k])];
         const double mean = jb.yet->n_trials ? double(jb.yet->n_events) / double(jb.yet->n_trials) : 0.0;
-        tiled_passes(int32_t(k), a.t_begin, a.t_end, mean, kTiledStageCost * double(jb.layer->catalog), a.n_groups, split,
-                     items);
+        tiled_passes(int32_t(k), a.t_begin, a.t_end, mean, kTiledStageCost * double(a.catalog), passes);
+    }
+    const bool few = int64_t(passes.size()) < kTiledFewRounds * c->n_cu;
+    std::vector<size_t> at(b->tjobs.size(), SIZE_MAX);
+    size_t used = 0;
+    for (size_t k = 0; few && k < b->tjobs.size(); ++k) {
+        const TiledArgs &a = b->tjobs[k];
+        const size_t need = tiled_split_bytes(a.t_end - a.t_begin, a.n_groups);
+        if (a.n_groups <= 1 || used + need > kBatchPartBytes) continue;
+        at[k] = used;
+        used += need;
+        b->split.push_back(int32_t(k));
+        b->split_max = std::max(b->split_max, a.t_end - a.t_begin);
+    }
+    const auto costlier = [](const std::pair<double, TiledItem> &x, const std::pair<double, TiledItem> &y) {
+        return x.first > y.first;
+    };
+    std::stable_sort(passes.begin(), passes.end(), costlier);
+    double total = 0.0, before = 0.0;
+    for (const auto &p : passes) total += p.first;
+    for (const auto &p : passes) {
+        const int32_t groups = b->tjobs[size_t(p.second.job)].n_groups;
+        int32_t span = groups;
+        if (at[size_t(p.second.job)] != SIZE_MAX) {
+            const double item = total / ((before < kTiledLongShare * total ? kTiledLong : kTiledShort) * c->n_cu);
+            const int32_t spans = int32_t(std::max(1.0, std::min(double(groups), std::ceil(p.first / item))));
+            span = (groups + spans - 1) / spans;
+        }
+        before += p.first;
+        for (int32_t g = 0; g < groups; g += span) {
+            TiledItem it = p.second;
+            const int32_t g1 = std::min(g + span, groups);
+            it.groups = uint32_t(g) | uint32_t(g1) << 16;
+            items.emplace_back(p.first * double(g1 - g) / double(groups), it);
+        }
     }
     ara_status s = ARA_OK;
     if (used > 0) s = dev_alloc(c, &b->d_part, used, "batch tiled sums");
     if (s == ARA_OK && used > 0) s = dev_alloc(c, &b->d_split, b->split.size() * 4, "batch tiled split jobs");
     if (s != ARA_OK) return s;
     for (size_t k = 0; k < b->tjobs.size(); ++k)
-        if (at[k] != SIZE_MAX) tiled_split(b->tjobs[k], static_cast<char *>(b->d_part) + at[k], 1);
+        if (at[k] != SIZE_MAX) set_split(b->tjobs[k], static_cast<char *>(b->d_part) + at[k],
+                                         TiledSplit{1, b->tjobs[k].group_bins, b->tjobs[k].n_groups, 1});
     if (used > 0) {
         const hipError_t e = hipMemcpy(b->d_split, b->split.data(), b->split.size() * 4, hipMemcpyHostToDevice);
         if (e != hipSuccess) return hip_fail(c, e, "batch tiled upload");
     }
-    // costliest passes first, so that the last ones taken are short
-    std::stable_sort(items.begin(), items.end(),
-                     [](const std::pair<double, TiledItem> &x, const std::pair<double, TiledItem> &y) {
-                         return x.first > y.first;
-                     });
+    std::stable_sort(items.begin(), items.end(), costlier);
     for (const auto &it : items) b->titems.push_back(it.second);
     return ARA_OK;
 }

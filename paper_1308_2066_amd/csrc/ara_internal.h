@@ -263,31 +263,43 @@ struct TiledArgs {
     const double *occ;          // the layer's occurrence-net values, one per catalog event
     int32_t catalog;
     int32_t n_bins;
-    int32_t group_bins;         // bins per group (the last group may have fewer)
+    int32_t group_bins;         // bins per group (the last group may have fewer): tiled_group_bins
     int32_t n_groups;
     double agg_r, agg_l;
     double *ylt;
     double *part;               // split: [n_groups][part_stride] sums, 16-byte aligned; null: whole
     int64_t part_stride;        // even, at least t_end - t_begin + 1
     int32_t chunks;             // split: chunks of per_wg trials
-    int32_t pad_;
+    int32_t span_groups;        // split: groups a workgroup goes through
 };
-// Bin groups of a YET, and the chunks a launch over n of its trials is split into (0:
-// whole); see k_trial_tiled.hip.
-constexpr int32_t kTiledMaxGroups = 32;
+// Bins per group: at most 20 groups, by the catalog alone, so that every analysis of a trial
+// adds its bins in the same order, whatever YET holds it and whatever the launch.  More groups
+// split a launch of few trials further (20,000 trials over 92 bins: 31 groups 28 us, 19 33,
+// 12 45), and cost a launch of more trials the traffic of their sums (200,000 over 62 bins: 9
+// groups 119 us, 16 131, 21 134).
+constexpr int32_t kTiledMaxGroups = 20;
+inline int32_t tiled_group_bins(int32_t n_bins) { return (n_bins + kTiledMaxGroups - 1) / kTiledMaxGroups; }
+__host__ __device__ inline int32_t tiled_spans(int32_t groups, int32_t span_groups) {
+    return (groups + span_groups - 1) / span_groups;
+}
 constexpr int kXcds = 8;
-int32_t tiled_group_count(int64_t n, int32_t n_bins, int n_cu);
-int64_t tiled_chunks(int64_t n, int32_t n_bins, int32_t groups, int n_cu);
+// How a launch over n trials is split: chunks of trials (0: whole) x spans of span_groups of
+// the n_groups groups of group_bins bins.
+struct TiledSplit {
+    int64_t chunks;
+    int32_t group_bins, n_groups, span_groups;
+};
+TiledSplit tiled_split(int64_t n, int32_t n_bins, int n_cu, bool occ_max);
 // occ_max: each trial's largest occurrence-net loss into a.ylt instead of the YLT;
 // start/stop (or null): HIP events attached to the launch (its first dispatch's start, its
 // last one's end)
 hipError_t launch_trial_tiled(const TiledArgs &a, int grid, hipStream_t s, bool occ_max = false,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-// A pass of the tiled kernel as a work item: analysis `job`, trials [t0, t1), bin group
-// `group`, or every group (-1).
+// A pass of the tiled kernel as a work item: analysis `job`, trials [t0, t1), bin groups
+// [groups & 0xFFFF, groups >> 16).
 struct TiledItem {
     int32_t job;
-    int32_t group;
+    uint32_t groups;
     int64_t t0, t1;
 };
 static_assert(sizeof(TiledItem) == 24, "six words");

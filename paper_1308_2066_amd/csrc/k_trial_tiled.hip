@@ -183,22 +183,23 @@ __device__ __forceinline__ void unit_run(const double *tab, const i32x4 &span, U
     }
 }
 
-// One pass of a workgroup over trials [pass, pass_end) (at most kTiledPassTrials, split
-// evenly over the waves) and bins [bin0, bin1) of analysis a: every bin staged once, each
-// lane's trials added bin by bin into its sums ws[64 g + lane].
+// One pass of a workgroup over trials [T0, T1) of each wave (at most kTiledWaveTrials) and bin
+// groups [g0, g1) of analysis a: every bin staged once, each lane's trials added bin by bin
+// in registers; where a group ends its sums go to ws[64 g + lane], the total so far (a.part null:
+// every group here), or to the group's row of a.part.
 // MAX = false: sums of the occurrence-net losses; MAX = true: each trial's largest.
-// Units u = 4 b + g (bin b, group g) take turns in two register slots (slot u % 2): unit
-// u + 2 is issued once unit u is added.  No load is issued under a condition, so
+// Units u = 4 b + g (bin b, group g of 64 trials) take turns in two register slots (slot
+// u % 2): unit u + 2 is issued once unit u is added.  No load is issued under a condition, so
 // that every wait counts only the loads issued after the one it waits for: past the last
 // bin, the last one's loads are issued again and its runs are empty.
 // B24: run starts in 3 bytes each, read as an unaligned 4-byte word (its top byte,
 // the next entry's first, masked off where the value is taken).
 template <bool MAX, bool B24>
-__device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64_t T1, int32_t bin0, int32_t bin1,
+__device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64_t T1, int32_t g0, int32_t g1,
                                            double *tab, double *ws, int lane) {
-#pragma unroll
-    for (int g = 0; g < kGroups; ++g)
-        if (64 * g + lane < kTiledWaveTrials) ws[64 * g + lane] = 0.0;
+    const int32_t bin0 = g0 * a.group_bins, bin1 = min(g1 * a.group_bins, a.n_bins);
+    int32_t bg = g0, bg_end = min(bin0 + a.group_bins, bin1);   // the bin group and its last bin + 1
+    double acc[kGroups] = {};
     // start of the run of trial T0 + 64 g + lane (the wave's span end past T1), and
     // the end of the group's last run (scalar)
     constexpr uint32_t kRunMask = B24 ? 0xFFFFFFu : 0xFFFFFFFFu;
@@ -257,10 +258,7 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64
             // a run ends where the next lane's starts; lane 63's at the group end
             const uint32_t nx = uint32_t(__builtin_amdgcn_ds_bpermute(((lane + 1) & 63) * 4, int(U[slot].s)));
             const uint32_t e = lane == 63 ? ge[g] : nx;
-            const int j = min(64 * g + lane, kTiledWaveTrials - 1);
-            double acc = ws[j];
-            unit_run<MAX>(tab, pc, U[slot], e, acc);
-            if (64 * g + lane < kTiledWaveTrials) ws[j] = acc;
+            unit_run<MAX>(tab, pc, U[slot], e, acc[g]);   // lanes past T1: empty runs
             U[slot].s = g < 2 ? sc[g + 2] : sn[g - 2];
             unit_issue(g < 2 ? rc : rn, U[slot]);
         }
@@ -268,48 +266,52 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64
         for (int g = 0; g < kGroups; ++g) sc[g] = sn[g], ge[g] = gn[g];
         rc = rn;
         pc = pn;
+        if (b + 1 != bg_end) continue;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            const int64_t t = T0 + 64 * g + lane;
+            if (t < T1) {
+                if (a.part) {
+                    a.part[bg * a.part_stride + (t - a.t_begin)] = acc[g];
+                } else {
+                    double x = ws[64 * g + lane];   // group 0: an earlier pass's
+                    x = bg > 0 ? x : 0.0;
+                    fold<MAX>(x, acc[g]);
+                    ws[64 * g + lane] = x;
+                }
+            }
+            acc[g] = 0.0;
+        }
+        ++bg;
+        bg_end = min(bg_end + a.group_bins, bin1);
     }
 }
 
 // Trials [t0, t1) (at most one pass) over bin groups [g0, g1) of analysis a.  A trial's
-// total is ((s_0 + s_1) + s_2) + ..., s_g its sum over group g's bins: whole (every group
-// here, the total so far in a.ylt, which only this lane touches), or with a.part one
-// group, whose s_g k_tiled_combine adds up in the same order.  So a trial's YLT does not
-// depend on how its groups are spread over workgroups.
+// total is ((s_0 + s_1) + s_2) + ..., s_g its sum over group g's bins, taken here (every
+// group) or, with a.part, by k_tiled_combine in the same order.  The groups depend on the
+// catalog alone, so a trial's YLT does not depend on how they are spread over workgroups,
+// nor on the other trials of its YET.
 template <bool MAX, bool B24>
 __device__ __forceinline__ void tiled_groups(const TiledArgs &a, int64_t t0, int64_t t1, int32_t g0, int32_t g1,
                                              double *tab, double *ws, int lane, uint32_t wave) {
     const int64_t per_wave = (t1 - t0 + kTiledWaves - 1) / kTiledWaves;
     const int64_t T0 = min(t0 + int64_t(wave) * per_wave, t1);
     const int64_t T1 = min(T0 + per_wave, t1);
+    tiled_pass<MAX, B24>(a, T0, T1, g0, g1, tab, ws, lane);
+    if (a.part) return;
 #pragma unroll 1
-    for (int32_t bg = g0; bg < g1; ++bg) {
-        const int32_t bin0 = bg * a.group_bins;
-        tiled_pass<MAX, B24>(a, T0, T1, bin0, min(bin0 + a.group_bins, a.n_bins), tab, ws, lane);
-#pragma unroll 1
-        for (int g = 0; g < kGroups; ++g) {
-            const int64_t t = T0 + 64 * g + lane;
-            if (t >= T1) continue;
-            double s = ws[64 * g + lane];
-            if (a.part) {
-                a.part[bg * a.part_stride + (t - a.t_begin)] = s;
-                continue;
-            }
-            double *y = a.ylt + (t - a.t_begin);
-            if (bg > 0) {
-                const double x = *y;
-                s = MAX ? (s > x ? s : x) : x + s;
-            }
-            *y = MAX || bg + 1 < a.n_groups ? s : excess(s, a.agg_r, a.agg_l);
-        }
+    for (int g = 0; g < kGroups; ++g) {
+        const int64_t t = T0 + 64 * g + lane;
+        if (t < T1) a.ylt[t - a.t_begin] = MAX ? ws[64 * g + lane] : excess(ws[64 * g + lane], a.agg_r, a.agg_l);
     }
 }
 
 // One analysis.  Whole (part null): workgroup w owns trials [t_begin + w
-// per_wg, + per_wg), in passes, over every bin group.  Split: item i = (bin group, chunk of
-// per_wg trials), a workgroup each, chunks of a group in a row; XCD x (workgroups x, x + 8,
-// ...) takes a contiguous eighth of the items, so its L2 holds the values of its own
-// groups' bins only.
+// per_wg, + per_wg), in passes, over every bin group.  Split: item i = (span of span_groups bin
+// groups, chunk of per_wg trials), a workgroup each, chunks of a span in a row; XCD x
+// (workgroups x, x + 8, ...) takes a contiguous eighth of the items, so its L2 holds the
+// values of its own spans' bins only.
 template <bool MAX, bool B24>
 __global__ __launch_bounds__(1024) void k_trial_tiled(TiledArgs a) {
     __shared__ __attribute__((aligned(16))) double tab[kBinEvents + 2];   // a bin's values, the zero slot
@@ -320,11 +322,11 @@ __global__ __launch_bounds__(1024) void k_trial_tiled(TiledArgs a) {
     int32_t g0 = 0, g1 = a.n_groups;
     int64_t wg0 = a.t_begin + int64_t(blockIdx.x) * a.per_wg;
     if (a.part) {
-        const int32_t items = a.chunks * a.n_groups, each = (items + kXcds - 1) / kXcds;
+        const int32_t items = a.chunks * tiled_spans(a.n_groups, a.span_groups), each = (items + kXcds - 1) / kXcds;
         const int32_t i = int32_t(blockIdx.x % kXcds) * each + int32_t(blockIdx.x / kXcds);
         if (i >= items || int32_t(blockIdx.x / kXcds) >= each) return;
-        g0 = i / a.chunks;
-        g1 = g0 + 1;
+        g0 = i / a.chunks * a.span_groups;
+        g1 = min(g0 + a.span_groups, a.n_groups);
         wg0 = a.t_begin + int64_t(i % a.chunks) * a.per_wg;
     }
     const int64_t wg1 = min(wg0 + a.per_wg, a.t_end);
@@ -371,7 +373,7 @@ __device__ __forceinline__ TiledArgs load_args(const TiledArgs *jobs, int32_t j)
 }
 
 // Many analyses in one launch (YLTs): each item is a pass over up to kTiledPassTrials
-// trials of one analysis, over every bin group or (split analyses) one of them, taken in
+// trials of one analysis, over every bin group or (split analyses) some of them, taken in
 // list order from a counter by whichever workgroup is free; a workgroup stops once the
 // counter passes the list.  A trial's YLT does not depend on the pass that holds it, so
 // these give the bits of k_trial_tiled.
@@ -391,11 +393,12 @@ __global__ __launch_bounds__(1024) void k_trial_tiled_items(const TiledArgs *__r
         __syncthreads();   // every wave has read `took` before it is taken again
         if (it >= uint32_t(n_items)) return;
         const uint32_t *iw = reinterpret_cast<const uint32_t *>(items + it);
-        const int32_t job = int32_t(sload(iw + 0)), group = int32_t(sload(iw + 1));
+        const int32_t job = int32_t(sload(iw + 0));
+        const uint32_t groups = sload(iw + 1);
         const int64_t t0 = int64_t(uint64_t(sload(iw + 2)) | (uint64_t(sload(iw + 3)) << 32));
         const int64_t t1 = int64_t(uint64_t(sload(iw + 4)) | (uint64_t(sload(iw + 5)) << 32));
         const TiledArgs a = load_args(jobs, job);
-        const int32_t g0 = group < 0 ? 0 : group, g1 = group < 0 ? a.n_groups : group + 1;
+        const int32_t g0 = int32_t(groups & 0xFFFFu), g1 = int32_t(groups >> 16);
         double *ws = sums + wave * kTiledWaveTrials;
         if (a.boff24) tiled_groups<false, true>(a, t0, t1, g0, g1, tab, ws, lane, wave);
         else tiled_groups<false, false>(a, t0, t1, g0, g1, tab, ws, lane, wave);
@@ -430,7 +433,7 @@ hipError_t launch_trial_tiled_items(const TiledArgs *jobs, const TiledItem *item
 
 hipError_t launch_trial_tiled(const TiledArgs &a, int grid, hipStream_t s, bool occ_max, hipEvent_t start,
                               hipEvent_t stop) {
-    const int items = a.part ? (a.chunks * a.n_groups + kXcds - 1) / kXcds * kXcds : grid;
+    const int items = a.part ? (a.chunks * tiled_spans(a.n_groups, a.span_groups) + kXcds - 1) / kXcds * kXcds : grid;
     const dim3 g(items), b(kTiledWaves * 64);
     hipEvent_t end = a.part ? nullptr : stop;
     if (a.boff24) {
@@ -449,58 +452,52 @@ hipError_t launch_trial_tiled(const TiledArgs &a, int grid, hipStream_t s, bool 
 }
 
 // ---------------------------------------------------------------------------------
-// Bin groups.  Every workgroup stages the bins it goes through (about 5 us each, from the
-// L2, with few trials; 8.2 us with a full pass of about 16 occurrences per trial), so a
-// launch of few trials spread over all CUs was bound by the staging: 10^5 trials of 1000
-// occurrences over 62 bins took 330 us on 256 workgroups of 391 trials, 50,000 of 600 over
-// 19 bins 122 us.  Instead a workgroup takes a chunk of up to a full pass of trials and a
-// few bins: 75 us + 5 us for the sums in the first case, 31 + 5 us in the second.  Costs in
-// full-pass bin times: 0.75 per workgroup (start, first bin's load,
-// sums written), 0.6 per bin at least.
-static double bin_cost(double trials) { return std::max(0.6, trials / kTiledPassTrials); }
-
-static double split_cost(int64_t n, int64_t chunks, int32_t n_bins, int32_t groups, int n_cu) {
-    const double rounds = double((chunks * groups + n_cu - 1) / n_cu);
-    const int32_t gb = (n_bins + groups - 1) / groups;
-    // the sums' traffic at 4 TB/s and the combining launch
-    return rounds * (0.75 + gb * bin_cost(double(n) / double(chunks))) + 0.7 + double(n) * groups * 16.0 / 4e12 / 8.2e-6;
+// Splitting.  Every workgroup stages the bins it goes through, so a launch of few trials
+// spread over all CUs was bound by the staging: 10^5 trials of 1000 occurrences over 62 bins
+// took 330 us on 256 workgroups of 391 trials, 50,000 of 600 over 19 bins 122 us.  Instead a
+// workgroup takes a chunk of up to a full pass of trials and a span of the bin groups: 64 and
+// 28 us with the adding up.  Costs in full-pass bin times (8.2 us): 0.75 per workgroup
+// (start, first bin's load, sums written), and per bin what its own trials take (3.3 us and
+// 3.7 more for a full pass) or, with every CU busy, their share of the memory path.
+static double bin_cost(double trials, double wgs, int n_cu) {
+    const double x = trials / kTiledPassTrials;
+    return std::max(0.4 + 0.45 * x, x * std::min(1.0, wgs / n_cu));
 }
 
-static double whole_cost(int64_t n, int32_t n_bins, int32_t groups, int n_cu) {
+static double whole_cost(int64_t n, int32_t n_bins, int n_cu) {
     const int64_t wgs = std::max<int64_t>(1, std::min<int64_t>(n_cu, (n + 63) / 64));
     const int64_t per = (n + wgs - 1) / wgs, passes = (per + kTiledPassTrials - 1) / kTiledPassTrials;
-    return double(passes) * (0.75 * groups + n_bins * bin_cost(double(per) / double(passes)));
+    return double(passes) * (0.75 + n_bins * bin_cost(double(per) / double(passes), double(wgs), n_cu));
 }
 
-static double best_split(int64_t n, int32_t n_bins, int32_t groups, int n_cu, int64_t *chunks) {
-    double best = 1e300;
+// The split of n trials over n_bins bins that costs least, or chunks = 0: whole.  Sums are
+// taken by bin groups; maxima, which are the same in any order, by spans of bins.
+TiledSplit tiled_split(int64_t n, int32_t n_bins, int n_cu, bool occ_max) {
+    const int32_t gb = occ_max ? (n_bins + 63) / 64 : tiled_group_bins(n_bins), groups = (n_bins + gb - 1) / gb;
     const int64_t least = (n + kTiledPassTrials - 1) / kTiledPassTrials;
-    for (int64_t k = least; k <= 4 * least && (k == least || n / k >= 64); k += least) {
-        const double c = split_cost(n, k, n_bins, groups, n_cu);
-        if (c < best) best = c, *chunks = k;
+    TiledSplit best{0, 0, 0, 0};
+    double cost = whole_cost(n, n_bins, n_cu);
+    for (int32_t span = 1; span < groups; ++span) {
+        const int32_t spans = tiled_spans(groups, span);
+        if (span > 1 && tiled_spans(groups, span - 1) == spans) continue;
+        const int32_t bins = std::min(span * gb, n_bins), parts = occ_max ? spans : groups;
+        // the parts written and read at 4 TB/s, and the combining launch
+        const double sums = 0.7 + double(n) * parts * 16.0 / 4e12 / 8.2e-6;
+        // as many chunks as fill so many rounds of the CUs, of at least a group of 64 trials
+        const int64_t first = (least * spans + n_cu - 1) / n_cu;
+        for (int64_t rounds = first; rounds < first + 3; ++rounds) {
+            const int64_t chunks = std::max(least, std::min(rounds * n_cu / spans, n / 64));
+            const int64_t wgs = chunks * spans, full = wgs / n_cu, rest = wgs % n_cu;
+            const double trials = double(n) / double(chunks);
+            double c = sums + double(full) * (0.75 + bins * bin_cost(trials, n_cu, n_cu));
+            if (rest > 0) c += 0.75 + bins * bin_cost(trials, double(rest), n_cu);
+            if (c < cost) {
+                cost = c;
+                best = occ_max ? TiledSplit{chunks, bins, spans, 1} : TiledSplit{chunks, gb, groups, span};
+            }
+        }
     }
     return best;
-}
-
-// Groups of a YET of n trials: as many as its whole trial range is fastest with, so that
-// every trial range of it, alone or in a batch, adds in the same order.
-int32_t tiled_group_count(int64_t n, int32_t n_bins, int n_cu) {
-    int32_t best = 1;
-    double least = whole_cost(n, n_bins, 1, n_cu);
-    for (int32_t g = 2; g <= std::min(n_bins, kTiledMaxGroups); ++g) {
-        const int32_t gb = (n_bins + g - 1) / g, groups = (n_bins + gb - 1) / gb;
-        int64_t chunks = 0;
-        const double c = best_split(n, n_bins, groups, n_cu, &chunks);
-        if (c < 0.97 * least) least = c, best = groups;   // fewer groups unless it pays
-    }
-    return best;
-}
-
-// Chunks to split n trials into, or 0: whole.
-int64_t tiled_chunks(int64_t n, int32_t n_bins, int32_t groups, int n_cu) {
-    if (groups <= 1) return 0;
-    int64_t chunks = 0;
-    return best_split(n, n_bins, groups, n_cu, &chunks) < whole_cost(n, n_bins, groups, n_cu) ? chunks : 0;
 }
 
 }  // namespace ara
