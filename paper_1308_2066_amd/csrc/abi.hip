@@ -1436,20 +1436,72 @@ static RiskJob risk_job(const double *y, int64_t n, const int64_t *ks, int32_t m
     return j;
 }
 
+// Jobs whose risk measures one launch_risk takes (the jobs of further sets may use the same
+// workspaces).
+struct RiskSet {
+    const RiskJob *host, *dev;
+    int n_short, n_long;
+};
+
+// The launches report here, and the YLTs that need further rounds in a pinned word of their own.
+static RiskOut risk_out(ara_ctx *c) { return RiskOut{c->d_err, c->h_err, c->h_err + 2}; }
+
+// Finishes the sets after a launch of each that left some YLT open (blocking).
+static ara_status risk_finish(ara_ctx *c, const RiskSet *sets, size_t n_sets) {
+    const RiskOut out = risk_out(c);
+    volatile uint32_t *open = out.open_out;
+    const auto with_long = std::count_if(sets, sets + n_sets, [](const RiskSet &t) { return t.n_long > 0; });
+    for (size_t i = 0; i < n_sets; ++i) {
+        const RiskSet &t = sets[i];
+        if (t.n_long == 0) continue;
+        hipError_t e = hipSuccess;
+        if (with_long > 1) {   // a later set may have had its workspaces
+            *open = 0;
+            e = launch_risk(t.host, t.dev, t.n_short, t.n_long, out, c->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        }
+        for (int round = 1; e == hipSuccess && *open; ++round) {
+            if (round > kRiskMaxRounds) return fail(c, ARA_E_DEVICE, "risk measures: no end after %d rounds", kRiskMaxRounds);
+            *open = 0;
+            e = launch_risk_round(t.host + t.n_short, t.dev ? t.dev + t.n_short : nullptr, t.n_long, round, out, c->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        }
+        if (e != hipSuccess) return hip_fail(c, e, "risk measures");
+    }
+    return ARA_OK;
+}
+
+// The sets' risk measures into their jobs' results (pinned host memory); the kernels write
+// them and the error word straight to the host.  Blocking.
+static ara_status risk_run(ara_ctx *c, const RiskSet *sets, size_t n_sets) {
+    const RiskOut out = risk_out(c);
+    *out.open_out = 0;
+    hipError_t e = hipSuccess;
+    for (size_t i = 0; i < n_sets && e == hipSuccess; ++i)
+        e = launch_risk(sets[i].host, sets[i].dev, sets[i].n_short, sets[i].n_long, out, c->stream);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(c->stream);
+        return hip_fail(c, e, "risk measures");
+    }
+    const ara_status s = sync_and_check(c, nullptr, n_sets > 0);
+    if (s != ARA_OK || *static_cast<volatile uint32_t *>(out.open_out) == 0) return s;
+    return risk_finish(c, sets, n_sets);
+}
+
 // PML/TVaR of the n_rp ranks ks of the device YLT dy (selection in the sort workspace
-// w), results to the host (blocking).  Allocates nothing.  The kernels write the results
-// and the error word straight to pinned host memory.
+// w), results to the host (blocking).  Allocates nothing.
 static ara_status risk_on_device(ara_ctx *c, const double *dy, int64_t n, const int64_t *ks, int32_t n_rp, double *pml,
                                  double *tvar, void *w) {
     void *ws = reinterpret_cast<void *>((reinterpret_cast<uintptr_t>(w) + 255) & ~uintptr_t(255));
-    hipError_t e = hipSuccess;
-    for (int32_t base = 0; base < n_rp && e == hipSuccess; base += kRiskGroup) {
-        const int32_t m = std::min<int32_t>(kRiskGroup, n_rp - base);
-        const RiskJob j = risk_job(dy, n, ks + base, m, c->h_out + 2 * base, ws);
-        const bool one = n <= kRiskOneWg;
-        e = launch_risk(&j, nullptr, one ? 1 : 0, one ? 0 : 1, c->d_err, c->h_err, c->stream);
+    RiskJob jobs[(kMaxReturnPeriods + kRiskGroup - 1) / kRiskGroup];
+    RiskSet sets[(kMaxReturnPeriods + kRiskGroup - 1) / kRiskGroup];
+    size_t n_sets = 0;
+    const int one = n <= kRiskOneWg ? 1 : 0;
+    for (int32_t base = 0; base < n_rp; base += kRiskGroup, ++n_sets) {
+        jobs[n_sets] = risk_job(dy, n, ks + base, std::min<int32_t>(kRiskGroup, n_rp - base), c->h_out + 2 * base, ws);
+        sets[n_sets] = RiskSet{&jobs[n_sets], nullptr, one, 1 - one};
     }
-    ara_status s = e == hipSuccess ? sync_and_check(c, nullptr, n_rp > 0) : hip_fail(c, e, "risk measures");
+    const ara_status s = risk_run(c, sets, n_sets);
     if (s != ARA_OK) return s;
     for (int32_t base = 0; base < n_rp; base += kRiskGroup) {
         const int32_t m = std::min<int32_t>(kRiskGroup, n_rp - base);
@@ -1543,6 +1595,7 @@ struct ara_batch {
     std::vector<double> risk_rps;
     std::vector<RiskJob> rjobs;      // short YLTs first (RiskJob), one per job and group of return periods
     std::vector<std::pair<int, int>> rlaunch;   // per launch: short and long descriptors, in order
+    std::vector<RiskSet> rsets;                 // the same
     RiskJob *d_rjobs = nullptr;
     double *h_risk = nullptr;        // pinned: [job][2 n_rp], per group of return periods PML then TVaR
     void *risk_ws = nullptr;         // the workspaces of one launch's long YLTs
@@ -2038,6 +2091,7 @@ static void batch_risk_free(ara_batch *b) {
     b->h_risk = nullptr;
     b->rjobs.clear();
     b->rlaunch.clear();
+    b->rsets.clear();
     b->risk_rps.clear();
 }
 
@@ -2094,6 +2148,11 @@ static ara_status batch_risk_plan(ara_batch *b, const double *rps, int32_t n_rp)
         batch_risk_free(b);
         return hip_fail(c, e, "batch risk jobs upload");
     }
+    size_t at = 0;
+    for (const auto &l : b->rlaunch) {
+        b->rsets.push_back(RiskSet{b->rjobs.data() + at, b->d_rjobs + at, l.first, l.second});
+        at += size_t(l.first + l.second);
+    }
     b->risk_rps.assign(rps, rps + n_rp);
     return ARA_OK;
 }
@@ -2110,15 +2169,7 @@ extern "C" ara_status ara_batch_risk(ara_batch *b, const double *rps, int32_t n_
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
     ara_status s = batch_risk_plan(b, rps, n_rp);
     if (s != ARA_OK) return s;
-    hipError_t e = hipSuccess;
-    size_t at = 0;
-    for (size_t l = 0; l < b->rlaunch.size() && e == hipSuccess; ++l) {
-        const int ns = b->rlaunch[l].first, nl = b->rlaunch[l].second;
-        e = launch_risk(b->rjobs.data() + at, b->d_rjobs + at, ns, nl, c->d_err, c->h_err, c->stream);
-        at += size_t(ns + nl);
-    }
-    if (e != hipSuccess) return hip_fail(c, e, "batch risk measures");
-    s = sync_and_check(c, nullptr, true);   // the kernels wrote the results and the error word to the host
+    s = risk_run(c, b->rsets.data(), b->rsets.size());
     if (s != ARA_OK) return s;
     for (int32_t j = 0; j < nj; ++j) {
         const double *src = b->h_risk + size_t(j) * 2 * n_rp;
@@ -2211,6 +2262,8 @@ struct ServerLane {
     double *h_res = nullptr;          // pinned: [slot][2 * n_rp], written by the risk kernels
     unsigned char *ws = nullptr;      // workspaces of the risk measures of long YLTs
     size_t ws_bytes = 0;
+    std::vector<RiskJob> risks;       // the iteration's risk measures, and their launches
+    std::vector<RiskSet> risk_sets;
     std::vector<ServerRequest *> reqs;   // the iteration in flight (empty: the lane is free)
     ara_status launch_status = ARA_OK;   // an error while enqueueing it (then its event is not waited on)
 };
@@ -2253,7 +2306,9 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
     std::vector<EltDesc> descs;
     std::vector<LayerBuild> builds;
     std::vector<BatchJob> jobs;
-    std::vector<RiskJob> risks;
+    std::vector<RiskJob> &risks = ln.risks;
+    risks.clear();
+    ln.risk_sets.clear();
     std::vector<int64_t> tb, te, ml(size_t(nj), std::max<int64_t>(1, int64_t(std::llround(mean_len))));
     for (int32_t i = 0; i < nj; ++i) {
         ServerRequest *r = take[size_t(i)];
@@ -2347,11 +2402,15 @@ static ara_status server_launch(ara_server *sv, ServerLane &ln, const std::vecto
                       false, nullptr, nullptr);
     }
     const RiskJob *d_risks = reinterpret_cast<const RiskJob *>(ln.d_stage + o_risks);
-    if (e == hipSuccess && ns > 0) e = launch_risk(risks.data(), d_risks, ns, 0, pc->d_err, pc->h_err, ln.stream);
-    for (size_t l = 0; l < ends.size() && e == hipSuccess; ++l) {
+    if (ns > 0) ln.risk_sets.push_back(RiskSet{risks.data(), d_risks, ns, 0});
+    for (size_t l = 0; l < ends.size(); ++l) {
         const int32_t i0 = l == 0 ? ns : ends[l - 1];
-        e = launch_risk(risks.data() + i0, d_risks + i0, 0, ends[l] - i0, pc->d_err, pc->h_err, ln.stream);
+        ln.risk_sets.push_back(RiskSet{risks.data() + i0, d_risks + i0, 0, ends[l] - i0});
     }
+    const RiskOut out = risk_out(pc);
+    *out.open_out = 0;
+    for (const RiskSet &t : ln.risk_sets)
+        if (e == hipSuccess) e = launch_risk(t.host, t.dev, t.n_short, t.n_long, out, ln.stream);
     if (e == hipSuccess) e = hipEventRecord(ln.done, ln.stream);
     return e == hipSuccess ? ARA_OK : hip_fail(pc, e, "server iteration");
 }
@@ -2369,6 +2428,7 @@ static void server_finish(ara_server *sv, ServerLane &ln) {
         (void)hipStreamSynchronize(ln.stream);
     }
     if (s == ARA_OK && *pc->h_err) s = sync_and_check(pc);   // reports and clears the device error word
+    if (s == ARA_OK && *risk_out(pc).open_out) s = risk_finish(pc, ln.risk_sets.data(), ln.risk_sets.size());
     for (size_t i = 0; i < ln.reqs.size(); ++i) {
         ServerRequest *r = ln.reqs[i];
         if (s == ARA_OK) {

@@ -335,11 +335,23 @@ struct RiskArgs {
     RiskJob one;
     const uint32_t *err;    // the device error word, copied to *err_out (may be null) with the results
     uint32_t *err_out;
+    uint32_t *open_out;     // set to 1 when a YLT stays open
+    int32_t round, pad_;
+};
+// Where a launch reports beside its results: the device error word and its copy, and a pinned
+// word that the caller clears before, set if any YLT stays open.
+struct RiskOut {
+    const uint32_t *err;
+    uint32_t *err_out, *open_out;
 };
 size_t risk_workspace_bytes(int64_t n, int m);
 // jobs [0, n_short) have n <= kRiskOneWg, the n_long after them are longer; dev: the same
 // array in device memory (null: one job, host[0]).  Asynchronous.
-hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int n_long, const uint32_t *err,
-                       uint32_t *err_out, hipStream_t s);
+hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int n_long, const RiskOut &out, hipStream_t s);
+// A further round (1, 2, ...) of the long jobs among which some stayed open; their workspaces
+// hold what the last round left.  No more than kRiskMaxRounds are needed.
+constexpr int kRiskMaxRounds = 8;
+hipError_t launch_risk_round(const RiskJob *host, const RiskJob *dev, int n_long, int round, const RiskOut &out,
+                             hipStream_t s);
 
 }  // namespace ara

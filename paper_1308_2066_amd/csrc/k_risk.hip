@@ -16,13 +16,18 @@
 // limit share it) and 4096 equal bins of [L, T]; keys past T, nine in ten when the
 // shortest return period is 10, are not counted at all.  In a YLT without negative losses
 // zeros (quiet years) come last: they are counted on their own and do not stretch the
-// bins.  The few keys of each rank's bin then go to LDS.  A rank that the counts do not
-// reach (the sample misled) is found by refine(), which needs no sample, in more passes.
+// bins.  The few keys of each rank's bin are then copied out and sorted out.
 //
-//   up to kRiskOneWg losses: one workgroup (k_risk_one).
+//   up to kRiskOneWg losses: one workgroup (k_risk_one); a rank that the counts do not reach
+//   (the sample misled), or whose bin is large, is found by refine(), in more passes.
 //   longer: k_risk_sample (one workgroup; clears the counts), k_risk_bins, k_risk_collect
 //   (the last workgroup to finish picks K), k_risk_sum (tile sums; the last workgroup to
-//   finish forms PML and TVaR).
+//   finish forms PML and TVaR).  Where a rank's range holds more than kRiskCollect keys of more
+//   than one value, the YLT stays open: the host, which waits for the results anyway, then
+//   launches rounds of k_risk_narrow (1024 to 4096 bins of the range's smallest to largest key, by
+//   the whole grid), k_risk_collect and k_risk_sum until none is.  A round narrows a range at
+//   least 512 times.  (One workgroup went through the YLT alone for such a rank: 2.6 ms for 10^6 losses
+//   half of which are close, 18 ms for the 1000-year loss of 10^7, 134 ms of 5 10^7.)
 // Both take many YLTs at once (one descriptor each), so a batch pays for the launches
 // once.
 //
@@ -50,7 +55,7 @@ namespace ara {
 constexpr int kRiskThreads = 1024;
 constexpr int kRiskWaves = kRiskThreads / 64;
 constexpr int kRiskBins = 4096;
-constexpr int kRiskSample = 1024;      // one loss per thread
+constexpr int kNarrowBins = 16384;     // bins of k_risk_narrow's ranges together
 constexpr int kRiskTile = 2048;        // losses per tile of the TVaR sum
 constexpr int kRiskBlocks = 128;       // most workgroups of a pass over one YLT
 constexpr int kRiskRow = 4096;         // fewest losses per workgroup
@@ -138,11 +143,10 @@ struct Counts {          // beside the bins
     uint32_t below, equal, zero;
 };
 
-// The right shift that maps keys 0 .. range (>= 1) to kRiskBins bins.
-__device__ __forceinline__ uint32_t bin_shift(uint64_t range) {
-    constexpr int own = __builtin_ctz(kRiskBins);
+// The right shift that maps keys 0 .. range (>= 1) to 2^log bins.
+__device__ __forceinline__ uint32_t bin_shift(uint64_t range, int log = __builtin_ctz(kRiskBins)) {
     const int bits = 64 - __builtin_clzll(range);
-    return bits > own ? uint32_t(bits - own) : 0u;
+    return bits > log ? uint32_t(bits - log) : 0u;
 }
 
 __device__ __forceinline__ bool in_bins(const Binning &b, uint64_t k) { return k > b.lo && k <= b.hi; }
@@ -234,16 +238,18 @@ __device__ __forceinline__ uint64_t range_end(uint64_t lo, uint64_t span, uint64
     return span < hi - lo ? lo + span : hi;
 }
 
-// Rank k after the counting pass (a wave on its own).  Keys come in the order: below lo,
-// equal to lo, bins, and with zeros_last zeros.  A bin's first key is kept out of [lo, ..]
-// when it is b.lo itself, and its last one ends at b.hi.
-__device__ __forceinline__ RankState pick_bin(const uint32_t *row, const Binning &b, const Counts &n, int64_t k) {
+// Rank k of `losses` after the counting pass (a wave on its own).  Keys come in the order:
+// below lo, equal to lo, bins, with zeros_last zeros, and the rest (`past` is set: they were
+// not counted one by one).  A bin's first key is kept out of [lo, ..] when it is b.lo itself,
+// and its last one ends at b.hi.
+__device__ __forceinline__ RankState pick_bin(const uint32_t *row, const Binning &b, const Counts &n, int64_t k,
+                                              int64_t losses, bool &past) {
     RankState s;
+    past = false;
     s.solved = false;
     s.K = b.lo;
-    s.lo = 0, s.span = ~0ull;      // unless found below: anywhere among all keys
+    s.lo = 0;
     s.left = k, s.copies = 0;
-    s.count = ~0u;
     if (k <= int64_t(n.below)) {
         s.span = b.lo - 1ull;
         s.count = n.below;
@@ -263,12 +269,23 @@ __device__ __forceinline__ RankState pick_bin(const uint32_t *row, const Binning
         s.span = end - s.lo;
         return s;
     }
-    // past the bins: a zero, if the bins held every positive loss
-    if (b.zeros_last && b.hi == kZeroKey - 1ull && k <= before + int64_t(total) + int64_t(n.zero)) {
-        s.K = kZeroKey;
-        s.copies = k - before - int64_t(total);
-        s.solved = true;
+    // past the bins: a zero, if the bins held every positive loss, or one of the rest
+    int64_t counted = before + int64_t(total);
+    s.lo = b.hi + 1ull;   // b.hi is not the last key there is: the bins would hold the rank
+    if (b.zeros_last && b.hi == kZeroKey - 1ull) {
+        if (k <= counted + int64_t(n.zero)) {
+            s.K = kZeroKey;
+            s.copies = k - counted;
+            s.solved = true;
+            return s;
+        }
+        counted += int64_t(n.zero);
+        s.lo = kZeroKey + 1ull;
     }
+    s.span = ~0ull - s.lo;
+    s.left = k - counted;
+    s.count = uint32_t(losses - counted);
+    past = true;
     return s;
 }
 
@@ -403,40 +420,58 @@ __device__ __forceinline__ void refine(Each each, RankState s, uint64_t &K, int6
     }
 }
 
-// What to count for ranks up to k_max of y[0, n), from a sample (whole workgroup; lds.bins
-// cleared on return).  Sample j is a loss of the j-th of 1024 equal stretches of the
-// YLT, at a place within it that varies from stretch to stretch.
+// What to count for ranks up to k_max of y[0, n), from a sample of PER losses per thread
+// (whole workgroup; lds.bins cleared on return).  Sample j is a loss of the j-th of as many
+// equal stretches of the YLT, at a place within it that varies from stretch to stretch.
+template <int PER>
 struct Sampled {
-    double loss;
-    bool have;
+    double loss[PER];
+    bool have[PER];
 };
-__device__ __forceinline__ Sampled sample_loss(const double *__restrict__ y, int64_t n) {
-    const int tid = threadIdx.x;
-    const int64_t a = int64_t(tid) * n / kRiskSample, e = int64_t(tid + 1) * n / kRiskSample;
-    Sampled s{0.0, e > a};
-    if (s.have) s.loss = y[a + __umulhi(uint32_t(tid) * 2654435761u, uint32_t(e - a))];
+template <int PER>
+__device__ __forceinline__ Sampled<PER> sample_losses(const double *__restrict__ y, int64_t n) {
+    Sampled<PER> s;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const uint32_t j = uint32_t(threadIdx.x) + uint32_t(u) * kRiskThreads;
+        const int64_t a = int64_t(j) * n / (PER * kRiskThreads), e = int64_t(j + 1) * n / (PER * kRiskThreads);
+        s.have[u] = e > a;
+        s.loss[u] = 0.0;
+        if (s.have[u]) s.loss[u] = y[a + __umulhi(j * 2654435761u, uint32_t(e - a))];
+    }
     return s;
 }
-__device__ __forceinline__ Binning sample_binning(Sampled own, int64_t n, int64_t k_max, RefineLds &lds) {
+template <int PER>
+__device__ __forceinline__ Binning sample_binning(const Sampled<PER> &own, int64_t n, int64_t k_max, RefineLds &lds) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool have = own.have;
-    const uint64_t key = have ? desc_key(own.loss) : ~0ull;
+    uint64_t key[PER];
+    uint64_t lo = ~0ull, hi = 0ull;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        key[u] = own.have[u] ? desc_key(own.loss[u]) : ~0ull;
+        lo = umin(lo, key[u]);
+        if (own.have[u]) hi = umax(hi, key[u]);
+    }
     for (int i = tid; i < kRiskBins; i += kRiskThreads) lds.bins[i] = 0u;
     // no negative loss sampled: zeros are taken to come last
-    uint64_t lo = key, hi = have ? key : 0ull;
     wg_range(lo, hi, lds);
     Binning b;
     b.lo = lo;
     b.zeros_last = hi <= kZeroKey && lo < kZeroKey ? 1u : 0u;
     const uint64_t last = b.zeros_last ? kZeroKey - 1ull : ~0ull;   // the bins' last key unless the sample ends them before
     __syncthreads();
-    uint64_t top = have && key <= last ? key : 0ull, none = ~0ull;
+    uint64_t top = 0ull, none = ~0ull;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (own.have[u] && key[u] <= last) top = umax(top, key[u]);
     wg_range(none, top, lds);
-    const int64_t ns = n < kRiskSample ? n : kRiskSample;
+    const int64_t ns = min(n, int64_t(PER * kRiskThreads));
     const double q = double(k_max) / double(n), at = q * double(ns);
     const int64_t place = int64_t(at + 5.0 * __builtin_sqrt(at * (1.0 - q)) + 6.0);
     const uint32_t width = top > lo ? bin_shift(top - lo) : 0u;
-    if (have && key <= top) atomicAdd(&lds.bins[(key - lo) >> width], 1u);
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (own.have[u] && key[u] <= top) atomicAdd(&lds.bins[(key[u] - lo) >> width], 1u);
     __syncthreads();
     if (wave == 0) {
         uint32_t total;
@@ -509,10 +544,10 @@ __device__ __forceinline__ void add_counts(const Counts &n, Counts *to) {   // l
 }
 
 // Bins of up to kRiskCollect keys together: where each rank's lie among the copied keys
-// (ranks of one bin share the first one's; larger bins are not copied), and at
-// off[kRiskGroup] the number of copied keys.  st[0, m) set, first and off written; whole
-// workgroup, with barriers on both sides.
-__device__ __forceinline__ void place_bins(const RankState *st, int m, int wave, int *first, uint32_t *off) {
+// (ranks of one bin share the first one's), at off[kRiskGroup] the number of copied keys, and in
+// *large a bit for the first rank of each larger bin, which is not copied.  st[0, m) set; first
+// (-1: solved), off and *large written; whole workgroup, with barriers on both sides.
+__device__ __forceinline__ void place_bins(const RankState *st, int m, int wave, int *first, uint32_t *off, uint32_t *large) {
     const int lane = threadIdx.x & 63;
     if (wave < m) {
         const int f = st[wave].solved ? -1 : first_of_bin(st, wave);
@@ -520,11 +555,12 @@ __device__ __forceinline__ void place_bins(const RankState *st, int m, int wave,
     }
     __syncthreads();
     if (wave == 0) {
-        const bool own = lane < m && first[lane] == lane && st[lane].count <= uint32_t(kRiskCollect);
-        const uint32_t c = own ? st[lane].count : 0u;
+        const bool own = lane < m && first[lane] == lane, copied = own && st[lane].count <= uint32_t(kRiskCollect);
+        const uint32_t c = copied ? st[lane].count : 0u;
         const uint32_t inc = wave_scan(c);
+        const uint64_t rest = __ballot(own && !copied);
         if (lane < m) off[lane] = inc - c;
-        if (lane == 63) off[kRiskGroup] = inc;
+        if (lane == 63) off[kRiskGroup] = inc, *large = uint32_t(rest);
     }
     __syncthreads();
 }
@@ -690,7 +726,7 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
     __shared__ Counts cnt;
     __shared__ RankState st[64];
     __shared__ int first[kRiskGroup];
-    __shared__ uint32_t off[kRiskGroup + 1], to_below;
+    __shared__ uint32_t off[kRiskGroup + 1], large, to_below;
     __shared__ uint64_t K[kRiskGroup];
     __shared__ uint64_t cand[kRiskCollect];
     __shared__ double tile_s[kRiskGroup][kOneTiles];
@@ -702,7 +738,7 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
     if (tid == 0) cnt = Counts{0u, 0u, 0u}, to_below = 0u;
     const int nt = int(risk_tiles(n)), i0 = wave, i1 = wave + kRiskWaves;
     static_assert(4 * kOneTiles <= 2 * kRiskWaves, "two quarters per wave");
-    const Sampled own = sample_loss(y, n);
+    const Sampled<1> own = sample_losses<1>(y, n);
     Quarter x0, x1;   // past the last tile: zeros
     quarter_losses(y, n, i0 >> 2, i0 & 3, x0);
     quarter_losses(y, n, i1 >> 2, i1 & 3, x1);
@@ -716,11 +752,13 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
     add_counts(c, &cnt);
     __syncthreads();
     if (wave < m) {   // wave r picks rank r's bin
-        const RankState s = pick_bin(ref.bins, b, cnt, job_rank(a, blockIdx.x, wave));
+        bool past;
+        RankState s = pick_bin(ref.bins, b, cnt, job_rank(a, blockIdx.x, wave), n, past);
+        if (past) s.count = ~0u;   // their bins have no place for copies
         if (lane == 0) st[wave] = s;
     }
     __syncthreads();
-    place_bins(st, m, wave, first, off);
+    place_bins(st, m, wave, first, off, &large);
     const bool fits = off[kRiskGroup] <= uint32_t(kRiskCollect);   // the copied keys fit in LDS
     if (fits && off[kRiskGroup] > 0u) {
         // the count of a rank's bin becomes where its next key goes (the keys below b.lo: to_below)
@@ -791,15 +829,21 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_one(RiskArgs a) {
 
 // ------------------------------------------------------------------ longer YLTs
 // Workspace of one YLT and group of ranks (risk_workspace_bytes), 256-byte aligned.
+enum : uint32_t { kRiskDone = 0, kRiskOpen = 1, kRiskPicked = 2 };   // picked: every K is known, not the sums
 struct RiskWs {
     uint32_t *done;      // [2]: workgroups that finished k_risk_collect, k_risk_sum
+    uint32_t *open;      // kRiskDone ...
+    uint32_t *ranges;    // of an open YLT: a bit for the first rank of each range to narrow
     Counts *counts;
     Binning *binning;
     uint32_t *n_cand;    // [kRiskGroup] keys copied out per bin
-    uint64_t *b_lo, *b_hi;   // [kRiskGroup] range of a bin too large to copy out
+    uint64_t *b_lo, *b_hi;   // [2][kRiskGroup] smallest and largest key of a range too large to copy out:
+                             // of k_risk_collect's round r in the half r & 1
     uint64_t *K;         // [kRiskGroup]
     int64_t *copies;     // [kRiskGroup]
+    RankState *state;    // [kRiskGroup], of an open YLT
     uint32_t *bins;      // [kRiskBins]
+    uint32_t *narrow;    // [kNarrowBins], of the ranges too large to copy out, one after another
     double *tile_sum;    // [m][tiles]
     uint64_t *cand;      // the copied bins, one after another: at most min(n, m kRiskCollect) keys
 };
@@ -809,24 +853,29 @@ __host__ __device__ inline int risk_blocks(int64_t n) {
     const int64_t b = (n + kRiskRow - 1) / kRiskRow;
     return int(b < kRiskBlocks ? b : kRiskBlocks);
 }
-constexpr size_t kRiskCtrlBytes = 1024;
+constexpr size_t kRiskCtrlBytes = 2048;
 
 __device__ __forceinline__ RiskWs risk_ws(const JobView &j) {
     RiskWs w;
     unsigned char *p = j.ws;
     w.done = reinterpret_cast<uint32_t *>(p);
+    w.open = w.done + 2;
+    w.ranges = w.done + 3;
     w.counts = reinterpret_cast<Counts *>(p + 16);
     w.binning = reinterpret_cast<Binning *>(p + 32);
     w.n_cand = reinterpret_cast<uint32_t *>(p + 64);
     w.b_lo = reinterpret_cast<uint64_t *>(p + 128);
-    w.b_hi = w.b_lo + kRiskGroup;
-    w.K = w.b_hi + kRiskGroup;
+    w.b_hi = w.b_lo + 2 * kRiskGroup;
+    w.K = w.b_hi + 2 * kRiskGroup;
     w.copies = reinterpret_cast<int64_t *>(w.K + kRiskGroup);
+    w.state = reinterpret_cast<RankState *>(w.copies + kRiskGroup);
     static_assert(sizeof(Counts) <= 16 && sizeof(Binning) <= 32 && 4 * kRiskGroup <= 64 &&
-                  128 + 4 * kRiskGroup * 8 <= kRiskCtrlBytes, "control block");
+                  128 + kRiskGroup * (6 * 8 + sizeof(RankState)) <= kRiskCtrlBytes, "control block");
     p += kRiskCtrlBytes;
     w.bins = reinterpret_cast<uint32_t *>(p);
     p += kRiskBins * 4;
+    w.narrow = reinterpret_cast<uint32_t *>(p);
+    p += kNarrowBins * 4;
     w.tile_sum = reinterpret_cast<double *>(p);
     p += risk_align(size_t(j.m) * size_t(risk_tiles(j.n)) * 8);
     w.cand = reinterpret_cast<uint64_t *>(p);
@@ -835,25 +884,35 @@ __device__ __forceinline__ RiskWs risk_ws(const JobView &j) {
 
 size_t risk_workspace_bytes(int64_t n, int m) {
     if (n <= kRiskOneWg) return 0;
-    return kRiskCtrlBytes + size_t(kRiskBins) * 4 + risk_align(size_t(m) * size_t(risk_tiles(n)) * 8) +
+    return kRiskCtrlBytes + size_t(kRiskBins + kNarrowBins) * 4 +
+           risk_align(size_t(m) * size_t(risk_tiles(n)) * 8) +
            risk_align(size_t(std::min<int64_t>(n, int64_t(m) * kRiskCollect)) * 8);
 }
+
+// log2 of the bins of each of n ranges in k_risk_narrow.
+__device__ __forceinline__ int narrow_log(int n) { return n <= 4 ? 12 : n <= 8 ? 11 : 10; }
+static_assert(4 << 12 <= kNarrowBins && 8 << 11 <= kNarrowBins && kRiskGroup << 10 <= kNarrowBins, "bins of all ranges");
 
 template <typename F>
 __device__ __forceinline__ void each_keys_of_grid(const JobView &j, int nb, F f) {
     each_keys(j.y, j.n, int64_t(blockIdx.x) * kRiskThreads, uint32_t(nb) * kRiskThreads, f);
 }
 
-// The binning from the sample; clears the counts.
+// The binning from the sample; clears the counts.  The keys below the smallest one sampled are
+// a range of their own, of n / (1024 PER) keys or so, which a rank of a long return period
+// lies in: with one loss per thread it is too large to copy out from about 5 10^6 losses on.
+constexpr int64_t kRiskSampleMore = int64_t(1) << 22;   // longer YLTs: PER = 4
+template <int PER>
 __global__ __launch_bounds__(kRiskThreads) void k_risk_sample(RiskArgs a) {
     __shared__ RefineLds ref;
     const JobView j = job_view(a, blockIdx.x);
+    if ((j.n > kRiskSampleMore) != (PER > 1)) return;
     const RiskWs w = risk_ws(j);
     const int tid = threadIdx.x;
     for (int i = tid; i < kRiskBins; i += kRiskThreads) w.bins[i] = 0u;
     if (tid < 2) w.done[tid] = 0u;
     if (tid < kRiskGroup) w.n_cand[tid] = 0u, w.b_lo[tid] = ~0ull, w.b_hi[tid] = 0ull;
-    const Binning b = sample_binning(sample_loss(j.y, j.n), j.n, j.k_max, ref);
+    const Binning b = sample_binning(sample_losses<PER>(j.y, j.n), j.n, j.k_max, ref);
     if (tid == 0) {
         *w.counts = Counts{0u, 0u, 0u};
         *w.binning = b;
@@ -882,48 +941,96 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_bins(RiskArgs a) {
         if (bins[i]) atomicAdd(&w.bins[i], bins[i]);
 }
 
-// The keys left in each rank's bin, copied out; the last workgroup picks each rank's K
-// among them.  A bin of more than kRiskCollect keys is not copied: its smallest and
-// largest key are kept instead (equal for a loss that occurs that often), else the last
-// workgroup goes through the YLT for it.
+// The keys of each open rank's range, copied out; the last workgroup picks each rank's K
+// among them.  Of a range of more than kRiskCollect keys the smallest and largest are kept
+// instead: equal for a loss that occurs that often, else the YLT stays open.  FIRST: the
+// ranges are bins that k_risk_bins counted, in later rounds k_risk_narrow's.  (One kernel for
+// both took 22 us for 10^6 losses, this 15.)
+constexpr int kRangesAtOnce = 4;   // large ranges per pass over the keys
+template <bool FIRST>
 __global__ __launch_bounds__(kRiskThreads) void k_risk_collect(RiskArgs a) {
     __shared__ RefineLds ref;
     __shared__ RankState st[64];
     __shared__ int first[kRiskGroup];
-    __shared__ uint32_t off[kRiskGroup + 1];
+    __shared__ uint32_t off[kRiskGroup + 1], large;
     __shared__ uint32_t last;
+    __shared__ uint64_t ends[2][kRangesAtOnce][kRiskWaves];
     const JobView j = job_view(a, blockIdx.y);
-    const int nb = min(risk_blocks(j.n), int(gridDim.x)), m = j.m;
+    const int nb = min(risk_blocks(j.n), int(gridDim.x)), m = j.m, half = FIRST ? 0 : a.round & 1;
     if (int(blockIdx.x) >= nb) return;
     const RiskWs w = risk_ws(j);
+    if (!FIRST && *w.open != kRiskOpen) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     RankState s;
-    if (wave < m) {
-        s = pick_bin(w.bins, *w.binning, *w.counts, job_rank(a, blockIdx.y, wave));
-        if (lane == 0) st[wave] = s;
+    if (FIRST) {
+        bool past;
+        if (wave < m) s = pick_bin(w.bins, *w.binning, *w.counts, job_rank(a, blockIdx.y, wave), j.n, past);
+    } else {
+        if (tid < m) st[tid] = w.state[tid];
+        __syncthreads();
+        if (wave < m) {
+            s = st[wave];
+            if (!s.solved) {
+                const int f = first_of_bin(st, wave), at = (half ^ 1) * kRiskGroup + f;
+                const uint64_t lo = w.b_lo[at], hi = w.b_hi[at];
+                const int log = narrow_log(__popc(*w.ranges));
+                const uint32_t *row = w.narrow + (__popc(*w.ranges & ((1u << f) - 1u)) << log), width = bin_shift(hi - lo, log);
+                uint32_t total;
+                if (log == 12) (void)wave_pick<64>(row, lo, width, s.left, s, total);
+                else if (log == 11) (void)wave_pick<32>(row, lo, width, s.left, s, total);
+                else (void)wave_pick<16>(row, lo, width, s.left, s, total);
+                s.span = range_end(s.lo, s.span, hi) - s.lo;
+            }
+        }
+        __syncthreads();
     }
+    if (wave < m && lane == 0) st[wave] = s;
     __syncthreads();
-    place_bins(st, m, wave, first, off);
-    each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
-        copy_bins(k, in, st, first, m, [&](int r, uint32_t c) { return atomicAdd(&w.n_cand[r], c); },
-                  [&](int r, uint32_t i, uint64_t x) { agent_store(&w.cand[off[r] + i], x); });
-    });
+    place_bins(st, m, wave, first, off, &large);
+    if (off[kRiskGroup] > 0u)
+        each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
+            copy_bins(k, in, st, first, m, [&](int r, uint32_t c) { return atomicAdd(&w.n_cand[r], c); },
+                      [&](int r, uint32_t i, uint64_t x) { agent_store(&w.cand[off[r] + i], x); });
+        });
 #pragma unroll 1
-    for (int r = 0; r < m; ++r) {
-        if (first[r] != r || st[r].count <= uint32_t(kRiskCollect) || st[r].count == ~0u) continue;
-        const uint64_t lo = st[r].lo, span = st[r].span;
-        uint64_t mn = ~0ull, mx = 0ull;
+    for (uint32_t left = large; __builtin_expect(left != 0u, 0);) {
+        int r[kRangesAtOnce];   // -1: none
+        uint64_t lo[kRangesAtOnce], span[kRangesAtOnce], mn[kRangesAtOnce], mx[kRangesAtOnce];
+#pragma unroll
+        for (int q = 0; q < kRangesAtOnce; ++q) {
+            r[q] = left ? __builtin_ctz(left) : -1;
+            left &= left - 1u;
+            lo[q] = st[max(r[q], 0)].lo, span[q] = st[max(r[q], 0)].span, mn[q] = ~0ull, mx[q] = 0ull;
+        }
         each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
 #pragma unroll
-            for (int u = 0; u < kRiskLoads; ++u)
-                if ((in >> u & 1u) && k[u] - lo <= span) mn = umin(mn, k[u]), mx = umax(mx, k[u]);
+            for (int q = 0; q < kRangesAtOnce; ++q) {
+                if (r[q] < 0) continue;
+#pragma unroll
+                for (int u = 0; u < kRiskLoads; ++u)
+                    if ((in >> u & 1u) && k[u] - lo[q] <= span[q]) mn[q] = umin(mn[q], k[u]), mx[q] = umax(mx[q], k[u]);
+            }
         });
-        mn = wave_min(mn);
-        mx = wave_max(mx);
-        if (lane == 0 && mn <= mx) {
-            atomicMin(reinterpret_cast<unsigned long long *>(&w.b_lo[r]), static_cast<unsigned long long>(mn));
-            atomicMax(reinterpret_cast<unsigned long long *>(&w.b_hi[r]), static_cast<unsigned long long>(mx));
+        // one addition per workgroup: one per wave, all on the same two words, took 20 us
+#pragma unroll
+        for (int q = 0; q < kRangesAtOnce; ++q) {
+            if (r[q] < 0) continue;
+            mn[q] = wave_min(mn[q]);
+            mx[q] = wave_max(mx[q]);
+            if (lane == 0) ends[0][q][wave] = mn[q], ends[1][q][wave] = mx[q];
         }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRangesAtOnce; ++q) {
+            if (r[q] < 0 || wave != q) continue;
+            const uint64_t l = wave_min(ends[0][q][lane & (kRiskWaves - 1)]), h = wave_max(ends[1][q][lane & (kRiskWaves - 1)]);
+            if (lane == 0 && l <= h) {
+                const int at = half * kRiskGroup + r[q];
+                atomicMin(reinterpret_cast<unsigned long long *>(&w.b_lo[at]), static_cast<unsigned long long>(l));
+                atomicMax(reinterpret_cast<unsigned long long *>(&w.b_hi[at]), static_cast<unsigned long long>(h));
+            }
+        }
+        __syncthreads();
     }
     if (!last_to_finish(&w.done[0], uint32_t(nb), &last)) return;
     if (wave < m) {
@@ -932,34 +1039,102 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_collect(RiskArgs a) {
             const uint64_t *from = w.cand + off[f];
             wave_select_any(int(s.count), s.left, s.K, s.copies, [&](int i) { return agent_load(&from[i]); });
             s.solved = true;
-        } else if (!s.solved && s.count > uint32_t(kRiskCollect) && s.count != ~0u) {
-            const uint64_t lo = agent_load(&w.b_lo[f]), hi = agent_load(&w.b_hi[f]);
+        } else if (!s.solved && s.count > uint32_t(kRiskCollect)) {
+            const int at = half * kRiskGroup + f;
+            const uint64_t lo = agent_load(&w.b_lo[at]), hi = agent_load(&w.b_hi[at]);
             if (lo == hi) s.K = lo, s.copies = s.left, s.solved = true;
         }
         if (lane == 0) st[wave] = s;
     }
     __syncthreads();
+    const uint64_t unsolved = __ballot(lane < m && !st[lane].solved);
+    uint64_t open = 0;
 #pragma unroll 1
-    for (int r = 0; r < m; ++r) {
-        if (st[r].solved) continue;
+    for (int r = 0; __builtin_expect(unsolved >> r != 0, 0); ++r) {
+        if (!(unsolved >> r & 1)) continue;
+        if (st[r].count > uint32_t(kRiskCollect)) {
+            open |= 1ull << r;
+            continue;
+        }
         uint64_t K;
         int64_t copies;
-        if (st[r].count <= uint32_t(kRiskCollect)) {
-            const uint64_t *c = w.cand + off[first[r]];
-            const int nc = int(st[r].count);
-            refine([&](auto f) { for (int i = tid; i < nc; i += kRiskThreads) f(agent_load(&c[i])); }, st[r], K, copies, ref);
-        } else {
-            refine([&](auto f) { for (int64_t i = tid; i < j.n; i += kRiskThreads) f(desc_key(j.y[i])); }, st[r], K, copies,
-                   ref);
-        }
+        const uint64_t *c = w.cand + off[first[r]];
+        const int nc = int(st[r].count);
+        refine([&](auto f) { for (int i = tid; i < nc; i += kRiskThreads) f(agent_load(&c[i])); }, st[r], K, copies, ref);
         __syncthreads();
-        if (tid == 0) st[r].K = K, st[r].copies = copies;
+        if (tid == 0) st[r].K = K, st[r].copies = copies, st[r].solved = true;
     }
     __syncthreads();
     if (tid < m) {
         w.K[tid] = st[tid].K;
         w.copies[tid] = st[tid].copies;
     }
+    if (tid == 0) *w.open = open ? kRiskOpen : kRiskPicked;
+    if (__builtin_expect(open == 0, 1)) return;
+    // for the next round
+    if (tid < m) w.state[tid] = st[tid];
+    for (int i = tid; i < kNarrowBins; i += kRiskThreads) w.narrow[i] = 0u;
+    if (tid == 0) w.done[0] = 0u, *w.ranges = large & uint32_t(open);
+    if (tid < kRiskGroup) {
+        w.n_cand[tid] = 0u;
+        w.b_lo[(half ^ 1) * kRiskGroup + tid] = ~0ull, w.b_hi[(half ^ 1) * kRiskGroup + tid] = 0ull;
+    }
+}
+
+// Counts the keys of the open ranks' ranges, each in 2^narrow_log bins from its smallest key to
+// its largest (one addition where a wave's keys fall in one bin: a loss that many years share
+// would otherwise be added one after another).
+__global__ __launch_bounds__(kRiskThreads) void k_risk_narrow(RiskArgs a) {
+    __shared__ uint32_t bins[kNarrowBins];
+    const JobView j = job_view(a, blockIdx.y);
+    const int nb = min(risk_blocks(j.n), int(gridDim.x));
+    if (int(blockIdx.x) >= nb) return;
+    const RiskWs w = risk_ws(j);
+    if (*w.open != kRiskOpen) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t ranges = *w.ranges;
+    const int log = narrow_log(__popc(ranges)), n_bins = __popc(ranges) << log;
+    for (int i = tid; i < n_bins; i += kRiskThreads) bins[i] = 0u;
+    __syncthreads();
+    const uint64_t *b_lo = w.b_lo + ((a.round & 1) ^ 1) * kRiskGroup, *b_hi = w.b_hi + ((a.round & 1) ^ 1) * kRiskGroup;
+    int done = 0;
+#pragma unroll 1
+    for (uint32_t left = ranges; left != 0u; done += kRangesAtOnce) {
+        int r[kRangesAtOnce];
+        uint64_t lo[kRangesAtOnce], span[kRangesAtOnce];
+        uint32_t width[kRangesAtOnce];
+#pragma unroll
+        for (int q = 0; q < kRangesAtOnce; ++q) {
+            r[q] = left ? __builtin_ctz(left) : -1;
+            left &= left - 1u;
+            lo[q] = b_lo[max(r[q], 0)], span[q] = b_hi[max(r[q], 0)] - lo[q];
+            width[q] = r[q] < 0 ? 0u : bin_shift(span[q], log);
+        }
+        each_keys_of_grid(j, nb, [&](const uint64_t (&k)[kRiskLoads], uint32_t in) {
+#pragma unroll
+            for (int q = 0; q < kRangesAtOnce; ++q) {
+                if (r[q] < 0) continue;
+                uint32_t *row = bins + ((done + q) << log);
+#pragma unroll
+                for (int u = 0; u < kRiskLoads; ++u) {
+                    const bool own = (in >> u & 1u) && k[u] - lo[q] <= span[q];
+                    const uint64_t all = __ballot(own);
+                    if (all == 0) continue;
+                    const uint32_t at = own ? uint32_t((k[u] - lo[q]) >> width[q]) : 0u;
+                    const int lead = __ffsll(static_cast<unsigned long long>(all)) - 1;
+                    const uint32_t at0 = uint32_t(__builtin_amdgcn_readlane(int(at), lead));
+                    if (__ballot(own && at != at0) == 0) {
+                        if (lane == lead) atomicAdd(&row[at], uint32_t(__popcll(all)));
+                    } else if (own) {
+                        atomicAdd(&row[at], 1u);
+                    }
+                }
+            }
+        });
+    }
+    __syncthreads();
+    for (int i = tid; i < n_bins; i += kRiskThreads)
+        if (bins[i]) atomicAdd(&w.narrow[i], bins[i]);
 }
 
 // Each tile's sum of the losses below each rank's K, four waves per tile; the last
@@ -979,6 +1154,13 @@ __global__ __launch_bounds__(kSumWaves * 64) void k_risk_sum(RiskArgs a) {
     const int64_t tile = int64_t(blockIdx.x) * kSumTiles + t;
     Quarter x;
     quarter_losses(j.y, j.n, tile, q, x);   // past the last tile: zeros
+    if (const uint32_t open = *w.open; open != kRiskPicked) {   // summed in an earlier round, or open
+        if (open == kRiskOpen && blockIdx.x == 0 && tid == 0) {
+            *a.open_out = 1u;
+            if (a.err_out) *a.err_out = *a.err;
+        }
+        return;
+    }
     quarter_keys(x);
 #pragma unroll 1
     for (int r0 = 0; r0 < m; r0 += kSumRanks) {
@@ -997,7 +1179,9 @@ __global__ __launch_bounds__(kSumWaves * 64) void k_risk_sum(RiskArgs a) {
         const double s = wave_sum_tiles(tiles, [&](int64_t t) { return agent_load(&w.tile_sum[r * tiles + t]); });
         if (lane == 0) write_measures(j.out, m, r, w.K[r], w.copies[r], s, job_rank(a, blockIdx.y, r));
     }
-    if (tid == 0 && a.err_out) *a.err_out = *a.err;
+    if (tid != 0) return;
+    *w.open = kRiskDone;
+    if (a.err_out) *a.err_out = *a.err;
 }
 
 // Workgroups per YLT of a pass over several: no more together than are resident at once, where
@@ -1021,33 +1205,66 @@ static int blocks_each(const RiskJob *jobs, int n_jobs, int resident) {
     return fits;
 }
 
-hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int n_long, const uint32_t *err,
-                       uint32_t *err_out, hipStream_t s) {
+// Grids of the passes over jobs[0, n): (workgroups of the counting, of the collection, of the
+// sums) per YLT.
+struct RiskGrids {
+    dim3 bins, collect, sum;
+};
+static hipError_t risk_grids(const RiskJob *jobs, int n_long, RiskGrids &g) {
+    int64_t n = 0;
+    for (int i = 0; i < n_long; ++i) n = std::max(n, jobs[i].n);
+    const int64_t tiles = risk_tiles(n);
+    if (tiles > int64_t(INT32_MAX) || n_long > 65535) return hipErrorInvalidValue;
+    g.bins = dim3(unsigned(std::min(risk_blocks(n), blocks_each(jobs, n_long, kResidentBins))), unsigned(n_long));
+    g.collect = dim3(unsigned(std::min(risk_blocks(n), blocks_each(jobs, n_long, kResidentCollect))), unsigned(n_long));
+    g.sum = dim3(unsigned((tiles + kSumTiles - 1) / kSumTiles), unsigned(n_long));
+    return hipSuccess;
+}
+
+static RiskArgs risk_args(const RiskJob *host, const RiskJob *dev, const RiskOut &out, int round) {
     RiskArgs a{};
-    a.err = err;
-    a.err_out = err_out;
+    a.jobs = dev;
+    if (!dev) a.one = host[0];
+    a.err = out.err;
+    a.err_out = out.err_out;
+    a.open_out = out.open_out;
+    a.round = round;
+    return a;
+}
+
+hipError_t launch_risk(const RiskJob *host, const RiskJob *dev, int n_short, int n_long, const RiskOut &out, hipStream_t s) {
+    const dim3 block(kRiskThreads);
     if (n_short > 0) {
-        a.jobs = dev;
-        if (!dev) a.one = host[0];
-        hipLaunchKernelGGL(k_risk_one, dim3(unsigned(n_short)), dim3(kRiskThreads), 0, s, a);
+        hipLaunchKernelGGL(k_risk_one, dim3(unsigned(n_short)), block, 0, s, risk_args(host, dev, out, 0));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (n_long <= 0) return hipSuccess;
-    a.jobs = dev ? dev + n_short : nullptr;
-    if (!dev) a.one = host[0];
-    int64_t n = 0;
-    for (int i = n_short; i < n_short + n_long; ++i) n = std::max(n, host[i].n);
-    const int64_t tiles = risk_tiles(n);
-    if (tiles > int64_t(INT32_MAX) || n_long > 65535) return hipErrorInvalidValue;
+    host += n_short;
+    const RiskArgs a = risk_args(host, dev ? dev + n_short : nullptr, out, 0);
+    RiskGrids g;
+    const hipError_t e = risk_grids(host, n_long, g);
+    if (e != hipSuccess) return e;
+    bool some = false, more = false;
+    for (int i = 0; i < n_long; ++i) (host[i].n > kRiskSampleMore ? more : some) = true;
+    if (some) hipLaunchKernelGGL(k_risk_sample<1>, dim3(unsigned(n_long)), block, 0, s, a);
+    if (more) hipLaunchKernelGGL(k_risk_sample<4>, dim3(unsigned(n_long)), block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_bins, g.bins, block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_collect<true>, g.collect, block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_sum, g.sum, dim3(kSumWaves * 64), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_risk_round(const RiskJob *host, const RiskJob *dev, int n_long, int round, const RiskOut &out,
+                             hipStream_t s) {
+    const RiskArgs a = risk_args(host, dev, out, round);
+    RiskGrids g;
+    const hipError_t e = risk_grids(host, n_long, g);
+    if (e != hipSuccess) return e;
     const dim3 block(kRiskThreads);
-    const int bins = std::min(risk_blocks(n), blocks_each(host + n_short, n_long, kResidentBins));
-    const int collect = std::min(risk_blocks(n), blocks_each(host + n_short, n_long, kResidentCollect));
-    hipLaunchKernelGGL(k_risk_sample, dim3(unsigned(n_long)), block, 0, s, a);
-    hipLaunchKernelGGL(k_risk_bins, dim3(unsigned(bins), unsigned(n_long)), block, 0, s, a);
-    hipLaunchKernelGGL(k_risk_collect, dim3(unsigned(collect), unsigned(n_long)), block, 0, s, a);
-    const dim3 sum_grid(unsigned((tiles + kSumTiles - 1) / kSumTiles), unsigned(n_long));
-    hipLaunchKernelGGL(k_risk_sum, sum_grid, dim3(kSumWaves * 64), 0, s, a);
+    hipLaunchKernelGGL(k_risk_narrow, g.bins, block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_collect<false>, g.collect, block, 0, s, a);
+    hipLaunchKernelGGL(k_risk_sum, g.sum, dim3(kSumWaves * 64), 0, s, a);
     return hipGetLastError();
 }
 
