@@ -181,13 +181,17 @@ static ara_status sync_and_check(ara_ctx *c, bool *wide = nullptr, bool copied =
 // is idle whatever streams its last user ran on.
 constexpr size_t kKeepBytes = size_t(4) << 30;
 
-// Sizes of a MiB and more in sixteen steps per power of two, so that YETs and tables of
-// nearly the same size share blocks.
-static size_t block_size(size_t bytes) {
+// Whether a block's size varies a little from one handle to the next (a YET's arrays, staging):
+// then sizes of a MiB and more go in sixteen steps per power of two, so that nearly equal
+// ones share blocks.  Sizes that would not be kept are taken as they are.
+enum BlockFit { kExactBlock, kSharedBlock };
+static size_t block_size(size_t bytes, BlockFit fit) {
     if (bytes == 0) bytes = 16;
-    if (bytes < (size_t(1) << 20)) return (bytes + 255) & ~size_t(255);
-    const size_t step = size_t(1) << (63 - __builtin_clzll(bytes) - 4);
-    return (bytes + step - 1) & ~(step - 1);
+    const size_t exact = (bytes + 255) & ~size_t(255);
+    if (fit == kExactBlock || exact < (size_t(1) << 20)) return exact;
+    const size_t step = size_t(1) << (63 - __builtin_clzll(exact) - 4);
+    const size_t shared = (exact + step - 1) & ~(step - 1);
+    return shared <= kKeepBytes ? shared : exact;
 }
 
 static void blocks_return(ara_ctx *c, size_t keep) {
@@ -201,9 +205,9 @@ static void blocks_return(ara_ctx *c, size_t keep) {
 }
 
 template <typename T>
-static ara_status dev_alloc(ara_ctx *c, T **p, size_t bytes, const char *what) {
+static ara_status dev_alloc(ara_ctx *c, T **p, size_t bytes, const char *what, BlockFit fit = kExactBlock) {
     *p = nullptr;
-    const size_t take = block_size(bytes);
+    size_t take = block_size(bytes, fit);
     void *q = nullptr;
     for (size_t i = c->kept.size(); i-- > 0;)
         if (c->kept[i].second == take) {
@@ -217,6 +221,12 @@ static ara_status dev_alloc(ara_ctx *c, T **p, size_t bytes, const char *what) {
         if (e != hipSuccess && !c->kept.empty()) {
             (void)hipGetLastError();
             blocks_return(c, 0);
+            e = hipMalloc(&q, take);
+        }
+        const size_t exact = block_size(bytes, kExactBlock);
+        if (e != hipSuccess && exact < take) {   // what was asked for may still fit
+            (void)hipGetLastError();
+            take = exact;
             e = hipMalloc(&q, take);
         }
         if (e != hipSuccess) {
@@ -625,14 +635,14 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
     bool b24 = c->yet_run_bytes == 3 && one_wait && nb <= 64;
     uint32_t *sums = nullptr;
     size_t ids16_bytes = size_t(y->n_events + 8 * int64_t(nb)) * 2 + 16;
-    ara_status s = dev_alloc(c, &sums, bin_offsets_scratch_words(n, nb) * 4, "binned yet scan");
+    ara_status s = dev_alloc(c, &sums, bin_offsets_scratch_words(n, nb) * 4, "binned yet scan", kSharedBlock);
     if (s == ARA_OK) s = dev_alloc(c, &y->region, size_t(nb + 1) * 8, "binned yet regions");
-    if (s == ARA_OK && one_wait) s = dev_alloc(c, &y->ids16, ids16_bytes, "binned yet ids");
+    if (s == ARA_OK && one_wait) s = dev_alloc(c, &y->ids16, ids16_bytes, "binned yet ids", kSharedBlock);
     while (s == ARA_OK) {
         // 3-byte form: 16 bytes of slack after the last row (the tiled kernel reads the
         // aligned words around an entry, up to 2 bytes past its row)
-        if (b24) s = dev_alloc(c, &y->boff24, size_t(nb) * size_t(y->stride) * 3 + 16, "binned yet run starts");
-        else s = dev_alloc(c, &y->boff, size_t(nb) * size_t(y->stride) * 4, "binned yet run starts");
+        if (b24) s = dev_alloc(c, &y->boff24, size_t(nb) * size_t(y->stride) * 3 + 16, "binned yet run starts", kSharedBlock);
+        else s = dev_alloc(c, &y->boff, size_t(nb) * size_t(y->stride) * 4, "binned yet run starts", kSharedBlock);
         if (s != ARA_OK) break;
         const RunStarts r{y->boff, y->boff24, y->stride};
         hipError_t e = launch_bin_offsets(y->ids, y->offs, y->n_events, n, nb, r, y->catalog, sums, c->d_err,
@@ -668,7 +678,7 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
             return ARA_OK;
         }
         ids16_bytes = size_t(total) * 2 + 16;
-        if (s == ARA_OK) s = dev_alloc(c, &y->ids16, ids16_bytes, "binned yet ids");
+        if (s == ARA_OK) s = dev_alloc(c, &y->ids16, ids16_bytes, "binned yet ids", kSharedBlock);
         if (s == ARA_OK) {
             e = launch_bin_scatter(y->ids, y->offs, y->n_events, n, nb, r, y->region, y->ids16, c->d_err, c->stream);
             s = e == hipSuccess ? sync_and_check(c) : hip_fail(c, e, "binned yet scatter");
@@ -708,8 +718,8 @@ extern "C" ara_status ara_yet_create(ara_ctx *c, const int32_t *ids, int64_t n_e
     if (y->owns) {
         int32_t *di = nullptr;
         int64_t *doff = nullptr;
-        ara_status s = dev_alloc(c, &di, size_t(n_events) * 4, "yet ids");
-        if (s == ARA_OK) s = dev_alloc(c, &doff, size_t(n_trials + 1) * 8, "yet offsets");
+        ara_status s = dev_alloc(c, &di, size_t(n_events) * 4, "yet ids", kSharedBlock);
+        if (s == ARA_OK) s = dev_alloc(c, &doff, size_t(n_trials + 1) * 8, "yet offsets", kSharedBlock);
         if (s != ARA_OK) {
             dev_free(c, di);
             delete y;
@@ -738,7 +748,7 @@ extern "C" ara_status ara_yet_create(ara_ctx *c, const int32_t *ids, int64_t n_e
         s = e == hipSuccess ? sync_and_check(c) : hip_fail(c, e, "validate yet");
     }
     if (s == ARA_OK && !y->ids16 && c->yet_packing && n_events > 0 && catalog <= kMaxPackedCatalog) {
-        s = dev_alloc(c, &y->ids24, yet_packed_bytes(n_events), "packed yet ids");
+        s = dev_alloc(c, &y->ids24, yet_packed_bytes(n_events), "packed yet ids", kSharedBlock);
         if (s == ARA_OK) {
             y->copy_bytes = int64_t(yet_packed_bytes(n_events));
             e = launch_yet_pack(y->ids, n_events, y->ids24, c->stream);
@@ -1187,7 +1197,7 @@ extern "C" ara_status ara_analyze(ara_ctx *c, const ara_yet *y, const ara_layer 
     if (s != ARA_OK) return s;
     double *dst = ylt;
     if (mem == ARA_MEM_HOST) {
-        s = dev_alloc(c, &dst, size_t(t1 - t0) * 8, "ylt staging");
+        s = dev_alloc(c, &dst, size_t(t1 - t0) * 8, "ylt staging", kSharedBlock);
         if (s != ARA_OK) return s;
     }
     // trial indices inside a launch are 32-bit: split very long ranges
@@ -1239,7 +1249,7 @@ extern "C" ara_status ara_analyze_occ_max(ara_ctx *c, const ara_yet *y, const ar
     const int64_t grid = std::min<int64_t>(int64_t(c->n_cu) * std::min(8, by_lds), (t1 - t0 + 255) / 256);
     double *dst = out;
     if (mem == ARA_MEM_HOST) {
-        s = dev_alloc(c, &dst, size_t(t1 - t0) * 8, "occurrence maxima staging");
+        s = dev_alloc(c, &dst, size_t(t1 - t0) * 8, "occurrence maxima staging", kSharedBlock);
         if (s != ARA_OK) return s;
     }
     hipError_t e = hipSuccess;
@@ -1296,7 +1306,7 @@ extern "C" ara_status ara_analyze_events(ara_ctx *c, const ara_yet *y, const ara
         for (int k = 0; k < 5; ++k) {
             dev[k] = nullptr;
             if (host[k] && len[k] > 0) {
-                s = dev_alloc(c, &dev[k], len[k] * 8, "event output staging");
+                s = dev_alloc(c, &dev[k], len[k] * 8, "event output staging", kSharedBlock);
                 if (s != ARA_OK) {
                     for (int j = 0; j < k; ++j) dev_free(c, dev[j]);
                     return s;
@@ -1338,9 +1348,9 @@ extern "C" ara_status ara_lookup(ara_ctx *c, const ara_layer *L, const int32_t *
     double *dg = g, *dout = o;
     if (mem == ARA_MEM_HOST) {
         int32_t *ti = nullptr;
-        s = dev_alloc(c, &ti, size_t(n) * 4, "lookup ids");
-        if (s == ARA_OK) s = dev_alloc(c, &dg, size_t(n) * 8, "lookup gross");
-        if (s == ARA_OK) s = dev_alloc(c, &dout, size_t(n) * 8, "lookup occ");
+        s = dev_alloc(c, &ti, size_t(n) * 4, "lookup ids", kSharedBlock);
+        if (s == ARA_OK) s = dev_alloc(c, &dg, size_t(n) * 8, "lookup gross", kSharedBlock);
+        if (s == ARA_OK) s = dev_alloc(c, &dout, size_t(n) * 8, "lookup occ", kSharedBlock);
         if (s == ARA_OK) {
             hipError_t e = hipMemcpy(ti, ids, size_t(n) * 4, hipMemcpyHostToDevice);
             if (e != hipSuccess) s = hip_fail(c, e, "lookup upload");
@@ -1389,7 +1399,7 @@ static ara_status workspace_for(ara_ctx *c, int64_t n, void *ws, size_t ws_bytes
         if (ws_bytes < need) return fail(c, ARA_E_INVALID_ARG, "workspace %zu bytes < %zu needed", ws_bytes, need);
         return ARA_OK;
     }
-    ara_status s = dev_alloc(c, use, need, "sort workspace");
+    ara_status s = dev_alloc(c, use, need, "sort workspace", kSharedBlock);
     *owned = s == ARA_OK;
     return s;
 }
@@ -1526,7 +1536,7 @@ extern "C" ara_status ara_risk_measures(ara_ctx *c, const double *ylt, int64_t n
     const double *dy = ylt;
     double *tmp = nullptr;
     if (mem == ARA_MEM_HOST) {
-        s = dev_alloc(c, &tmp, size_t(n) * 8, "ylt upload");
+        s = dev_alloc(c, &tmp, size_t(n) * 8, "ylt upload", kSharedBlock);
         if (s != ARA_OK) return s;
         hipError_t e = hipMemcpy(tmp, ylt, size_t(n) * 8, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
