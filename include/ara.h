@@ -116,13 +116,17 @@ typedef enum ara_option {
                                    3 (with at most 64 bins and fewer than 2^31 occurrences; 4 when
                                    a bin holds 2^24 occurrences or more): a quarter less memory for
                                    the run starts, about 2% more time in the tiled kernel          */
-    ARA_OPT_KERNEL_TIMING = 8   /* n in 1..4096: ara_analyze times its trial kernel with a pair of
+    ARA_OPT_KERNEL_TIMING = 8,  /* n in 1..4096: ara_analyze times its trial kernel with a pair of
                                    HIP events, the pairs of the last n calls kept in a ring (for
                                    the tiled kernel, events attached to its launch: the start of
                                    its first dispatch and the end of its last; for the others,
                                    recorded on the stream just around the launches); setting the
                                    option waits for the stream and starts a new ring.
                                    ara_kernel_ms reads it.  0 (default): no timing             */
+    ARA_OPT_KEPT_BYTES = 9      /* most device memory of released handles that the context keeps for
+                                   the next ones: 0 .. 2^32 (default 2^32; 0: none).  What is kept
+                                   beyond it goes back at once, all of it when the context is
+                                   destroyed or an allocation of any context on the device fails   */
 } ara_option;
 
 typedef struct ara_ctx ara_ctx;

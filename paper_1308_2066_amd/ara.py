@@ -62,6 +62,7 @@ ARA_OPT_TRIAL_MODE = 5
 ARA_OPT_YET_BINNING = 6
 ARA_OPT_YET_RUN_BYTES = 7
 ARA_OPT_KERNEL_TIMING = 8
+ARA_OPT_KEPT_BYTES = 9
 
 ARA_BUILD_TABLES = 1
 

@@ -48,8 +48,10 @@ struct ara_ctx {
     };
     std::vector<Scratch> tiled_ws;
     std::map<void *, size_t> blocks;                    // device memory of live handles: see dev_alloc
-    std::vector<std::pair<void *, size_t>> kept;        // blocks given back, oldest first
+    std::vector<std::pair<void *, size_t>> kept;        // blocks given back, oldest first (g_blocks_mu)
     size_t kept_bytes = 0;
+    size_t keep_limit = size_t(4) << 30;                // ARA_OPT_KEPT_BYTES
+    ara_ctx *next = nullptr;         // the process's contexts (g_blocks_mu)
     int live = 0;                    // handles alive on this context
     std::string msg;
 };
@@ -173,13 +175,16 @@ static ara_status sync_and_check(ara_ctx *c, bool *wide = nullptr, bool copied =
 }
 
 // Device memory of the context's handles.  A block that a handle gives back is kept for
-// the next one, up to kKeepBytes in all: mapping and unmapping device memory takes far
+// the next one, up to keep_limit in all: mapping and unmapping device memory takes far
 // longer than the kernels that use it (10 ms of an 11 ms ingest of 2x10^8 occurrences that
-// replaced a YET of the same size).  The oldest blocks beyond that are returned, all of
-// them when an allocation fails and when the context is destroyed.  A block is kept only
+// replaced a YET of the same size).  The oldest blocks beyond that are returned, all of them
+// when the option is set to 0 and when the context is destroyed, and those of every context on
+// the device when an allocation of any of them fails.  A block is kept only
 // once every stream of the device has finished, as hipFree would wait for, so a reused one
 // is idle whatever streams its last user ran on.
-constexpr size_t kKeepBytes = size_t(4) << 30;
+constexpr size_t kKeepBytes = size_t(4) << 30;   // default, and the largest block kept
+static std::mutex g_blocks_mu;                   // every context's `kept` and `next`
+static ara_ctx *g_contexts = nullptr;
 
 // Whether a block's size varies a little from one handle to the next (a YET's arrays, staging):
 // then sizes of a MiB and more go in sixteen steps per power of two, so that nearly equal
@@ -194,6 +199,7 @@ static size_t block_size(size_t bytes, BlockFit fit) {
     return shared <= kKeepBytes ? shared : exact;
 }
 
+// The oldest kept blocks beyond `keep` bytes go back (with g_blocks_mu held).
 static void blocks_return(ara_ctx *c, size_t keep) {
     size_t n = 0;
     while (n < c->kept.size() && c->kept_bytes > keep) {
@@ -204,35 +210,46 @@ static void blocks_return(ara_ctx *c, size_t keep) {
     c->kept.erase(c->kept.begin(), c->kept.begin() + ptrdiff_t(n));
 }
 
+// hipMalloc; if it fails, once more after what the device's contexts keep has gone back.
+static hipError_t device_malloc(ara_ctx *c, void **q, size_t bytes) {
+    hipError_t e = hipMalloc(q, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    bool more = false;
+    {
+        std::lock_guard<std::mutex> lock(g_blocks_mu);
+        for (ara_ctx *x = g_contexts; x; x = x->next)
+            if (x->device == c->device && !x->kept.empty()) blocks_return(x, 0), more = true;
+    }
+    if (!more) return e;
+    e = hipMalloc(q, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 template <typename T>
 static ara_status dev_alloc(ara_ctx *c, T **p, size_t bytes, const char *what, BlockFit fit = kExactBlock) {
     *p = nullptr;
     size_t take = block_size(bytes, fit);
     void *q = nullptr;
-    for (size_t i = c->kept.size(); i-- > 0;)
-        if (c->kept[i].second == take) {
-            q = c->kept[i].first;
-            c->kept.erase(c->kept.begin() + ptrdiff_t(i));
-            c->kept_bytes -= take;
-            break;
-        }
+    {
+        std::lock_guard<std::mutex> lock(g_blocks_mu);
+        for (size_t i = c->kept.size(); i-- > 0;)
+            if (c->kept[i].second == take) {
+                q = c->kept[i].first;
+                c->kept.erase(c->kept.begin() + ptrdiff_t(i));
+                c->kept_bytes -= take;
+                break;
+            }
+    }
     if (!q) {
-        hipError_t e = hipMalloc(&q, take);
-        if (e != hipSuccess && !c->kept.empty()) {
-            (void)hipGetLastError();
-            blocks_return(c, 0);
-            e = hipMalloc(&q, take);
-        }
+        hipError_t e = device_malloc(c, &q, take);
         const size_t exact = block_size(bytes, kExactBlock);
         if (e != hipSuccess && exact < take) {   // what was asked for may still fit
-            (void)hipGetLastError();
             take = exact;
-            e = hipMalloc(&q, take);
+            e = device_malloc(c, &q, take);
         }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return hip_fail(c, e, what);
-        }
+        if (e != hipSuccess) return hip_fail(c, e, what);
     }
     try {
         c->blocks[q] = take;
@@ -250,12 +267,13 @@ static void dev_free(ara_ctx *c, const void *p) {
     const auto it = c->blocks.find(q);
     const size_t bytes = it == c->blocks.end() ? 0 : it->second;
     if (it != c->blocks.end()) c->blocks.erase(it);
-    if (bytes == 0 || bytes > kKeepBytes || hipDeviceSynchronize() != hipSuccess) {
+    if (bytes == 0 || bytes > c->keep_limit || hipDeviceSynchronize() != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(q);
         return;
     }
-    blocks_return(c, kKeepBytes - bytes);
+    std::lock_guard<std::mutex> lock(g_blocks_mu);
+    blocks_return(c, c->keep_limit - bytes);
     try {
         c->kept.emplace_back(q, bytes);
         c->kept_bytes += bytes;
@@ -490,6 +508,11 @@ extern "C" ara_status ara_ctx_create(int device, void *hip_stream, ara_ctx **out
         delete c;
         return ARA_E_DEVICE;
     }
+    {
+        std::lock_guard<std::mutex> lock(g_blocks_mu);
+        c->next = g_contexts;
+        g_contexts = c;
+    }
     *out = c;
     return ARA_OK;
 }
@@ -501,7 +524,13 @@ extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
     (void)hipStreamSynchronize(c->stream);
     (void)hipFree(c->d_err);   // with d_out
     for (auto &w : c->tiled_ws) (void)hipFree(w.p);
-    blocks_return(c, 0);
+    {
+        std::lock_guard<std::mutex> lock(g_blocks_mu);
+        ara_ctx **at = &g_contexts;
+        while (*at != c) at = &(*at)->next;
+        *at = c->next;
+        blocks_return(c, 0);
+    }
     for (hipEvent_t ev : c->k_ev) (void)hipEventDestroy(ev);
     if (c->h_err) (void)hipHostFree(c->h_err);   // with h_out
     delete c;
@@ -545,6 +574,14 @@ extern "C" ara_status ara_set_option(ara_ctx *c, int option, int64_t v) {
         if (v != 3 && v != 4) return fail(c, ARA_E_INVALID_ARG, "bad run start size %lld", (long long)v);
         c->yet_run_bytes = int(v);
         return ARA_OK;
+    case ARA_OPT_KEPT_BYTES: {
+        if (v < 0 || v > int64_t(kKeepBytes)) return fail(c, ARA_E_INVALID_ARG, "bad kept bytes %lld", (long long)v);
+        HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
+        std::lock_guard<std::mutex> lock(g_blocks_mu);
+        c->keep_limit = size_t(v);
+        blocks_return(c, c->keep_limit);
+        return ARA_OK;
+    }
     case ARA_OPT_KERNEL_TIMING: {
         if (v < 0 || v > kMaxTimedLaunches) return fail(c, ARA_E_INVALID_ARG, "bad timing ring size %lld", (long long)v);
         HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
@@ -2608,7 +2645,8 @@ extern "C" ara_status ara_server_create(ara_ctx *c, const ara_yet *y, ara_elt *c
     if (budget == 0) {
         size_t fr = 0, tot = 0;
         HIP_OR_RETURN(c, hipMemGetInfo(&fr, &tot), "memory info");
-        budget = int64_t(fr / 4);
+        std::lock_guard<std::mutex> lock(g_blocks_mu);
+        budget = int64_t((fr + c->kept_bytes) / 4);   // kept blocks are as good as free
     }
     const int64_t slot_bytes = server_slot_bytes(y->catalog, n_pool);
     const int32_t per_lane = int32_t(std::max<int64_t>(1, std::min<int64_t>(cfg->max_batch, budget / 2 / (2 * slot_bytes))));
