@@ -311,8 +311,8 @@ ara_status ara_layer_release(ara_layer *layer);
  * value 0 at 0, so the differences telescope.  ylt has trial_end - trial_begin
  * doubles in memory `ylt_mem`.  The YET and the layer must share a catalog size.
  * Asynchronous for ARA_MEM_DEVICE output; blocking for ARA_MEM_HOST.  Launches of the
- * tiled placement over few trials keep a workspace of at most 128 MB per stream they run on
- * (up to four streams) until the context is destroyed.  With the tiled placement a trial's bits
+ * tiled placement over few trials keep a workspace of at most 128 MB until the context is
+ * destroyed, launches that overlap on several streams up to four.  With the tiled placement a trial's bits
  * depend on its occurrences, the layer and the catalog size alone: a YET cut into shards gives the
  * whole YET's.  Trials with no events get 0.  Kernel-detected errors: ARA_E_EVENT_ID_RANGE, ARA_E_BAD_OFFSETS.
  * Errors: ARA_E_INVALID_ARG, ARA_E_UNSUPPORTED (forced placement too small), ARA_E_DEVICE. */

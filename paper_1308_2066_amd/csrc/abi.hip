@@ -39,14 +39,21 @@ struct ara_ctx {
     std::vector<hipEvent_t> k_ev;    // ARA_OPT_KERNEL_TIMING: a ring of (start, stop) event pairs
     int64_t k_count = 0;             // trial kernels timed since the option was set
     std::map<std::string, std::pair<int64_t, bool>> tuned;   // batch shape -> (events per item, interleave)
-    // workspaces of split tiled launches, one per stream they ran on (launches on one stream
-    // follow each other; on two streams they may overlap): see tiled_scratch
+    // workspaces of split tiled launches (tiled_scratch): the stream of the last launch in each,
+    // and what is known of its end
+    enum Busy { kIdle, kRunning, kRecorded };   // has ended; may not have; `done` is recorded after it
     struct Scratch {
-        hipStream_t stream;
         void *p;
         size_t bytes;
+        hipStream_t stream;
+        hipEvent_t done;
+        Busy busy;
     };
     std::vector<Scratch> tiled_ws;
+    bool streams = false;            // the stream has been changed
+    std::vector<void *> tiled_old;   // smaller ones, replaced: launches may still use them
+    size_t tiled_need = 0;           // the most that a whole YET of this context takes
+    bool tiled_fixed = false;        // a server lane's: neither more nor larger ones
     std::map<void *, size_t> blocks;                    // device memory of live handles: see dev_alloc
     std::vector<std::pair<void *, size_t>> kept;        // blocks given back, oldest first (g_blocks_mu)
     size_t kept_bytes = 0;
@@ -152,6 +159,8 @@ static ara_status err_bits_status(uint32_t bits) {
     return ARA_OK;
 }
 
+static void scratch_waited(ara_ctx *c);
+
 // Waits for the context stream, then reads and clears the device error word.  With
 // `wide`, the ERR_BIN_WIDE bit (not an input error) is returned there.  `copied`: the
 // caller has already queued the error word's copy to h_err.
@@ -160,6 +169,7 @@ static ara_status sync_and_check(ara_ctx *c, bool *wide = nullptr, bool copied =
         HIP_OR_RETURN(c, hipMemcpyAsync(c->h_err, c->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream),
                       "read error word");
     HIP_OR_RETURN(c, hipStreamSynchronize(c->stream), "stream synchronize");
+    scratch_waited(c);
     uint32_t bits = *c->h_err;
     if (bits) {
         HIP_OR_RETURN(c, launch_fill_u32(c->d_err, 1, 0u, c->stream), "clear error word");
@@ -210,9 +220,18 @@ static void blocks_return(ara_ctx *c, size_t keep) {
     c->kept.erase(c->kept.begin(), c->kept.begin() + ptrdiff_t(n));
 }
 
-// hipMalloc; if it fails, once more after what the device's contexts keep has gone back.
+// hipMalloc without disturbing a stream capture (in global mode) of another thread.
+static hipError_t raw_malloc(void **q, size_t bytes) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool changed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t e = hipMalloc(q, bytes);
+    if (changed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return e;
+}
+
+// Device memory; if there is none, once more after what the device's contexts keep has gone back.
 static hipError_t device_malloc(ara_ctx *c, void **q, size_t bytes) {
-    hipError_t e = hipMalloc(q, bytes);
+    hipError_t e = raw_malloc(q, bytes);
     if (e == hipSuccess) return e;
     (void)hipGetLastError();
     bool more = false;
@@ -222,7 +241,7 @@ static hipError_t device_malloc(ara_ctx *c, void **q, size_t bytes) {
             if (x->device == c->device && !x->kept.empty()) blocks_return(x, 0), more = true;
     }
     if (!more) return e;
-    e = hipMalloc(q, bytes);
+    e = raw_malloc(q, bytes);
     if (e != hipSuccess) (void)hipGetLastError();
     return e;
 }
@@ -517,13 +536,19 @@ extern "C" ara_status ara_ctx_create(int device, void *hip_stream, ara_ctx **out
     return ARA_OK;
 }
 
+static void tiled_trim(ara_ctx *c);
+
 extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
     if (!c) return ARA_E_INVALID_ARG;
     if (c->live > 0) return fail(c, ARA_E_BUSY, "%d handles still alive on this context", c->live);
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     (void)hipFree(c->d_err);   // with d_out
-    for (auto &w : c->tiled_ws) (void)hipFree(w.p);
+    tiled_trim(c);
+    for (auto &w : c->tiled_ws) {
+        (void)hipFree(w.p);
+        (void)hipEventDestroy(w.done);
+    }
     {
         std::lock_guard<std::mutex> lock(g_blocks_mu);
         ara_ctx **at = &g_contexts;
@@ -539,6 +564,7 @@ extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
 
 extern "C" ara_status ara_ctx_set_stream(ara_ctx *c, void *hip_stream) {
     if (!c) return ARA_E_INVALID_ARG;
+    c->streams = c->streams || c->stream != reinterpret_cast<hipStream_t>(hip_stream);
     c->stream = reinterpret_cast<hipStream_t>(hip_stream);
     return ARA_OK;
 }
@@ -628,6 +654,10 @@ extern "C" ara_status ara_sync(ara_ctx *c) {
     HIP_OR_RETURN(c, hipSetDevice(c->device), "set device");
     return sync_and_check(c);
 }
+
+// Workspace of a split tiled launch over n trials, and the most that one may take.
+static size_t tiled_split_bytes(int64_t n, int32_t groups) { return size_t((n + 2) & ~int64_t(1)) * size_t(groups) * 8; }
+constexpr size_t kTiledWsBytes = size_t(128) << 20;
 
 // ------------------------------------------------------------------ YET
 static void yet_free_binned(ara_yet *y) {
@@ -727,6 +757,8 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
         y->n_bins = nb;
         y->group_bins = tiled_group_bins(nb);
         y->n_groups = (nb + y->group_bins - 1) / y->group_bins;
+        if (tiled_split(n, nb, c->n_cu, false).chunks > 0)
+            c->tiled_need = std::max(c->tiled_need, std::min(kTiledWsBytes, tiled_split_bytes(n, y->n_groups)));
         y->copy_bytes = int64_t(ids16_bytes) + int64_t(nb + 1) * 8 + int64_t(nb) * y->stride * (y->boff24 ? 3 : 4) +
                         (y->boff24 ? 16 : 0);
         return ARA_OK;
@@ -817,6 +849,7 @@ extern "C" ara_status ara_yet_release(ara_yet *y) {
     }
     dev_free(y->ctx, y->ids24);
     yet_free_binned(y);
+    tiled_trim(y->ctx);
     y->ctx->live--;
     delete y;
     return ARA_OK;
@@ -1163,41 +1196,83 @@ static void set_split(TiledArgs &a, void *p, const TiledSplit &how) {
     a.span_groups = how.span_groups;
     a.per_wg = (n + how.chunks - 1) / how.chunks;
 }
-static size_t tiled_split_bytes(int64_t n, int32_t groups) { return size_t((n + 2) & ~int64_t(1)) * size_t(groups) * 8; }
 
-// Workspace of `bytes` for a split tiled launch on the context's stream, or null: while the
+// A workspace of `bytes` for a split tiled launch on the context's stream: the one its last
+// launch was in (launches on a stream follow each other, and hipStreamDestroy waits for them),
+// else one whose last launch has ended, else a new one, up to kTiledWsCount.  Whether it has
+// ended is known once the stream has been waited for and, on a context that has had several
+// streams, from an event after each launch (6 us each, so not before).  Null while the
 // stream is being captured (a graph may be replayed on any stream, at any time), for more
-// than kTiledWsBytes, for more than kTiledWsStreams streams, or without memory.  The
-// launch then runs whole, with the same bits.
-constexpr size_t kTiledWsBytes = size_t(128) << 20;
-constexpr size_t kTiledWsStreams = 4;
+// than kTiledWsBytes, with all of them in use on other streams, or without memory: the
+// launch then runs whole, with the same bits.  Nothing here waits: a workspace that is too
+// small is replaced and freed later (tiled_trim).
+constexpr size_t kTiledWsCount = 4;
 
-static void *tiled_scratch(ara_ctx *c, size_t bytes) {
+static bool scratch_idle(ara_ctx::Scratch &w) {
+    if (w.busy == ara_ctx::kRecorded) {
+        if (hipEventQuery(w.done) == hipSuccess) w.busy = ara_ctx::kIdle;
+        else (void)hipGetLastError();
+    }
+    return w.busy == ara_ctx::kIdle;
+}
+
+static ara_ctx::Scratch *tiled_scratch(ara_ctx *c, size_t bytes) {
     if (bytes > kTiledWsBytes) return nullptr;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         return nullptr;
     }
-    size_t i = 0;
-    while (i < c->tiled_ws.size() && c->tiled_ws[i].stream != c->stream) ++i;
-    if (i < c->tiled_ws.size() && c->tiled_ws[i].bytes >= bytes) return c->tiled_ws[i].p;
-    if (i == c->tiled_ws.size() && i >= kTiledWsStreams) return nullptr;
-    void *p = nullptr;
-    const size_t take = std::max(bytes, size_t(4) << 20);
-    if (hipMalloc(&p, take) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
+    ara_ctx::Scratch *w = nullptr;
+    if (c->stream != hipStreamPerThread)   // (another stream in each thread)
+        for (auto &x : c->tiled_ws)
+            if (x.stream == c->stream) w = &x;
+    for (size_t i = 0; !w && i < c->tiled_ws.size(); ++i)
+        if (scratch_idle(c->tiled_ws[i])) w = &c->tiled_ws[i];
+    if (!w || w->bytes < bytes) {
+        if (c->tiled_fixed || (!w && c->tiled_ws.size() >= kTiledWsCount)) return nullptr;
+        const size_t take =
+            std::min(kTiledWsBytes, std::max({bytes, c->tiled_need, w ? 2 * w->bytes : 0, size_t(4) << 20}));
+        void *p = nullptr;
+        try {
+            c->tiled_old.reserve(c->tiled_old.size() + 1);
+            c->tiled_ws.reserve(kTiledWsCount);
+        } catch (...) {
+            return nullptr;
+        }
+        if (device_malloc(c, &p, take) != hipSuccess) return nullptr;
+        if (w) {
+            c->tiled_old.push_back(w->p);
+        } else {
+            hipEvent_t ev = nullptr;
+            if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                (void)hipFree(p);
+                return nullptr;
+            }
+            c->tiled_ws.push_back({});
+            w = &c->tiled_ws.back();
+            w->done = ev;
+        }
+        w->p = p;
+        w->bytes = take;
     }
-    if (i == c->tiled_ws.size()) {
-        c->tiled_ws.push_back({c->stream, p, take});
-    } else {
-        (void)hipStreamSynchronize(c->stream);   // earlier launches may still use the smaller one
-        (void)hipFree(c->tiled_ws[i].p);
-        c->tiled_ws[i].p = p;
-        c->tiled_ws[i].bytes = take;
-    }
-    return p;
+    w->stream = c->stream;
+    w->busy = ara_ctx::kRunning;
+    return w;
+}
+
+// The context's stream has been waited for.
+static void scratch_waited(ara_ctx *c) {
+    if (c->stream == hipStreamPerThread) return;
+    for (auto &w : c->tiled_ws)
+        if (w.stream == c->stream) w.busy = ara_ctx::kIdle;
+}
+
+// Frees replaced workspaces (waits for the device: in calls that do anyway).
+static void tiled_trim(ara_ctx *c) {
+    for (void *p : c->tiled_old) (void)hipFree(p);
+    c->tiled_old.clear();
 }
 
 // The tiled kernel over trials [t0, t1) on the context's stream, split over bin groups
@@ -1206,11 +1281,14 @@ static hipError_t run_tiled(ara_ctx *c, const ara_yet *y, const ara_layer *L, in
                             bool occ_max, hipEvent_t start, hipEvent_t stop) {
     TiledArgs a = tiled_args(y, L, t0, t1, out, grid);
     const TiledSplit how = tiled_split(t1 - t0, y->n_bins, c->n_cu, occ_max);
-    if (how.chunks > 0) {
-        void *p = tiled_scratch(c, tiled_split_bytes(t1 - t0, how.n_groups));
-        if (p) set_split(a, p, how);
+    ara_ctx::Scratch *w = how.chunks > 0 ? tiled_scratch(c, tiled_split_bytes(t1 - t0, how.n_groups)) : nullptr;
+    if (w) set_split(a, w->p, how);
+    hipError_t e = launch_trial_tiled(a, grid, c->stream, occ_max, start, stop);
+    if (e == hipSuccess && w && (c->streams || c->stream == hipStreamPerThread)) {
+        e = hipEventRecord(w->done, c->stream);
+        if (e == hipSuccess) w->busy = ara_ctx::kRecorded;
     }
-    return launch_trial_tiled(a, grid, c->stream, occ_max, start, stop);
+    return e;
 }
 
 static ara_status check_analysis(ara_ctx *c, const ara_yet *y, const ara_layer *L, int64_t t0, int64_t t1) {
