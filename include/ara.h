@@ -478,8 +478,9 @@ ara_status ara_batch_release(ara_batch *batch);
  *
  * Admission by memory: memory_budget bytes (0 = a quarter of free HBM) hold the slots'
  * tables (2 lanes x slots_per_lane x slot_bytes, at most half of the budget, and at
- * most max_batch slots per lane) and an arena for the YLTs of admitted requests (the
- * rest).  A request is admitted when its lane has a free slot and its own YLT (8 bytes
+ * most max_batch slots per lane), over a YET with a binned copy each lane's workspace of
+ * split tiled launches (at most 128 MB, where the rest still holds two YLTs of every trial)
+ * and an arena for the YLTs of admitted requests (the rest).  A request is admitted when its lane has a free slot and its own YLT (8 bytes
  * per trial of its range) fits in the arena beside those of the requests in flight;
  * otherwise it, and every request after it, waits for an iteration to complete.
  *
@@ -492,7 +493,7 @@ typedef struct ara_server ara_server;
 
 typedef struct ara_server_config {
     int32_t max_batch;              /* slots per lane (requests per iteration), >= 1            */
-    int64_t memory_budget;          /* bytes for slots' tables + the YLT arena; 0 = 1/4 of free HBM */
+    int64_t memory_budget;          /* bytes for slots' tables, workspaces and YLTs; 0 = 1/4 of free HBM */
     int32_t n_rp;                   /* return periods of every request, 1..16                   */
     const double *return_periods;   /* n_rp values >= 1 (copied)                                */
 } ara_server_config;

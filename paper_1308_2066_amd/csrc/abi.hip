@@ -2385,6 +2385,7 @@ struct ServerLane {
     size_t stage_bytes = 0;
     int32_t mode_off[kBatchModes] = {}, mode_cnt[kBatchModes] = {};
     double *h_res = nullptr;          // pinned: [slot][2 * n_rp], written by the risk kernels
+    void *split = nullptr;            // workspace of split tiled launches (in pc's list)
     unsigned char *ws = nullptr;      // workspaces of the risk measures of long YLTs
     size_t ws_bytes = 0;
     std::vector<RiskJob> risks;       // the iteration's risk measures, and their launches
@@ -2406,6 +2407,7 @@ struct ara_server {
     YltRing ring;
     int32_t slots_per_lane = 0;
     int64_t slot_bytes = 0;
+    size_t split_bytes = 0;           // a lane's workspace of split tiled launches (0: none)
     std::thread worker;
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
@@ -2649,6 +2651,8 @@ static void server_free(ara_server *sv) {
             if (L) ara_layer_release(L);
         dev_free(sv->ctx, ln.d_stage);
         dev_free(sv->ctx, ln.ws);
+        dev_free(sv->ctx, ln.split);
+        if (ln.pc) ln.pc->tiled_ws.clear();   // ln.split, no event
         if (ln.h_stage) (void)hipHostFree(ln.h_stage);
         if (ln.h_res) (void)hipHostFree(ln.h_res);
         if (ln.done) (void)hipEventDestroy(ln.done);
@@ -2681,6 +2685,13 @@ static ara_status server_lane_create(ara_ctx *c, ara_server *sv, ServerLane &ln,
     ln.pc->grid_per_cu = c->grid_per_cu;
     ln.pc->trial_mode = c->trial_mode;
     ln.pc->yet_packing = c->yet_packing;
+    // the worker allocates nothing: tiled requests that need more, or find none, run whole
+    ln.pc->tiled_fixed = true;
+    if (sv->split_bytes > 0) {
+        if (dev_alloc(c, &ln.split, sv->split_bytes, "server tiled workspace") == ARA_OK)
+            ln.pc->tiled_ws.push_back({ln.split, sv->split_bytes, ln.stream, nullptr, ara_ctx::kRunning});
+        else c->msg.clear();
+    }
     const ara_layer_terms none{0.0, INFINITY, 0.0, INFINITY};
     ln.slots.assign(size_t(ns), nullptr);
     for (int32_t i = 0; i < ns && s == ARA_OK; ++i)
@@ -2728,7 +2739,13 @@ extern "C" ara_status ara_server_create(ara_ctx *c, const ara_yet *y, ara_elt *c
     }
     const int64_t slot_bytes = server_slot_bytes(y->catalog, n_pool);
     const int32_t per_lane = int32_t(std::max<int64_t>(1, std::min<int64_t>(cfg->max_batch, budget / 2 / (2 * slot_bytes))));
-    const int64_t arena = (budget - 2 * int64_t(per_lane) * slot_bytes) / 8;
+    int64_t arena = (budget - 2 * int64_t(per_lane) * slot_bytes) / 8;
+    // the lanes' workspaces of split tiled launches come out of the arena where it still holds
+    // the YLTs of two requests of every trial
+    const int64_t split =
+        y->ids16 ? int64_t(std::min(kTiledWsBytes, tiled_split_bytes(y->n_trials, y->n_groups)) + 255) / 256 * 256 : 0;
+    const bool splits = split > 0 && arena - split / 4 >= 2 * y->n_trials;
+    if (splits) arena -= split / 4;
     if (arena < 1)
         return fail(c, ARA_E_OOM, "server: two slots need %lld bytes, budget %lld", (long long)(2 * slot_bytes),
                     (long long)budget);
@@ -2740,6 +2757,7 @@ extern "C" ara_status ara_server_create(ara_ctx *c, const ara_yet *y, ara_elt *c
     sv->rps.assign(cfg->return_periods, cfg->return_periods + cfg->n_rp);
     sv->slots_per_lane = per_lane;
     sv->slot_bytes = slot_bytes;
+    sv->split_bytes = splits ? size_t(split) : 0;
     sv->ring.cap = arena;
     ara_status s = dev_alloc(c, &sv->arena, size_t(arena) * 8, "server ylt arena");
     for (int k = 0; k < 2 && s == ARA_OK; ++k) s = server_lane_create(c, sv, sv->lanes[k], n_pool, cfg);
