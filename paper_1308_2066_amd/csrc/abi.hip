@@ -1853,6 +1853,22 @@ static ara_status batch_tiled_items(ara_batch *b) {
         b->split.push_back(int32_t(k));
         b->split_max = std::max(b->split_max, a.t_end - a.t_begin);
     }
+    ara_status s = ARA_OK;
+    if (used > 0) {
+        s = dev_alloc(c, &b->d_part, used, "batch tiled sums");
+        if (s == ARA_OK) s = dev_alloc(c, &b->d_split, b->split.size() * 4, "batch tiled split jobs");
+        if (s == ARA_E_OOM) {   // whole passes need no sums
+            c->msg.clear();
+            dev_free(c, b->d_part);
+            b->d_part = nullptr;
+            b->split.clear();
+            b->split_max = 0;
+            at.assign(at.size(), SIZE_MAX);
+            used = 0;
+        } else if (s != ARA_OK) {
+            return s;
+        }
+    }
     const auto costlier = [](const std::pair<double, TiledItem> &x, const std::pair<double, TiledItem> &y) {
         return x.first > y.first;
     };
@@ -1875,10 +1891,6 @@ static ara_status batch_tiled_items(ara_batch *b) {
             items.emplace_back(p.first * double(g1 - g) / double(groups), it);
         }
     }
-    ara_status s = ARA_OK;
-    if (used > 0) s = dev_alloc(c, &b->d_part, used, "batch tiled sums");
-    if (s == ARA_OK && used > 0) s = dev_alloc(c, &b->d_split, b->split.size() * 4, "batch tiled split jobs");
-    if (s != ARA_OK) return s;
     for (size_t k = 0; k < b->tjobs.size(); ++k)
         if (at[k] != SIZE_MAX) set_split(b->tjobs[k], static_cast<char *>(b->d_part) + at[k],
                                          TiledSplit{1, b->tjobs[k].group_bins, b->tjobs[k].n_groups, 1});
