@@ -2154,17 +2154,26 @@ extern "C" ara_status ara_tune_cache_load(ara_ctx *c, const char *path) {
     FILE *f = std::fopen(path, "r");
     if (!f) return fail(c, ARA_E_INVALID_ARG, "tuning cache %s: cannot open", path);
     std::map<std::string, std::pair<int64_t, bool>> got;
-    char line[8192];
+    std::string line;   // as long as the batch shape makes it (some 20 characters a job)
     ara_status s = ARA_OK;
-    while (std::fgets(line, sizeof line, f)) {
+    const auto next_line = [&] {
+        char part[4096];
+        line.clear();
+        while (std::fgets(part, sizeof part, f)) {
+            line += part;
+            if (line.back() == '\n') break;
+        }
+        return !line.empty();
+    };
+    while (next_line()) {
         if (line[0] == '#' || line[0] == '\n') continue;
         long long ev = 0;
         int inter = 0, used = 0;
-        if (std::sscanf(line, "%lld %d %n", &ev, &inter, &used) != 2 || ev < 1 || (inter != 0 && inter != 1)) {
+        if (std::sscanf(line.c_str(), "%lld %d %n", &ev, &inter, &used) != 2 || ev < 1 || (inter != 0 && inter != 1)) {
             s = fail(c, ARA_E_INVALID_ARG, "tuning cache %s: bad line", path);
             break;
         }
-        std::string key(line + used);
+        std::string key(line, size_t(used));
         while (!key.empty() && (key.back() == '\n' || key.back() == '\r')) key.pop_back();
         if (key.empty()) {
             s = fail(c, ARA_E_INVALID_ARG, "tuning cache %s: line without a shape", path);
