@@ -64,30 +64,15 @@ typedef const __attribute__((address_space(4))) int64_t *const_i64_ptr;
 __device__ __forceinline__ int64_t offset_at(const int64_t *offs, int64_t t) { return ((const_i64_ptr)offs)[t]; }
 
 // Issue the four 16-byte ID loads of a segment starting at event sbase, `avail`
-// events readable (0..kSeg; bytes past them are outside the buffer record and read
-// as 0 without a memory access).  Always issued, so the number of outstanding
-// vector-memory operations is the same on every path.
+// events readable (0..kSeg).  A raw buffer load is checked dword by dword: the words of a
+// 16-byte load that lie past the record read as 0 without a memory access, those before its
+// end as they are (every kernel here that reads up to an unaligned end relies on it).
+// Always issued, so the number of outstanding vector-memory operations is the same on every path.
 __device__ __forceinline__ void load_ids(const int32_t *ids, int64_t sbase, int avail, int lane, u32x4 (&r)[kNch]) {
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(ids + sbase), 0, avail * 4, kBufWord3);
 #pragma unroll
     for (int k = 0; k < kNch; ++k)
         r[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, k * kChunk * 4 + lane * 16, 0, kNonTemporal);
-    if (avail & 3) {
-        // The YET ends inside one lane's 16-byte group: fetch that group's IDs one
-        // dword at a time so a partially covered 16-byte load cannot drop them.
-        const int g = (avail & ~3) - lane * 4;
-#pragma unroll
-        for (int k = 0; k < kNch; ++k) {
-            if (g == k * kChunk) {
-                const int e0 = k * kChunk + lane * 4;
-                for (int j = 0; j < 4; ++j) {
-                    uint32_t v = 0;
-                    if (e0 + j < avail) v = __builtin_amdgcn_raw_buffer_load_b32(rs, (e0 + j) * 4, 0, 0);
-                    r[k][j] = v;
-                }
-            }
-        }
-    }
 }
 
 // Packed IDs (3 bytes each, 12-byte groups of 4 events, zero-padded to whole groups):
