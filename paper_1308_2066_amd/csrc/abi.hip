@@ -24,10 +24,9 @@ struct ara_ctx {
     hipStream_t stream = nullptr;
     int n_cu = 0;
     int lds_max = 0;
-    uint32_t *d_err = nullptr;       // device error bits (word 0), then d_out
-    double *d_out = nullptr;         // small device result staging
-    double *h_out = nullptr;         // pinned host mirror of d_out
-    uint32_t *h_err = nullptr;       // pinned host error word
+    uint32_t *d_err = nullptr;       // device error bits
+    uint32_t *h_err = nullptr;       // pinned: their copy, a count read back, the risk measures' open flag; then h_out
+    double *h_out = nullptr;         // pinned: results that kernels write to the host
     void *scratch = nullptr;         // device address of this device's `scratch` array
     int placement = ARA_PLACE_AUTO;
     int block_threads = 0;           // 0 = automatic
@@ -149,7 +148,7 @@ static ara_status hip_fail(ara_ctx *c, hipError_t e, const char *what) {
 static bool bad_retention(double r) { return !(r >= 0.0) || std::isinf(r); }
 static bool bad_limit(double l) { return !(l >= 0.0); }
 
-constexpr size_t kErrBytes = 16;   // the error word and spare words before the result staging
+constexpr size_t kErrBytes = 16;   // the error word and the words after it
 
 static ara_status err_bits_status(uint32_t bits) {
     if (bits & ERR_ID_RANGE) return ARA_E_EVENT_ID_RANGE;
@@ -163,7 +162,7 @@ static void scratch_waited(ara_ctx *c);
 
 // Waits for the context stream, then reads and clears the device error word.  With
 // `wide`, the ERR_BIN_WIDE bit (not an input error) is returned there.  `copied`: the
-// caller has already queued the error word's copy to h_err.
+// kernels waited for have written the error word to h_err themselves.
 static ara_status sync_and_check(ara_ctx *c, bool *wide = nullptr, bool copied = false) {
     if (!copied)
         HIP_OR_RETURN(c, hipMemcpyAsync(c->h_err, c->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream),
@@ -507,14 +506,10 @@ extern "C" ara_status ara_ctx_create(int device, void *hip_stream, ara_ctx **out
     e = prepare_trial_kernels();
     if (e == hipSuccess) e = prepare_ingest_kernels();
     if (e == hipSuccess) { step = "scratch address"; e = scratch_address(device, &c->scratch); }
-    // the error word (and a spare word) followed by the result staging, on the device and
-    // pinned on the host, so one copy brings back results and error bits together
-    const size_t blk = kErrBytes + kStageDoubles * sizeof(double);
-    if (e == hipSuccess) { step = "error word and result staging"; e = hipMalloc(&c->d_err, blk); }
-    if (e == hipSuccess) c->d_out = reinterpret_cast<double *>(reinterpret_cast<char *>(c->d_err) + kErrBytes);
+    if (e == hipSuccess) { step = "error word"; e = hipMalloc(&c->d_err, kErrBytes); }
     if (e == hipSuccess) {
-        step = "pinned error word and staging";
-        e = hipHostMalloc(reinterpret_cast<void **>(&c->h_err), blk, hipHostMallocDefault);
+        step = "pinned error word and results";
+        e = hipHostMalloc(reinterpret_cast<void **>(&c->h_err), kErrBytes + kStageDoubles * sizeof(double), hipHostMallocDefault);
     }
     if (e == hipSuccess) c->h_out = reinterpret_cast<double *>(reinterpret_cast<char *>(c->h_err) + kErrBytes);
     if (e == hipSuccess) { step = "clear error word"; e = launch_fill_u32(c->d_err, kErrBytes / 4, 0u, c->stream); }
@@ -543,7 +538,7 @@ extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
     if (c->live > 0) return fail(c, ARA_E_BUSY, "%d handles still alive on this context", c->live);
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    (void)hipFree(c->d_err);   // with d_out
+    (void)hipFree(c->d_err);
     tiled_trim(c);
     for (auto &w : c->tiled_ws) {
         (void)hipFree(w.p);

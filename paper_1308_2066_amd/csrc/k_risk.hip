@@ -48,7 +48,7 @@
 // another, and no fence writes an L2 back (one per workgroup cost 50 us a pass).
 #include <algorithm>
 
-#include "ara_internal.h"
+#include "order_keys.h"
 
 namespace ara {
 
@@ -65,18 +65,6 @@ constexpr uint32_t kFewKeys = 1024;    // a bin that one wave sorts out
 constexpr int kWaveKeys = int(kFewKeys) / 64;
 static_assert(kRiskGroup <= kRiskWaves, "one wave per rank");
 static_assert(kRiskTile == 8 * 256, "a tile is 8 losses for each of 256 slots");
-
-__device__ __forceinline__ uint64_t desc_key(double d) {
-    uint64_t u = __builtin_bit_cast(uint64_t, d + 0.0);   // -0.0 + 0.0 == +0.0
-    u = (u >> 63) ? ~u : (u | 0x8000000000000000ull);       // ascending order key
-    return ~u;                                             // descending
-}
-
-__device__ __forceinline__ double key_value(uint64_t k) {
-    uint64_t u = ~k;
-    u = (u >> 63) ? (u & 0x7FFFFFFFFFFFFFFFull) : ~u;
-    return __builtin_bit_cast(double, u);
-}
 
 constexpr uint64_t kZeroKey = 0x7FFFFFFFFFFFFFFFull;   // desc_key(0.0): keys above it are negative losses
 

@@ -20,7 +20,7 @@
 // wave ranks its keys by matching digits across lanes with 8 ballots; the tile's keys
 // are placed in LDS in output order first, so a store instruction writes runs of
 // consecutive output positions.
-#include "ara_internal.h"
+#include "order_keys.h"
 
 namespace ara {
 
@@ -31,18 +31,6 @@ constexpr int kWavesPerTile = kSortThreads / 64;            // 16
 constexpr int kWaveKeys = 64 * kSortPerThread;              // consecutive keys a wave owns
 constexpr int kPasses = 8;
 static_assert(kSortThreads >= 256 && kSortThreads % 64 == 0, "the first 256 threads take one digit each");
-
-__device__ __forceinline__ uint64_t desc_key(double d) {
-    uint64_t u = __builtin_bit_cast(uint64_t, d + 0.0);   // -0.0 + 0.0 == +0.0
-    u = (u >> 63) ? ~u : (u | 0x8000000000000000ull);       // ascending order key
-    return ~u;                                             // descending
-}
-
-__device__ __forceinline__ double key_value(uint64_t k) {
-    uint64_t u = ~k;
-    u = (u >> 63) ? (u & 0x7FFFFFFFFFFFFFFFull) : ~u;
-    return __builtin_bit_cast(double, u);
-}
 
 static inline int64_t sort_tiles(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
 

@@ -1,6 +1,6 @@
-// Trial kernel for catalogs whose occurrence filter fits in LDS: one persistent
-// workgroup per CU stages the filter and its waves walk the trials (device code in
-// trial_bitmap.h).
+// Trial kernel with the occurrence filter in LDS (folded for catalogs past 2^20 events): one
+// persistent workgroup per CU stages the filter and its waves walk the trials (device code
+// in trial_bitmap.h).
 #include "trial_bitmap.h"
 
 namespace ara {

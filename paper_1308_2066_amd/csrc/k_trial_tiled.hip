@@ -58,21 +58,6 @@ __device__ __forceinline__ double lds_f64(const double *tab, uint32_t byte_addr)
     return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(tab) + byte_addr);
 }
 
-// LDS byte address of the value of the bin-local ID in the low / high half of w.  The
-// low half is shifted from its 16-bit field directly (one instruction).
-__device__ __forceinline__ uint32_t addr_lo(uint32_t w) {
-    uint32_t r;
-    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-        : "=v"(r) : "v"(3u), "v"(w));
-    return r;
-}
-__device__ __forceinline__ uint32_t addr_hi(uint32_t w) {
-    uint32_t r;
-    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
-        : "=v"(r) : "v"(3u), "v"(w));
-    return r;
-}
-
 template <bool MAX>
 __device__ __forceinline__ void fold(double &acc, double v) {
     if (MAX) acc = v > acc ? v : acc;   // occurrence-net losses are >= +0.0
@@ -145,7 +130,7 @@ __device__ __forceinline__ void load_ids_now(const i32x4 &span, uint32_t at, u32
 // 0.490.)
 template <bool MAX>
 __device__ __forceinline__ void add4(const double *tab, uint32_t w0, uint32_t w1, uint32_t p, uint32_t len, double &acc) {
-    uint32_t at[4] = {addr_lo(w0), addr_hi(w0), addr_lo(w1), addr_hi(w1)};
+    uint32_t at[4] = {value_lo(w0), value_hi(w0), value_lo(w1), value_hi(w1)};
     double v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = lds_f64(tab, p + uint32_t(j) < len ? at[j] : kZeroAddr);

@@ -24,7 +24,8 @@
 // lane: 16 bytes of int32 IDs, or 12 bytes of the YET's packed 3-byte copy, which
 // cuts the dominant stream by a quarter).  Per segment:
 //   filter  each lane tests the LDS bit of its events, up to 16 (one LDS read each, all
-//           issued together); only events whose occurrence-net loss is nonzero pass;
+//           issued together): events whose occurrence-net loss is nonzero pass, and in a
+//           folded filter those that share a bit with one;
 //   queue   passing events are appended to the wave's LDS queue in slot-then-lane
 //           order (mbcnt positions), so they end up dense;
 //   rows    the queue is resolved 64 events at a time, their values from the table;

@@ -57,6 +57,21 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
     return int64_t((uint64_t(hi) << 32) | lo);
 }
 
+// LDS byte address of the binary64 value of the 16-bit ID in the low / high half of w, shifted
+// from its field directly (one instruction).
+__device__ __forceinline__ uint32_t value_lo(uint32_t w) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+        : "=v"(r) : "v"(3u), "v"(w));
+    return r;
+}
+__device__ __forceinline__ uint32_t value_hi(uint32_t w) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+        : "=v"(r) : "v"(3u), "v"(w));
+    return r;
+}
+
 // Trial offsets are read through the scalar data path (constant address space):
 // they are wave-uniform and their loads then wait on the scalar counter instead of
 // joining the in-order vector-memory queue behind the event-ID prefetch.

@@ -340,20 +340,6 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
-// LDS byte address of the value of the ID in the low / high half of w.
-__device__ __forceinline__ uint32_t value_lo(uint32_t w) {
-    uint32_t r;
-    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-        : "=v"(r) : "v"(3u), "v"(w));
-    return r;
-}
-__device__ __forceinline__ uint32_t value_hi(uint32_t w) {
-    uint32_t r;
-    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
-        : "=v"(r) : "v"(3u), "v"(w));
-    return r;
-}
-
 // Adds the 8 IDs of a row's piece q in order: all of them, or those before the r-th (TAIL,
 // any r) and from the lead-th on (FIRST: the trial's first piece, lead < 4).  The others
 // become 0xFFFF, which the clamp turns into the zero entry's: by a row of masks in LDS for
