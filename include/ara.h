@@ -208,7 +208,8 @@ ara_status ara_kernel_ms(ara_ctx *ctx, float *ms);
  * per-(bin, trial) offsets.  Analyses of layers whose table does not fit in LDS then
  * read that copy (ARA_PLACE_LDS_TILES); other placements then stream the int32 IDs.
  * If the device has no memory for it, the handle is created without it.  Device
- * memory the handle adds to the caller's arrays (ara_yet_memory gives it exactly):
+ * memory the handle adds to the caller's arrays (ara_yet_memory gives it exactly; the blocks
+ * that hold it, of a MiB and more and up to 4 GiB, are up to a sixteenth larger):
  * with a binned copy 2 bytes per occurrence plus 4 bytes per (bin, trial + 2, rounded
  * up to a multiple of 8), 3 with ARA_OPT_YET_RUN_BYTES = 3, plus about 24 bytes per
  * bin, else 3 bytes per occurrence with a packed copy.

@@ -35,7 +35,7 @@
 // dependent kernels takes 4.5-5 us whatever it does (8 MB of losses are 1.3 us of HBM), so
 // the passes that replaced one 8-bit digit each (12 launches, 105 us for 10^6 distinct
 // losses and 135 us when a rank fell among capped years, whose bucket never became small)
-// are now four (36 us for 10^6 losses, 27 us for 50,000).  Within a launch, code that runs
+// are now four (34 us for 10^6 losses, 24 us for 50,000).  Within a launch, code that runs
 // once costs its fetch: with every loop over a thread's 16 keys unrolled for each rank (31 KB
 // of code) k_risk_one took 21 us for 1000 losses (11 now).  Counting every key in bins of the
 // whole range took 26 us for 10^6 losses: most years fall in a few of those bins, and LDS
@@ -304,7 +304,7 @@ __device__ __forceinline__ void wave_select(uint64_t key, int c, int64_t left, u
 // by halving the range of the keys still in question, which ends at once when they are all
 // one loss (losses that come from few events are shared by many years).  Each rank has its
 // own wave; refine() takes the workgroup through them one after another, and k_risk_collect
-// took 25 us for the three ranks of 10^5 trials' largest occurrences, now 15.
+// took 25 us for the three ranks of 10^5 trials' largest occurrences, now 13.
 template <typename Key>
 __device__ __forceinline__ void wave_select_any(int count, int64_t left, uint64_t &K, int64_t &copies, Key key) {
     const int lane = threadIdx.x & 63;
@@ -555,8 +555,8 @@ __device__ __forceinline__ void place_bins(const RankState *st, int m, int wave,
 
 // Copies the keys of each rank's bin (the first ranks' of them), a whole wave together:
 // reserve(r, c) by one lane gives the wave room for its c keys of rank r, put(r, place, key)
-// stores one.  One returning atomic per rank, not one per key register (k_risk_collect, for the
-// largest occurrences of 10^5 trials: 15 us, with wave_pick's banks 14.3).
+// stores one.  One returning atomic per rank, not one per key register (with wave_pick's banks
+// k_risk_collect went from 15 to 14.3 us for the largest occurrences of 10^5 trials).
 template <typename Reserve, typename Put>
 __device__ __forceinline__ void copy_bins(const uint64_t (&k)[kRiskLoads], uint32_t in, const RankState *st,
                                           const int *first, int m, Reserve reserve, Put put) {
@@ -933,7 +933,7 @@ __global__ __launch_bounds__(kRiskThreads) void k_risk_bins(RiskArgs a) {
 // among them.  Of a range of more than kRiskCollect keys the smallest and largest are kept
 // instead: equal for a loss that occurs that often, else the YLT stays open.  FIRST: the
 // ranges are bins that k_risk_bins counted, in later rounds k_risk_narrow's.  (One kernel for
-// both took 22 us for 10^6 losses, this 15.)
+// both took 22 us for 10^6 losses, this 14.)
 constexpr int kRangesAtOnce = 4;   // large ranges per pass over the keys
 template <bool FIRST>
 __global__ __launch_bounds__(kRiskThreads) void k_risk_collect(RiskArgs a) {
@@ -1176,7 +1176,7 @@ __global__ __launch_bounds__(kSumWaves * 64) void k_risk_sum(RiskArgs a) {
 // that can be had, since each has a fixed part (clearing and adding its bins; in the collection,
 // picking the ranks' bins and being counted) however few losses it takes.  A workgroup of
 // k_risk_bins leaves room for another on its CU, one of k_risk_collect does not.  15 YLTs of
-// 10^5 to 10^6 losses with 128 workgroups each: bins 32 us, collection 65; now 24 and 50.
+// 10^5 to 10^6 losses with 128 workgroups each: bins 32 us, collection 65; now 25 and 39.
 constexpr int kResidentBins = 512, kResidentCollect = 256;
 static int blocks_each(const RiskJob *jobs, int n_jobs, int resident) {
     auto total = [&](int most) {

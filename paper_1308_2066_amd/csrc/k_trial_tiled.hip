@@ -22,13 +22,15 @@
 //   run is read 32 IDs at a time when reached.  Each bin's values are loaded into registers
 //   while the previous bin is added, and written to LDS between two barriers.
 //   (Three slots, two groups ahead, need an unrolled loop over three bins and more
-//   registers than a wave has: 30 KB of code and 15 spilled registers.  Two take 17 KB and
+//   registers than a wave has: 30 KB of code and 15 spilled registers.  Two take 18 KB and
 //   none, and are faster everywhere: 10^6 trials of 1000 occurrences over 62 bins 0.483 ->
 //   0.470 ms, 50,000 of 600 over 19 bins 36 -> 30 us.  With runs of 36 to 88 occurrences
 //   per bin the rest of the run, read 8 IDs at a time with a wait each, took another 5% of
 //   eight uneven analyses: 638 -> 602 -> 575 us.)
-// A trial's P is added in a fixed order (bin groups, bins, positions): the same bits on
-// every run.  The per-trial sums live in LDS (one binary64 per trial of the wave).
+// A trial's P is added in a fixed order (bin groups, bins, positions) that depends on the
+// catalog alone: the same bits on every run, in every launch and in every YET that holds the
+// trial.  A group's sums are in registers (a lane's four trials), the totals in LDS (one
+// binary64 per trial of the wave).
 #include <algorithm>
 
 #include <hip/hip_ext.h>
@@ -179,9 +181,12 @@ __device__ __forceinline__ void unit_run(const double *tab, const i32x4 &span, U
 // bin, the last one's loads are issued again and its runs are empty.
 // B24: run starts in 3 bytes each, read as an unaligned 4-byte word (its top byte,
 // the next entry's first, masked off where the value is taken).
+// rare: the same arguments in memory, for what a group's end needs (kept in registers over the
+// loop, they spilled others: 0.52 ms with 3-byte run starts, now 0.48).
+typedef const __attribute__((address_space(4))) TiledArgs *ArgsInMemory;
 template <bool MAX, bool B24>
-__device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64_t T1, int32_t g0, int32_t g1,
-                                           double *tab, double *ws, int lane) {
+__device__ __forceinline__ void tiled_pass(const TiledArgs &a, ArgsInMemory rare, int64_t T0, int64_t T1, int32_t g0,
+                                           int32_t g1, double *tab, double *ws, int lane) {
     const int32_t bin0 = g0 * a.group_bins, bin1 = min(g1 * a.group_bins, a.n_bins);
     int32_t bg = g0, bg_end = min(bin0 + a.group_bins, bin1);   // the bin group and its last bin + 1
     double acc[kGroups] = {};
@@ -252,12 +257,15 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64
         rc = rn;
         pc = pn;
         if (b + 1 != bg_end) continue;
+        ArgsInMemory m = rare;
+        asm volatile("" : "+s"(m));   // read here, not before the loop
+        double *part = m->part ? m->part + (bg * m->part_stride - m->t_begin) : nullptr;
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
             const int64_t t = T0 + 64 * g + lane;
             if (t < T1) {
-                if (a.part) {
-                    a.part[bg * a.part_stride + (t - a.t_begin)] = acc[g];
+                if (part) {
+                    part[t] = acc[g];
                 } else {
                     double x = ws[64 * g + lane];   // group 0: an earlier pass's
                     x = bg > 0 ? x : 0.0;
@@ -268,7 +276,7 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64
             acc[g] = 0.0;
         }
         ++bg;
-        bg_end = min(bg_end + a.group_bins, bin1);
+        bg_end = min(bg_end + m->group_bins, bin1);
     }
 }
 
@@ -278,17 +286,19 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, int64_t T0, int64
 // catalog alone, so a trial's YLT does not depend on how they are spread over workgroups,
 // nor on the other trials of its YET.
 template <bool MAX, bool B24>
-__device__ __forceinline__ void tiled_groups(const TiledArgs &a, int64_t t0, int64_t t1, int32_t g0, int32_t g1,
+__device__ __forceinline__ void tiled_groups(const TiledArgs &a, ArgsInMemory rare, int64_t t0, int64_t t1, int32_t g0, int32_t g1,
                                              double *tab, double *ws, int lane, uint32_t wave) {
     const int64_t per_wave = (t1 - t0 + kTiledWaves - 1) / kTiledWaves;
     const int64_t T0 = min(t0 + int64_t(wave) * per_wave, t1);
     const int64_t T1 = min(T0 + per_wave, t1);
-    tiled_pass<MAX, B24>(a, T0, T1, g0, g1, tab, ws, lane);
-    if (a.part) return;
+    tiled_pass<MAX, B24>(a, rare, T0, T1, g0, g1, tab, ws, lane);
+    asm volatile("" : "+s"(rare));
+    if (rare->part) return;
 #pragma unroll 1
     for (int g = 0; g < kGroups; ++g) {
         const int64_t t = T0 + 64 * g + lane;
-        if (t < T1) a.ylt[t - a.t_begin] = MAX ? ws[64 * g + lane] : excess(ws[64 * g + lane], a.agg_r, a.agg_l);
+        if (t < T1)
+            rare->ylt[t - rare->t_begin] = MAX ? ws[64 * g + lane] : excess(ws[64 * g + lane], rare->agg_r, rare->agg_l);
     }
 }
 
@@ -317,8 +327,9 @@ __global__ __launch_bounds__(1024) void k_trial_tiled(TiledArgs a) {
     const int64_t wg1 = min(wg0 + a.per_wg, a.t_end);
 #pragma unroll 1
     for (int64_t pass = wg0; pass < wg1; pass += kTiledPassTrials)
-        tiled_groups<MAX, B24>(a, pass, min(pass + int64_t(kTiledPassTrials), wg1), g0, g1, tab,
-                               sums + wave * kTiledWaveTrials, lane, wave);
+        tiled_groups<MAX, B24>(a, (ArgsInMemory)__builtin_amdgcn_kernarg_segment_ptr(), pass,   // its only argument
+                               min(pass + int64_t(kTiledPassTrials), wg1), g0, g1, tab, sums + wave * kTiledWaveTrials, lane,
+                               wave);
 }
 
 // The totals of split analyses from their bin groups' sums (grid.y: the analysis), two
@@ -385,8 +396,9 @@ __global__ __launch_bounds__(1024) void k_trial_tiled_items(const TiledArgs *__r
         const TiledArgs a = load_args(jobs, job);
         const int32_t g0 = int32_t(groups & 0xFFFFu), g1 = int32_t(groups >> 16);
         double *ws = sums + wave * kTiledWaveTrials;
-        if (a.boff24) tiled_groups<false, true>(a, t0, t1, g0, g1, tab, ws, lane, wave);
-        else tiled_groups<false, false>(a, t0, t1, g0, g1, tab, ws, lane, wave);
+        const ArgsInMemory rare = (ArgsInMemory)(jobs + job);
+        if (a.boff24) tiled_groups<false, true>(a, rare, t0, t1, g0, g1, tab, ws, lane, wave);
+        else tiled_groups<false, false>(a, rare, t0, t1, g0, g1, tab, ws, lane, wave);
     }
 }
 
