@@ -667,6 +667,9 @@ static void yet_free_binned(ara_yet *y) {
     y->n_bins = 0;
 }
 
+// Mean occurrences of a trial in a bin.
+static double mean_run(const ara_yet *y) { return double(y->n_events) / (double(y->n_trials) * double(y->n_bins)); }
+
 // Whether a YET of these sizes gets a catalog-binned copy (see ara_yet_create).
 static bool yet_binning_applies(const ara_ctx *c, const ara_yet *y) {
     const int32_t nb = catalog_bins(y->catalog);
@@ -752,7 +755,7 @@ static ara_status yet_build_binned(ara_ctx *c, ara_yet *y, bool *ids_checked) {
         y->n_bins = nb;
         y->group_bins = tiled_group_bins(nb);
         y->n_groups = (nb + y->group_bins - 1) / y->group_bins;
-        if (tiled_split(n, nb, c->n_cu, false).chunks > 0)
+        if (tiled_split(n, nb, mean_run(y), c->n_cu, false).chunks > 0)
             c->tiled_need = std::max(c->tiled_need, std::min(kTiledWsBytes, tiled_split_bytes(n, y->n_groups)));
         y->copy_bytes = int64_t(ids16_bytes) + int64_t(nb + 1) * 8 + int64_t(nb) * y->stride * (y->boff24 ? 3 : 4) +
                         (y->boff24 ? 16 : 0);
@@ -1189,6 +1192,7 @@ static void set_split(TiledArgs &a, void *p, const TiledSplit &how) {
     a.group_bins = how.group_bins;
     a.n_groups = how.n_groups;
     a.span_groups = how.span_groups;
+    a.first_row = how.span_groups - 1;
     a.per_wg = (n + how.chunks - 1) / how.chunks;
 }
 
@@ -1275,7 +1279,7 @@ static void tiled_trim(ara_ctx *c) {
 static hipError_t run_tiled(ara_ctx *c, const ara_yet *y, const ara_layer *L, int64_t t0, int64_t t1, double *out, int grid,
                             bool occ_max, hipEvent_t start, hipEvent_t stop) {
     TiledArgs a = tiled_args(y, L, t0, t1, out, grid);
-    const TiledSplit how = tiled_split(t1 - t0, y->n_bins, c->n_cu, occ_max);
+    const TiledSplit how = tiled_split(t1 - t0, y->n_bins, mean_run(y), c->n_cu, occ_max);
     ara_ctx::Scratch *w = how.chunks > 0 ? tiled_scratch(c, tiled_split_bytes(t1 - t0, how.n_groups)) : nullptr;
     if (w) set_split(a, w->p, how);
     hipError_t e = launch_trial_tiled(a, grid, c->stream, occ_max, start, stop);

@@ -271,12 +271,14 @@ struct TiledArgs {
     int64_t part_stride;        // even, at least t_end - t_begin + 1
     int32_t chunks;             // split: chunks of per_wg trials
     int32_t span_groups;        // split: groups a workgroup goes through
+    int32_t first_row;          // split: the row of `part` that holds the total up to its group
+    int32_t pad_;
 };
 // Bins per group: at most 20 groups, by the catalog alone, so that every analysis of a trial
 // adds its bins in the same order, whatever YET holds it and whatever the launch.  More groups
 // split a launch of few trials further (20,000 trials over 92 bins: 31 groups 28 us, 19 33,
 // 12 45), and cost a launch of more trials the traffic of their sums (200,000 over 62 bins: 9
-// groups 119 us, 16 131, 21 134).
+// groups 119 us, 16 129, 21 134).
 constexpr int32_t kTiledMaxGroups = 20;
 inline int32_t tiled_group_bins(int32_t n_bins) { return (n_bins + kTiledMaxGroups - 1) / kTiledMaxGroups; }
 __host__ __device__ inline int32_t tiled_spans(int32_t groups, int32_t span_groups) {
@@ -289,7 +291,8 @@ struct TiledSplit {
     int64_t chunks;
     int32_t group_bins, n_groups, span_groups;
 };
-TiledSplit tiled_split(int64_t n, int32_t n_bins, int n_cu, bool occ_max);
+// run: mean occurrences of a trial in a bin
+TiledSplit tiled_split(int64_t n, int32_t n_bins, double run, int n_cu, bool occ_max);
 // occ_max: each trial's largest occurrence-net loss into a.ylt instead of the YLT;
 // start/stop (or null): HIP events attached to the launch (its first dispatch's start, its
 // last one's end)

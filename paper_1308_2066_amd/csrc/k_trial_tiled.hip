@@ -172,8 +172,8 @@ __device__ __forceinline__ void unit_run(const double *tab, const i32x4 &span, U
 
 // One pass of a workgroup over trials [T0, T1) of each wave (at most kTiledWaveTrials) and bin
 // groups [g0, g1) of analysis a: every bin staged once, each lane's trials added bin by bin
-// in registers; where a group ends its sums go to ws[64 g + lane], the total so far (a.part null:
-// every group here), or to the group's row of a.part.
+// in registers; where a group ends its sums join the total so far in ws[64 g + lane] (groups
+// up to a.first_row, all of them without a.part), or go to the group's row of a.part.
 // MAX = false: sums of the occurrence-net losses; MAX = true: each trial's largest.
 // Units u = 4 b + g (bin b, group g of 64 trials) take turns in two register slots (slot
 // u % 2): unit u + 2 is issued once unit u is added.  No load is issued under a condition, so
@@ -259,7 +259,7 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, ArgsInMemory rare
         if (b + 1 != bg_end) continue;
         ArgsInMemory m = rare;
         asm volatile("" : "+s"(m));   // read here, not before the loop
-        double *part = m->part ? m->part + (bg * m->part_stride - m->t_begin) : nullptr;
+        double *part = m->part && bg > m->first_row ? m->part + (bg * m->part_stride - m->t_begin) : nullptr;
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
             const int64_t t = T0 + 64 * g + lane;
@@ -282,7 +282,8 @@ __device__ __forceinline__ void tiled_pass(const TiledArgs &a, ArgsInMemory rare
 
 // Trials [t0, t1) (at most one pass) over bin groups [g0, g1) of analysis a.  A trial's
 // total is ((s_0 + s_1) + s_2) + ..., s_g its sum over group g's bins, taken here (every
-// group) or, with a.part, by k_tiled_combine in the same order.  The groups depend on the
+// group) or, with a.part, by k_tiled_combine in the same order: row first_row of a.part holds
+// the total up to its group, each later row its own group's sum.  The groups depend on the
 // catalog alone, so a trial's YLT does not depend on how they are spread over workgroups,
 // nor on the other trials of its YET.
 template <bool MAX, bool B24>
@@ -293,12 +294,14 @@ __device__ __forceinline__ void tiled_groups(const TiledArgs &a, ArgsInMemory ra
     const int64_t T1 = min(T0 + per_wave, t1);
     tiled_pass<MAX, B24>(a, rare, T0, T1, g0, g1, tab, ws, lane);
     asm volatile("" : "+s"(rare));
-    if (rare->part) return;
+    const bool whole = rare->part == nullptr;
+    if (!whole && g0 > rare->first_row) return;
+    double *out = whole ? rare->ylt : rare->part + rare->first_row * rare->part_stride;
+    const double r = whole ? rare->agg_r : 0.0, l = whole ? rare->agg_l : __builtin_inf();
 #pragma unroll 1
     for (int g = 0; g < kGroups; ++g) {
         const int64_t t = T0 + 64 * g + lane;
-        if (t < T1)
-            rare->ylt[t - rare->t_begin] = MAX ? ws[64 * g + lane] : excess(ws[64 * g + lane], rare->agg_r, rare->agg_l);
+        if (t < T1) out[t - rare->t_begin] = MAX ? ws[64 * g + lane] : excess(ws[64 * g + lane], r, l);
     }
 }
 
@@ -338,9 +341,10 @@ template <bool MAX>
 __device__ __forceinline__ void combine_groups(const TiledArgs &a) {
     const int64_t n = a.t_end - a.t_begin;
     for (int64_t i = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 2; i < n; i += int64_t(gridDim.x) * 512) {
-        f64x2 s = *reinterpret_cast<const f64x2 *>(a.part + i);   // part rows are 16-byte aligned and padded
+        // part rows are 16-byte aligned and padded
+        f64x2 s = *reinterpret_cast<const f64x2 *>(a.part + a.first_row * a.part_stride + i);
 #pragma unroll 4
-        for (int32_t g = 1; g < a.n_groups; ++g) {
+        for (int32_t g = a.first_row + 1; g < a.n_groups; ++g) {
             const f64x2 x = *reinterpret_cast<const f64x2 *>(a.part + g * a.part_stride + i);
 #pragma unroll
             for (int k = 0; k < 2; ++k) s[k] = MAX ? (x[k] > s[k] ? x[k] : s[k]) : s[k] + x[k];
@@ -453,41 +457,41 @@ hipError_t launch_trial_tiled(const TiledArgs &a, int grid, hipStream_t s, bool 
 // spread over all CUs was bound by the staging: 10^5 trials of 1000 occurrences over 62 bins
 // took 330 us on 256 workgroups of 391 trials, 50,000 of 600 over 19 bins 122 us.  Instead a
 // workgroup takes a chunk of up to a full pass of trials and a span of the bin groups: 64 and
-// 28 us with the adding up.  Costs in full-pass bin times (8.2 us): 0.75 per workgroup
-// (start, first bin's load, sums written), and per bin what its own trials take (3.3 us and
-// 3.7 more for a full pass) or, with every CU busy, their share of the memory path.
-static double bin_cost(double trials, double wgs, int n_cu) {
-    const double x = trials / kTiledPassTrials;
-    return std::max(0.4 + 0.45 * x, x * std::min(1.0, wgs / n_cu));
+// 28 us with the adding up.  Costs in us: 6 per workgroup (start, first bin's load, sums
+// written); a bin's staging, and for each 64 trials of a wave, however many of them it has,
+// what a run of `run` occurrences takes (325,634 trials of 19.4 per bin: 2 spans of 128 chunks,
+// three 64s per wave, 7.4 us a bin; 3 of 85, four, 8.6: 167 and 146 us in all; 250,000 of 13.5:
+// 5.7 and 7.0).
+static double bin_us(int64_t trials, double run) {
+    const int64_t groups = ((trials + kTiledWaves - 1) / kTiledWaves + 63) / 64;
+    return 2.0 + double(groups) * (0.55 + 0.055 * run);
 }
 
-static double whole_cost(int64_t n, int32_t n_bins, int n_cu) {
+static double whole_us(int64_t n, int32_t n_bins, double run, int n_cu) {
     const int64_t wgs = std::max<int64_t>(1, std::min<int64_t>(n_cu, (n + 63) / 64));
     const int64_t per = (n + wgs - 1) / wgs, passes = (per + kTiledPassTrials - 1) / kTiledPassTrials;
-    return double(passes) * (0.75 + n_bins * bin_cost(double(per) / double(passes), double(wgs), n_cu));
+    return double(passes) * (6.0 + n_bins * bin_us((per + passes - 1) / passes, run));
 }
 
 // The split of n trials over n_bins bins that costs least, or chunks = 0: whole.  Sums are
 // taken by bin groups; maxima, which are the same in any order, by spans of bins.
-TiledSplit tiled_split(int64_t n, int32_t n_bins, int n_cu, bool occ_max) {
+TiledSplit tiled_split(int64_t n, int32_t n_bins, double run, int n_cu, bool occ_max) {
     const int32_t gb = occ_max ? (n_bins + 63) / 64 : tiled_group_bins(n_bins), groups = (n_bins + gb - 1) / gb;
     const int64_t least = (n + kTiledPassTrials - 1) / kTiledPassTrials;
     TiledSplit best{0, 0, 0, 0};
-    double cost = whole_cost(n, n_bins, n_cu);
+    double cost = whole_us(n, n_bins, run, n_cu);
     for (int32_t span = 1; span < groups; ++span) {
         const int32_t spans = tiled_spans(groups, span);
         if (span > 1 && tiled_spans(groups, span - 1) == spans) continue;
-        const int32_t bins = std::min(span * gb, n_bins), parts = occ_max ? spans : groups;
+        const int32_t bins = std::min(span * gb, n_bins), parts = occ_max ? spans : groups - span + 1;
         // the parts written and read at 4 TB/s, and the combining launch
-        const double sums = 0.7 + double(n) * parts * 16.0 / 4e12 / 8.2e-6;
+        const double sums = 5.7 + double(n) * parts * 16.0 / 4e6;
         // as many chunks as fill so many rounds of the CUs, of at least a group of 64 trials
         const int64_t first = (least * spans + n_cu - 1) / n_cu;
         for (int64_t rounds = first; rounds < first + 3; ++rounds) {
             const int64_t chunks = std::max(least, std::min(rounds * n_cu / spans, n / 64));
-            const int64_t wgs = chunks * spans, full = wgs / n_cu, rest = wgs % n_cu;
-            const double trials = double(n) / double(chunks);
-            double c = sums + double(full) * (0.75 + bins * bin_cost(trials, n_cu, n_cu));
-            if (rest > 0) c += 0.75 + bins * bin_cost(trials, double(rest), n_cu);
+            const double c = double((chunks * spans + n_cu - 1) / n_cu) * (6.0 + bins * bin_us((n + chunks - 1) / chunks, run)) +
+                             sums;
             if (c < cost) {
                 cost = c;
                 best = occ_max ? TiledSplit{chunks, bins, spans, 1} : TiledSplit{chunks, gb, groups, span};
