@@ -49,7 +49,7 @@ struct ara_ctx {
         Busy busy;
     };
     std::vector<Scratch> tiled_ws;
-    bool streams = false;            // the stream has been changed
+    bool streams = false;            // split launches have run on several streams
     std::vector<void *> tiled_old;   // smaller ones, replaced: launches may still use them
     size_t tiled_need = 0;           // the most that a whole YET of this context takes
     bool tiled_fixed = false;        // a server lane's: neither more nor larger ones
@@ -559,7 +559,6 @@ extern "C" ara_status ara_ctx_destroy(ara_ctx *c) {
 
 extern "C" ara_status ara_ctx_set_stream(ara_ctx *c, void *hip_stream) {
     if (!c) return ARA_E_INVALID_ARG;
-    c->streams = c->streams || c->stream != reinterpret_cast<hipStream_t>(hip_stream);
     c->stream = reinterpret_cast<hipStream_t>(hip_stream);
     return ARA_OK;
 }
@@ -1199,8 +1198,8 @@ static void set_split(TiledArgs &a, void *p, const TiledSplit &how) {
 // A workspace of `bytes` for a split tiled launch on the context's stream: the one its last
 // launch was in (launches on a stream follow each other, and hipStreamDestroy waits for them),
 // else one whose last launch has ended, else a new one, up to kTiledWsCount.  Whether it has
-// ended is known once the stream has been waited for and, on a context that has had several
-// streams, from an event after each launch (6 us each, so not before).  Null while the
+// ended is known once the stream has been waited for and, on a context that has had them on
+// several streams, from an event after each launch (6 us each, so not before).  Null while the
 // stream is being captured (a graph may be replayed on any stream, at any time), for more
 // than kTiledWsBytes, with all of them in use on other streams, or without memory: the
 // launch then runs whole, with the same bits.  Nothing here waits: a workspace that is too
@@ -1226,6 +1225,7 @@ static ara_ctx::Scratch *tiled_scratch(ara_ctx *c, size_t bytes) {
     if (c->stream != hipStreamPerThread)   // (another stream in each thread)
         for (auto &x : c->tiled_ws)
             if (x.stream == c->stream) w = &x;
+    if (!w && !c->tiled_ws.empty()) c->streams = true;
     for (size_t i = 0; !w && i < c->tiled_ws.size(); ++i)
         if (scratch_idle(c->tiled_ws[i])) w = &c->tiled_ws[i];
     if (!w || w->bytes < bytes) {
