@@ -413,7 +413,10 @@ typedef struct ara_job {
 typedef struct ara_batch ara_batch;
 
 /* Plans the batch: validates every job (as ara_analyze would) and uploads their
- * descriptors.  Errors: those of ara_analyze's argument checks, ARA_E_OOM. */
+ * descriptors.  Small batches of analyses of large catalogs also take up to 256 MB
+ * for their trials' sums by groups of catalog bins; without that room they run
+ * without, slower and with the same results.  Errors: those of ara_analyze's
+ * argument checks, ARA_E_OOM. */
 ara_status ara_batch_create(ara_ctx *ctx, const ara_job *jobs, int32_t n_jobs, ara_batch **out);
 
 /* Computes every job's YLT on the context's stream.  The jobs are split into work

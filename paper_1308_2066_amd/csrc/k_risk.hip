@@ -9,7 +9,7 @@
 // +0.0) and a fixed tree over the slots; then the tile sums, slot t adding tiles t,
 // t + 256, ... in turn, and the same tree.  So every path below gives the same bits.
 //
-// K is found from a sample of 1024 losses, one pass that counts bins and one that copies a
+// K is found from a sample of 1024 losses (4096 past 2^22), one pass that counts bins and one that copies a
 // few keys out.  The sample gives the smallest sampled key L and a key T that the largest
 // rank asked for lies below (five standard deviations beyond its place in the sample).
 // The pass counts the keys below L, the keys equal to L (years capped at the aggregate
